@@ -135,8 +135,8 @@ int fc_build_maps(const fastcot_config* c, ModelMap* mm, WorkspaceMap* wm, Kerne
         size_t cache = (size_t)k.L * k.B * k.Hkv * kv_alloc_planes(k.kvp) * k.S * k.Dh * esz;
         wm->kc = take(cache); wm->vc = take(cache);
         wm->rope_cos = take((size_t)k.S * (k.Dh / 2) * 4); wm->rope_sin = take((size_t)k.S * (k.Dh / 2) * 4);
-        wm->x = take(M * d * 4); wm->nx = take(M * d * 4); wm->qkv = take(M * k.qkvN * 4); wm->qrot = take(M * qd * 4);
-        wm->att = take(M * qd * 4); wm->gu = take(M * 2 * F * 4); wm->h = take(M * F * 4);
+        wm->x = take(M * d * 4); wm->qkv = take(M * k.qkvN * 4); wm->qrot = take(M * qd * 4);
+        wm->att = take(M * qd * 4); wm->h = take(M * F * 4);
         wm->logits = take(M * k.V * 4); wm->topv = take(M * 4);
         fc_fast_scratch_sizes(k, &wm->gemm_part_bytes, &wm->attn_part_bytes);
         wm->gemm_part = take(wm->gemm_part_bytes); wm->gemm_cnt = take(FC_MAX_COUNTERS * 4);
@@ -415,26 +415,22 @@ static int forward_plain(fastcot_ctx* c, int lmhead, int R) {
     char* ws = c->ws; const char* wt = c->weights;
     int32_t* stp = state_ptr(c);
     const StateMap& sm = c->wm.st;
-    float* x = (float*)(ws + c->wm.x); float* nx = (float*)(ws + c->wm.nx); float* qkv = (float*)(ws + c->wm.qkv);
-    float* att = (float*)(ws + c->wm.att); float* gu = (float*)(ws + c->wm.gu); float* h = (float*)(ws + c->wm.h);
+    float* x = (float*)(ws + c->wm.x); float* qkv = (float*)(ws + c->wm.qkv); float* qrot = (float*)(ws + c->wm.qrot);
+    float* att = (float*)(ws + c->wm.att); float* h = (float*)(ws + c->wm.h);
     LAUNCH(c, KK_EMBED, fc_embed(wt + c->mm.emb_off, dt, stp + sm.win, x, M, d, kd.V, c->st));
     for (int l = 0; l < kd.L; ++l) {
         const char* lb = wt + c->mm.layers_off + (size_t)l * c->mm.layer_stride;
-        LAUNCH(c, KK_RMSNORM, fc_rmsnorm_plain(x, (const float*)(lb + c->mm.g1_off), nx, M, d, kd.eps, c->st));
-        LAUNCH(c, KK_QKV, fc_gemm_plain(lb + c->mm.qkv.off, dt, d, c->mm.qkv.NP, kd.qkvN, nx, d, qkv, kd.qkvN, M, 0, c->st));
-        LAUNCH(c, KK_ROPE, fc_rope_cache_plain(qkv, (float*)(ws + c->wm.qrot), kd, l, stp + sm.n, (const float*)(ws + c->wm.rope_cos),
-                                               (const float*)(ws + c->wm.rope_sin), ws + c->wm.kc, ws + c->wm.vc, dt, c->st));
-        LAUNCH(c, KK_ATTN, fc_attn_plain((const float*)(ws + c->wm.qrot), qd, ws + c->wm.kc, ws + c->wm.vc, dt, kd, l, stp + sm.n, att, c->st));
+        LAUNCH(c, KK_QKV, fc_qkv_plain(lb + c->mm.qkv.off, dt, kd, l, x, (const float*)(lb + c->mm.g1_off), qkv, qrot, stp + sm.n,
+                                       (const float*)(ws + c->wm.rope_cos), (const float*)(ws + c->wm.rope_sin), ws + c->wm.kc, ws + c->wm.vc, c->st));
+        LAUNCH(c, KK_ATTN, fc_attn_plain(qrot, qd, ws + c->wm.kc, ws + c->wm.vc, dt, kd, l, stp + sm.n, 0, att, c->st));
         LAUNCH(c, KK_O, fc_gemm_plain(lb + c->mm.o.off, dt, qd, c->mm.o.NP, d, att, qd, x, d, M, 1, c->st));
-        LAUNCH(c, KK_RMSNORM, fc_rmsnorm_plain(x, (const float*)(lb + c->mm.g2_off), nx, M, d, kd.eps, c->st));
-        LAUNCH(c, KK_GU, fc_gemm_plain(lb + c->mm.gu.off, dt, d, c->mm.gu.NP, 2 * kd.F, nx, d, gu, 2 * kd.F, M, 0, c->st));
-        LAUNCH(c, KK_SWIGLU, fc_swiglu_plain(gu, h, M, kd.F, 2 * kd.F, c->st));
+        LAUNCH(c, KK_GU, fc_swiglu_plain(lb + c->mm.gu.off, dt, d, kd.F, x, d, h, M, (const float*)(lb + c->mm.g2_off), kd.eps, c->st));
         LAUNCH(c, KK_DOWN, fc_gemm_plain(lb + c->mm.down.off, dt, kd.F, c->mm.down.NP, d, h, kd.F, x, d, M, 1, c->st));
     }
     if (lmhead) {
         float* logits = c->dbg_logits ? c->dbg_logits : (float*)(ws + c->wm.logits);
-        LAUNCH(c, KK_RMSNORM, fc_rmsnorm_plain(x, (const float*)(wt + c->mm.gf_off), nx, M, d, kd.eps, c->st));
-        LAUNCH(c, KK_LM, fc_gemm_plain(wt + c->mm.lm.off, dt, d, c->mm.lm.NP, kd.V, nx, d, logits, kd.V, M, 0, c->st));
+        LAUNCH(c, KK_LM, fc_gemm_plain(wt + c->mm.lm.off, dt, d, c->mm.lm.NP, kd.V, x, d, logits, kd.V, M, 0, c->st,
+                                       (const float*)(wt + c->mm.gf_off), kd.eps));
         LAUNCH(c, KK_ARGMAX, fc_argmax_plain(logits, M, kd.V, stp + sm.o, (float*)(ws + c->wm.topv), c->st));
     }
     return 0;

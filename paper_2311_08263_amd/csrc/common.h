@@ -121,7 +121,7 @@ struct RowMap { const int32_t* rowb; const int32_t* rowj; const int32_t* rstart;
 struct WorkspaceMap {
     size_t kc, vc;              // KV cache [L][B][Hkv][planes][S/32 blocks][32 * Dh] in fragment order (k_index, v_index)
     size_t rope_cos, rope_sin;  // fp32 [S][Dh/2]
-    size_t x, nx, qkv, qrot, att, gu, h, logits, topv;
+    size_t x, qkv, qrot, att, h, logits, topv;
     size_t gemm_part, gemm_cnt, attn_part, attn_cnt, amax_part;
     size_t state;
     size_t total;

@@ -347,7 +347,7 @@ hipError_t fc_attn_iso(const float* q, const void* kc, const void* vc, int n, in
     k_set_i32<<<1, 64, 0, st>>>((int32_t*)sc, n);
     if (dt != FASTCOT_BF16 || Dh != 128 || W > 32 || S % 32 || H > FC_MAX_COUNTERS) {
         KernelDims kd{}; kd.L = 1; kd.H = H; kd.Hkv = Hkv; kd.Dh = Dh; kd.B = 1; kd.S = S; kd.W = W; kd.M = W; kd.kvp = 1;
-        return fc_attn_plain(q, H * Dh, kc, vc, dt, kd, 0, (const int32_t*)sc, out, st);
+        return fc_attn_plain(q, H * Dh, kc, vc, dt, kd, 0, (const int32_t*)sc, 0, out, st);
     }
     AttnArgs at; memset(&at, 0, sizeof(at));
     at.q = q; at.ldq = H * 128; at.kc = (const bf16_t*)kc; at.vc = (const bf16_t*)vc; at.layer = 0; at.B = 1; at.H = H;

@@ -5,18 +5,30 @@
 // text of the last failure of a context-less call (what fastcot_last_error(NULL) returns)
 void fc_set_error(const char* msg);
 
-// ---- plain kernels (one thread per output; used for fp32 models and as the on-device cross-check)
+// ---- plain kernels (fp32 arithmetic without matrix cores; used for fp32 models and as the on-device cross-check)
 // x[m] = embedding of win[m] (dense), or of win[rowb[m] * W + rowj[m]] with a row map
 hipError_t fc_embed(const void* emb, int dt, const int32_t* win, float* x, int M, int d, int V, hipStream_t st,
                     RowMap rm = RowMap{nullptr, nullptr, nullptr}, int W = 0);
-hipError_t fc_rmsnorm_plain(const float* x, const float* g, float* out, int M, int d, float eps, hipStream_t st);
+// argument block of the plain GEMM (a norm in front where gain is given; the QKV fields only for fc_qkv_plain)
+struct PlainGemm {
+    const void* W; int32_t K, NP, N;       // fused matrix: K inputs, N of NP columns
+    const float* X; int32_t ldx;
+    float* Y; int32_t ldy, M;
+    const float* gain; float eps;
+    KernelDims kd; int32_t layer;
+    float* qrot; const int32_t* n_state; const float* cosT; const float* sinT; void* kc; void* vc;
+};
 hipError_t fc_gemm_plain(const void* W, int dt, int K, int NP, int N, const float* X, int ldx, float* Y, int ldy,
-                         int M, int accumulate, hipStream_t st);
-hipError_t fc_rope_cache_plain(const float* qkv, float* qrot, const KernelDims& kd, int layer, const int32_t* n_state,
-                               const float* cosT, const float* sinT, void* kc, void* vc, int dt, hipStream_t st);
+                         int M, int accumulate, hipStream_t st, const float* gain = nullptr, float eps = 0.f);
+// QKV product of the normed rows, rotary embedding and cache write; qkv keeps the product as it was before the rotation
+hipError_t fc_qkv_plain(const void* W, int dt, const KernelDims& kd, int layer, const float* X, const float* gain, float* qkv, float* qrot,
+                        const int32_t* n_state, const float* cosT, const float* sinT, void* kc, void* vc, hipStream_t st);
+// committed lengths from n_state[b], or n_host for every sequence where that is NULL
 hipError_t fc_attn_plain(const float* q, int ldq, const void* kc, const void* vc, int dt, const KernelDims& kd,
-                         int layer, const int32_t* n_state, float* out, hipStream_t st);
-hipError_t fc_swiglu_plain(const float* gu, float* h, int M, int F, int ldgu, hipStream_t st);
+                         int layer, const int32_t* n_state, int n_host, float* out, hipStream_t st);
+// gate/up product of the normed rows and SwiGLU: h [M][F]
+hipError_t fc_swiglu_plain(const void* W, int dt, int K, int F, const float* X, int ldx, float* h, int M, const float* gain,
+                           float eps, hipStream_t st);
 hipError_t fc_argmax_plain(const float* logits, int M, int V, int32_t* ids, float* top, hipStream_t st);
 
 // ---- decoding-state kernels

@@ -1,8 +1,8 @@
-// Plain kernels: one thread per output element, fp32 arithmetic, no matrix cores.
-// They run fp32 models (the small parity configuration) and serve as the on-device
-// cross-check of the MFMA kernels.  Each follows the model definition the benchmark
-// configurations fix (RMSNorm, rotary embedding pairing i with i + Dh/2, grouped-query
-// attention with the causal mask of Eq. (2), SwiGLU).
+// Plain kernels: fp32 arithmetic, no matrix cores.  They run fp32 models (the small parity configuration) and
+// bf16 shapes the MFMA kernels do not cover, and serve as the on-device cross-check of the MFMA kernels.  Each
+// follows the model definition the benchmark configurations fix (RMSNorm, rotary embedding pairing i with
+// i + Dh/2, grouped-query attention with the causal mask of Eq. (2), SwiGLU).  Like the MFMA path a layer is five
+// launches: QKV (norm, rotary embedding and cache write inside), attention, O, gate/up (norm and SwiGLU inside), down.
 #include "kernels.h"
 
 template <int DT> __device__ inline float wat(const void* W, size_t i) {
@@ -25,15 +25,31 @@ template <int DT> __device__ inline void kvstore(void* C, size_t i, size_t plane
     ((bf16_t*)C)[i] = hi;
     if (kvp == 2) ((bf16_t*)C)[i + plane] = f32_to_bf16(v - bf16_to_f32(hi));
 }
-template <int DT> __device__ inline float kvload(const void* C, size_t i, size_t plane, int kvp) {
-    if (DT == FASTCOT_F32) return ((const float*)C)[i];
+// eight cached values that lie next to each other in plane 0 (i a multiple of 8)
+template <int DT> __device__ inline void kvload8(const void* C, size_t i, size_t plane, int kvp, float (&v)[8]) {
+    if (DT == FASTCOT_F32) {
+        const float4 a = *(const float4*)((const float*)C + i), b = *(const float4*)((const float*)C + i + 4);
+        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+        return;
+    }
+    const uint4 h = *(const uint4*)((const bf16_t*)C + i);
+    const uint32_t hw[4] = {h.x, h.y, h.z, h.w};
     if (kvp == 3) {
         const size_t blk = i / plane * plane;
-        return kv24_join(((const bf16_t*)C)[i], ((const uint8_t*)((const bf16_t*)C + blk + plane))[i - blk]);
+        const uint2 r = *(const uint2*)((const uint8_t*)((const bf16_t*)C + blk + plane) + (i - blk));
+        const uint32_t rw[2] = {r.x, r.y};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = kv24_join((hw[e >> 1] >> (16 * (e & 1))) & 0xFFFFu, (rw[e >> 2] >> (8 * (e & 3))) & 0xFFu);
+        return;
     }
-    float v = bf16_to_f32(((const bf16_t*)C)[i]);
-    if (kvp == 2) v += bf16_to_f32(((const bf16_t*)C)[i + plane]);
-    return v;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) { v[2 * p] = __uint_as_float(hw[p] << 16); v[2 * p + 1] = __uint_as_float(hw[p] & 0xFFFF0000u); }
+    if (kvp == 2) {
+        const uint4 l = *(const uint4*)((const bf16_t*)C + i + plane);
+        const uint32_t lw[4] = {l.x, l.y, l.z, l.w};
+#pragma unroll
+        for (int p = 0; p < 4; ++p) { v[2 * p] += __uint_as_float(lw[p] << 16); v[2 * p + 1] += __uint_as_float(lw[p] & 0xFFFF0000u); }
+    }
 }
 
 // ------------------------------------------------------------------ embedding gather
@@ -60,7 +76,160 @@ hipError_t fc_embed(const void* emb, int dt, const int32_t* win, float* x, int M
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ RMSNorm
+// ------------------------------------------------------------------ GEMM  Y[m][n] (+)= sum_k norm(X)[m][k] W[k][n]
+// Bound by latency at the sizes it is meant for (256-wide fp32 layers: all weights in L2, a launch is a few load
+// round trips), so K is spread wide and nothing is staged: eight waves, wave w on k-tiles of 32 inputs w, w + 8, ...;
+// lane (column lm, octet g) loads 8 weights of its column and the 8 inputs of every row (the 16 lanes of an octet
+// share the address), and the partial sums meet by two lane exchanges and one LDS round.  A workgroup computes 8 rows
+// x 16 * NC columns: NC = 1 gives the most workgroups; NC = 4 reads the activations once for four tiles.  A norm in
+// front (gain != NULL) costs no pass of its own: the gain multiplies the inputs, the row's 1 / rms the sums.
+// One thread per output with K serial, as it was, took 34-88 us for each product of the 256-wide model; this takes
+// 5-6.6 us.
+enum { PEPI_STORE = 0, PEPI_ADD = 1, PEPI_SWIGLU = 2, PEPI_QKV = 3 };
+template <int DT, int EPI, int NC>
+__global__ __launch_bounds__(512) void k_gemm_plain(PlainGemm a) {
+    constexpr int RB = 8;
+    __shared__ float part[8][NC][RB][16];
+    __shared__ float part_ss[8][RB];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, lm = lane & 15, g = lane >> 4;
+    const int nt0 = blockIdx.x * NC, m0 = blockIdx.y * RB, NT = a.NP >> 4, KT = (a.K + 31) >> 5;
+    const float* xr[RB];
+#pragma unroll
+    for (int r = 0; r < RB; ++r) xr[r] = a.X + (size_t)(m0 + r < a.M ? m0 + r : a.M - 1) * a.ldx;   // rows past M repeat the last one, never written
+    float acc[NC][RB], ss[RB];
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+        ss[r] = 0.f;
+#pragma unroll
+        for (int j = 0; j < NC; ++j) acc[j][r] = 0.f;
+    }
+#pragma unroll 2
+    for (int kt = w; kt < KT; kt += 8) {
+        const bool in = kt * 32 + 8 * g < a.K;             // K is a multiple of 16: an octet is inside or past the end
+        const int k0 = in ? kt * 32 + 8 * g : 0;
+        float wv[NC][8];
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            const int nt = nt0 + j < NT ? nt0 + j : NT - 1;
+            if (DT == FASTCOT_F32) {
+                const float* p = (const float*)a.W + (size_t)k0 * a.NP + nt * 16 + lm;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) wv[j][e] = p[(size_t)e * a.NP];
+            } else {
+                const uint4 h = *((const uint4*)a.W + ((size_t)nt * (a.K >> 5) + kt) * 64 + lane);
+                const uint32_t hw[4] = {h.x, h.y, h.z, h.w};
+#pragma unroll
+                for (int p = 0; p < 4; ++p) { wv[j][2 * p] = __uint_as_float(hw[p] << 16); wv[j][2 * p + 1] = __uint_as_float(hw[p] & 0xFFFF0000u); }
+            }
+        }
+        float gv[8];
+        if (a.gain) {
+            const float4 g0 = *(const float4*)(a.gain + k0), g1 = *(const float4*)(a.gain + k0 + 4);
+            gv[0] = g0.x; gv[1] = g0.y; gv[2] = g0.z; gv[3] = g0.w; gv[4] = g1.x; gv[5] = g1.y; gv[6] = g1.z; gv[7] = g1.w;
+        }
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const float4 x0 = *(const float4*)(xr[r] + k0), x1 = *(const float4*)(xr[r] + k0 + 4);
+            float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                x[e] = in ? x[e] : 0.f;
+                if (a.gain) { ss[r] += x[e] * x[e]; x[e] *= gv[e]; }
+#pragma unroll
+                for (int j = 0; j < NC; ++j) acc[j][r] += x[e] * wv[j][e];
+            }
+        }
+    }
+    // octets: two exchanges; then each of the four octet groups publishes two rows of the wave's sums
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            acc[j][r] += __shfl_xor(acc[j][r], 16, 64);
+            acc[j][r] += __shfl_xor(acc[j][r], 32, 64);
+            if (g == (r >> 1)) part[w][j][r][lm] = acc[j][r];
+        }
+        if (a.gain) {
+            ss[r] += __shfl_xor(ss[r], 16, 64);
+            ss[r] += __shfl_xor(ss[r], 32, 64);
+            if (lane == 0) part_ss[w][r] = ss[r];
+        }
+    }
+    __syncthreads();
+    if (tid >= NC * 128) return;
+    const int j = tid >> 7, r = (tid >> 4) & 7, c = tid & 15, m = m0 + r, nt = nt0 + j, n = nt * 16 + c;
+    float v = 0.f;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v += part[q][j][r][c];
+    if (a.gain) {
+        float s = 0.f;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s += part_ss[q][r];
+        v *= 1.0f / sqrtf(s / (float)a.K + a.eps);
+    }
+    const float other = __shfl_xor(v, 8, 64);             // the value 8 columns away: rotary partner, or gate <-> up
+    if (m >= a.M || nt >= NT) return;
+    if (EPI == PEPI_STORE) { if (n < a.N) a.Y[(size_t)m * a.ldy + n] = v; }
+    else if (EPI == PEPI_ADD) { if (n < a.N) a.Y[(size_t)m * a.ldy + n] += v; }
+    else if (EPI == PEPI_SWIGLU) {                         // columns 0..7 of a tile: gate of features 8 * nt ..; 8..15: their up values
+        if (c < 8) a.Y[(size_t)m * a.ldy + nt * 8 + c] = v / (1.0f + expf(-v)) * other;
+    } else {
+        // row m = b*W + j sits at absolute position n[b] + j; the product is in packed column order (head_col).
+        // Rotated q goes to qrot in natural order, k heads are rotated and stored to the K cache, v heads stored to
+        // the transposed V cache.
+        const KernelDims& kd = a.kd;
+        const int b = m / kd.W, pos = a.n_state[b] + m % kd.W, half = kd.Dh >> 1, hh = n / kd.Dh, cc = n % kd.Dh;
+        a.Y[(size_t)m * a.ldy + n] = v;
+        if (pos >= kd.S) return;                           // capacity guard: never write outside the cache
+        const size_t plane = (size_t)kd.S * kd.Dh;
+        if (hh < kd.H + kd.Hkv) {
+            const int i = 8 * (cc >> 4) + (c & 7), el = c < 8 ? i : i + half;
+            const float co = a.cosT[(size_t)pos * half + i], si = a.sinT[(size_t)pos * half + i];
+            const float rot = c < 8 ? v * co - other * si : v * co + other * si;
+            if (hh < kd.H) a.qrot[(size_t)m * kd.H * kd.Dh + (size_t)hh * kd.Dh + el] = rot;
+            else kvstore<DT>(a.kc, kv_block(kd, a.layer, b, hh - kd.H) + k_index(pos, el, kd.Dh), plane, kd.kvp, rot);
+        } else
+            kvstore<DT>(a.vc, kv_block(kd, a.layer, b, hh - kd.H - kd.Hkv) + v_index(cc, pos, kd.Dh), plane, kd.kvp, v);
+    }
+}
+template <int DT, int EPI> static hipError_t launch_gemm_plain(const PlainGemm& a, hipStream_t st) {
+    const int NT = a.NP >> 4, rb = (a.M + 7) / 8;
+    // four tiles per workgroup only where that leaves several workgroups per CU
+    if ((size_t)NT * rb >= 4096) k_gemm_plain<DT, EPI, 4><<<dim3((NT + 3) / 4, rb), 512, 0, st>>>(a);
+    else k_gemm_plain<DT, EPI, 1><<<dim3(NT, rb), 512, 0, st>>>(a);
+    return hipGetLastError();
+}
+template <int DT> static hipError_t launch_gemm_plain_epi(int epi, const PlainGemm& a, hipStream_t st) {
+    switch (epi) {
+        case PEPI_STORE: return launch_gemm_plain<DT, PEPI_STORE>(a, st);
+        case PEPI_ADD: return launch_gemm_plain<DT, PEPI_ADD>(a, st);
+        case PEPI_SWIGLU: return launch_gemm_plain<DT, PEPI_SWIGLU>(a, st);
+        case PEPI_QKV: return launch_gemm_plain<DT, PEPI_QKV>(a, st);
+    }
+    return hipErrorInvalidValue;
+}
+static hipError_t gemm_plain_any(int epi, int dt, const PlainGemm& a, hipStream_t st) {
+    if (a.M < 1 || a.K < 16 || a.K % (dt == FASTCOT_F32 ? 16 : 32) || a.NP < 16 || a.NP % 16 || a.ldx % 4) return hipErrorInvalidValue;
+    return dt == FASTCOT_F32 ? launch_gemm_plain_epi<FASTCOT_F32>(epi, a, st) : launch_gemm_plain_epi<FASTCOT_BF16>(epi, a, st);
+}
+hipError_t fc_gemm_plain(const void* W, int dt, int K, int NP, int N, const float* X, int ldx, float* Y, int ldy,
+                         int M, int accumulate, hipStream_t st, const float* gain, float eps) {
+    PlainGemm a{}; a.W = W; a.K = K; a.NP = NP; a.N = N; a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy; a.M = M; a.gain = gain; a.eps = eps;
+    return gemm_plain_any(accumulate ? PEPI_ADD : PEPI_STORE, dt, a, st);
+}
+hipError_t fc_swiglu_plain(const void* W, int dt, int K, int F, const float* X, int ldx, float* h, int M, const float* gain,
+                           float eps, hipStream_t st) {
+    PlainGemm a{}; a.W = W; a.K = K; a.NP = a.N = 2 * F; a.X = X; a.ldx = ldx; a.Y = h; a.ldy = F; a.M = M; a.gain = gain; a.eps = eps;
+    return gemm_plain_any(PEPI_SWIGLU, dt, a, st);
+}
+hipError_t fc_qkv_plain(const void* W, int dt, const KernelDims& kd, int layer, const float* X, const float* gain, float* qkv, float* qrot,
+                        const int32_t* n_state, const float* cosT, const float* sinT, void* kc, void* vc, hipStream_t st) {
+    PlainGemm a{}; a.W = W; a.K = kd.d; a.NP = a.N = kd.qkvN; a.X = X; a.ldx = kd.d; a.Y = qkv; a.ldy = kd.qkvN; a.M = kd.M;
+    a.gain = gain; a.eps = kd.eps; a.kd = kd; a.layer = layer; a.qrot = qrot; a.n_state = n_state; a.cosT = cosT; a.sinT = sinT; a.kc = kc; a.vc = vc;
+    return gemm_plain_any(PEPI_QKV, dt, a, st);
+}
+
+// ------------------------------------------------------------------ window-causal attention
 __device__ inline float block_sum(float v, float* red) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
     int w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
@@ -71,157 +240,77 @@ __device__ inline float block_sum(float v, float* red) {
     for (int i = 0; i < nw; ++i) s += red[i];
     return s;
 }
-__global__ void k_rmsnorm(const float* x, const float* g, float* out, int d, float eps) {
-    __shared__ float red[16];
-    const float* xr = x + (size_t)blockIdx.x * d;
-    float ss = 0;
-    for (int i = threadIdx.x; i < d; i += blockDim.x) ss += xr[i] * xr[i];
-    ss = block_sum(ss, red);
-    float r = 1.0f / sqrtf(ss / (float)d + eps);
-    for (int i = threadIdx.x; i < d; i += blockDim.x) out[(size_t)blockIdx.x * d + i] = xr[i] * r * g[i];
-}
-hipError_t fc_rmsnorm_plain(const float* x, const float* g, float* out, int M, int d, float eps, hipStream_t st) {
-    k_rmsnorm<<<M, 256, 0, st>>>(x, g, out, d, eps);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ GEMM  Y[m][n] (+)= sum_k X[m][k] W[k][n]
+// One workgroup (4 waves) per (row m, query head h): scores over cache positions 0 .. n[b]+j, softmax, weighted V.
+// Both passes read the cache in its own fragment order, eight values per lane and load: a wave takes 16 keys (lane =
+// key r, quarter p of the head elements; two exchanges add the quarters), then 16 head elements x 32 positions
+// (lane = element, octet of positions), and the waves' sums over their blocks meet in LDS.  With a thread per key and
+// a thread per head element walking all keys one by one a 64-row window over 1088 keys and 40 heads took 647 us; now 172 us.
 template <int DT>
-__global__ void k_gemm_plain(const void* W, int K, int NP, int N, const float* X, int ldx, float* Y, int ldy,
-                             int M, int accumulate) {
-    constexpr int RB = 8;
-    int n = blockIdx.x * blockDim.x + threadIdx.x;
-    int m0 = blockIdx.y * RB;
-    if (n >= N) return;
-    float acc[RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r) acc[r] = 0.f;
-    for (int k = 0; k < K; ++k) {
-        float w = (DT == FASTCOT_F32) ? ((const float*)W)[(size_t)k * NP + n]
-                                      : bf16_to_f32(((const bf16_t*)W)[frag_index(K, k, n)]);
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            int m = m0 + r < M ? m0 + r : M - 1;
-            acc[r] += X[(size_t)m * ldx + k] * w;
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-        if (m0 + r < M) {
-            float* y = Y + (size_t)(m0 + r) * ldy + n;
-            *y = accumulate ? *y + acc[r] : acc[r];
-        }
-}
-hipError_t fc_gemm_plain(const void* W, int dt, int K, int NP, int N, const float* X, int ldx, float* Y, int ldy,
-                         int M, int accumulate, hipStream_t st) {
-    dim3 grid((N + 255) / 256, (M + 7) / 8);
-    if (dt == FASTCOT_F32) k_gemm_plain<FASTCOT_F32><<<grid, 256, 0, st>>>(W, K, NP, N, X, ldx, Y, ldy, M, accumulate);
-    else k_gemm_plain<FASTCOT_BF16><<<grid, 256, 0, st>>>(W, K, NP, N, X, ldx, Y, ldy, M, accumulate);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ rotary embedding + KV-cache write
-// Row m = b*W + j sits at absolute position n[b] + j.  The GEMM output row is in packed column
-// order (head_col); rotated q goes to qrot in natural order, k heads are rotated and stored to the
-// K cache, v heads stored to the transposed V cache.
-template <int DT>
-__global__ void k_rope_cache(const float* qkv, float* qrot, KernelDims kd, int layer, const int32_t* n_state,
-                             const float* cosT, const float* sinT, void* kc, void* vc) {
-    int m = blockIdx.x, b = m / kd.W, j = m % kd.W;
-    int pos = n_state[b] + j;
-    if (pos >= kd.S) return;  // capacity guard: never write outside the cache
-    int half = kd.Dh / 2;
-    const size_t plane = (size_t)kd.S * kd.Dh;
-    const float* row = qkv + (size_t)m * kd.qkvN;
-    int nrot = (kd.H + kd.Hkv) * half;
-    for (int i = threadIdx.x; i < nrot; i += blockDim.x) {
-        int hh = i / half, e = i % half;
-        float c = cosT[(size_t)pos * half + e], s = sinT[(size_t)pos * half + e];
-        const float* v = row + (size_t)hh * kd.Dh;
-        float a = v[head_col(e, kd.Dh)], bb = v[head_col(e + half, kd.Dh)];
-        float ra = a * c - bb * s, rb = bb * c + a * s;
-        if (hh < kd.H) {
-            float* q = qrot + (size_t)m * kd.H * kd.Dh + (size_t)hh * kd.Dh;
-            q[e] = ra; q[e + half] = rb;
-        } else {
-            int kh = hh - kd.H;
-            size_t base = kv_block(kd, layer, b, kh);
-            kvstore<DT>(kc, base + k_index(pos, e, kd.Dh), plane, kd.kvp, ra);
-            kvstore<DT>(kc, base + k_index(pos, e + half, kd.Dh), plane, kd.kvp, rb);
-        }
-    }
-    const float* vrow = row + (size_t)(kd.H + kd.Hkv) * kd.Dh;
-    for (int i = threadIdx.x; i < kd.Hkv * kd.Dh; i += blockDim.x) {
-        int kh = i / kd.Dh, e = i % kd.Dh;
-        size_t base = kv_block(kd, layer, b, kh) + v_index(e, pos, kd.Dh);
-        kvstore<DT>(vc, base, plane, kd.kvp, vrow[i]);
-    }
-}
-hipError_t fc_rope_cache_plain(const float* qkv, float* qrot, const KernelDims& kd, int layer, const int32_t* n_state,
-                               const float* cosT, const float* sinT, void* kc, void* vc, int dt, hipStream_t st) {
-    if (dt == FASTCOT_F32) k_rope_cache<FASTCOT_F32><<<kd.M, 256, 0, st>>>(qkv, qrot, kd, layer, n_state, cosT, sinT, kc, vc);
-    else k_rope_cache<FASTCOT_BF16><<<kd.M, 256, 0, st>>>(qkv, qrot, kd, layer, n_state, cosT, sinT, kc, vc);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ window-causal attention
-// One block per (row m, query head h): scores over cache positions 0 .. n[b]+j, softmax, weighted V.
-template <int DT>
-__global__ void k_attn_plain(const float* q, int ldq, const void* kc, const void* vc, KernelDims kd, int layer,
-                             const int32_t* n_state, float* out) {
-    extern __shared__ float sc[];   // [S] scores, then [16] reduction scratch
-    float* red = sc + kd.S;
-    int m = blockIdx.x, h = blockIdx.y, b = m / kd.W, j = m % kd.W;
-    int last = n_state[b] + j;
+__global__ __launch_bounds__(256) void k_attn_plain(const float* q, int ldq, const void* kc, const void* vc, KernelDims kd, int layer,
+                                                    const int32_t* n_state, int n_host, float* out) {
+    extern __shared__ float sc[];   // [S] scores, [Dh] the query, [4][Dh] sums of the waves, [16] reduction scratch
+    float* qs = sc + kd.S; float* wsum = qs + kd.Dh; float* red = wsum + 4 * kd.Dh;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 15, p = lane >> 4;
+    const int m = blockIdx.x, h = blockIdx.y, b = m / kd.W, j = m % kd.W;
+    int last = (n_state ? n_state[b] : n_host) + j;
     if (last >= kd.S) last = kd.S - 1;
-    int kh = h / (kd.H / kd.Hkv);
-    const float* qv = q + (size_t)m * ldq + (size_t)h * kd.Dh;
-    const size_t kbase = kv_block(kd, layer, b, kh), plane = (size_t)kd.S * kd.Dh;
-    float scale = 1.0f / sqrtf((float)kd.Dh);
+    const int kh = h / (kd.H / kd.Hkv), Dh = kd.Dh, G = Dh >> 5, NB = (last >> 5) + 1;
+    const size_t kbase = kv_block(kd, layer, b, kh), plane = (size_t)kd.S * Dh;
+    for (int i = tid; i < Dh; i += 256) qs[i] = q[(size_t)m * ldq + (size_t)h * Dh + i];
+    __syncthreads();
+    const float scale = 1.0f / sqrtf((float)Dh);
     float mx = -3.0e38f;
-    for (int t = threadIdx.x; t <= last; t += blockDim.x) {
-        float s = 0;
-        for (int i = 0; i < kd.Dh; ++i) s += qv[i] * kvload<DT>(kc, kbase + k_index(t, i, kd.Dh), plane, kd.kvp);
+    for (int hb = w; hb < 2 * NB; hb += 4) {               // half block: tile hb % 2 of key block hb / 2
+        const int pos = (hb >> 1) * 32 + 8 * (r >> 2) + 4 * (hb & 1) + (r & 3);
+        float s = 0.f;
+#pragma unroll 4
+        for (int i = 0; i < G; ++i) {
+            float kv[8];
+            kvload8<DT>(kc, kbase + (size_t)(hb >> 1) * 32 * Dh + (size_t)(((hb & 1) * 4 + p) * 16 * G + r + 16 * i) * 8, plane, kd.kvp, kv);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s += qs[32 * i + 8 * p + e] * kv[e];
+        }
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
         s *= scale;
-        sc[t] = s;
-        mx = fmaxf(mx, s);
+        if (pos <= last) { if (p == 0) sc[pos] = s; mx = fmaxf(mx, s); }
     }
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_down(mx, o, 64));
-    int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    if ((threadIdx.x & 63) == 0) red[w] = mx;
+    for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    if (lane == 0) red[w] = mx;
     __syncthreads();
-    mx = red[0];
-    for (int i = 1; i < nw; ++i) mx = fmaxf(mx, red[i]);
-    float den = 0;
-    for (int t = threadIdx.x; t <= last; t += blockDim.x) { float e = expf(sc[t] - mx); sc[t] = e; den += e; }
-    den = block_sum(den, red);
-    __syncthreads();
-    for (int i = threadIdx.x; i < kd.Dh; i += blockDim.x) {
-        float acc = 0;                          // transposed V in blocks of 32 positions
-        for (int t = 0; t <= last; ++t) acc += sc[t] * kvload<DT>(vc, kbase + v_index(i, t, kd.Dh), plane, kd.kvp);
-        out[(size_t)m * kd.H * kd.Dh + (size_t)h * kd.Dh + i] = acc / den;
+    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    float den = 0.f;
+    for (int t = tid; t <= last; t += 256) { const float e = expf(sc[t] - mx); sc[t] = e; den += e; }
+    den = block_sum(den, red);                             // (its first barrier also publishes the weights)
+    for (int dt = 0; dt < Dh >> 4; ++dt) {
+        float acc = 0.f;
+#pragma unroll 4
+        for (int blk = w; blk < NB; blk += 4) {
+            float kv[8];
+            kvload8<DT>(vc, kbase + (size_t)blk * 32 * Dh + (size_t)(dt * 64 + lane) * 8, plane, kd.kvp, kv);
+            const int t0 = blk * 32 + 8 * p;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc += t0 + e <= last ? sc[t0 + e] * kv[e] : 0.f;
+        }
+        acc += __shfl_xor(acc, 16, 64);
+        acc += __shfl_xor(acc, 32, 64);
+        if (p == 0) wsum[w * Dh + dt * 16 + r] = acc;
     }
+    __syncthreads();
+    for (int i = tid; i < Dh; i += 256)
+        out[(size_t)m * kd.H * Dh + (size_t)h * Dh + i] = (wsum[i] + wsum[Dh + i] + wsum[2 * Dh + i] + wsum[3 * Dh + i]) / den;
 }
 hipError_t fc_attn_plain(const float* q, int ldq, const void* kc, const void* vc, int dt, const KernelDims& kd,
-                         int layer, const int32_t* n_state, float* out, hipStream_t st) {
+                         int layer, const int32_t* n_state, int n_host, float* out, hipStream_t st) {
     dim3 grid(kd.M, kd.H);
-    size_t sh = ((size_t)kd.S + 16) * sizeof(float);
-    if (dt == FASTCOT_F32) k_attn_plain<FASTCOT_F32><<<grid, 128, sh, st>>>(q, ldq, kc, vc, kd, layer, n_state, out);
-    else k_attn_plain<FASTCOT_BF16><<<grid, 128, sh, st>>>(q, ldq, kc, vc, kd, layer, n_state, out);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ SwiGLU on the fused gate/up output
-__global__ void k_swiglu(const float* gu, float* h, int M, int F, int ldgu) {
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (size_t)M * F) return;
-    int m = (int)(i / F), f = (int)(i % F);
-    float g = gu[(size_t)m * ldgu + gu_col(f, 0)], u = gu[(size_t)m * ldgu + gu_col(f, 1)];
-    h[i] = g / (1.0f + expf(-g)) * u;
-}
-hipError_t fc_swiglu_plain(const float* gu, float* h, int M, int F, int ldgu, hipStream_t st) {
-    size_t n = (size_t)M * F;
-    k_swiglu<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(gu, h, M, F, ldgu);
+    const size_t sh = ((size_t)kd.S + 5 * kd.Dh + 16) * sizeof(float);
+    const void* fn = dt == FASTCOT_F32 ? (const void*)k_attn_plain<FASTCOT_F32> : (const void*)k_attn_plain<FASTCOT_BF16>;
+    if (sh > 64 * 1024) {                                  // the longest caches: past the default limit of a launch
+        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+    }
+    if (dt == FASTCOT_F32) k_attn_plain<FASTCOT_F32><<<grid, 256, sh, st>>>(q, ldq, kc, vc, kd, layer, n_state, n_host, out);
+    else k_attn_plain<FASTCOT_BF16><<<grid, 256, sh, st>>>(q, ldq, kc, vc, kd, layer, n_state, n_host, out);
     return hipGetLastError();
 }
 

@@ -1,0 +1,75 @@
+"""GPU parity of single kernels at the sizes where their tilings end: against the same operation in 64 bits.
+
+Tolerances: a fp32 dot product of n terms summed in pieces of at most s carries a relative error of about
+sqrt(s) * 2^-24 against the norm of its terms; with activations, queries or probabilities as a bf16 hi + lo pair every
+factor adds at most 2^-17.  The bounds below are a few times that."""
+import numpy as np
+import pytest
+
+from gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fc():
+    import paper_2311_08263_amd as m
+    return m
+
+
+def rel(a, b):
+    import torch
+    a, b = a.double(), b.double()
+    return float(torch.linalg.norm(a - b) / torch.linalg.norm(b))
+
+
+def attn64(q, k, v, n):
+    import torch
+    W, H, Dh = q.shape
+    G = H // k.shape[1]
+    kk, vv = k.double().repeat_interleave(G, 1).permute(1, 0, 2), v.double().repeat_interleave(G, 1).permute(1, 0, 2)
+    s = torch.bmm(q.double().permute(1, 0, 2).contiguous(), kk.transpose(1, 2).contiguous()) / Dh ** 0.5
+    seen = torch.arange(n + W, device="cuda")[None, :] <= n + torch.arange(W, device="cuda")[:, None]
+    p = torch.softmax(s.masked_fill(~seen[None], float("-inf")), -1)
+    return torch.bmm(p, vv.contiguous()).permute(1, 0, 2).reshape(W, H * Dh)
+
+
+def attn_inputs(n, W, H, Hkv, Dh, dtype, seed=3):
+    import torch
+    g = torch.Generator(device="cuda"); g.manual_seed(seed)
+    q = torch.randn(W, H, Dh, generator=g, device="cuda")
+    k = torch.randn(n + W, Hkv, Dh, generator=g, device="cuda").to(dtype)
+    v = torch.randn(n + W, Hkv, Dh, generator=g, device="cuda").to(dtype)
+    return q, k, v
+
+
+@pytest.mark.parametrize("n,W,H,Hkv,Dh,f32", [(0, 1, 2, 2, 32, 1), (31, 1, 4, 4, 64, 1), (32, 9, 4, 2, 64, 1), (777, 3, 3, 1, 96, 1),
+                                              (130, 40, 4, 2, 256, 1), (500, 2, 4, 2, 64, 0), (15900, 2, 2, 1, 128, 1)])
+def test_plain_attention(fc, n, W, H, Hkv, Dh, f32):
+    """fp32 caches, and bf16 ones the matrix-core kernel does not cover: half blocks of 16 keys, the last partial
+    octet, head sizes of 1 to 8 groups, a cache whose scores need more than 64 KB of LDS.  Dot products are summed
+    in at most Dh + (n + W) / 32 terms at a time."""
+    import torch
+    say(f"plain attention n={n} W={W} H={H}/{Hkv} Dh={Dh} f32={f32}")
+    q, k, v = attn_inputs(n, W, H, Hkv, Dh, torch.float32 if f32 else torch.bfloat16)
+    S = (n + W + 31) // 32 * 32
+    kc, vc = fc.kv_scatter(k, v, S)
+    out = fc.attn_window(q, kc, vc, n)
+    assert rel(out, attn64(q, k, v, n)) < 2e-6
+
+
+@pytest.mark.parametrize("M,d,V", [(1, 32, 16), (9, 96, 1040), (17, 160, 16 * 2001), (40, 608, 16 * 1027)])
+def test_plain_lmhead(fc, M, d, V):
+    """Widths that are no multiple of 256 go through the plain product: k-tiles that leave waves idle, rows past the
+    last block of eight, one and four column tiles per workgroup with a remainder of one and three."""
+    import torch
+    say(f"plain lm head M={M} d={d} V={V}")
+    g = torch.Generator(device="cuda"); g.manual_seed(5)
+    w = (0.02 * torch.randn(d, V, generator=g, device="cuda")).bfloat16()
+    act = torch.randn(M, d, generator=g, device="cuda")
+    ids, top, logits, top2 = fc.lmhead_argmax(act, fc.lmhead_pack(w), V, want_logits=True, want_top2=True)
+    want = act.double() @ w.double()
+    assert rel(logits, want) < 1e-6
+    assert torch.equal(ids.long(), logits.argmax(1)) and torch.equal(top, logits.max(1).values)
+    two = torch.topk(logits, 2, dim=1).values
+    assert torch.equal(top2, two[:, 1])
