@@ -74,7 +74,7 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
     const int Wb = a.rstart ? a.rstart[b + 1] - a.rstart[b] : a.W, rbase = a.rstart ? a.rstart[b] : b * a.W;
     const int row0 = SUBR * sub, Wr = Wb - row0 < SUBR ? Wb - row0 : SUBR;        // rows of this unit
     if (Wr <= 0) return;                                     // a sequence with a smaller window of its own
-    const int n = a.n_state[b] + row0;                       // positions every row of the unit sees
+    const int n = (a.n_state ? a.n_state[b] : a.n_host) + row0;                       // positions every row of the unit sees
     int T = n + Wr;
     if (T > a.S) T = a.S;                                    // capacity guard (the host checks first)
     const int NB = (T + 31) >> 5;

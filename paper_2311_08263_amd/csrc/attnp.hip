@@ -38,7 +38,7 @@ __global__ __launch_bounds__(256, 2) void k_attnp(AttnArgs a) {
     // blocks of a head run latest first: they see the most keys
     const int bh = blockIdx.x / nrb, rbk = nrb - 1 - (int)(blockIdx.x % nrb);
     const int hr = bh % a.H, G = a.H / a.Hkv, kvh = hr % a.Hkv, h = kvh * G + hr / a.Hkv, b = bh / a.H;
-    const int n = a.n_state[b];
+    const int n = a.n_state ? a.n_state[b] : a.n_host;
     const int Wb = a.rstart ? a.rstart[b + 1] - a.rstart[b] : a.W, rbase = a.rstart ? a.rstart[b] : b * a.W;
     const int row_base = 128 * rbk, rows_wg = Wb - row_base < 128 ? Wb - row_base : 128;
     if (rows_wg <= 0) return;                             // a sequence with a smaller window of its own

@@ -86,7 +86,7 @@ extern "C" int fastcot_attn_window(const float* d_q, const void* d_k_cache, cons
 // caller buffer.  Every GPU holds its own copy of the array; its address is looked up once per device.
 #define FC_NOALLOC_MAX_H 64
 #define FC_NOALLOC_MAX_W 16
-#define FC_NOALLOC_BYTES (512 + (size_t)FC_NOALLOC_MAX_H * FC_MAX_ATTN_SPLITS * (8 * 64 * 4 + 128) * 4)
+#define FC_NOALLOC_BYTES (256 + (size_t)FC_MAX_COUNTERS * 4 + (size_t)FC_NOALLOC_MAX_H * FC_MAX_ATTN_SPLITS * (8 * 64 * 4 + 128) * 4)
 static __device__ __align__(256) unsigned char scratch[FC_NOALLOC_BYTES];
 #define FC_NOALLOC_MAX_DEVICES 64
 static void* g_scratch_ptr[FC_NOALLOC_MAX_DEVICES];
