@@ -18,6 +18,7 @@ struct AttnArgs {
                            // 16 = always one query tile (windows of 17..32 rows as two units that read K/V separately)
     bf16_t* ofrag;         // not NULL: the output also as bf16 hi + lo B-fragments [row tile][H*128/32][hi|lo][64][8],
                            // the layout the many-row O projection reads
+    int32_t terms;         // bf16 parts of queries and probabilities: 3, or 2 for any other value (see attn16.hip)
     float* part;           // split partials
     int32_t* cnt;          // one arrival counter per (sequence, head), zero between launches
     int32_t bpw;           // key blocks (of 32) per workgroup that decide how many of the launched splits are used

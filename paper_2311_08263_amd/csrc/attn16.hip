@@ -32,6 +32,21 @@ __device__ inline void split8(const float* v, Frag& hi, Frag& lo) {
     lo.u = (u32x4_t){l[0], l[1], l[2], l[3]};
 }
 
+// three bf16 parts: what hi and lo leave over of a fp32 value fits a third
+__device__ inline void split8(const float* v, Frag& hi, Frag& lo, Frag& lo2) {
+    uint32_t h[4], l[4], m[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float a = v[2 * e], b = v[2 * e + 1];
+        h[e] = pk_bf16(a, b);
+        const float ra = a - __uint_as_float(h[e] << 16), rb = b - __uint_as_float(h[e] & 0xFFFF0000u);
+        pk_bf16_hilo(ra, rb, l[e], m[e]);
+    }
+    hi.u = (u32x4_t){h[0], h[1], h[2], h[3]};
+    lo.u = (u32x4_t){l[0], l[1], l[2], l[3]};
+    lo2.u = (u32x4_t){m[0], m[1], m[2], m[3]};
+}
+
 #define NEG_BIG (-1.0e30f)
 #define PART_FLOATS (8 * 64 * 4 + 128)   // per (bh, split, qt): O^T tiles, then m[64], l[64] per lane
 
@@ -54,7 +69,9 @@ __device__ inline void expand_lo8(const u32x4_t& h, uint32_t b0, uint32_t b1, Fr
 }
 
 // KVP: 1 = one bf16 plane, 2 = bf16 hi + bf16 lo planes, 3 = bf16 hi plane + a plane of 8-bit residuals
-template <int QT, int KVP>
+// TERMS: bf16 parts of a query or probability: 2 (17 bits, what the step's path uses) or 3 (25 bits: all of the fp32
+// value, for windows of more than 32 rows of the isolated call, whose results are those of fp32 arithmetic; KVP 1 only)
+template <int QT, int KVP, int TERMS = 2>
 __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
     extern __shared__ float lds[];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -91,7 +108,7 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
     const bf16_t* vbase = a.vc + ((((size_t)a.layer * a.B + b) * a.Hkv + kvh) * NPL) * plane;
 
     // Q as B operand: lane (row lm, dh 32*g + 8*s + e), hi and lo
-    Frag qh[QT][4], ql[QT][4];
+    Frag qh[QT][4], ql[QT][4], qm[TERMS == 3 ? QT : 1][4];
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {
         int j = qt * 16 + lm;
@@ -101,7 +118,8 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
         for (int s = 0; s < 4; ++s) {
             float4 x0 = *(const float4*)(qr + 8 * s), x1 = *(const float4*)(qr + 8 * s + 4);
             float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-            split8(v, qh[qt][s], ql[qt][s]);
+            if constexpr (TERMS == 3) split8(v, qh[qt][s], ql[qt][s], qm[qt][s]);
+            else split8(v, qh[qt][s], ql[qt][s]);
         }
     }
 
@@ -174,6 +192,7 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
                 for (int s = 0; s < 4; ++s) {
                     sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[0][t][s].v, qh[qt][s].v, sc[t], 0, 0, 0);
                     sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[0][t][s].v, ql[qt][s].v, sc[t], 0, 0, 0);
+                    if constexpr (TERMS == 3) sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[0][t][s].v, qm[qt][s].v, sc[t], 0, 0, 0);
                     if (KVP >= 2)   // lo x lo is below fp32 resolution and is dropped
                         sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[NPL - 1][t][s].v, qh[qt][s].v, sc[t], 0, 0, 0);
                 }
@@ -204,13 +223,15 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
             }
             mrun[qt] = mnew;
             lrun[qt] = lrun[qt] * alpha + ps;
-            Frag ph, pl;
-            split8(p, ph, pl);
+            Frag ph, pl, pm;
+            if constexpr (TERMS == 3) split8(p, ph, pl, pm);
+            else split8(p, ph, pl);
 #pragma unroll
             for (int dt = 0; dt < 8; ++dt) {
                 acc[qt][dt] *= alpha;
                 acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[0][dt].v, ph.v, acc[qt][dt], 0, 0, 0);
                 acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[0][dt].v, pl.v, acc[qt][dt], 0, 0, 0);
+                if constexpr (TERMS == 3) acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[0][dt].v, pm.v, acc[qt][dt], 0, 0, 0);
                 if (KVP >= 2)
                     acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[NPL - 1][dt].v, ph.v, acc[qt][dt], 0, 0, 0);
             }
@@ -393,6 +414,9 @@ hipError_t fc_attn16(const AttnArgs& a, int Bact, int nsplit, hipStream_t st) {
     if (a.kvp == 2) {
         if (QT == 2) k_attn16<2, 2><<<grid, 256, l2, st>>>(a);
         else k_attn16<1, 2><<<grid, 256, l1, st>>>(a);
+    } else if (a.kvp == 1 && a.terms == 3) {
+        if (QT == 2) return hipErrorInvalidValue;        // (three parts of two query tiles do not fit the registers)
+        k_attn16<1, 1, 3><<<grid, 256, l1, st>>>(a);
     } else if (a.kvp == 1) {
         if (QT == 2) k_attn16<2, 1><<<grid, 256, l2, st>>>(a);
         else k_attn16<1, 1><<<grid, 256, l1, st>>>(a);

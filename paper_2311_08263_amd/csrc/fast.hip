@@ -346,7 +346,8 @@ size_t fc_attn_iso_scratch_bytes(int W, int H, int Dh) {
 hipError_t fc_attn_iso(const float* q, const void* kc, const void* vc, int n, int W, int H, int Hkv, int Dh, int S,
                        int dt, float* out, void* scratch, hipStream_t st) {
     char* sc = (char*)scratch;
-    if (dt != FASTCOT_BF16 || Dh != 128 || W > 32 || S % 32 || H > FC_MAX_COUNTERS) {
+    const int units = H * (W > 32 ? (W + 15) / 16 : 1);
+    if (dt != FASTCOT_BF16 || Dh != 128 || S % 32 || units > FC_MAX_COUNTERS) {
         KernelDims kd{}; kd.L = 1; kd.H = H; kd.Hkv = Hkv; kd.Dh = Dh; kd.B = 1; kd.S = S; kd.W = W; kd.M = W; kd.kvp = 1;
         return fc_attn_plain(q, H * Dh, kc, vc, dt, kd, 0, nullptr, n, out, st);
     }
@@ -355,7 +356,15 @@ hipError_t fc_attn_iso(const float* q, const void* kc, const void* vc, int n, in
     at.Hkv = Hkv; at.S = S; at.W = W; at.kvp = 1; at.n_host = n; at.out = out; at.ldo = H * 128;
     at.cnt = (int32_t*)(sc + 256); at.bpw = 2;
     at.part = (float*)(sc + ISO_PART_OFF);
-    return fc_attn16(at, 1, iso_attn_splits(n + W), st);
+    int splits = iso_attn_splits(n + W);
+    // More than 32 rows: units of 16 rows, queries and probabilities as three bf16 parts, because such a call has
+    // always computed in fp32 (error against 64 bits 7e-7; two parts would be 3e-6, three are 3.4e-7); key splits
+    // only while every workgroup has a CU to itself.  64 rows, 1088 keys, 40 heads: plain kernel 172 us, this 15.7 us.
+    if (W > 32) {
+        at.terms = 3; at.subrows = 16;
+        while (splits > 1 && units * splits > fc_num_cus()) --splits;
+    }
+    return fc_attn16(at, 1, splits, st);
 }
 
 // scratch: winners per workgroup [workgroups][32] value + index, then room for logits (plain path only)

@@ -58,6 +58,29 @@ def test_plain_attention(fc, n, W, H, Hkv, Dh, f32):
     assert rel(out, attn64(q, k, v, n)) < 2e-6
 
 
+@pytest.mark.parametrize("n,W,H,Hkv", [(0, 33, 2, 2), (1024, 64, 40, 40), (37, 48, 8, 2), (4000, 49, 4, 1), (5, 300, 3, 3), (777, 96, 64, 8)])
+def test_wide_window_attention(fc, n, W, H, Hkv):
+    """More than 32 rows: units of 16 rows with three-part queries and probabilities, with and without key splits,
+    the last unit of 1 row, grouped heads.  The three parts hold 24 bits, so the bound is that of fp32 sums."""
+    say(f"wide window attention n={n} W={W} H={H}/{Hkv}")
+    import torch
+    q, k, v = attn_inputs(n, W, H, Hkv, 128, torch.bfloat16)
+    kc, vc = fc.kv_scatter(k, v, (n + W + 31) // 32 * 32)
+    assert rel(fc.attn_window(q, kc, vc, n), attn64(q, k, v, n)) < 1e-6
+
+
+def test_one_scratch_for_calls_of_different_shapes(fc):
+    """A scratch zeroed once serves any order of shapes it is large enough for."""
+    import torch
+    say("attention: one scratch, several shapes")
+    shapes = [(2048, 16, 32, 32), (700, 64, 64, 8), (300, 5, 4, 4), (2000, 40, 8, 8), (900, 32, 64, 64), (3000, 33, 4, 4)]
+    scratch = torch.zeros(max(fc.lib().fastcot_attn_scratch_bytes(W, H, 128) for _, W, H, _ in shapes), dtype=torch.uint8, device="cuda")
+    for n, W, H, Hkv in shapes + shapes[::-1]:
+        q, k, v = attn_inputs(n, W, H, Hkv, 128, torch.bfloat16)
+        kc, vc = fc.kv_scatter(k, v, (n + W + 31) // 32 * 32)
+        assert rel(fc.attn_window(q, kc, vc, n, scratch), attn64(q, k, v, n)) < 1.5e-5
+
+
 @pytest.mark.parametrize("M,d,V", [(1, 32, 16), (9, 96, 1040), (17, 160, 16 * 2001), (40, 608, 16 * 1027)])
 def test_plain_lmhead(fc, M, d, V):
     """Widths that are no multiple of 256 go through the plain product: k-tiles that leave waves idle, rows past the
