@@ -157,9 +157,7 @@ hipError_t fc_fast_forward(const FastArgs& a) {
     bool x_frag = false, att_frag = false, h_frag = false;
     const float* next_gain = nullptr;          // gain the next reduction folds into the fragments of x
     // LM head: one winner per row and column block (16, 8 or 4 n-tiles)
-    const int lm_cw = fc_gemm256_cw(EPI_LMHEAD, M, kd.V / 16);
-    const int lm_cols = (fc_gemm256_mode(EPI_LMHEAD, M, d, kd.V / 16, 1, lm_cw) == 3 ? 8 : 4) * lm_cw;
-    const int lm_ncb = (kd.V / 16 + lm_cols - 1) / lm_cols;
+    const int lm_ncb = fc_gemm256_lm_blocks(M, d, kd.V / 16);
     big.amax_val = g.amax_val; big.amax_idx = (int32_t*)(g.amax_val + (size_t)lm_ncb * big.amax_stride);
     int gi = 0;        // which GEMM of the plan
     auto gemm = [&](int epi, const void* W, int K, int N, const float* X, int ldx, const float* gain,
@@ -367,11 +365,18 @@ hipError_t fc_attn_iso(const float* q, const void* kc, const void* vc, int n, in
     return fc_attn16(at, 1, splits, st);
 }
 
-// scratch: winners per workgroup [workgroups][32] value + index, then room for logits (plain path only)
+// scratch: winners per workgroup [workgroups][32] value + index, then room for logits (where they are not asked for),
+// then, for more than 32 rows, the activations as three bf16 parts and the winners per column block
 static int lm_iso_grid(int M, int d, int V) { return fc_gemmco_grid(V / 16, M > 16 ? fc_gemmco_most(32, d, false) : 8); }
+// more than 32 rows of a width the many-row kernel takes, within its 32-bit byte offsets
+static bool lm_iso_many(int M, int d, int V) {
+    return M > 32 && d % 256 == 0 && (size_t)V * d * 2 < ((size_t)1 << 32) && fc_split_bytes(M, d, 3) < ((size_t)1 << 32);
+}
+static size_t lm_iso_logits_end(int M, int V) { return FC_ALIGN((size_t)(V / 16 + 1) * 32 * 8 + 256 + (size_t)M * V * 4); }
 size_t fc_lmhead_iso_scratch_bytes(int M, int d, int V) {
-    const size_t G = (size_t)(V / 16 + 1);
-    return G * 32 * 8 + 256 + (size_t)M * V * 4;
+    const size_t base = lm_iso_logits_end(M, V);
+    if (!lm_iso_many(M, d, V)) return base;
+    return base + FC_ALIGN(fc_split_bytes(M, d, 3)) + (size_t)(V / 64 + 1) * ((M + 15) / 16 * 16) * 8;
 }
 // largest logit of every row among the ids other than the row's winner
 __global__ void k_top2(const float* logits, int V, const int32_t* ids, float* top2) {
@@ -389,6 +394,23 @@ hipError_t fc_lmhead_iso(const float* act, const void* packed, int M, int d, int
     char* sc = (char*)scratch;
     float* lg_scratch = (float*)(sc + (size_t)(V / 16 + 1) * 32 * 8 + 256);
     if (top2 && !logits) logits = lg_scratch;              // the runner-up is read off the logits
+    if (lm_iso_many(M, d, V)) {
+        // the many-row kernel on activations in three bf16 parts: such a call has always computed in fp32, and two
+        // parts would leave the logits 2.3e-6 off.  256 rows x 5120 x 32000: plain product 3.19 ms, this 186 us.
+        const size_t off = lm_iso_logits_end(M, V);
+        Gemm256Args g; memset(&g, 0, sizeof(g));
+        g.W = (const bf16_t*)packed; g.K = d; g.NT = V / 16; g.AF = (bf16_t*)(sc + off); g.planes = 3; g.M = M; g.out = logits; g.ldo = V;
+        g.sk = 1; g.amax_stride = (M + 15) / 16 * 16;
+        g.amax_val = (float*)(sc + off + FC_ALIGN(fc_split_bytes(M, d, 3)));
+        const int ncb = fc_gemm256_lm_blocks(M, d, V / 16);
+        g.amax_idx = (int32_t*)(g.amax_val + (size_t)ncb * g.amax_stride);
+        hipError_t e = fc_split(act, d, M, d, nullptr, 0.f, (bf16_t*)(sc + off), st, 3);
+        if (e == hipSuccess) e = fc_gemm256(EPI_LMHEAD, g, st);
+        if (e == hipSuccess) e = fc_argmax_final(g.amax_val, g.amax_idx, ncb, g.amax_stride, M, ids, top, st);
+        if (e != hipSuccess || !top2) return e;
+        k_top2<<<M, 256, 0, st>>>(logits, V, ids, top2);
+        return hipGetLastError();
+    }
     if (M > 32 || d % 256) {
         float* lg = logits ? logits : lg_scratch;
         hipError_t e = fc_gemm_plain(packed, FASTCOT_BF16, d, V, V, act, d, lg, V, M, 0, st);

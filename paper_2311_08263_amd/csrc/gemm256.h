@@ -6,6 +6,7 @@ struct Gemm256Args {
     const bf16_t* W;       // fused matrix in fragment order
     int32_t K, NT;         // inputs (multiple of 256), n-tiles
     const bf16_t* AF;      // activations as bf16 hi + lo B-fragments [row tile][k-tile][hi|lo][64 lanes][8] (fc_split)
+    int32_t planes;        // 3 = fragments of three parts (LM head only); any other value: hi + lo
     int32_t M;             // rows
     float* out;            // RESID: residual stream (+=); SWIGLU: hidden [M][F]; QKV: q [M][H*128]; LMHEAD: logits or NULL
     int32_t ldo;
@@ -32,9 +33,10 @@ struct Gemm256Args {
 #define FC_GEMM256_MAX_SK 8
 int fc_gemm256_cw(int epi, int M, int NT);          // n-tiles per wave the launcher picks: 4, 2 or 1 (64 x 256, 64 x 128, 64 x 64 tiles)
 int fc_gemm256_mode(int epi, int M, int K, int NT, int sk, int cw);   // 1, 2 or 3: see gemm256.hip; 3 doubles the columns per workgroup
+int fc_gemm256_lm_blocks(int M, int K, int NT);   // column blocks (winners per row) of an LM head launch
 int fc_gemm256_sk(int M, int K, int NT);   // slices that fill the chip for a matrix with few columns
 
 // X [M][ldx] fp32 -> AF; gain != NULL applies RMSNorm (fp32 statistics over the K inputs) first
-hipError_t fc_split(const float* X, int ldx, int M, int K, const float* gain, float eps, bf16_t* AF, hipStream_t st);
-static inline size_t fc_split_bytes(int M, int K) { return (size_t)((M + 15) / 16) * 16 * K * 4; }
+hipError_t fc_split(const float* X, int ldx, int M, int K, const float* gain, float eps, bf16_t* AF, hipStream_t st, int planes = 2);
+static inline size_t fc_split_bytes(int M, int K, int planes = 2) { return (size_t)((M + 15) / 16) * 16 * K * 2 * planes; }
 hipError_t fc_gemm256(int epi, const Gemm256Args& a, hipStream_t st);

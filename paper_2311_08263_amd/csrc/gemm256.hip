@@ -38,7 +38,8 @@ __device__ inline float up16(uint32_t b) { return __uint_as_float(b << 16); }
 // ------------------------------------------------------------------ activation split (+ RMSNorm)
 // grid (row tiles of 16 rows, K chunks); X [M][K] fp32 -> AF [MT][KT][2][64][8] bf16.  With a gain every
 // workgroup computes the statistics of its 16 rows over the whole row (the rows sit in L2) and then
-// converts its own K chunk.
+// converts its own K chunk.  NPL = 3 writes three parts (hi, lo and what the two leave over: all 24 bits).
+template <int NPL>
 __global__ __launch_bounds__(512) void k_split(const float* X, int ldx, int M, int K, const float* gain, float eps,
                                                bf16_t* AF) {
     __shared__ float red[8][16];
@@ -68,7 +69,7 @@ __global__ __launch_bounds__(512) void k_split(const float* X, int ldx, int M, i
         __syncthreads();
         scale = rs[lm];
     }
-    u32x4_t* dst = (u32x4_t*)AF + (size_t)mt * KT * 2 * 64 + lane;
+    u32x4_t* dst = (u32x4_t*)AF + (size_t)mt * KT * NPL * 64 + lane;
     for (int kt = kt_lo + w; kt < kt_hi; kt += 8) {
         const float4 a = *(const float4*)(xr + kt * 32), b = *(const float4*)(xr + kt * 32 + 4);
         float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
@@ -78,20 +79,28 @@ __global__ __launch_bounds__(512) void k_split(const float* X, int ldx, int M, i
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = v[e] * scale * g[e];
         }
-        uint32_t h[4], l[4];
+        uint32_t h[4], l[4], l2[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) pk_bf16_hilo(v[2 * e], v[2 * e + 1], h[e], l[e]);
-        dst[(size_t)kt * 128] = (u32x4_t){h[0], h[1], h[2], h[3]};
-        dst[(size_t)kt * 128 + 64] = (u32x4_t){l[0], l[1], l[2], l[3]};
+        for (int e = 0; e < 4; ++e) {
+            if (NPL == 2) pk_bf16_hilo(v[2 * e], v[2 * e + 1], h[e], l[e]);
+            else {
+                h[e] = pk_bf16(v[2 * e], v[2 * e + 1]);
+                pk_bf16_hilo(v[2 * e] - __uint_as_float(h[e] << 16), v[2 * e + 1] - __uint_as_float(h[e] & 0xFFFF0000u), l[e], l2[e]);
+            }
+        }
+        dst[(size_t)kt * (64 * NPL)] = (u32x4_t){h[0], h[1], h[2], h[3]};
+        dst[(size_t)kt * (64 * NPL) + 64] = (u32x4_t){l[0], l[1], l[2], l[3]};
+        if (NPL == 3) dst[(size_t)kt * (64 * NPL) + 128] = (u32x4_t){l2[0], l2[1], l2[2], l2[3]};
     }
 }
 
-hipError_t fc_split(const float* X, int ldx, int M, int K, const float* gain, float eps, bf16_t* AF, hipStream_t st) {
-    if (M < 1 || K % 256) return hipErrorInvalidValue;
+hipError_t fc_split(const float* X, int ldx, int M, int K, const float* gain, float eps, bf16_t* AF, hipStream_t st, int planes) {
+    if (M < 1 || K % 256 || (planes != 2 && planes != 3)) return hipErrorInvalidValue;
     const int MT = (M + 15) / 16;
     int kc = (512 + MT - 1) / MT;                       // about 512 workgroups, at least 8 k-tiles each
     if (kc > K / 256) kc = K / 256;
-    k_split<<<dim3(MT, kc), 512, 0, st>>>(X, ldx, M, K, gain, eps, AF);
+    if (planes == 3) k_split<3><<<dim3(MT, kc), 512, 0, st>>>(X, ldx, M, K, gain, eps, AF);
+    else k_split<2><<<dim3(MT, kc), 512, 0, st>>>(X, ldx, M, K, gain, eps, AF);
     return hipGetLastError();
 }
 
@@ -106,13 +115,15 @@ hipError_t fc_split(const float* X, int ldx, int M, int K, const float* gain, fl
 // KG = 3: eight waves per workgroup, two groups of four that take neighbouring column blocks (a tile of 64 rows x
 // 128 * CW columns) and share the activation stage; used where that brings the launch down to one workgroup per
 // CU (with four waves two workgroups would share a CU, each staging the same activations).
-template <int EPI, int CW, int KG>
+// NPL = bf16 parts of an activation: 2 (hi + lo), or 3 for the isolated LM head, whose logits are those of fp32
+// arithmetic (eight waves only: 96 KB of stages).
+template <int EPI, int CW, int KG, int NPL = 2>
 __global__ __launch_bounds__(KG == 1 ? 256 : 512, KG == 1 ? 2 : 1) void k_gemm256(Gemm256Args a) {
-    __shared__ u32x4_t stage[2][4][4][2][64];           // [buffer][k-tile][row tile][hi|lo][lane]: 2 x 32 KB
+    __shared__ u32x4_t stage[2][4][4][NPL][64];         // [buffer][k-tile][row tile][part][lane]: 2 x 32 KB (NPL = 2)
     constexpr bool KSPLIT = KG == 2, CSPLIT = KG == 3;
     constexpr int NWV = KG == 1 ? 4 : 8;                 // waves
     __shared__ float rowpart[NWV][64];
-    constexpr int NTH = 64 * NWV, SL = 32 / NWV;         // threads, 16-byte stage loads per thread
+    constexpr int NTH = 64 * NWV, SL = 16 * NPL / NWV;   // threads, 16-byte stage loads per thread
     const int tid = threadIdx.x, lane = tid & 63, w = (tid >> 6) & 3, kg = tid >> 8, w8 = tid >> 6;
     const int lm = lane & 15, g4 = lane >> 4;
     const int KT = a.K >> 5, NS = KT >> 2, MT = (a.M + 15) >> 4;
@@ -146,12 +157,12 @@ __global__ __launch_bounds__(KG == 1 ? 256 : 512, KG == 1 ? 2 : 1) void k_gemm25
 #pragma unroll
     for (int i = 0; i < SL; ++i) {
         const int idx = tid + NTH * i, f = idx >> 6, ln = idx & 63;
-        const int ktl = f >> 3, mtl = (f >> 1) & 3, part = f & 1;
+        const int ktl = f / (4 * NPL), mtl = (f / NPL) & 3, part = f % NPL;
         const int mt = mt0 + mtl < MT ? mt0 + mtl : MT - 1;
-        aoff[i] = ((((uint32_t)mt * KT + ktl) * 2 + part) * 64 + ln) * 16;
+        aoff[i] = ((((uint32_t)mt * KT + ktl) * NPL + part) * 64 + ln) * 16;
     }
     auto stage_load = [&](u32x4_t (&r)[SL], int s) {
-        const char* base = AFb + (size_t)s * 8192;            // 4 k-tiles x (hi, lo) x 1 KB
+        const char* base = AFb + (size_t)s * (4096 * NPL);    // 4 k-tiles x parts x 1 KB
 #pragma unroll
         for (int i = 0; i < SL; ++i) r[i] = *(const u32x4_t*)(base + aoff[i]);
     };
@@ -159,7 +170,7 @@ __global__ __launch_bounds__(KG == 1 ? 256 : 512, KG == 1 ? 2 : 1) void k_gemm25
 #pragma unroll
         for (int i = 0; i < SL; ++i) {
             const int idx = tid + NTH * i, f = idx >> 6, ln = idx & 63;
-            stage[buf][f >> 3][(f >> 1) & 3][f & 1][ln] = r[i];
+            stage[buf][f / (4 * NPL)][(f / NPL) & 3][f % NPL][ln] = r[i];
         }
     };
     const char* Wb = (const char*)a.W;
@@ -202,14 +213,14 @@ __global__ __launch_bounds__(KG == 1 ? 256 : 512, KG == 1 ? 2 : 1) void k_gemm25
 
 #define STEP(WSET, U)                                                                               \
     do {                                                                                            \
-        Frag ah[4], al[4];                                                                          \
-        _Pragma("unroll") for (int m = 0; m < 4; ++m) { ah[m].u = stage[buf][U][m][0][lane]; al[m].u = stage[buf][U][m][1][lane]; } \
+        Frag ap[4][NPL];                                                                            \
+        _Pragma("unroll") for (int m = 0; m < 4; ++m)                                               \
+            _Pragma("unroll") for (int p = 0; p < NPL; ++p) ap[m][p].u = stage[buf][U][m][p][lane]; \
         _Pragma("unroll") for (int j = 0; j < CW; ++j) {                                            \
             Frag wf; wf.u = WSET[j];                                                                \
-            _Pragma("unroll") for (int m = 0; m < 4; ++m) {                                         \
-                acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf.v, ah[m].v, acc[j][m], 0, 0, 0); \
-                acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf.v, al[m].v, acc[j][m], 0, 0, 0); \
-            }                                                                                       \
+            _Pragma("unroll") for (int m = 0; m < 4; ++m)                                           \
+                _Pragma("unroll") for (int p = 0; p < NPL; ++p)                                     \
+                    acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf.v, ap[m][p].v, acc[j][m], 0, 0, 0); \
         }                                                                                           \
         wload(WSET, 4 * s + U + 4);                                                                 \
         __builtin_amdgcn_sched_barrier(0);   /* keep these loads here: four k-tiles ahead of their use */ \
@@ -510,6 +521,11 @@ int fc_gemm256_mode(int epi, int M, int K, int NT, int sk, int cw) {
     return 1;
 }
 
+int fc_gemm256_lm_blocks(int M, int K, int NT) {
+    const int cw = fc_gemm256_cw(EPI_LMHEAD, M, NT), cols = (fc_gemm256_mode(EPI_LMHEAD, M, K, NT, 1, cw) == 3 ? 8 : 4) * cw;
+    return (NT + cols - 1) / cols;
+}
+
 int fc_gemm256_sk(int M, int K, int NT) {
     const int nwg = ((NT + 15) / 16) * (((M + 15) / 16 + 3) / 4), NS = K / 128;
     if (nwg >= 200) return 1;
@@ -523,6 +539,13 @@ int fc_gemm256_sk(int M, int K, int NT) {
 
 template <int CW, int KG>
 static hipError_t launch256(int epi, const Gemm256Args& a, dim3 grid, hipStream_t st) {
+    if constexpr (KG != 1) {
+        if (a.planes == 3) {
+            if (epi != EPI_LMHEAD) return hipErrorInvalidValue;
+            k_gemm256<EPI_LMHEAD, CW, KG, 3><<<grid, 512, 0, st>>>(a);
+            return hipGetLastError();
+        }
+    }
     switch (epi) {
         case EPI_RESID: k_gemm256<EPI_RESID, CW, KG><<<grid, KG == 1 ? 256 : 512, 0, st>>>(a); break;
         case EPI_SWIGLU: k_gemm256<EPI_SWIGLU, CW, KG><<<grid, KG == 1 ? 256 : 512, 0, st>>>(a); break;
@@ -537,11 +560,12 @@ hipError_t fc_gemm256(int epi, const Gemm256Args& a, hipStream_t st) {
     if (a.M < 1 || a.K % 256 || a.NT < 1 || a.sk < 1 || a.sk > FC_GEMM256_MAX_SK || a.sk > a.K / 128) return hipErrorInvalidValue;
     if (a.sk > 1 && (epi != EPI_RESID || !a.part)) return hipErrorInvalidValue;
     // the kernel addresses weights and fragments with 32-bit byte offsets from their bases
-    if ((size_t)a.NT * 16 * a.K * 2 >= ((size_t)1 << 32) || (size_t)((a.M + 15) / 16) * 16 * a.K * 4 >= ((size_t)1 << 32)) return hipErrorInvalidValue;
+    if ((size_t)a.NT * 16 * a.K * 2 >= ((size_t)1 << 32) || (size_t)((a.M + 15) / 16) * 16 * a.K * (a.planes == 3 ? 6 : 4) >= ((size_t)1 << 32)) return hipErrorInvalidValue;
     // narrow tiles when wide ones would leave most of the chip idle
     const int nrb = ((a.M + 15) / 16 + 3) / 4;
     const int cw = (a.cw == 1 || a.cw == 2 || a.cw == 4) ? a.cw : fc_gemm256_cw(epi, a.M, a.NT);
-    const int mode = fc_gemm256_mode(epi, a.M, a.K, a.NT, a.sk, cw);
+    int mode = fc_gemm256_mode(epi, a.M, a.K, a.NT, a.sk, cw);
+    if (a.planes == 3 && mode == 1) mode = 2;            // three parts: the eight-wave forms only
     const int wcols = mode == 3 ? 8 * cw : 4 * cw;
     const int units = ((a.NT + wcols - 1) / wcols) * a.sk;
     dim3 grid((unsigned)((units + 7) / 8) * 8 * nrb);

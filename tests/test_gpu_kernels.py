@@ -96,3 +96,22 @@ def test_plain_lmhead(fc, M, d, V):
     assert torch.equal(ids.long(), logits.argmax(1)) and torch.equal(top, logits.max(1).values)
     two = torch.topk(logits, 2, dim=1).values
     assert torch.equal(top2, two[:, 1])
+
+
+@pytest.mark.parametrize("M,d,V", [(33, 256, 16), (40, 256, 16 * 65), (256, 1024, 16 * 501), (77, 512, 32000), (300, 2048, 16 * 999), (1030, 256, 4096)])
+def test_many_row_lmhead(fc, M, d, V):
+    """More than 32 rows through the many-row kernel on three-part activations: every tile width, last column blocks
+    of one tile, last row blocks of one row, the narrowest K; ids, top and runner-up are read off the same logits."""
+    import torch
+    say(f"many-row lm head M={M} d={d} V={V}")
+    g = torch.Generator(device="cuda"); g.manual_seed(6)
+    w = (0.02 * torch.randn(d, V, generator=g, device="cuda")).bfloat16()
+    act = torch.randn(M, d, generator=g, device="cuda")
+    packed = fc.lmhead_pack(w)
+    ids, top, logits, top2 = fc.lmhead_argmax(act, packed, V, want_logits=True, want_top2=True)
+    assert rel(logits, act.double() @ w.double()) < 1e-6
+    assert torch.equal(ids.long(), logits.argmax(1)) and torch.equal(top, logits.max(1).values)
+    if V > 16:
+        assert torch.equal(top2, torch.topk(logits, 2, dim=1).values[:, 1])
+    ids2, top_2, none, two = fc.lmhead_argmax(act, packed, V, want_top2=True)      # logits in the scratch
+    assert none is None and torch.equal(ids, ids2) and torch.equal(top, top_2) and torch.equal(top2, two)
