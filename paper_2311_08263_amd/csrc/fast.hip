@@ -94,7 +94,7 @@ static ManyRowScratch many_row_scratch(const KernelDims& kd) {
     m.af_att = m.af_x + up(fc_split_bytes(kd.M, kd.d));
     m.af_h = m.af_att + up(fc_split_bytes(kd.M, kd.H * kd.Dh));
     m.ssq = m.af_h + up(fc_split_bytes(kd.M, kd.F));
-    m.part = m.ssq + up((size_t)(kd.d / 256 + 1) * MP * 4);
+    m.part = m.ssq + up((size_t)(kd.d / 16) * MP * 4);      // at most one partial sum per column tile
     m.end = m.part + (size_t)FC_GEMM256_MAX_SK * kd.M * kd.d * 4;
     return m;
 }
@@ -152,12 +152,12 @@ hipError_t fc_fast_forward(const FastArgs& a) {
     bf16_t* af_h = (bf16_t*)(ws + wm.gemm_part + mrs.af_h); float* ssq = (float*)(ws + wm.gemm_part + mrs.ssq);
     big.part = (float*)(ws + wm.gemm_part + mrs.part);
     big.eps = kd.eps;
-    // which fragment buffers hold what their fp32 twin would: x (with the gain of the norm that comes next, row
-    // scale still to be applied by the consumer), attention output, hidden activations
-    bool x_frag = false, att_frag = false, h_frag = false;
-    const float* next_gain = nullptr;          // gain the next reduction folds into the fragments of x
-    // LM head: one winner per row and column block (16, 8 or 4 n-tiles)
-    const int lm_ncb = fc_gemm256_lm_blocks(M, d, kd.V / 16);
+    // the fragment buffers hold what their fp32 twins would: x (with the gain of the norm that comes next, row scale
+    // still to be applied by the consumer from x_nssq partial sums of squares), attention output, hidden activations
+    int x_nssq = d / 256;
+    const float* next_gain = nullptr;          // gain the next residual GEMM folds into the fragments of x
+    // LM head: one winner per row and column block
+    const int lm_ncb = fc_gemm256_plan(EPI_LMHEAD, M, kd.V / 16, 1, 2).ncb;
     big.amax_val = g.amax_val; big.amax_idx = (int32_t*)(g.amax_val + (size_t)lm_ncb * big.amax_stride);
     int gi = 0;        // which GEMM of the plan
     auto gemm = [&](int epi, const void* W, int K, int N, const float* X, int ldx, const float* gain,
@@ -176,26 +176,19 @@ hipError_t fc_fast_forward(const FastArgs& a) {
             co.amax_idx = (int32_t*)(co.amax_val + (size_t)nw * (M > 16 ? 32 : 16));
             return fc_gemmco(epi, co, nw, a.st);
         }
-        if (M > 32) {        // matrix-core bound: activations split once, tiles of 64 rows x 256 columns
-            // the input: fragments a producer has already written (x after a fused reduction, attention output,
-            // hidden activations), else split here (RMSNorm included)
+        if (M > 32) {        // many rows: the input is fragments its producer has written
             bf16_t* af = X == x ? af_x : (X == att ? af_att : af_h);
-            const bool ready = X == x ? x_frag : (X == att ? att_frag : h_frag);
-            big.ssq = nullptr; big.nssq = 0;
-            if (!ready) {
-                hipError_t e = fc_split(X, ldx, M, K, gain, kd.eps, af, a.st);
-                if (e != hipSuccess) return e;
-            } else if (X == x) { big.ssq = ssq; big.nssq = d / 256; }
+            big.ssq = X == x ? ssq : nullptr; big.nssq = X == x ? x_nssq : 0;
             big.sk = epi == EPI_RESID ? fc_gemm256_sk(M, K, N / 16) : 1;
             big.W = (const bf16_t*)W; big.K = K; big.NT = N / 16; big.AF = af; big.out = out; big.ldo = ldo; big.layer = g.layer;
             big.hfrag = nullptr; big.rf_AF = nullptr; big.rf_gain = nullptr; big.rf_ssq = nullptr;
             if (epi == EPI_SWIGLU) {            // the hidden activations leave as fragments (fp32 copy only for debugging)
-                big.hfrag = af_h; h_frag = true;
+                big.hfrag = af_h;
                 if (a.dbg_stop < 0) big.out = nullptr;
             }
             if (epi == EPI_RESID) {
-                x_frag = big.sk > 1 && d % 256 == 0 && next_gain != nullptr;
-                if (x_frag) { big.rf_AF = af_x; big.rf_gain = next_gain; big.rf_ssq = ssq; }
+                big.rf_AF = af_x; big.rf_gain = next_gain; big.rf_ssq = ssq;
+                x_nssq = fc_gemm256_nssq(M, N / 16, big.sk);
             }
             return fc_gemm256(epi, big, a.st);
         }
@@ -214,7 +207,11 @@ hipError_t fc_fast_forward(const FastArgs& a) {
         }
         return hipErrorInvalidValue;
     }
-    FLAUNCH(KK_EMBED, fc_embed(wt + mm.emb_off, FASTCOT_BF16, stp + wm.st.win, x, M, d, kd.V, a.st, a.rm, kd.W));
+    if (M > 32)
+        FLAUNCH(KK_EMBED, fc_embed_split(wt + mm.emb_off, stp + wm.st.win, x, M, d, kd.V, a.rm, kd.W,
+                                         (const float*)(kd.L > 0 ? wt + mm.layers_off + mm.g1_off : wt + mm.gf_off), af_x, ssq, a.st));
+    else
+        FLAUNCH(KK_EMBED, fc_embed(wt + mm.emb_off, FASTCOT_BF16, stp + wm.st.win, x, M, d, kd.V, a.st, a.rm, kd.W));
     int nstage = 0;
 #define DBG_STOP() do { if (a.dbg_stop >= 0 && nstage++ >= a.dbg_stop) return hipSuccess; } while (0)
     for (int l = 0; l < kd.L; ++l) {
@@ -225,7 +222,7 @@ hipError_t fc_fast_forward(const FastArgs& a) {
         FLAUNCH(KK_QKV, gemm(EPI_QKV, lb + mm.qkv.off, d, kd.qkvN, x, d, (const float*)(lb + mm.g1_off), q, qd));
         DBG_STOP();
         if (M > 32) {                  // the many-row O projection reads fragments: attention writes them itself
-            at.ofrag = af_att; att_frag = true;
+            at.ofrag = af_att;
             at.out = a.dbg_stop >= 0 ? att : nullptr;
         }
         // windows of more than 16 rows at a small batch: workgroups of one query tile each instead of two
@@ -376,7 +373,7 @@ static size_t lm_iso_logits_end(int M, int V) { return FC_ALIGN((size_t)(V / 16 
 size_t fc_lmhead_iso_scratch_bytes(int M, int d, int V) {
     const size_t base = lm_iso_logits_end(M, V);
     if (!lm_iso_many(M, d, V)) return base;
-    return base + FC_ALIGN(fc_split_bytes(M, d, 3)) + (size_t)(V / 64 + 1) * ((M + 15) / 16 * 16) * 8;
+    return base + FC_ALIGN(fc_split_bytes(M, d, 3)) + (size_t)(V / 16) * ((M + 15) / 16 * 16) * 8;
 }
 // largest logit of every row among the ids other than the row's winner
 __global__ void k_top2(const float* logits, int V, const int32_t* ids, float* top2) {
@@ -402,9 +399,9 @@ hipError_t fc_lmhead_iso(const float* act, const void* packed, int M, int d, int
         g.W = (const bf16_t*)packed; g.K = d; g.NT = V / 16; g.AF = (bf16_t*)(sc + off); g.planes = 3; g.M = M; g.out = logits; g.ldo = V;
         g.sk = 1; g.amax_stride = (M + 15) / 16 * 16;
         g.amax_val = (float*)(sc + off + FC_ALIGN(fc_split_bytes(M, d, 3)));
-        const int ncb = fc_gemm256_lm_blocks(M, d, V / 16);
+        const int ncb = fc_gemm256_plan(EPI_LMHEAD, M, V / 16, 1, 3).ncb;
         g.amax_idx = (int32_t*)(g.amax_val + (size_t)ncb * g.amax_stride);
-        hipError_t e = fc_split(act, d, M, d, nullptr, 0.f, (bf16_t*)(sc + off), st, 3);
+        hipError_t e = fc_split3(act, d, M, d, (bf16_t*)(sc + off), st);
         if (e == hipSuccess) e = fc_gemm256(EPI_LMHEAD, g, st);
         if (e == hipSuccess) e = fc_argmax_final(g.amax_val, g.amax_idx, ncb, g.amax_stride, M, ids, top, st);
         if (e != hipSuccess || !top2) return e;

@@ -115,3 +115,31 @@ def test_many_row_lmhead(fc, M, d, V):
         assert torch.equal(top2, torch.topk(logits, 2, dim=1).values[:, 1])
     ids2, top_2, none, two = fc.lmhead_argmax(act, packed, V, want_top2=True)      # logits in the scratch
     assert none is None and torch.equal(ids, ids2) and torch.equal(top, top_2) and torch.equal(top2, two)
+
+
+@pytest.mark.parametrize("B,W,P", [(1, 33, 20), (3, 16, 40), (1, 77, 30), (1, 80, 81), (2, 65, 97), (9, 16, 130), (1, 250, 300), (1, 33, 1027)])
+def test_many_row_steps(fc, B, W, P):
+    """Passes of more than 32 rows, row counts that end blocks of three and of four row tiles early, prompts in one and in
+    two chunks: the logits of the same step through the plain kernels.  Activations are hi + lo pairs in one and fp32 in
+    the other path (2^-17 per product, a few layers of them)."""
+    import torch
+    import synthgen
+    say(f"many-row step B={B} W={W} P={P}")
+    shape = synthgen.ModelShape(2, 512, 4, 2, 128, 768, 1040, init_std=0.05)
+    cfg = fc.Config.from_shape(shape, B, (P + 3 * W + 63) // 32 * 32, W)
+    packed = fc.load_synth_weights(cfg, shape)
+    prompts, buf = synthgen.prompts(B, P, shape.vocab, seed=7), synthgen.buffer_init(B, 2 * W + 8, shape.vocab, seed=8)
+    lens = [P - b for b in range(B)]
+    out = []
+    for plain in (0, 1):
+        ctx = fc.Context(cfg, packed)
+        if plain:
+            ctx.set_option(fc.binding.OPT_PLAIN_KERNELS, 1)
+        ctx.prefill(prompts, lens, buf)
+        dbg = ctx.debug_logits(True)
+        torch.cuda.synchronize()
+        ctx.step()
+        torch.cuda.synchronize()
+        out.append(dbg[:B * W].clone())
+        ctx.close()
+    assert rel(out[0], out[1]) < 1e-4
