@@ -225,12 +225,14 @@ hipError_t fc_fast_forward(const FastArgs& a) {
             at.ofrag = af_att;
             at.out = a.dbg_stop >= 0 ? att : nullptr;
         }
-        // windows of more than 16 rows at a small batch: workgroups of one query tile each instead of two
-        // (they read K/V twice, which costs nothing while the launch is latency-bound: 7B, 32 rows, 17.4 -> 13.9 us)
+        // windows of more than 16 rows at a small batch: workgroups of one query tile each instead of two (they read
+        // K/V twice, which costs nothing while the launch is latency-bound: 7B, 32 rows, prompt 256 17.5 -> 13.0 us, prompt
+        // 1500 23.8 -> 23.2; batch 4, prompt 700 30.6 -> 28.1), up to 128 K (position, K/V head) pairs of cache capacity, 128 MB as hi + lo
+        // pairs: beyond, the second reading shows (prompt 4000 37.0 -> 44.8 us; batch 4, prompt 1500 47.2 -> 47.6)
         int attn_splits = a.plan->attn_splits;
         at.subrows = 0;
         const int units16 = (kd.W + 15) / 16;
-        if (kd.W > 16 && a.Bact * kd.H * units16 <= fc_num_cus() && kd.S <= 8192) {   // (long caches: K/V traffic counts)
+        if (kd.W > 16 && a.Bact * kd.H * units16 <= fc_num_cus() && (size_t)a.Bact * kd.Hkv * kd.S <= 128 * 1024) {
             at.subrows = 16;
             while (attn_splits > 1 && a.Bact * kd.H * units16 * attn_splits > fc_num_cus()) --attn_splits;
         }
@@ -353,12 +355,11 @@ hipError_t fc_attn_iso(const float* q, const void* kc, const void* vc, int n, in
     at.part = (float*)(sc + ISO_PART_OFF);
     int splits = iso_attn_splits(n + W);
     // More than 32 rows: units of 16 rows, queries and probabilities as three bf16 parts, because such a call has
-    // always computed in fp32 (error against 64 bits 7e-7; two parts would be 3e-6, three are 3.4e-7); key splits
-    // only while every workgroup has a CU to itself.  64 rows, 1088 keys, 40 heads: plain kernel 172 us, this 15.7 us.
-    if (W > 32) {
-        at.terms = 3; at.subrows = 16;
-        while (splits > 1 && units * splits > fc_num_cus()) --splits;
-    }
+    // always computed in fp32 (error against 64 bits 7e-7; two parts would be 3e-6, three are 3.4e-7).
+    // 64 rows, 1088 keys, 40 heads: plain kernel 172 us, this 15.7 us.
+    // Key splits only while every workgroup has a CU to itself (64 heads on 8, 782 keys: 8 splits 11.3 us, 4 splits 10.4 us).
+    if (W > 32) { at.terms = 3; at.subrows = 16; }
+    while (splits > 1 && units * splits > fc_num_cus()) --splits;
     return fc_attn16(at, 1, splits, st);
 }
 
