@@ -131,7 +131,9 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) acc[qt][dt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
     }
-    const float scale = 0.08838834764831845f;   // 1/sqrt(128)
+    // the softmax runs in powers of two: log2(e) / sqrt(128) is folded into the exponent's fused multiply-add, and maxima and
+    // partial results are kept in that unit
+    const float scale2 = 0.08838834764831845f * 1.4426950408889634f;
 
     // one 32-key block: K tiles and V^T tiles of block `blk` into registers
     struct KV { Frag kf[NPL][2][4], vf[NPL][8]; };
@@ -173,6 +175,8 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
     };
     auto compute = [&](KV& r, int blk) {
         const int kb = blk << 5;
+        // every row sees all 32 keys: no test (with two query tiles the branch costs registers that are not there)
+        const bool whole = QT == 1 && kb + 31 <= n && kb + 31 < T;
         if (KVP == 3) {          // the residual bytes become bf16 lo operands
 #pragma unroll
             for (int t = 0; t < 2; ++t)
@@ -204,21 +208,20 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
             float bm = NEG_BIG;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int key = kb + 8 * g + e;
-                const bool vis = key <= lastvis && key < T;
-                p[e] = vis ? sc[e >> 2][e & 3] * scale : NEG_BIG;
+                p[e] = sc[e >> 2][e & 3];
+                if (!whole) { const int key = kb + 8 * g + e; if (key > lastvis || key >= T) p[e] = NEG_BIG; }
                 bm = fmaxf(bm, p[e]);
             }
             bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
             bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
-            const float mnew = fmaxf(mrun[qt], bm);
-            const float alpha = expf(mrun[qt] - mnew);
+            // (a block in which a row sees nothing leaves bm at NEG_BIG: every weight is 0)
+            const float mnew = fmaxf(mrun[qt], bm * scale2);
+            const float alpha = __builtin_amdgcn_exp2f(mrun[qt] - mnew);
             float ps = 0.f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int key = kb + 8 * g + e;
-                const bool vis = key <= lastvis && key < T;
-                p[e] = vis ? expf(p[e] - mnew) : 0.f;
+                const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(p[e], scale2, -mnew));
+                p[e] = !whole && p[e] == NEG_BIG ? 0.f : w;
                 ps += p[e];
             }
             mrun[qt] = mnew;
@@ -292,7 +295,7 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const float* src = lds + (size_t)(v * QT + qt) * PART_FLOATS;
-            const float wgt = expf(mv[v] - m);
+            const float wgt = __builtin_amdgcn_exp2f(mv[v] - m);
             l += src[2112 + lane] * wgt;
 #pragma unroll
             for (int t = 0; t < 2; ++t) o2[qt][t] += *(const f32x4_t*)(src + ((2 * wv + t) * 64 + lane) * 4) * wgt;
@@ -351,7 +354,7 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
                     const bool valid = s0 + u < nsp;
                     const float mu = valid ? ms[u] : NEG_BIG;
                     const float mnew = fmaxf(m, mu);
-                    const float wa = expf(m - mnew), wb = valid ? expf(mu - mnew) : 0.f;
+                    const float wa = __builtin_amdgcn_exp2f(m - mnew), wb = valid ? __builtin_amdgcn_exp2f(mu - mnew) : 0.f;
                     l = l * wa + ls[u] * wb;
                     o2[qt][0] = o2[qt][0] * wa + os[u][0] * wb;
                     o2[qt][1] = o2[qt][1] * wa + os[u][1] * wb;
