@@ -100,6 +100,7 @@ static ManyRowScratch many_row_scratch(const KernelDims& kd) {
 }
 
 void fc_fast_scratch_sizes(const KernelDims& kd, size_t* gemm_part_bytes, size_t* attn_part_bytes) {
+    if (!fc_fast_supported(kd, 1)) { *gemm_part_bytes = *attn_part_bytes = 4096; return; }   // the plain kernels use neither
     // column-owner kernel with K slices per owner: per workgroup up to 16 partial tiles of 1 KB and 32 partial row
     // sums; at most as many workgroups as the widest matrix has n-tiles
     int nmax = 2 * kd.F;
