@@ -74,7 +74,9 @@ __device__ inline void expand_lo8(const u32x4_t& h, uint32_t b0, uint32_t b1, Fr
 template <int QT, int KVP, int TERMS = 2>
 __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
     extern __shared__ float lds[];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    // the wave index as a scalar: the block loop below is then uniform control flow
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lm = lane & 15, g = lane >> 4;
     // a window of more rows than a workgroup takes (16 per query tile) is cut into sub-windows: sub-window `sub` of a sequence is a
     // unit of its own whose rows see the committed positions plus the window rows up to their own (the
@@ -107,21 +109,29 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
     const bf16_t* kbase = a.kc + ((((size_t)a.layer * a.B + b) * a.Hkv + kvh) * NPL) * plane;
     const bf16_t* vbase = a.vc + ((((size_t)a.layer * a.B + b) * a.Hkv + kvh) * NPL) * plane;
 
-    // Q as B operand: lane (row lm, dh 32*g + 8*s + e), hi and lo
+    // Q as B operand: lane (row lm, dh 32*g + 8*s + e), hi and lo.  The rows are requested here and split where they are
+    // first needed, behind the requests for the first block.
     Frag qh[QT][4], ql[QT][4], qm[TERMS == 3 ? QT : 1][4];
+    float4 qx[QT][4][2];
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {
         int j = qt * 16 + lm;
         if (j >= Wr) j = Wr - 1;
         const float* qr = a.q + (size_t)(rbase + row0 + j) * a.ldq + h * 128 + 32 * g;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            float4 x0 = *(const float4*)(qr + 8 * s), x1 = *(const float4*)(qr + 8 * s + 4);
-            float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-            if constexpr (TERMS == 3) split8(v, qh[qt][s], ql[qt][s], qm[qt][s]);
-            else split8(v, qh[qt][s], ql[qt][s]);
-        }
+        for (int s = 0; s < 4; ++s) { qx[qt][s][0] = *(const float4*)(qr + 8 * s); qx[qt][s][1] = *(const float4*)(qr + 8 * s + 4); }
     }
+    auto split_q = [&]() {
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const float4 x0 = qx[qt][s][0], x1 = qx[qt][s][1];
+                const float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+                if constexpr (TERMS == 3) split8(v, qh[qt][s], ql[qt][s], qm[qt][s]);
+                else split8(v, qh[qt][s], ql[qt][s]);
+            }
+    };
 
     f32x4_t acc[QT][8];
     float mrun[QT], lrun[QT];
@@ -138,7 +148,7 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
     // one 32-key block: K tiles and V^T tiles of block `blk` into registers
     struct KV { Frag kf[NPL][2][4], vf[NPL][8]; };
     auto load = [&](KV& r, int blk_want) {
-        const int blk = blk_want < NB ? blk_want : NB - 1;       // past the end: a valid block, never used
+        const int blk = blk_want < NB ? blk_want : NB - 1;       // past the end (two query tiles): a valid block, never used
         Frag (&kf)[NPL][2][4] = r.kf; Frag (&vf)[NPL][8] = r.vf;
         // K tiles (A operand): tile t row r=lm <-> key 32*blk + 8*(lm/4) + 4*t + lm%4 ; dh 32*g + 8*s..
         // (the cache stores each block as these eight fragments, one contiguous kilobyte each; the loads are
@@ -207,9 +217,13 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
             float p[8];
             float bm = NEG_BIG;
 #pragma unroll
+            for (int e = 0; e < 8; ++e) p[e] = sc[e >> 2][e & 3];
+            if (!whole) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { const int key = kb + 8 * g + e; p[e] = key > lastvis || key >= T ? NEG_BIG : p[e]; }
+            }
+#pragma unroll
             for (int e = 0; e < 8; ++e) {
-                p[e] = sc[e >> 2][e & 3];
-                if (!whole) { const int key = kb + 8 * g + e; if (key > lastvis || key >= T) p[e] = NEG_BIG; }
                 bm = fmaxf(bm, p[e]);
             }
             bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
@@ -240,23 +254,48 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
             }
         }
     };
-    // two register sets: the next block of this wave travels while the current one is used.  With one
-    // query tile there are registers to spare and the scheduler is told to keep all loads of the next
-    // block ahead of the current block's arithmetic; with two tiles the compiler is left to reuse each
-    // register as soon as it is free (two workgroups share a CU instead).
-    {
+    // two register sets: the next block of this wave travels while the current one is used.
+    int blk = blk0 + wv, left = blk < blk1 ? (blk1 - blk + 3) >> 2 : 0;      // this wave's blocks: blk, blk + 4, ...
+    if constexpr (QT == 1) {
+        // There are registers to spare: all loads of the next block stay ahead of the current block's arithmetic.  The loop
+        // has one exit and the last one or two blocks follow it: with an exit after each block the paths met again at the
+        // loop's head, where a register set may or may not have had loads pending, and the compiler waited there for everything
+        // in flight before it requested the next block (7B heads: 1500 keys as hi + lo pairs 18.9 -> 14.0 us, 272 keys
+        // 10.6 -> 8.4 us; one plane, 2064 keys 12.0 -> 10.8 us).
+        if (left > 0) {
+            KV ra, rb;
+            load(ra, blk);
+            __builtin_amdgcn_sched_barrier(0);
+            split_q();
+            for (; left > 2; left -= 2, blk += 8) {
+                load(rb, blk + 4);
+                __builtin_amdgcn_sched_barrier(0);
+                compute(ra, blk);
+                load(ra, blk + 8);
+                __builtin_amdgcn_sched_barrier(0);
+                compute(rb, blk + 4);
+            }
+            if (left == 2) {
+                load(rb, blk + 4);
+                __builtin_amdgcn_sched_barrier(0);
+                compute(ra, blk);
+                compute(rb, blk + 4);
+            } else
+                compute(ra, blk);
+        }
+    } else {
+        // two query tiles: the compiler is left to reuse each register as soon as it is free (two workgroups share a CU
+        // instead; the form above spills)
+        split_q();
         KV ra, rb;
-        int blk = blk0 + wv;
-        if (blk < blk1) {
+        if (left > 0) {
             load(ra, blk);
             for (;;) {
                 load(rb, blk + 4);
-                if (QT == 1) __builtin_amdgcn_sched_barrier(0);
                 compute(ra, blk);
                 blk += 4;
                 if (blk >= blk1) break;
                 load(ra, blk + 4);
-                if (QT == 1) __builtin_amdgcn_sched_barrier(0);
                 compute(rb, blk);
                 blk += 4;
                 if (blk >= blk1) break;

@@ -39,7 +39,8 @@ __global__ __launch_bounds__(512, 2) void k_attnp(AttnArgs a) {
     constexpr int KVW = 2 * 2 * 2 * KVP * 512, XCW = 8 * XW / 4;
     __shared__ u32x4_t lds[KVW > XCW ? KVW : XCW];
     u32x4_t (*kv)[2][2 * KVP][512] = (u32x4_t (*)[2][2 * KVP][512])lds;   // [buffer][block of the pair][K hi, (K lo,) V hi (, V lo)][8 fragments x 64 lanes]
-    const int tid = threadIdx.x & 255, kg = threadIdx.x >> 8, lane = tid & 63, wv = tid >> 6;   // kg: which block of a pair
+    const int tid = threadIdx.x & 255, lane = tid & 63;
+    const int w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kg = w8 >> 2, wv = w8 & 3;   // kg: which block of a pair
     const int lm = lane & 15, g = lane >> 4;
     const int nrb = (a.W + 127) >> 7;
     // query heads that share a K/V head follow each other at a stride of Hkv (same XCD, see attn16.hip); the row
@@ -134,9 +135,13 @@ __global__ __launch_bounds__(512, 2) void k_attnp(AttnArgs a) {
             float p[8];
             float bm = NEG_BIG;
 #pragma unroll
+            for (int e = 0; e < 8; ++e) p[e] = sc[qt][e >> 2][e & 3];
+            if (!whole) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { const int key = kb + 8 * g + e; p[e] = key > lastvis || key >= T ? NEG_BIG : p[e]; }
+            }
+#pragma unroll
             for (int e = 0; e < 8; ++e) {
-                p[e] = sc[qt][e >> 2][e & 3];
-                if (!whole) { const int key = kb + 8 * g + e; if (key > lastvis || key >= T) p[e] = NEG_BIG; }
                 bm = fmaxf(bm, p[e]);
             }
             bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
