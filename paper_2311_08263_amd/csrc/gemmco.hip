@@ -78,17 +78,9 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
     // waits for every load in flight): past the end of the slice, or for n-tiles this workgroup does
     // not own, the address falls back to the first tile of the matrix (cached), and the activations
     // of such k-tiles are zeroed at use.
+    // Loads return in order, so the activations of a batch are requested before its weights: its first k-tile is then
+    // ready when its own weights are, not when the last load of the batch is.
     auto load = [&](Batch<NW, KB, MT>& b, int ib) {
-#pragma unroll
-        for (int t = 0; t < KB; ++t) {
-            const int kt = kt_begin + rot_batch(ib) * KB + t;
-            const bool kv = ib < nb && kt < kt_end;
-#pragma unroll
-            for (int j = 0; j < NW; ++j) {
-                const bool v = kv && nt0 + j < nt1;
-                b.wt[t][j] = __builtin_nontemporal_load(wbase + (v ? ((size_t)(nt0 + j) * KT + kt) * 64 : 0));
-            }
-        }
 #pragma unroll
         for (int t = 0; t < KB; ++t) {
             const int kt = kt_begin + rot_batch(ib) * KB + t;
@@ -97,6 +89,16 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
             for (int mt = 0; mt < MT; ++mt) {
                 b.xa[t][mt][0] = *(const float4*)(xr[mt] + kc * 32);
                 b.xa[t][mt][1] = *(const float4*)(xr[mt] + kc * 32 + 4);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < KB; ++t) {
+            const int kt = kt_begin + rot_batch(ib) * KB + t;
+            const bool kv = ib < nb && kt < kt_end;
+#pragma unroll
+            for (int j = 0; j < NW; ++j) {
+                const bool v = kv && nt0 + j < nt1;
+                b.wt[t][j] = __builtin_nontemporal_load(wbase + (v ? ((size_t)(nt0 + j) * KT + kt) * 64 : 0));
             }
         }
     };
@@ -176,11 +178,33 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
         }
     }
 
+    // The norm gain goes through LDS once per workgroup.  It is requested before the weights: its store to LDS would
+    // otherwise wait for every weight load in front of it.  (Gains of more than 8192 inputs: the rest in gain_store.)
+    f32x4_t gr0, gr1, gr2, gr3;
+    const float* gsrc = a.gain ? a.gain : a.X;             // (without a norm: any readable row, not used)
+    if (EPI != EPI_RESID) {
+        const int k = tid * 4;
+        gr0 = *(const f32x4_t*)(gsrc + (k < a.K ? k : 0)); gr1 = *(const f32x4_t*)(gsrc + (k + 2048 < a.K ? k + 2048 : 0));
+        gr2 = *(const f32x4_t*)(gsrc + (k + 4096 < a.K ? k + 4096 : 0)); gr3 = *(const f32x4_t*)(gsrc + (k + 6144 < a.K ? k + 6144 : 0));
+    }
+    auto gain_store = [&]() {
+        if (EPI != EPI_RESID && a.gain) {
+            const int k0 = tid * 4;
+            if (k0 < a.K) *(f32x4_t*)(lds_gain + k0) = gr0;
+            if (k0 + 2048 < a.K) *(f32x4_t*)(lds_gain + k0 + 2048) = gr1;
+            if (k0 + 4096 < a.K) *(f32x4_t*)(lds_gain + k0 + 4096) = gr2;
+            if (k0 + 6144 < a.K) *(f32x4_t*)(lds_gain + k0 + 6144) = gr3;
+            for (int k = tid * 4 + 8192; k < a.K; k += 2048) *(float4*)(lds_gain + k) = *(const float4*)(a.gain + k);
+            __syncthreads();
+        }
+    };
+
     if constexpr (KW > 0) {
         // Up-front variant for short K slices (at most KW k-tiles per wave): the wave requests its weights at
         // once, as many k-tiles as 28-32 fragments of registers hold (KA), and refills the slot of a k-tile that
         // has been used with the k-tile KA further on; the slice then costs about one memory round trip instead
-        // of one per batch.  Activations (L2 hits) travel one k-tile ahead.  (A ring of the same depth with a
+        // of one per batch.  Activations (L2 hits) travel three k-tiles ahead, the first ones in front of the weights: loads
+        // return in order, and one k-tile ahead an activation waited for the refill requested a step before it.  (A ring of the same depth with a
         // run-time trip count, with or without the activations travelling in the ring, was no faster than the
         // batches: what pays is the burst at the start of the kernel.)
         constexpr int FR = EPI == EPI_QKV ? 28 : 32;       // (the QKV epilogue keeps its rotary factors in registers too)
@@ -194,13 +218,8 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
                 wk[j] = __builtin_nontemporal_load(wbase + (v ? ((size_t)(nt0 + j) * KT + kt) * 64 : 0));
             }
         };
-#pragma unroll
-        for (int t = 0; t < KA; ++t) wload(wt[t], t);
-        if (a.gain) {       // the norm gain goes through LDS once per workgroup
-            for (int i = tid * 4; i < a.K; i += 512 * 4) *(float4*)(lds_gain + i) = *(const float4*)(a.gain + i);
-            __syncthreads();
-        }
-        float4 xa[2][MT][2];
+        constexpr int XD = 3;                              // activations travel XD k-tiles ahead
+        float4 xa[XD + 1][MT][2];
         auto xload = [&](float4 (&x)[MT][2], int t) {
             const int kt = kt_begin + t, kc = kt < kt_end ? kt : kt_begin;
 #pragma unroll
@@ -209,12 +228,17 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
                 x[mt][1] = *(const float4*)(xr[mt] + kc * 32 + 4);
             }
         };
-        xload(xa[0], 0);
+#pragma unroll
+        for (int t = 0; t < XD && t < KW; ++t) xload(xa[t], t);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < KA; ++t) wload(wt[t], t);
+        gain_store();
 #pragma unroll
         for (int t = 0; t < KW; ++t) {
-            if (t + 1 < KW) xload(xa[(t + 1) & 1], t + 1);
+            if (t + XD < KW) xload(xa[(t + XD) % (XD + 1)], t + XD);
             __builtin_amdgcn_sched_barrier(0);
-            ktile(wt[t % KA], xa[t & 1], kt_begin + t, kt_begin + t < kt_end);
+            ktile(wt[t % KA], xa[t % (XD + 1)], kt_begin + t, kt_begin + t < kt_end);
             if (t + KA < KW) wload(wt[t % KA], t + KA);
         }
     } else {
@@ -226,10 +250,7 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
     if (DB) {
         Batch<NW, KB, MT> B;
         load(B, 1);
-        if (a.gain) {       // the norm gain goes through LDS once per workgroup
-            for (int i = tid * 4; i < a.K; i += 512 * 4) *(float4*)(lds_gain + i) = *(const float4*)(a.gain + i);
-            __syncthreads();
-        }
+        gain_store();
         for (int ib = 0; ib < nb; ib += 2) {
             compute(A, ib);
             load(A, ib + 2);
@@ -239,10 +260,7 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
             __builtin_amdgcn_sched_barrier(0);
         }
     } else {
-        if (a.gain) {
-            for (int i = tid * 4; i < a.K; i += 512 * 4) *(float4*)(lds_gain + i) = *(const float4*)(a.gain + i);
-            __syncthreads();
-        }
+        gain_store();
         for (int ib = 0; ib < nb; ++ib) {
             compute(A, ib);
             load(A, ib + 1);
