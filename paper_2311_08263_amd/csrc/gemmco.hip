@@ -75,9 +75,14 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
     const u32x4_t* wbase = (const u32x4_t*)a.W + lane;
 
     // All loads are unconditional (a conditionally loaded register batch would be copied, and a copy
-    // waits for every load in flight): past the end of the slice, or for n-tiles this workgroup does
-    // not own, the address falls back to the first tile of the matrix (cached), and the activations
-    // of such k-tiles are zeroed at use.
+    // waits for every load in flight): past the end of the slice, or for n-tiles this workgroup does not own, the address
+    // stays at the last tile or k-tile of its own, which has just been requested, and the activations of such k-tiles
+    // are zeroed at use.  (With one fixed tile of the matrix there, every workgroup of fewer tiles than the widest one, and every
+    // wave at its end, asked the same L2 channels for the same kilobyte, and the kernel ended when those had come back: 7B gate/up 34.1 -> 33.0 us,
+    // down 22.9 -> 22.2, 70B gate/up 147.4 -> 143.7.)
+    const int kt_last = kt_end > kt_begin ? kt_end - 1 : (kt_begin < KT ? kt_begin : KT - 1);
+    const int nt_last = nt1 > nt0 ? nt1 - 1 : (nt0 < a.NT ? nt0 : a.NT - 1);
+    auto wptr = [&](int j, int kt) { return wbase + ((size_t)(nt0 + j < nt_last ? nt0 + j : nt_last) * KT + (kt < kt_last ? kt : kt_last)) * 64; };
     // Loads return in order, so the activations of a batch are requested before its weights: its first k-tile is then
     // ready when its own weights are, not when the last load of the batch is.
     auto load = [&](Batch<NW, KB, MT>& b, int ib) {
@@ -94,12 +99,8 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
 #pragma unroll
         for (int t = 0; t < KB; ++t) {
             const int kt = kt_begin + rot_batch(ib) * KB + t;
-            const bool kv = ib < nb && kt < kt_end;
 #pragma unroll
-            for (int j = 0; j < NW; ++j) {
-                const bool v = kv && nt0 + j < nt1;
-                b.wt[t][j] = __builtin_nontemporal_load(wbase + (v ? ((size_t)(nt0 + j) * KT + kt) * 64 : 0));
-            }
+            for (int j = 0; j < NW; ++j) b.wt[t][j] = __builtin_nontemporal_load(wptr(j, kt));
         }
     };
 
@@ -213,10 +214,7 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
         auto wload = [&](u32x4_t (&wk)[NW], int t) {
             const int kt = kt_begin + t;
 #pragma unroll
-            for (int j = 0; j < NW; ++j) {
-                const bool v = kt < kt_end && nt0 + j < nt1;
-                wk[j] = __builtin_nontemporal_load(wbase + (v ? ((size_t)(nt0 + j) * KT + kt) * 64 : 0));
-            }
+            for (int j = 0; j < NW; ++j) wk[j] = __builtin_nontemporal_load(wptr(j, kt));
         };
         constexpr int XD = 3;                              // activations travel XD k-tiles ahead
         float4 xa[XD + 1][MT][2];
@@ -251,7 +249,8 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
         Batch<NW, KB, MT> B;
         load(B, 1);
         gain_store();
-        for (int ib = 0; ib < nb; ib += 2) {
+        int ib = 0;
+        for (; ib + 2 < nb; ib += 2) {
             compute(A, ib);
             load(A, ib + 2);
             __builtin_amdgcn_sched_barrier(0);          // the loads stay here, ahead of the other batch's arithmetic
@@ -259,12 +258,16 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
             load(B, ib + 3);
             __builtin_amdgcn_sched_barrier(0);
         }
+        compute(A, ib);                                 // the last one or two request nothing more
+        if (ib + 1 < nb) compute(B, ib + 1);
     } else {
         gain_store();
-        for (int ib = 0; ib < nb; ++ib) {
+        int ib = 0;
+        for (; ib + 1 < nb; ++ib) {
             compute(A, ib);
             load(A, ib + 1);
         }
+        compute(A, ib);                                 // the last one requests nothing more
     }
     }
 
