@@ -115,15 +115,24 @@ def _check(rc: int, ctx=None) -> None:
         raise FastcotError(rc, (lib().fastcot_last_error(ctx) or b"").decode())
 
 
+_gpu_torch = None
+
+
 def _torch():
-    import torch
-    if not torch.cuda.is_available():
-        raise RuntimeError("the FastCoT library needs a GPU (no CPU fallback exists)")
-    return torch
+    """The torch module, once a GPU has been seen (asked on every call until then)."""
+    global _gpu_torch
+    if _gpu_torch is None:
+        import torch
+        if not torch.cuda.is_available():
+            raise RuntimeError("the FastCoT library needs a GPU (no CPU fallback exists)")
+        _gpu_torch = torch
+    return _gpu_torch
 
 
 def _stream_ptr() -> int:
-    return _torch().cuda.current_stream().cuda_stream
+    # the handle itself, without the Stream object around it, which alone took 2.7 us of a call
+    torch = _torch()
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _i32arr(a):
