@@ -65,8 +65,9 @@ typedef struct fastcot_ctx fastcot_ctx;
 
 /* Bytes of the library's packed device weight layout / of the device workspace (KV cache,
  * activations, token buffers, counters) for a configuration.  0 on an invalid configuration.
- * The activations are sized for the largest pass: a step of max_batch * window rows, or, for bf16 models
- * on the matrix-core kernels, a prompt chunk of up to 1024 rows in all (Sec. 4.1, the first forward). */
+ * The activations are sized for the largest pass: a step of max_batch * window rows, or a prompt chunk (Sec. 4.1, the
+ * first forward) of up to 1024 rows in all for bf16 models on the matrix-core kernels, of up to 128 rows per sequence on
+ * the plain kernels. */
 size_t fastcot_weight_bytes(const fastcot_config* cfg);
 size_t fastcot_workspace_bytes(const fastcot_config* cfg);
 
@@ -178,7 +179,7 @@ int fastcot_answer(fastcot_ctx* ctx, const int32_t* trigger_ids, int32_t n_trigg
 int fastcot_debug_logits(fastcot_ctx* ctx, float* d_logits);
 
 /* Options of a context.
- * FASTCOT_OPT_PLAIN_KERNELS = 1 routes every step through the plain one-thread-per-output kernels (always used
+ * FASTCOT_OPT_PLAIN_KERNELS = 1 routes every step through the plain fp32-arithmetic kernels (always used
  * for fp32 models, and for bf16 models whose shape the matrix-core kernels do not cover: head_dim other than 128,
  * or d_model / d_ffn / n_heads*head_dim not multiples of 256 -- fastcot_last_error() says so after fastcot_init);
  * 0 (default) uses the matrix-core kernels for bf16.

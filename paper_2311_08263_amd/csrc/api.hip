@@ -308,7 +308,7 @@ extern "C" int fastcot_init(const fastcot_config* cfg, const void* d_packed, voi
     // a bf16 model the matrix-core kernels do not cover runs through the plain kernels: say so (not an error)
     if (cfg->dtype == FASTCOT_BF16 && !fc_fast_supported(c->kd, c->kd.B * c->kd.W)) {
         c->opt_plain = 1;
-        snprintf(c->err, sizeof(c->err), "note: this bf16 model runs on the plain one-thread-per-output kernels: the matrix-core kernels need "
+        snprintf(c->err, sizeof(c->err), "note: this bf16 model runs on the plain kernels: the matrix-core kernels need "
                  "head_dim 128 and d_model, d_ffn, n_heads*head_dim multiples of 256");
     }
     *out = c;
