@@ -109,6 +109,10 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
     const bf16_t* kbase = a.kc + ((((size_t)a.layer * a.B + b) * a.Hkv + kvh) * NPL) * plane;
     const bf16_t* vbase = a.vc + ((((size_t)a.layer * a.B + b) * a.Hkv + kvh) * NPL) * plane;
 
+    // The softmax runs in powers of two: the queries are multiplied by log2(e) / sqrt(128) before they are split, so scores,
+    // maxima and partial results are in that unit.  (Multiplied into the exponent's fused multiply-add instead, the largest
+    // score's own exponent was what rounding had left of the maximum: beyond 2^31 its weight was infinite or zero.)
+    const float scale2 = 0.08838834764831845f * 1.4426950408889634f;
     // Q as B operand: lane (row lm, dh 32*g + 8*s + e), hi and lo.  The rows are requested here and split where they are
     // first needed, behind the requests for the first block.
     Frag qh[QT][4], ql[QT][4], qm[TERMS == 3 ? QT : 1][4];
@@ -127,7 +131,7 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 const float4 x0 = qx[qt][s][0], x1 = qx[qt][s][1];
-                const float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+                const float v[8] = {x0.x * scale2, x0.y * scale2, x0.z * scale2, x0.w * scale2, x1.x * scale2, x1.y * scale2, x1.z * scale2, x1.w * scale2};
                 if constexpr (TERMS == 3) split8(v, qh[qt][s], ql[qt][s], qm[qt][s]);
                 else split8(v, qh[qt][s], ql[qt][s]);
             }
@@ -141,10 +145,6 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) acc[qt][dt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
     }
-    // the softmax runs in powers of two: log2(e) / sqrt(128) is folded into the exponent's fused multiply-add, and maxima and
-    // partial results are kept in that unit
-    const float scale2 = 0.08838834764831845f * 1.4426950408889634f;
-
     // one 32-key block: K tiles and V^T tiles of block `blk` into registers
     struct KV { Frag kf[NPL][2][4], vf[NPL][8]; };
     auto load = [&](KV& r, int blk_want) {
@@ -229,12 +229,12 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
             bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
             bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
             // (a block in which a row sees nothing leaves bm at NEG_BIG: every weight is 0)
-            const float mnew = fmaxf(mrun[qt], bm * scale2);
+            const float mnew = fmaxf(mrun[qt], bm);
             const float alpha = __builtin_amdgcn_exp2f(mrun[qt] - mnew);
             float ps = 0.f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(p[e], scale2, -mnew));
+                const float w = __builtin_amdgcn_exp2f(p[e] - mnew);
                 p[e] = !whole && p[e] == NEG_BIG ? 0.f : w;
                 ps += p[e];
             }

@@ -13,8 +13,8 @@
 // skips the blocks none of its rows can see.
 // Bound: a wave alternates matrix instructions and softmax arithmetic; with the key blocks dealt to two waves per SIMD
 // the one's fill the other's gaps (7B heads, rows 0..1023 / 1024..2047 of a prompt: one wave per SIMD and expf
-// 92 / 172 us; this 65 / 115 us).  Softmax runs in powers of two with the scale folded into the exponent's fused
-// multiply-add, and the visibility test only in blocks that some row does not see whole.
+// 92 / 172 us; this 65 / 115 us).  Softmax runs in powers of two with the scale folded into the queries, and
+// the visibility test only in blocks that some row does not see whole.
 #include "attn16.h"
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
@@ -61,7 +61,9 @@ __global__ __launch_bounds__(512, 2) void k_attnp(AttnArgs a) {
     const bf16_t* kbase = a.kc + ((((size_t)a.layer * a.B + b) * a.Hkv + kvh) * KVP) * plane;
     const bf16_t* vbase = a.vc + ((((size_t)a.layer * a.B + b) * a.Hkv + kvh) * KVP) * plane;
 
-    // Q as B operand: lane (row lm, dh 32*g + 8*s + e), hi and lo
+    // Q as B operand: lane (row lm, dh 32*g + 8*s + e), times log2(e) / sqrt(128) (the softmax runs in powers of two, and a
+    // score meets the maximum in its own rounding, see attn16.hip), hi and lo
+    const float scale2 = 0.08838834764831845f * 1.4426950408889634f;
     Frag qh[2][4], ql[2][4];
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
@@ -71,7 +73,7 @@ __global__ __launch_bounds__(512, 2) void k_attnp(AttnArgs a) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             const float4 x0 = *(const float4*)(qr + 8 * s), x1 = *(const float4*)(qr + 8 * s + 4);
-            const float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+            const float v[8] = {x0.x * scale2, x0.y * scale2, x0.z * scale2, x0.w * scale2, x1.x * scale2, x1.y * scale2, x1.z * scale2, x1.w * scale2};
             split8p(v, qh[qt][s], ql[qt][s]);
         }
     }
@@ -83,7 +85,6 @@ __global__ __launch_bounds__(512, 2) void k_attnp(AttnArgs a) {
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) acc[qt][dt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
     }
-    const float scale2 = 0.08838834764831845f * 1.4426950408889634f;   // log2(e) / sqrt(128): the softmax runs in powers of two
 
     // block copy: 4 (or 2) chunks of 8 KB, 512 sixteen-byte words each; thread t of the 256 that will use the block takes
     // words t and t + 256 of every chunk
@@ -147,12 +148,12 @@ __global__ __launch_bounds__(512, 2) void k_attnp(AttnArgs a) {
             bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
             bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
             // (a block in which a row sees nothing leaves bm at NEG_BIG: the maximum stays, every weight is 0)
-            const float mnew = fmaxf(mrun[qt], bm * scale2);
+            const float mnew = fmaxf(mrun[qt], bm);
             alpha[qt] = __builtin_amdgcn_exp2f(mrun[qt] - mnew);
             float ps = 0.f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(p[e], scale2, -mnew));
+                const float w = __builtin_amdgcn_exp2f(p[e] - mnew);
                 p[e] = !whole && p[e] == NEG_BIG ? 0.f : w;
                 ps += p[e];
             }

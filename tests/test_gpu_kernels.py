@@ -69,6 +69,55 @@ def test_wide_window_attention(fc, n, W, H, Hkv):
     assert rel(fc.attn_window(q, kc, vc, n), attn64(q, k, v, n)) < 1e-6
 
 
+@pytest.mark.parametrize("W", [9, 20, 33])
+def test_attention_of_very_large_scores(fc, W):
+    """Scores of about 1e11, which rounding alone moves by thousands: the largest score's weight is still one.  (Two keys
+    that lie within the 2^-17 of a query would change places; none do here: the result is that of 64 bits.)"""
+    import torch
+    say(f"attention of very large scores W={W}")
+    n, H = 300, 4
+    q, k, v = attn_inputs(n, W, H, 2, 128, torch.bfloat16)
+    q, k = q * 1e5, (k.float() * 1e5).bfloat16()
+    out = fc.attn_window(q, *fc.kv_scatter(k, v, (n + W + 31) // 32 * 32), n)
+    assert rel(out, attn64(q, k, v, n)) < 1.5e-5
+
+
+@pytest.mark.parametrize("W,planes", [(16, 2), (16, 3), (24, 2), (24, 1), (48, 2)])
+def test_steps_of_very_large_scores(fc, W, planes):
+    """The same in a model (query and key weights times 2^20, scores of about 1e13): a prompt through the many-row
+    attention kernel and one step, against the plain kernels.  A row in which two keys do change places differs
+    altogether, so the bound is on the median row."""
+    import torch
+    import synthgen
+    say(f"step of very large scores W={W} planes={planes}")
+    shape, B, P = synthgen.ModelShape(2, 512, 4, 2, 128, 768, 1040, init_std=0.05), 1, 140
+    cfg = fc.Config.from_shape(shape, B, 256, W)
+
+    def weights():
+        for sp in synthgen.weight_tensors(shape):
+            a = synthgen.weight_array(shape, sp, as_bf16_bits=True)
+            if sp.name in ("wq", "wk"):
+                a = np.where(a & 0x7F80, a + (20 << 7), a).astype(np.uint16)
+            yield sp.name, sp.layer, a
+    packed = fc.pack_weights(cfg, weights())
+    prompts, buf = synthgen.prompts(B, P, shape.vocab, seed=7), synthgen.buffer_init(B, 2 * W + 8, shape.vocab, seed=8)
+    out = []
+    for plain in (0, 1):
+        ctx = fc.Context(cfg, packed)
+        ctx.set_option(fc.binding.OPT_KV_PLANES, planes)
+        ctx.set_option(fc.binding.OPT_PLAIN_KERNELS if plain else fc.binding.PLAN_ATTN_MANY_ROWS, 1 if plain else 2)
+        ctx.prefill(prompts, [P], buf)
+        dbg = ctx.debug_logits(True)
+        torch.cuda.synchronize()
+        ctx.step()
+        torch.cuda.synchronize()
+        out.append(dbg[:W].double())
+        ctx.close()
+    assert torch.isfinite(out[0]).all()
+    err = torch.linalg.norm(out[0] - out[1], dim=1) / torch.linalg.norm(out[1], dim=1)
+    assert float(err.median()) < (2e-2 if planes == 1 else 1e-4)
+
+
 def test_one_scratch_for_calls_of_different_shapes(fc):
     """A scratch zeroed once serves any order of shapes it is large enough for."""
     import torch
