@@ -256,7 +256,8 @@ const char* fastcot_kernel_name(int32_t kind);
  * rotated); k_cache / vt_cache in the library's single-plane cache layout for one sequence: per kv head
  * max_seq/32 blocks of 32 positions x Dh elements, each block stored in the order of the attention
  * kernel's matrix-core operand fragments (written by fastcot_kv_scatter; max_seq and Dh multiples of 32),
- * elements of `dtype`, positions 0..n+W-1 filled; row j attends positions 0..n+j.  out device fp32 [W][H*Dh].  scratch: device,
+ * elements of `dtype`, positions 0..n+W-1 filled; row j attends positions 0..n+j, and nothing beyond them reaches its
+ * result, whatever is there (NaN and infinities included).  out device fp32 [W][H*Dh].  scratch: device,
  * fastcot_attn_scratch_bytes() bytes, zeroed once by the caller before first use.
  * fastcot_kv_scatter writes canonical k, v (device, [S][Hkv][Dh], `dtype`) into that layout. */
 size_t fastcot_attn_scratch_bytes(int32_t W, int32_t H, int32_t Dh);

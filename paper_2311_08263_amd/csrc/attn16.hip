@@ -404,6 +404,65 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
         }
         if (tid == 0) st_agent_i32(a.cnt + bh, 0);
     }
+    if constexpr (KVP == 1) {
+        // A row with a NaN in it is computed once more, key by key in fp32 and over the keys it sees only.  The matrix
+        // instructions multiply what a row does not see by a weight of zero (positions past the window, which nobody has
+        // to fill, and later window rows), and zero times an infinity or NaN in V is NaN; so is a query or a product of
+        // its parts past the range of bf16.  A row whose own keys make it NaN stays so.  Where nothing is NaN this is eight
+        // comparisons (40 heads, 64 rows, 1088 keys 13.95 -> 14.07 us; 32 heads, 16 rows, 2064 keys 11.8 us both ways);
+        // each wave redoes the 32 head elements it finishes.
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) {
+            const float inv = 1.0f / lw[qt];
+            bool nan = false;
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) { const float x = o2[qt][t][r] * inv; nan = nan || x != x; }
+            const unsigned long long lanes = __ballot(nan && qt * 16 + lm < Wr);
+            uint32_t rows = (uint32_t)(lanes | lanes >> 16 | lanes >> 32 | lanes >> 48) & 0xFFFFu;
+            while (__builtin_expect(rows != 0, 0)) {
+                const int j = __builtin_ctz(rows);
+                rows &= rows - 1;
+                int last = n + qt * 16 + j;
+                if (last >= T) last = T - 1;
+                const float* qr = a.q + (size_t)(rbase + row0 + qt * 16 + j) * a.ldq + h * 128;
+                auto score = [&](int t) {
+#pragma clang fp contract(off)
+                    // (uncontracted: the caller's difference to the maximum then takes the product as it was rounded there)
+                    float s = 0.f;
+#pragma unroll 1
+                    for (int i = 0; i < 128; i += 8) {
+                        const u32x4_t kw = *(const u32x4_t*)(kbase + k_index(t, i, 128));
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) { s += qr[i + 2 * e] * __uint_as_float(kw[e] << 16); s += qr[i + 2 * e + 1] * __uint_as_float(kw[e] & 0xFFFF0000u); }
+                    }
+                    return s * 0.08838834764831845f;
+                };
+                float mx = -3.0e38f;
+                for (int t = lane; t <= last; t += 64) mx = fmaxf(mx, score(t));
+                for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+                float den = 0.f, sum = 0.f;
+                for (int t0 = 0; t0 <= last; t0 += 64) {     // lane = key, then lane = (parity of the key, head element)
+                    const float p = t0 + lane <= last ? expf(score(t0 + lane) - mx) : 0.f;
+                    den += p;
+#pragma unroll 1
+                    for (int u = lane >> 5; u < 64; u += 2) {
+                        const float pu = __shfl(p, u, 64);
+                        if (t0 + u <= last) sum += pu * __uint_as_float((uint32_t)vbase[v_index(32 * wv + (lane & 31), t0 + u, 128)] << 16);
+                    }
+                }
+                for (int o = 32; o > 0; o >>= 1) den += __shfl_xor(den, o, 64);
+                sum += __shfl_xor(sum, 32, 64);
+                sum /= den;
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) { const float x = __shfl(sum, 16 * t + 4 * g + r, 64); if (lm == j) o2[qt][t][r] = x; }
+                if (lm == j) lw[qt] = 1.0f;
+            }
+        }
+    }
     // out[row][h*128 + 16*dt + 4*g + r] = O / l, this wave's tiles dt = 2*wv, 2*wv + 1
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {

@@ -69,6 +69,41 @@ def test_wide_window_attention(fc, n, W, H, Hkv):
     assert rel(fc.attn_window(q, kc, vc, n), attn64(q, k, v, n)) < 1e-6
 
 
+@pytest.mark.parametrize("n,W,H,Hkv", [(250, 5, 4, 2), (5, 16, 2, 2), (40, 17, 4, 4), (2000, 32, 8, 2), (0, 33, 2, 1), (777, 33, 8, 8), (3001, 64, 4, 4)])
+def test_attention_takes_nothing_from_hidden_positions(fc, n, W, H, Hkv):
+    """Positions past the window hold NaN and infinities (nobody has to fill them), and so do two head elements of V in
+    the last window row, which only that row sees: every other row is what it is without them, and the last row is
+    infinite and NaN in those two elements alone.  Bounds as in the tests above."""
+    import torch
+    say(f"hidden positions n={n} W={W} H={H}/{Hkv}")
+    q, k, v = attn_inputs(n, W, H, Hkv, 128, torch.bfloat16)
+    S = (n + W + 31) // 32 * 32
+    assert S > n + W
+    want = attn64(q, k, v, n).view(W, H, 128)
+    kp, vp = (torch.full((S, Hkv, 128), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    kp[n + W::2], vp[n + W::2] = float("inf"), float("-inf")
+    kp[:n + W], vp[:n + W] = k, v
+    vp[n + W - 1, :, 37], vp[n + W - 1, :, 90] = float("inf"), float("nan")
+    out = fc.attn_window(q, *fc.kv_scatter(kp, vp, S), n).view(W, H, 128)
+    assert torch.isinf(out[-1, :, 37]).all() and torch.isnan(out[-1, :, 90]).all()
+    out[-1, :, 37], out[-1, :, 90] = want[-1, :, 37].float(), want[-1, :, 90].float()
+    assert rel(out, want) < (1e-6 if W > 32 else 1.5e-5)
+
+
+@pytest.mark.parametrize("W", [9, 20, 33])
+def test_attention_over_the_range_of_fp32(fc, W):
+    """Queries that round to a bf16 infinity, and rows all of whose scores lie below -1e33."""
+    import torch
+    say(f"attention at the ends of the range W={W}")
+    n, H = 300, 2
+    q, k, v = attn_inputs(n, W, H, H, 128, torch.bfloat16)
+    big = q.clone(); big[1::3] = torch.sign(big[1::3]) * 3.4e38
+    small = (k.float() * 1e-30).bfloat16()
+    for qq, kk in ((big, small), (q.abs() * 1e18, -(k.abs().float() * 1e15).bfloat16())):
+        out = fc.attn_window(qq.contiguous(), *fc.kv_scatter(kk, v, (n + W + 31) // 32 * 32), n)
+        assert rel(out, attn64(qq, kk, v, n)) < (1e-6 if W > 32 else 1.5e-5)
+
+
 @pytest.mark.parametrize("W", [9, 20, 33])
 def test_attention_of_very_large_scores(fc, W):
     """Scores of about 1e11, which rounding alone moves by thousands: the largest score's weight is still one.  (Two keys
