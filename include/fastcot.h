@@ -292,7 +292,7 @@ int fastcot_stream_read_chain(const void* d_src, size_t src_bytes, const uint64_
                               void* d_sink16, void* hip_stream);
 
 /* LM head fused with argmax (Eq. 1/2, lowest id on ties): act device fp32 [M][d] (already
- * normalised), packed W_lm as written by fastcot_lmhead_pack from canonical bf16 [d][V];
+ * normalised), packed W_lm as written by fastcot_lmhead_pack from canonical bf16 [d][V] (finite weights);
  * ids device int32 [M], top device fp32 [M] (the winning logit); d_top2 nullable fp32 [M], the largest logit
  * among all other ids (top - top2 is the margin of the decision; asking for it makes the call write the
  * logits, to d_logits or to the scratch); d_logits nullable fp32 [M][V].

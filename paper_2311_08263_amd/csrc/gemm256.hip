@@ -47,12 +47,30 @@ __global__ __launch_bounds__(512) void k_split3(const float* X, int ldx, int M, 
     for (int kt = kt_lo + w; kt < kt_hi; kt += 8) {
         const float4 a = *(const float4*)(xr + kt * 32), b = *(const float4*)(xr + kt * 32 + 4);
         const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-        uint32_t h[4], l[4], l2[4];
+        uint32_t h[4], l[4], l2[4], bad = 0;
+        float r[8];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             h[e] = pk_bf16(v[2 * e], v[2 * e + 1]);
-            pk_bf16_hilo(v[2 * e] - __uint_as_float(h[e] << 16), v[2 * e + 1] - __uint_as_float(h[e] & 0xFFFF0000u), l[e], l2[e]);
+            r[2 * e] = v[2 * e] - __uint_as_float(h[e] << 16);
+            r[2 * e + 1] = v[2 * e + 1] - __uint_as_float(h[e] & 0xFFFF0000u);
+            bad |= (h[e] & 0x7F807F80u) + 0x00800080u;
         }
+        if (__builtin_expect((bad & 0x80008000u) != 0, 0)) {
+            // A hi part that is not finite.  Finite values that round up to infinity are cut off instead; infinities and NaN
+            // leave nothing over (their difference would be NaN, and so every logit of a row whose logits are infinite).
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t hi = (h[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
+                if ((hi & 0x7F80u) != 0x7F80u) continue;
+                r[e] = 0.f;
+                if ((__float_as_uint(v[e]) & 0x7F800000u) == 0x7F800000u) continue;
+                h[e >> 1] -= 1u << (16 * (e & 1));                       // the largest finite bf16 of that sign
+                r[e] = v[e] - __uint_as_float((hi - 1) << 16);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) pk_bf16_hilo(r[2 * e], r[2 * e + 1], l[e], l2[e]);
         dst[(size_t)kt * 192] = (u32x4_t){h[0], h[1], h[2], h[3]};
         dst[(size_t)kt * 192 + 64] = (u32x4_t){l[0], l[1], l[2], l[3]};
         dst[(size_t)kt * 192 + 128] = (u32x4_t){l2[0], l2[1], l2[2], l2[3]};

@@ -201,6 +201,31 @@ def test_many_row_lmhead(fc, M, d, V):
     assert none is None and torch.equal(ids, ids2) and torch.equal(top, top_2) and torch.equal(top2, two)
 
 
+@pytest.mark.parametrize("M,d,V", [(33, 256, 1040), (70, 512, 16 * 65), (40, 96, 1040)])
+def test_lmhead_of_infinite_activations(fc, M, d, V):
+    """Rows with an infinity, a NaN, and values that round up to a bf16 infinity, among ordinary ones; the last shape goes
+    through the plain product.  An infinite activation makes the logits infinite by the sign of its weights, and the
+    lowest id of the positive ones wins."""
+    import torch
+    say(f"lm head, infinite activations M={M} d={d} V={V}")
+    g = torch.Generator(device="cuda"); g.manual_seed(8)
+    w = (0.02 * torch.randn(d, V, generator=g, device="cuda")).bfloat16()
+    w[w == 0] = 0.01
+    act = torch.randn(M, d, generator=g, device="cuda")
+    act[2, 5], act[9, 40], act[17, 63] = float("inf"), float("-inf"), float("nan")
+    act[20, 8], act[20, 9], act[M - 1, d - 1] = 3.4e38, -3.395e38, -3.402823466e38
+    ids, top, logits, top2 = fc.lmhead_argmax(act, fc.lmhead_pack(w), V, want_logits=True, want_top2=True)
+    want = act.double() @ w.double()
+    for m, f, s in ((2, 5, 1), (9, 40, -1)):
+        assert torch.equal(logits[m].double(), want[m]) and torch.isinf(want[m]).all()
+        assert int(ids[m]) == int((s * w[f] > 0).nonzero()[0]) and float(top[m]) == float(top2[m]) == float("inf")
+    assert torch.isnan(logits[17]).all()
+    rows = torch.tensor([m for m in range(M) if m not in (2, 9, 17)], device="cuda")
+    for m in rows.tolist():
+        assert rel(logits[m], want[m]) < 1e-6
+    assert torch.equal(ids[rows].long(), logits[rows].argmax(1)) and torch.equal(top[rows], logits[rows].max(1).values)
+
+
 @pytest.mark.parametrize("B,W,P", [(1, 33, 20), (3, 16, 40), (1, 77, 30), (1, 80, 81), (2, 65, 97), (9, 16, 130), (1, 250, 300), (1, 33, 1027)])
 def test_many_row_steps(fc, B, W, P):
     """Passes of more than 32 rows, row counts that end blocks of three and of four row tiles early, prompts in one and in
