@@ -381,7 +381,7 @@ size_t fc_lmhead_iso_scratch_bytes(int M, int d, int V) {
 __global__ void k_top2(const float* logits, int V, const int32_t* ids, float* top2) {
     __shared__ float sv[4];
     const int m = blockIdx.x, win = ids[m];
-    float best = -3.0e38f;
+    float best = -INFINITY;
     for (int n = threadIdx.x; n < V; n += blockDim.x) { const float v = logits[(size_t)m * V + n]; if (n != win && v > best) best = v; }
     for (int o = 32; o > 0; o >>= 1) best = fmaxf(best, __shfl_xor(best, o, 64));
     if ((threadIdx.x & 63) == 0) sv[threadIdx.x >> 6] = best;

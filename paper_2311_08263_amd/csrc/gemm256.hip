@@ -326,7 +326,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm256(Gemm256Args a) {
     float rscale[RT];
 #pragma unroll
     for (int m = 0; m < RT; ++m) {
-        best[m] = -3.0e38f; bidx[m] = 0x7fffffff;
+        best[m] = -INFINITY; bidx[m] = 0x7fffffff;
         rscale[m] = 1.0f;
         if (EPI != EPI_RESID && a.ssq) {
             const int r = m * 16 + lm;

@@ -383,7 +383,7 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
         }
         if (tid == 0) st_agent_i32(a.xcnt + owner, 0);
     }
-    float best = -3.0e38f; int bi = 0x7fffffff;          // LM head: the wave's winner per row over its tiles
+    float best = -INFINITY; int bi = 0x7fffffff;          // LM head: the wave's winner per row over its tiles
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
         const int nt = ntf[f];
@@ -482,7 +482,7 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
         __syncthreads();
         if (tid < 16 * MT) {                 // row tid: the waves whose tiles are row tile tid / 16
             const int rt = tid >> 4, r16 = tid & 15;
-            float bv = -3.0e38f; int bx = 0x7fffffff;
+            float bv = -INFINITY; int bx = 0x7fffffff;
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
                 if (q % MT != rt) continue;
@@ -642,7 +642,7 @@ __global__ void k_argmax_final(const float* val, const int32_t* idx, int nparts,
     __shared__ float bv[4];
     __shared__ int bi[4];
     const int m = blockIdx.x;
-    float best = -3.0e38f; int b = 0x7fffffff;
+    float best = -INFINITY; int b = 0x7fffffff;
     for (int c = threadIdx.x; c < nparts; c += blockDim.x) {
         float v = val[(size_t)c * stride + m]; int i = idx[(size_t)c * stride + m];
         if (v > best || (v == best && i < b)) { best = v; b = i; }
@@ -657,7 +657,7 @@ __global__ void k_argmax_final(const float* val, const int32_t* idx, int nparts,
         for (int q = 1; q < (int)(blockDim.x >> 6); ++q)
             if (bv[q] > best || (bv[q] == best && bi[q] < b)) { best = bv[q]; b = bi[q]; }
         const int dst = rm.rowb ? rm.rowb[m] * W + rm.rowj[m] : m;
-        ids[dst] = b; top[dst] = best;
+        ids[dst] = b == 0x7fffffff ? 0 : b; top[dst] = best;       // nothing but NaN: an id of the vocabulary all the same
     }
 }
 hipError_t fc_argmax_final(const float* val, const int32_t* idx, int nparts, int stride, int M, int32_t* ids, float* top,

@@ -319,7 +319,7 @@ __global__ void k_argmax(const float* logits, int V, int32_t* ids, float* top) {
     __shared__ float bv[4];
     __shared__ int bi[4];
     const float* r = logits + (size_t)blockIdx.x * V;
-    float best = -3.0e38f; int idx = 0x7fffffff;
+    float best = -INFINITY; int idx = 0x7fffffff;
     for (int i = threadIdx.x; i < V; i += blockDim.x) {
         float v = r[i];
         if (v > best || (v == best && i < idx)) { best = v; idx = i; }
@@ -333,7 +333,7 @@ __global__ void k_argmax(const float* logits, int V, int32_t* ids, float* top) {
     if (threadIdx.x == 0) {
         for (int w = 1; w < (int)(blockDim.x >> 6); ++w)
             if (bv[w] > best || (bv[w] == best && bi[w] < idx)) { best = bv[w]; idx = bi[w]; }
-        ids[blockIdx.x] = idx; top[blockIdx.x] = best;
+        ids[blockIdx.x] = idx == 0x7fffffff ? 0 : idx; top[blockIdx.x] = best;      // nothing but NaN: an id of the vocabulary all the same
     }
 }
 hipError_t fc_argmax_plain(const float* logits, int M, int V, int32_t* ids, float* top, hipStream_t st) {

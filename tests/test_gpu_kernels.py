@@ -226,6 +226,26 @@ def test_lmhead_of_infinite_activations(fc, M, d, V):
     assert torch.equal(ids[rows].long(), logits[rows].argmax(1)) and torch.equal(top[rows], logits[rows].max(1).values)
 
 
+@pytest.mark.parametrize("M,d", [(5, 256), (20, 512), (33, 256), (40, 96)])
+def test_lmhead_ids_stay_in_the_vocabulary(fc, M, d):
+    """A row of NaN has no largest logit and a row of -infinity only ties: id 0 for both, as the oracle's scan from the
+    first id has it, in all three kernels."""
+    import torch
+    say(f"lm head, rows without a winner M={M} d={d}")
+    V = 1040
+    g = torch.Generator(device="cuda"); g.manual_seed(9)
+    w = (0.02 * torch.randn(d, V, generator=g, device="cuda")).bfloat16()
+    w[3] = -w[3].abs() - 0.01
+    act = torch.randn(M, d, generator=g, device="cuda")
+    act[1, 7], act[3, 3] = float("nan"), float("inf")
+    ids, top, logits, top2 = fc.lmhead_argmax(act, fc.lmhead_pack(w), V, want_logits=True, want_top2=True)
+    assert int(ids[1]) == int(ids[3]) == 0
+    if M > 32:
+        assert torch.equal(logits[3], torch.full_like(logits[3], float("-inf"))) and float(top[3]) == float(top2[3]) == float("-inf")
+    rows = torch.tensor([m for m in range(M) if m not in (1, 3)], device="cuda")
+    assert torch.equal(ids[rows].long(), logits[rows].argmax(1)) and torch.equal(top[rows], logits[rows].max(1).values)
+
+
 @pytest.mark.parametrize("B,W,P", [(1, 33, 20), (3, 16, 40), (1, 77, 30), (1, 80, 81), (2, 65, 97), (9, 16, 130), (1, 250, 300), (1, 33, 1027)])
 def test_many_row_steps(fc, B, W, P):
     """Passes of more than 32 rows, row counts that end blocks of three and of four row tiles early, prompts in one and in
