@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <algorithm>
 #include <vector>
 #include "kernels.h"
 #include "fast.h"
@@ -34,6 +35,8 @@ struct fastcot_ctx {
     hipGraphExec_t graph_exec;
     hipGraph_t graph;
     int graph_valid;
+    int graph_one_tile;  // attention form of the captured step (fc_attn_one_tile)
+    int ctx_len, ctx_max;   // committed positions of the longest sequence, at least (prompt, then one per step), and at most
     FastPlan plan;
     // profiling of single launches
     int prof_on;
@@ -281,7 +284,7 @@ extern "C" int fastcot_init(const fastcot_config* cfg, const void* d_packed, voi
     if (fc_build_maps(cfg, &c->mm, &c->wm, &c->kd) != 0) { delete c; return fail(nullptr, FASTCOT_EINVAL, "invalid configuration: %s", cfg_problem(cfg)); }
     if (workspace_bytes < c->wm.total) { delete c; return fail(nullptr, FASTCOT_ECAPACITY, "workspace too small%s"); }
     c->cfg = *cfg; c->weights = (const char*)d_packed; c->ws = (char*)d_workspace; c->st = (hipStream_t)hip_stream;
-    c->Bact = 0; c->prefilled = 0; c->generated = 0; c->buf_len = 0; c->opt_tune = 1; c->opt_compact = 1;
+    c->Bact = 0; c->ctx_len = c->ctx_max = 0; c->graph_one_tile = 0; c->prefilled = 0; c->generated = 0; c->buf_len = 0; c->opt_tune = 1; c->opt_compact = 1;
     c->opt_packed = 1; c->rows_dirty = 1; c->rows_step = 0;
     c->opt_plain = (cfg->dtype == FASTCOT_F32); c->opt_graph = 1; c->dbg_stop = -1; c->dbg_logits = nullptr;
     c->graph_exec = nullptr; c->graph = nullptr; c->graph_valid = 0; c->prof_on = 0; c->prof_used = 0;
@@ -452,7 +455,7 @@ static int forward(fastcot_ctx* c, int lmhead, int R = 0, bool step = false) {
     if (R > c->kd.Rcap) return fail(c, FASTCOT_ECAPACITY, "pass of %s%ld rows per sequence exceeds the workspace (%ld)", "", (long)R, (long)c->kd.Rcap);
     if (c->opt_plain || !fc_fast_supported(c->kd, c->Bact * R)) return forward_plain(c, lmhead, R);
     FastArgs a;
-    a.kd = c->kd; a.kd.W = R; a.kd.M = c->Bact * R; a.Bact = c->Bact;
+    a.kd = c->kd; a.kd.W = R; a.kd.M = c->Bact * R; a.Bact = c->Bact; a.ctx_len = c->ctx_len + R;
     if (step && c->rows_step > 0) {          // sequences with windows of their own: only those rows
         const StateMap& sm = c->wm.st; const int32_t* stp = state_ptr(c);
         a.kd.M = c->rows_step;
@@ -507,8 +510,22 @@ static int rebuild_rows(fastcot_ctx* c) {
 static int enqueue_step(fastcot_ctx* c) {
     if (c->rows_dirty) { int rc = rebuild_rows(c); if (rc) return rc; }
     // the legacy default stream cannot be captured: launch kernel by kernel there
-    if (!c->opt_graph || c->prof_on || c->st == nullptr) return step_body(c);
+    if (!c->opt_graph || c->prof_on || c->st == nullptr) {
+        const int rc = step_body(c);
+        c->ctx_len += c->ctx_len < c->ctx_max;
+        return rc;
+    }
+    // a context that grows past the line between the two attention forms: the step is captured once more
+    int splits;
+    const int one = !c->opt_plain && fc_attn_one_tile(c->kd, c->Bact, c->plan, c->ctx_len + c->kd.W, &splits);
+    if (c->graph_valid && one != c->graph_one_tile) {
+        HIPCHK(c, hipStreamSynchronize(c->st));        // (the last replay may still run)
+        const int dirty = c->rows_dirty;
+        drop_graph(c);
+        c->rows_dirty = dirty;                         // nobody moved
+    }
     if (!c->graph_valid) {
+        c->graph_one_tile = one;
         HIPCHK(c, hipStreamBeginCapture(c->st, hipStreamCaptureModeThreadLocal));
         int rc = step_body(c);
         hipGraph_t g = nullptr;
@@ -520,6 +537,7 @@ static int enqueue_step(fastcot_ctx* c) {
         c->graph_valid = 1;
     }
     HIPCHK(c, hipGraphLaunch(c->graph_exec, c->st));
+    c->ctx_len += c->ctx_len < c->ctx_max;
     return 0;
 }
 
@@ -540,10 +558,13 @@ static int prefill_passes(fastcot_ctx* c, int B, int maxlen) {
         if (R < 1) R = rows_cap < 16 ? rows_cap : 16;          // 1-token prompts: no forward, only the window set-up
         const bool last = p0 + R >= maxlen - 1;
         HIPCHK(c, fc_prefill_window(stp, sm, B, R, kd.S, p0, c->st));
+        c->ctx_len = p0;
         if (left > 0) { int rc = forward(c, 0, R); if (rc) return rc; }
         HIPCHK(c, fc_prefill_advance(stp, sm, B, kd.W, kd.S, p0 + R, last, c->st));
         p0 += R;
     } while (p0 < maxlen - 1);
+    c->ctx_len = maxlen - 1;
+    c->ctx_max = maxlen - 1 + c->buf_len < kd.S ? maxlen - 1 + c->buf_len : kd.S;
     return 0;
 }
 
@@ -726,9 +747,11 @@ extern "C" int fastcot_join(fastcot_ctx* c, int32_t slot, const int32_t* prompt,
     // a pass of R rows uses the first R window entries, which at R > W are the other sequences' windows
     std::vector<int32_t> wins((size_t)B * kd.W);
     HIPCHK(c, hipMemcpy(wins.data(), stp + sm.win, wins.size() * 4, hipMemcpyDeviceToHost));
+    const int ctx_len = c->ctx_len, ctx_max = c->ctx_max;
     c->Bact = 1;                                   // the step graph, captured for B sequences, is not touched
     int rc = prefill_passes(c, 1, len);
     c->Bact = B;
+    c->ctx_len = std::max(c->ctx_len, ctx_len); c->ctx_max = std::max(c->ctx_max, ctx_max);
     if (rc) return rc;
     HIPCHK(c, hipStreamSynchronize(c->st));
     if (B > 1) HIPCHK(c, hipMemcpy(stp + sm.win + kd.W, wins.data() + kd.W, (size_t)(B - 1) * kd.W * 4, hipMemcpyHostToDevice));
@@ -911,6 +934,7 @@ extern "C" int fastcot_answer(fastcot_ctx* c, const int32_t* trigger_ids, int32_
         for (int b = 0; b < B; ++b)
             for (int j = 0; j < Rp && p0 + j + 1 < (int)ctxrows[b].size(); ++j) rows[(size_t)b * Rp + j] = ctxrows[b][p0 + j];
         HIPCHK(c, hipMemcpy(stp + sm.win, rows.data(), rows.size() * 4, hipMemcpyHostToDevice));
+        c->ctx_len = *std::max_element(hn.begin(), hn.end());
         int rc = forward(c, 0, Rp);
         if (rc) return rc;
         HIPCHK(c, hipStreamSynchronize(c->st));

@@ -20,6 +20,7 @@ struct FastPlan {
 struct FastArgs {
     KernelDims kd;     // kd.M = rows of this pass
     int Bact, lmhead;
+    int ctx_len = 0;   // positions of the longest sequence with this pass's rows, as far as the host knows (a lower bound)
     const ModelMap* mm;
     const WorkspaceMap* wm;
     const char* weights;
@@ -41,6 +42,8 @@ bool fc_fast_supported(const KernelDims& kd, int rows);
 void fc_fast_scratch_sizes(const KernelDims& kd, size_t* gemm_part_bytes, size_t* attn_part_bytes);
 void fc_fast_plan(const KernelDims& kd, FastPlan* plan);
 hipError_t fc_fast_forward(const FastArgs& a);
+// true: a pass of kd.W rows per sequence runs its attention as workgroups of one query tile, with *splits key splits
+bool fc_attn_one_tile(const KernelDims& kd, int Bact, const FastPlan& plan, int ctx_len, int* splits);
 // Times every column-owner GEMM of the pass shape a.kd (at most 32 rows) with one and with two weight batches in
 // flight per wave or the wave's whole K slice at once and records the fastest in the plan.  Only that choice is
 // measured: it moves loads, not additions, so the results are the same bits whichever wins.  Overwrites activations and layer 0's first cache rows:

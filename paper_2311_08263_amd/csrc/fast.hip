@@ -121,6 +121,34 @@ void fc_fast_scratch_sizes(const KernelDims& kd, size_t* gemm_part_bytes, size_t
         if (a.prof && (e_ = a.prof_mark(a.prof, -1)) != hipSuccess) return e_;       \
     } while (0)
 
+// Windows of more than 16 rows at a small batch: workgroups of one query tile each instead of two.  They read K/V twice,
+// which costs nothing while the launch is latency-bound, up to so many key blocks per wave (crossing points of both forms'
+// launch times over 8 to 64 heads, 1 to 8 sequences, 24 to 128 rows, 250 to 15500 positions as hi + lo pairs):
+//   7 with key splits (32 heads 5.8-6.3, 40 heads 6.8), 9 with one split, which saves the merge (8.4-10.6);
+//   more where the second reading comes out of the L2: 1.5 times that for 32 or more heads in groups of at least four
+//   (10.5-11.2), twice for 64 or more (15.5-22);
+//   1.5 times for windows above 32 rows, which the two-tile form reads more than once as well (9.2-12.6), 1.75 times where
+//   half of its last unit is empty (12.2-15);
+//   30 where the two-tile units need more than two workgroups per CU (24-31, 128 rows);
+//   no limit where they leave half of the CUs idle (16 heads on 4, 15500 positions: 51.8 / 65.8 us).
+// The choice is within 12 % of the faster form everywhere there, 0.2 % on average.  us with one / two tiles, 32 rows: 7B
+// prompt 128 10.1 / 15.6, 6000 50.5 / 45.1; batch 4, 512 21.5 / 27.4, 3000 90.4 / 76.4; 64 heads on 8, 512 14.4 / 18.1, 12000
+// 106.7 / 88.3.  The line is drawn at the context, not at the cache's capacity: short contexts are common in large caches.
+bool fc_attn_one_tile(const KernelDims& kd, int Bact, const FastPlan& plan, int ctx_len, int* splits) {
+    const int cus = fc_num_cus(), tiles = (kd.W + 15) / 16, units = Bact * kd.H * tiles, two = Bact * kd.H * ((tiles + 1) / 2) * plan.attn_splits;
+    *splits = plan.attn_splits;
+    if (kd.W <= 16 || units > cus) return false;
+    int sp = plan.attn_splits;
+    while (sp > 1 && units * sp > cus) --sp;
+    float most = sp == 1 ? 9.f : 7.f;                            // key blocks per wave
+    if (kd.H >= 4 * kd.Hkv && kd.H >= 32) most *= kd.H >= 64 ? 2.f : 1.5f;
+    if (tiles > 2) most *= tiles % 2 ? 1.75f : 1.5f;
+    if (two > 2 * cus && most < 30.f) most = 30.f;
+    if ((float)((ctx_len + 31) / 32) > most * (float)(4 * sp) && 2 * two > cus) return false;
+    *splits = sp;
+    return true;
+}
+
 hipError_t fc_fast_forward(const FastArgs& a) {
     const KernelDims& kd = a.kd;
     const ModelMap& mm = *a.mm; const WorkspaceMap& wm = *a.wm;
@@ -226,17 +254,8 @@ hipError_t fc_fast_forward(const FastArgs& a) {
             at.ofrag = af_att;
             at.out = a.dbg_stop >= 0 ? att : nullptr;
         }
-        // windows of more than 16 rows at a small batch: workgroups of one query tile each instead of two (they read
-        // K/V twice, which costs nothing while the launch is latency-bound: 7B, 32 rows, prompt 256 17.5 -> 13.0 us, prompt
-        // 1500 23.8 -> 23.2; batch 4, prompt 700 30.6 -> 28.1), up to 128 K (position, K/V head) pairs of cache capacity, 128 MB as hi + lo
-        // pairs: beyond, the second reading shows (prompt 4000 37.0 -> 44.8 us; batch 4, prompt 1500 47.2 -> 47.6)
-        int attn_splits = a.plan->attn_splits;
-        at.subrows = 0;
-        const int units16 = (kd.W + 15) / 16;
-        if (kd.W > 16 && a.Bact * kd.H * units16 <= fc_num_cus() && (size_t)a.Bact * kd.Hkv * kd.S <= 128 * 1024) {
-            at.subrows = 16;
-            while (attn_splits > 1 && a.Bact * kd.H * units16 * attn_splits > fc_num_cus()) --attn_splits;
-        }
+        int attn_splits;
+        at.subrows = fc_attn_one_tile(kd, a.Bact, *a.plan, a.ctx_len, &attn_splits) ? 16 : 0;
         // passes with many rows per sequence (prompt chunks): one walk over the keys per 128 rows, where that
         // still gives at least half of the CUs a workgroup
         const bool many = a.plan->attn_many == 2 ? kd.W > 32

@@ -272,3 +272,58 @@ def test_many_row_steps(fc, B, W, P):
         out.append(dbg[:B * W].clone())
         ctx.close()
     assert rel(out[0], out[1]) < 1e-4
+
+
+WIDE_HEADS = dict(n_layers=1, d_model=512, n_heads=32, n_kv_heads=32, head_dim=128, d_ffn=768, vocab=1040, init_std=0.05)
+
+
+def test_attention_form_follows_the_context(fc):
+    """Steps of 17 to 32 rows choose between one and two query tiles by the length of the context: a short one in a large
+    cache runs what it runs in a small one, bit for bit."""
+    import torch
+    import synthgen
+    shape, W, P = synthgen.ModelShape(**WIDE_HEADS), 32, 300
+    prompts, buf = synthgen.prompts(1, P, shape.vocab, seed=7), synthgen.buffer_init(1, 2 * W + 8, shape.vocab, seed=8)
+    out = []
+    for S in (512, 8192):
+        say(f"attention form, capacity {S}")
+        cfg = fc.Config.from_shape(shape, 1, S, W)
+        ctx = fc.Context(cfg, fc.load_synth_weights(cfg, shape))
+        ctx.prefill(prompts, [P], buf)
+        dbg = ctx.debug_logits(True)
+        torch.cuda.synchronize()
+        ctx.step()
+        torch.cuda.synchronize()
+        out.append(dbg.clone())
+        ctx.close()
+    assert torch.equal(out[0], out[1])
+
+
+def test_attention_form_changes_during_a_run(fc):
+    """Four sequences grow past the line between the two forms (1024 positions for 128 units of two tiles): with and
+    without a captured graph the same bits at every step, and the plain kernels' logits on both sides of it."""
+    import torch
+    import synthgen
+    shape, B, W, P, steps = synthgen.ModelShape(**WIDE_HEADS), 4, 32, 990, 6
+    cfg = fc.Config.from_shape(shape, B, 1152, W)
+    packed = fc.load_synth_weights(cfg, shape)
+    prompts, buf = synthgen.prompts(B, P, shape.vocab, seed=7), synthgen.buffer_init(B, 2 * W + 24, shape.vocab, seed=8)
+    runs = []
+    for opt in ((), (fc.binding.OPT_GRAPH, 0), (fc.binding.OPT_PLAIN_KERNELS, 1)):
+        say(f"attention form, run {opt}")
+        ctx = fc.Context(cfg, packed)
+        if opt:
+            ctx.set_option(*opt)
+        ctx.prefill(prompts, [P - b for b in range(B)], buf)
+        dbg = ctx.debug_logits(True)
+        torch.cuda.synchronize()
+        got = []
+        for _ in range(steps):
+            ctx.step()
+            torch.cuda.synchronize()
+            got.append(dbg.clone())
+        runs.append(got)
+        ctx.close()
+    for a, b, c in zip(*runs):
+        assert torch.equal(a, b)
+        assert rel(a, c) < 1e-4
