@@ -404,83 +404,31 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
         }
         if (tid == 0) st_agent_i32(a.cnt + bh, 0);
     }
-    if constexpr (KVP == 1) {
-        // A row with a NaN in it is computed once more, key by key in fp32 and over the keys it sees only.  The matrix
-        // instructions multiply what a row does not see by a weight of zero (positions past the window, which nobody has
-        // to fill, and later window rows), and zero times an infinity or NaN in V is NaN; so is a query or a product of
-        // its parts past the range of bf16.  A row whose own keys make it NaN stays so.  Where nothing is NaN this is eight
-        // comparisons (40 heads, 64 rows, 1088 keys 13.95 -> 14.07 us; 32 heads, 16 rows, 2064 keys 11.8 us both ways);
-        // each wave redoes the 32 head elements it finishes.
-#pragma unroll
-        for (int qt = 0; qt < QT; ++qt) {
-            const float inv = 1.0f / lw[qt];
-            bool nan = false;
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) { const float x = o2[qt][t][r] * inv; nan = nan || x != x; }
-            const unsigned long long lanes = __ballot(nan && qt * 16 + lm < Wr);
-            uint32_t rows = (uint32_t)(lanes | lanes >> 16 | lanes >> 32 | lanes >> 48) & 0xFFFFu;
-            while (__builtin_expect(rows != 0, 0)) {
-                const int j = __builtin_ctz(rows);
-                rows &= rows - 1;
-                int last = n + qt * 16 + j;
-                if (last >= T) last = T - 1;
-                const float* qr = a.q + (size_t)(rbase + row0 + qt * 16 + j) * a.ldq + h * 128;
-                auto score = [&](int t) {
-#pragma clang fp contract(off)
-                    // (uncontracted: the caller's difference to the maximum then takes the product as it was rounded there)
-                    float s = 0.f;
-#pragma unroll 1
-                    for (int i = 0; i < 128; i += 8) {
-                        const u32x4_t kw = *(const u32x4_t*)(kbase + k_index(t, i, 128));
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) { s += qr[i + 2 * e] * __uint_as_float(kw[e] << 16); s += qr[i + 2 * e + 1] * __uint_as_float(kw[e] & 0xFFFF0000u); }
-                    }
-                    return s * 0.08838834764831845f;
-                };
-                float mx = -3.0e38f;
-                for (int t = lane; t <= last; t += 64) mx = fmaxf(mx, score(t));
-                for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-                float den = 0.f, sum = 0.f;
-                for (int t0 = 0; t0 <= last; t0 += 64) {     // lane = key, then lane = (parity of the key, head element)
-                    const float p = t0 + lane <= last ? expf(score(t0 + lane) - mx) : 0.f;
-                    den += p;
-#pragma unroll 1
-                    for (int u = lane >> 5; u < 64; u += 2) {
-                        const float pu = __shfl(p, u, 64);
-                        if (t0 + u <= last) sum += pu * __uint_as_float((uint32_t)vbase[v_index(32 * wv + (lane & 31), t0 + u, 128)] << 16);
-                    }
-                }
-                for (int o = 32; o > 0; o >>= 1) den += __shfl_xor(den, o, 64);
-                sum += __shfl_xor(sum, 32, 64);
-                sum /= den;
-#pragma unroll
-                for (int t = 0; t < 2; ++t)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) { const float x = __shfl(sum, 16 * t + 4 * g + r, 64); if (lm == j) o2[qt][t][r] = x; }
-                if (lm == j) lw[qt] = 1.0f;
-            }
-        }
-    }
     // out[row][h*128 + 16*dt + 4*g + r] = O / l, this wave's tiles dt = 2*wv, 2*wv + 1
+    float nans[QT];                                          // 0, or NaN where something of the row is not finite
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {
         const int j = qt * 16 + lm;
+        nans[qt] = 0.f;
         if (j < Wr) {
             const float inv = 1.0f / lw[qt];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                o2[qt][t] *= inv;
+                if constexpr (KVP == 1) nans[qt] += o2[qt][t][0] * 0.f + o2[qt][t][1] * 0.f + o2[qt][t][2] * 0.f + o2[qt][t][3] * 0.f;
+            }
             const int row = rbase + row0 + j;
             if (a.out) {
                 float* o = a.out + (size_t)row * a.ldo + h * 128 + 4 * g;
 #pragma unroll
-                for (int t = 0; t < 2; ++t) *(f32x4_t*)(o + 16 * (2 * wv + t)) = o2[qt][t] * inv;
+                for (int t = 0; t < 2; ++t) *(f32x4_t*)(o + 16 * (2 * wv + t)) = o2[qt][t];
             }
             if (a.ofrag) {
                 // head elements 32 * wv + 16 * t + 4 * g + r: k-tile 4 * h + wv, octet 2 * t + g / 2, elements 4 * (g % 2) + r
                 const size_t KTo = (size_t)a.H * 4;
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
-                    const f32x4_t v = o2[qt][t] * inv;
+                    const f32x4_t v = o2[qt][t];
                     uint32_t h0, l0, h1, l1;
                     pk_bf16_hilo(v[0], v[1], h0, l0);
                     pk_bf16_hilo(v[2], v[3], h1, l1);
@@ -488,6 +436,66 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
                     *(uint2*)dst = make_uint2(h0, h1);
                     *(uint2*)(dst + 1024) = make_uint2(l0, l1);
                 }
+            }
+        }
+    }
+    if constexpr (KVP == 1) {
+        // A row with a NaN in it is computed once more, key by key in fp32 and over the keys it sees only.  The matrix
+        // instructions multiply what a row does not see by a weight of zero (positions past the window, which nobody has
+        // to fill, and later window rows), and zero times an infinity or NaN in V is NaN; so is a query or a product of
+        // its parts past the range of bf16.  A row whose own keys make it NaN (or infinite) stays so.  Each wave redoes
+        // the 32 head elements it has stored; the test runs behind the stores, where it costs 0.0-0.1 us with one
+        // query tile and 0.1-0.2 us with two (in front of them 0.1 and 0.4).
+        uint32_t rows = 0;
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) {
+            const unsigned long long lanes = __ballot(nans[qt] != 0.f);
+            rows |= ((uint32_t)(lanes | lanes >> 16 | lanes >> 32 | lanes >> 48) & 0xFFFFu) << (16 * qt);
+        }
+        if (__builtin_expect(rows == 0, 1)) return;
+        wait_vmem_done();                                    // the stores above come first
+        const int e = lane & 31;                             // lane = (parity of the key, head element)
+        while (rows) {
+            const int j = __builtin_ctz(rows), row = rbase + row0 + j;
+            rows &= rows - 1;
+            int last = n + j;
+            if (last >= T) last = T - 1;
+            const float* qr = a.q + (size_t)row * a.ldq + h * 128;
+            auto score = [&](int t) {
+#pragma clang fp contract(off)
+                // (uncontracted: the caller's difference to the maximum then takes the product as it was rounded there)
+                float s = 0.f;
+#pragma unroll 1
+                for (int i = 0; i < 128; i += 8) {
+                    const u32x4_t kw = *(const u32x4_t*)(kbase + k_index(t, i, 128));
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) { s += qr[i + 2 * u] * __uint_as_float(kw[u] << 16); s += qr[i + 2 * u + 1] * __uint_as_float(kw[u] & 0xFFFF0000u); }
+                }
+                return s * 0.08838834764831845f;
+            };
+            float mx = -3.0e38f;
+            for (int t = lane; t <= last; t += 64) mx = fmaxf(mx, score(t));
+            for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+            float den = 0.f, sum = 0.f;
+            for (int t0 = 0; t0 <= last; t0 += 64) {
+                const float p = t0 + lane <= last ? expf(score(t0 + lane) - mx) : 0.f;       // lane = key
+                den += p;
+#pragma unroll 1
+                for (int u = lane >> 5; u < 64; u += 2) {
+                    const float pu = __shfl(p, u, 64);
+                    if (t0 + u <= last) sum += pu * __uint_as_float((uint32_t)vbase[v_index(32 * wv + e, t0 + u, 128)] << 16);
+                }
+            }
+            for (int o = 32; o > 0; o >>= 1) den += __shfl_xor(den, o, 64);
+            sum += __shfl_xor(sum, 32, 64);
+            sum /= den;
+            if (a.out && lane < 32) a.out[(size_t)row * a.ldo + h * 128 + 32 * wv + e] = sum;
+            if (a.ofrag && lane < 32) {
+                uint32_t hi, lo;
+                pk_bf16_hilo(sum, 0.f, hi, lo);
+                bf16_t* dst = a.ofrag + ((((size_t)(row >> 4) * a.H * 4 + 4 * h + wv) * 2) * 64 + (row & 15) + 16 * (e >> 3)) * 8 + (e & 7);
+                dst[0] = (bf16_t)hi;
+                dst[512] = (bf16_t)lo;
             }
         }
     }
