@@ -377,9 +377,17 @@ hipError_t fc_attn_iso(const float* q, const void* kc, const void* vc, int n, in
     // More than 32 rows: units of 16 rows, queries and probabilities as three bf16 parts, because such a call has
     // always computed in fp32 (error against 64 bits 7e-7; two parts would be 3e-6, three are 3.4e-7).
     // 64 rows, 1088 keys, 40 heads: plain kernel 172 us, this 15.7 us.
-    // Key splits only while every workgroup has a CU to itself (64 heads on 8, 782 keys: 8 splits 11.3 us, 4 splits 10.4 us).
+    // Key splits only while every workgroup has a CU to itself (64 heads on 8, 782 keys, 5 rows: 8 splits 11.3 us, 4 splits
+    // 10.4 us; 17 rows, 1024 keys: 16.6 and 13.3 us).  Units of two query tiles are built for two workgroups per CU and may
+    // have them where heads share K/V and a wave would otherwise walk more than eight key blocks, of more than 96 (64 heads
+    // on 8, 17 rows: 5000 keys 26.3 -> 22.5 us, 15000 keys 65.2 -> 45.2; at 2048 keys 15.5 us without and 17.8 with; 40 heads
+    // with K/V of their own, 15000 keys: 58.4 without and 63.1 with).
     if (W > 32) { at.terms = 3; at.subrows = 16; }
+    const int most = splits;
     while (splits > 1 && units * splits > fc_num_cus()) --splits;
+    const int nb = (n + W + 31) / 32;
+    if (W > 16 && W <= 32 && H > Hkv && nb > 8 * 4 * splits && nb > 96)
+        for (splits = most; splits > 1 && units * splits > 2 * fc_num_cus();) --splits;
     return fc_attn16(at, 1, splits, st);
 }
 

@@ -153,6 +153,17 @@ def test_steps_of_very_large_scores(fc, W, planes):
     assert float(err.median()) < (2e-2 if planes == 1 else 1e-4)
 
 
+@pytest.mark.parametrize("n,W,H,Hkv", [(4050, 32, 64, 8), (4080, 32, 64, 8), (4100, 17, 64, 16), (9000, 24, 40, 8), (3000, 20, 128, 8), (200, 17, 512, 8)])
+def test_two_tile_attention_splits(fc, n, W, H, Hkv):
+    """17 to 32 rows over grouped heads: on both sides of the line beyond which two workgroups share a CU, with as many and
+    with fewer key splits than asked for, and more heads than CUs."""
+    say(f"two-tile attention n={n} W={W} H={H}/{Hkv}")
+    import torch
+    q, k, v = attn_inputs(n, W, H, Hkv, 128, torch.bfloat16)
+    kc, vc = fc.kv_scatter(k, v, (n + W + 31) // 32 * 32)
+    assert rel(fc.attn_window(q, kc, vc, n), attn64(q, k, v, n)) < 1.5e-5
+
+
 def test_one_scratch_for_calls_of_different_shapes(fc):
     """A scratch zeroed once serves any order of shapes it is large enough for."""
     import torch
