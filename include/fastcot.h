@@ -66,8 +66,8 @@ typedef struct fastcot_ctx fastcot_ctx;
 /* Bytes of the library's packed device weight layout / of the device workspace (KV cache,
  * activations, token buffers, counters) for a configuration.  0 on an invalid configuration.
  * The activations are sized for the largest pass: a step of max_batch * window rows, or a prompt chunk (Sec. 4.1, the
- * first forward) of up to 1024 rows in all for bf16 models on the matrix-core kernels, of up to 128 rows per sequence on
- * the plain kernels. */
+ * first forward): up to 1024 rows in all for bf16 models of the shapes the matrix-core kernels cover, for other models
+ * up to 128 rows per sequence within 512 in all, but at least 16 per sequence.  Logits are sized for a step's rows. */
 size_t fastcot_weight_bytes(const fastcot_config* cfg);
 size_t fastcot_workspace_bytes(const fastcot_config* cfg);
 

@@ -129,8 +129,8 @@ int fc_build_maps(const fastcot_config* c, ModelMap* mm, WorkspaceMap* wm, Kerne
         if (ch > k.S) ch = k.S;
         if (ch > k.Wcap) k.Wcap = ch;
     }
-    // prompt passes of the plain kernels: up to 128 rows per sequence, at most 512 rows in all (the window of a step
-    // stays limited to Wcap)
+    // prompt passes of the plain kernels: as many rows per sequence as a pass above, or up to 128 of them where those stay
+    // within 512 rows in all, and 16 in any case (the window of a step stays limited to Wcap)
     k.Rcap = k.Wcap;
     {
         int ch = 128;
@@ -149,14 +149,15 @@ int fc_build_maps(const fastcot_config* c, ModelMap* mm, WorkspaceMap* wm, Kerne
         wm->rope_cos = take((size_t)k.S * (k.Dh / 2) * 4); wm->rope_sin = take((size_t)k.S * (k.Dh / 2) * 4);
         wm->x = take(M * d * 4); wm->qkv = take(M * k.qkvN * 4); wm->qrot = take(M * qd * 4);
         wm->att = take(M * qd * 4); wm->h = take(M * F * 4);
-        wm->logits = take(M * k.V * 4); wm->topv = take(M * 4);
+        const size_t Mw = (size_t)k.B * k.Wcap;          // rows of a step: no other pass has logits
+        wm->logits = take(Mw * k.V * 4); wm->topv = take(Mw * 4);
         fc_fast_scratch_sizes(k, &wm->gemm_part_bytes, &wm->attn_part_bytes);
         wm->gemm_part = take(wm->gemm_part_bytes); wm->gemm_cnt = take(FC_MAX_COUNTERS * 4);
         wm->attn_part = take(wm->attn_part_bytes); wm->attn_cnt = take(FC_MAX_COUNTERS * 4);
         {
             // column-owner kernel: per workgroup 32 rows; many-row kernel: per column block all rows, at most a block per
             // column tile
-            size_t am = (size_t)(k.V / 16 + 8) * 32 * 8, am2 = (size_t)(k.V / 16 + 1) * ((M + 15) / 16 * 16) * 8;
+            size_t am = (size_t)(k.V / 16 + 8) * 32 * 8, am2 = (size_t)(k.V / 16 + 1) * ((Mw + 15) / 16 * 16) * 8;
             wm->amax_part = take(am > am2 ? am : am2);
         }     // winners per column group / per workgroup
         StateMap s; int w = 0;
@@ -452,7 +453,8 @@ static int forward_plain(fastcot_ctx* c, int lmhead, int R) {
 // only the sequences' own rows when they have windows of their own
 static int forward(fastcot_ctx* c, int lmhead, int R = 0, bool step = false) {
     if (R <= 0) R = c->kd.W;
-    if (R > c->kd.Rcap) return fail(c, FASTCOT_ECAPACITY, "pass of %s%ld rows per sequence exceeds the workspace (%ld)", "", (long)R, (long)c->kd.Rcap);
+    const int most = lmhead ? c->kd.Wcap : c->kd.Rcap;
+    if (R > most) return fail(c, FASTCOT_ECAPACITY, "pass of %s%ld rows per sequence exceeds the workspace (%ld)", "", (long)R, (long)most);
     if (c->opt_plain || !fc_fast_supported(c->kd, c->Bact * R)) return forward_plain(c, lmhead, R);
     FastArgs a;
     a.kd = c->kd; a.kd.W = R; a.kd.M = c->Bact * R; a.Bact = c->Bact; a.ctx_len = c->ctx_len + R;
@@ -1050,7 +1052,7 @@ extern "C" int fastcot_debug_read(fastcot_ctx* c, int32_t what, float* host, siz
         case 1: off = c->wm.qkv; cap = M * c->kd.qkvN; break;
         case 2: off = c->wm.att; cap = M * c->kd.H * c->kd.Dh; break;
         case 3: off = c->wm.h; cap = M * c->kd.F; break;
-        case 4: off = c->wm.logits; cap = M * c->kd.V; break;     // plain-path logits buffer
+        case 4: off = c->wm.logits; cap = (size_t)c->kd.B * c->kd.Wcap * c->kd.V; break;     // plain-path logits buffer
         default: return fail(c, FASTCOT_EINVAL, "unknown buffer%s");
     }
     if (count > cap) return fail(c, FASTCOT_ECAPACITY, "count exceeds the buffer%s");

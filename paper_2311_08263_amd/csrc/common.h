@@ -132,7 +132,8 @@ struct WorkspaceMap {
 struct KernelDims {    // model + capacities as the kernels need them
     int32_t L, d, H, Hkv, Dh, F, V, B, S, W, M;   // W = rows per sequence of a pass (the window, or a prefill chunk), M = rows of a pass
     int32_t Wcap;      // most rows per sequence a step, and a prompt pass of the matrix-core path, may have
-    int32_t Rcap;      // most rows per sequence any pass may have, prompt passes of the plain path included (the workspace is sized for B * Rcap rows)
+    int32_t Rcap;      // most rows per sequence any pass may have, prompt passes of the plain path included (activations are sized for
+                       // B * Rcap rows, logits for the B * Wcap rows a step may have)
     int32_t qkvN;      // (H + 2 Hkv) * Dh
     float eps;
     int32_t esz;       // bytes per weight / cache element

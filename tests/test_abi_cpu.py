@@ -36,6 +36,15 @@ def test_sizes_and_invalid_configs():
         assert L.fastcot_workspace_bytes(ctypes.byref(c)) == 0, field
 
 
+def test_logits_are_sized_for_the_rows_of_a_step():
+    """Prompt passes of the plain kernels have more rows per sequence than a step, but no logits: a larger vocabulary adds
+    four bytes per id and step row, and the winners of the argmax (eight bytes per sixteen ids and row)."""
+    L = binding.lib()
+    B, W, d = 4, 8, 256
+    size = [L.fastcot_workspace_bytes(ctypes.byref(binding.Config(2, d, 4, 4, 64, 688, V, 1e-5, 1e4, 0, B, 640, W))) for V in (16000, 32000)]
+    assert 0 < size[1] - size[0] <= 16000 * (B * W * 4 + 32 * 8 // 16) + 4096
+
+
 def test_null_arguments_are_rejected_without_a_gpu():
     L = binding.lib()
     assert L.fastcot_prefill(None, 1, None, 1, None, None, 1) == -1
