@@ -338,3 +338,38 @@ def test_attention_form_changes_during_a_run(fc):
     for a, b, c in zip(*runs):
         assert torch.equal(a, b)
         assert rel(a, c) < 1e-4
+
+
+@pytest.fixture(scope="module")
+def wide_model(fc):
+    """One layer whose QKV, gate/up and LM head have more column tiles than 8 * (CUs / 8 / row blocks) * 16."""
+    import synthgen
+    shape = synthgen.ModelShape(1, 512, 64, 64, 128, 28672, 32000, init_std=0.05)
+    return shape, fc.load_synth_weights(fc.Config.from_shape(shape, 1, 512, 16), shape)
+
+
+@pytest.mark.parametrize("W", [65, 77, 96, 129, 130, 144])
+def test_many_row_steps_over_wide_matrices(fc, wide_model, W):
+    """Row counts that run as blocks of three row tiles with the eight waves side by side: gate/up of 65 to 96 rows, QKV,
+    gate/up and LM head of 129 to 144, the ends of both ranges; the logits and the argmax of the same step through the
+    plain kernels (activations as hi + lo pairs in one and fp32 in the other path, 2^-17 per product)."""
+    import torch
+    import synthgen
+    say(f"many-row step over wide matrices W={W}")
+    shape, packed = wide_model
+    P = 9
+    cfg = fc.Config.from_shape(shape, 1, 512, W)
+    prompts, buf = synthgen.prompts(1, P, shape.vocab, seed=7), synthgen.buffer_init(1, 2 * W + 8, shape.vocab, seed=8)
+    out = []
+    for plain in (0, 1):
+        ctx = fc.Context(cfg, packed)
+        ctx.set_option(fc.binding.OPT_PLAIN_KERNELS, plain)
+        ctx.prefill(prompts, [P], buf)
+        dbg = ctx.debug_logits(True)
+        torch.cuda.synchronize()
+        ctx.step()
+        torch.cuda.synchronize()
+        out.append(dbg[:W].clone())
+        assert (ctx.state()["o"][0] == dbg[:W].argmax(1).cpu().numpy()).all()
+        ctx.close()
+    assert rel(out[0], out[1]) < 1e-4
