@@ -92,7 +92,7 @@ __global__ __launch_bounds__(512) void k_gemm_plain(PlainGemm a) {
     __shared__ float part[8][NC][RB][16];
     __shared__ float part_ss[8][RB];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, lm = lane & 15, g = lane >> 4;
-    const int nt0 = blockIdx.x * NC, m0 = blockIdx.y * RB, NT = a.NP >> 4, KT = (a.K + 31) >> 5;
+    const int nt0 = blockIdx.x * NC, m0 = blockIdx.y * RB, NT = a.NP >> 4, KT = a.K >> 5;
     const float* xr[RB];
 #pragma unroll
     for (int r = 0; r < RB; ++r) xr[r] = a.X + (size_t)(m0 + r < a.M ? m0 + r : a.M - 1) * a.ldx;   // rows past M repeat the last one, never written
@@ -103,10 +103,8 @@ __global__ __launch_bounds__(512) void k_gemm_plain(PlainGemm a) {
 #pragma unroll
         for (int j = 0; j < NC; ++j) acc[j][r] = 0.f;
     }
-#pragma unroll 2
-    for (int kt = w; kt < KT; kt += 8) {
-        const bool in = kt * 32 + 8 * g < a.K;             // K is a multiple of 16: an octet is inside or past the end
-        const int k0 = in ? kt * 32 + 8 * g : 0;
+    auto ktile = [&](int kt) {
+        const int k0 = kt * 32 + 8 * g;
         float wv[NC][8];
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
@@ -133,13 +131,18 @@ __global__ __launch_bounds__(512) void k_gemm_plain(PlainGemm a) {
             float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                x[e] = in ? x[e] : 0.f;
                 if (a.gain) { ss[r] += x[e] * x[e]; x[e] *= gv[e]; }
 #pragma unroll
                 for (int j = 0; j < NC; ++j) acc[j][r] += x[e] * wv[j][e];
             }
         }
-    }
+    };
+    // (one tile per workgroup: two workgroups share a CU instead of two k-tiles of one wave, which would take 175 registers)
+#pragma unroll (NC == 1 ? 1 : 2)
+    for (int kt = w; kt < KT; kt += 8) ktile(kt);
+    // K is a multiple of 16: what may be left is half a k-tile, two octets.  The other lanes take no part: zeroed inputs times
+    // some other row's weights would be NaN where those are infinite.
+    if (DT == FASTCOT_F32 && (a.K & 31) && w == (KT & 7) && g < 2) ktile(KT);
     // octets: two exchanges; then each of the four octet groups publishes two rows of the wave's sums
 #pragma unroll
     for (int r = 0; r < RB; ++r) {

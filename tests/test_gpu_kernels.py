@@ -193,6 +193,34 @@ def test_plain_lmhead(fc, M, d, V):
     assert torch.equal(top2, two[:, 1])
 
 
+@pytest.mark.parametrize("d", [272, 256, 16])
+def test_plain_product_past_the_last_octet(fc, d):
+    """A fp32 head of a width that ends in the middle of a k-tile: an infinite weight among the first eight rows (which
+    octets past the end read instead of nothing) makes its logit infinite and no other one."""
+    import torch
+    import synthgen
+    say(f"plain product d={d}, infinite weight")
+    shape = synthgen.ModelShape(0, d, 2, 2, 32, 48, 64, dtype="f32")
+    cfg = fc.Config.from_shape(shape, 1, 32, 4)
+    tensors = {sp.name: synthgen.weight_array(shape, sp) for sp in synthgen.weight_tensors(shape)}
+    tensors["wlm"][3, 17] = np.inf
+    ctx = fc.Context(cfg, fc.pack_weights(cfg, [(n, -1, t) for n, t in tensors.items()]))
+    prompt, buf = np.array([[5]], dtype=np.int32), np.arange(16, dtype=np.int32).reshape(1, 16)
+    ctx.prefill(prompt, [1], buf)
+    dbg = ctx.debug_logits(True)
+    torch.cuda.synchronize()
+    ctx.step()
+    torch.cuda.synchronize()
+    x = tensors["emb"][[5, 0, 1, 2]].astype(np.float64)
+    x /= np.sqrt((x * x).mean(1, keepdims=True) + shape.rms_eps)
+    want = torch.from_numpy(x @ tensors["wlm"].astype(np.float64)).cuda()
+    got = dbg[:4].clone()
+    assert torch.equal(got[:, 17].double(), want[:, 17]) and torch.isinf(want[:, 17]).all()
+    got[:, 17], want[:, 17] = 0, 0
+    assert rel(got, want) < 1e-6
+    ctx.close()
+
+
 @pytest.mark.parametrize("M,d,V", [(33, 256, 16), (40, 256, 16 * 65), (256, 1024, 16 * 501), (77, 512, 32000), (300, 2048, 16 * 999), (1030, 256, 4096)])
 def test_many_row_lmhead(fc, M, d, V):
     """More than 32 rows through the many-row kernel on three-part activations: every tile width, last column blocks
