@@ -66,7 +66,8 @@ void fc_set_error(const char* msg) { snprintf(g_err, 512, "%s", msg); }
 static const char* kKernelNames[FASTCOT_N_KERNEL_KINDS] = {
     "embed", "rmsnorm", "gemm_qkv", "rope_cache", "attention", "gemm_o", "gemm_gate_up", "swiglu",
     "gemm_down", "lm_head", "argmax", "accept_commit", "attn_combine", "reserved13", "empty_kernel", "reserved15"};
-enum { KK_EMBED = 0, KK_RMSNORM, KK_QKV, KK_ROPE, KK_ATTN, KK_O, KK_GU, KK_SWIGLU, KK_DOWN, KK_LM, KK_ARGMAX, KK_ACCEPT, KK_EMPTY = 14 };
+// (numbers and names are part of the interface; norm, rotary embedding and SwiGLU are parts of other launches: 1, 3, 7 stay at zero)
+enum { KK_EMBED = 0, KK_QKV = 2, KK_ATTN = 4, KK_O = 5, KK_GU = 6, KK_DOWN = 8, KK_LM = 9, KK_ARGMAX = 10, KK_ACCEPT = 11, KK_EMPTY = 14 };
 __global__ void k_empty() {}
 
 extern "C" const char* fastcot_kernel_name(int32_t kind) {

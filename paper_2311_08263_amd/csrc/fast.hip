@@ -186,7 +186,7 @@ hipError_t fc_fast_forward(const FastArgs& a) {
     int x_nssq = d / 256;
     const float* next_gain = nullptr;          // gain the next residual GEMM folds into the fragments of x
     // LM head: one winner per row and column block
-    const int lm_ncb = fc_gemm256_plan(EPI_LMHEAD, M, kd.V / 16, 1, 2).ncb;
+    const int lm_ncb = fc_gemm256_plan(M, kd.V / 16, 1, 2).ncb;
     big.amax_val = g.amax_val; big.amax_idx = (int32_t*)(g.amax_val + (size_t)lm_ncb * big.amax_stride);
     int gi = 0;        // which GEMM of the plan
     auto gemm = [&](int epi, const void* W, int K, int N, const float* X, int ldx, const float* gain,
@@ -428,7 +428,7 @@ hipError_t fc_lmhead_iso(const float* act, const void* packed, int M, int d, int
         g.W = (const bf16_t*)packed; g.K = d; g.NT = V / 16; g.AF = (bf16_t*)(sc + off); g.planes = 3; g.M = M; g.out = logits; g.ldo = V;
         g.sk = 1; g.amax_stride = (M + 15) / 16 * 16;
         g.amax_val = (float*)(sc + off + FC_ALIGN(fc_split_bytes(M, d, 3)));
-        const int ncb = fc_gemm256_plan(EPI_LMHEAD, M, V / 16, 1, 3).ncb;
+        const int ncb = fc_gemm256_plan(M, V / 16, 1, 3).ncb;
         g.amax_idx = (int32_t*)(g.amax_val + (size_t)ncb * g.amax_stride);
         hipError_t e = fc_split3(act, d, M, d, (bf16_t*)(sc + off), st);
         if (e == hipSuccess) e = fc_gemm256(EPI_LMHEAD, g, st);

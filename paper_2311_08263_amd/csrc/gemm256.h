@@ -14,7 +14,7 @@ struct Gemm256Args {
     bf16_t* kc; bf16_t* vc;
     int32_t layer, H, Hkv, B, S, Wn, kvp, kvq;
     RowMap rm;             // QKV: which sequence and slot a row is (dense when rm.rowb is NULL)
-    float* amax_val; int32_t* amax_idx;   // LM head: winners per column block of 256 [column blocks][amax_stride]
+    float* amax_val; int32_t* amax_idx;   // LM head: winners per column block [ncb][amax_stride]
     int32_t amax_stride;
     int32_t sk;            // K slices (RESID only when > 1: partial tiles to `part`, then added in slice order)
     float* part;           // [sk][M][NT*16] fp32
@@ -32,10 +32,10 @@ struct Gemm256Args {
 };
 #define FC_GEMM256_MAX_SK 8
 struct Gemm256Plan { int ksplit, cw, rt, ncb; };   // two k-groups, column tiles per wave, row tiles per block, column blocks (see gemm256.hip)
-Gemm256Plan fc_gemm256_plan(int epi, int M, int NT, int sk, int planes);
+Gemm256Plan fc_gemm256_plan(int M, int NT, int sk, int planes);
 int fc_gemm256_sk(int M, int K, int NT);   // slices that fill the chip for a matrix with few columns
 // partial sums per row that a residual GEMM of these sizes leaves in rf_ssq; never more than NT
-static inline int fc_gemm256_nssq(int M, int NT, int sk) { return sk > 1 ? NT / 16 : fc_gemm256_plan(EPI_RESID, M, NT, 1, 2).ncb; }
+static inline int fc_gemm256_nssq(int M, int NT, int sk) { return sk > 1 ? NT / 16 : fc_gemm256_plan(M, NT, 1, 2).ncb; }
 
 // X [M][ldx] fp32 -> AF, three parts
 hipError_t fc_split3(const float* X, int ldx, int M, int K, bf16_t* AF, hipStream_t st);

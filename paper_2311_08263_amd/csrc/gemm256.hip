@@ -583,7 +583,7 @@ int fc_gemm256_sk(int M, int K, int NT) {
 // three of the XCDs, a second round that cost 7B passes of 320 rows 22 %.)  Measured, blocks of fixed width (and four row tiles) -> dealt evenly: 7B QKV of 1024 rows 205 -> 185 us;
 // of 77 rows gate/up 64 -> 54 us, QKV 42 -> 40 us, LM head 71 -> 67 us; 13B gate/up of 256 rows 122 us either way (216 busy
 // CUs run at a higher clock than 256 do).
-Gemm256Plan fc_gemm256_plan(int epi, int M, int NT, int sk, int planes) {
+Gemm256Plan fc_gemm256_plan(int M, int NT, int sk, int planes) {
     Gemm256Plan p;
     const int MT = (M + 15) / 16, cus = fc_num_cus();
     const int b3 = (MT + 2) / 3, b4 = (MT + 3) / 4;
@@ -643,7 +643,7 @@ hipError_t fc_gemm256(int epi, const Gemm256Args& a0, hipStream_t st) {
     if (a.rf_AF && ((a.NT * 16) % 256 || !a.rf_gain || !a.rf_ssq)) return hipErrorInvalidValue;
     // the kernel addresses weights and fragments with 32-bit byte offsets from their bases
     if ((size_t)a.NT * 16 * a.K * 2 >= ((size_t)1 << 32) || (size_t)((a.M + 15) / 16) * 16 * a.K * (a.planes == 3 ? 6 : 4) >= ((size_t)1 << 32)) return hipErrorInvalidValue;
-    const Gemm256Plan p = fc_gemm256_plan(epi, a.M, a.NT, a.sk, a.planes);
+    const Gemm256Plan p = fc_gemm256_plan(a.M, a.NT, a.sk, a.planes);
     a.ncb = p.ncb;
     if ((size_t)a.NT * (a.ncb + 1) >= ((size_t)1 << 32)) return hipErrorInvalidValue;
     const size_t nrb = ((a.M + 15) / 16 + p.rt - 1) / p.rt, units = (size_t)p.ncb * a.sk;

@@ -182,7 +182,7 @@ __global__ __launch_bounds__(512) void k_gemm_plain(PlainGemm a) {
         // the transposed V cache.
         const KernelDims& kd = a.kd;
         const int b = m / kd.W, pos = a.n_state[b] + m % kd.W, half = kd.Dh >> 1, hh = n / kd.Dh, cc = n % kd.Dh;
-        a.Y[(size_t)m * a.ldy + n] = v;
+        a.Y[(size_t)m * a.ldy + n] = v;                    // read by fastcot_debug_read alone
         if (pos >= kd.S) return;                           // capacity guard: never write outside the cache
         const size_t plane = (size_t)kd.S * kd.Dh;
         if (hh < kd.H + kd.Hkv) {
