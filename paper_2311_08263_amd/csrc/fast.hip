@@ -376,7 +376,7 @@ hipError_t fc_attn_iso(const float* q, const void* kc, const void* vc, int n, in
     int splits = iso_attn_splits(n + W);
     // More than 32 rows: units of 16 rows, queries and probabilities as three bf16 parts, because such a call has
     // always computed in fp32 (error against 64 bits 7e-7; two parts would be 3e-6, three are 3.4e-7).
-    // 64 rows, 1088 keys, 40 heads: plain kernel 172 us, this 15.7 us.
+    // 64 rows, 1088 keys, 40 heads: plain kernel 172 us, this 14.0 us.
     // Key splits only while every workgroup has a CU to itself (64 heads on 8, 782 keys, 5 rows: 8 splits 11.3 us, 4 splits
     // 10.4 us; 17 rows, 1024 keys: 16.6 and 13.3 us).  Units of two query tiles are built for two workgroups per CU and may
     // have them where heads share K/V and a wave would otherwise walk more than eight key blocks, of more than 96 (64 heads
@@ -422,7 +422,7 @@ hipError_t fc_lmhead_iso(const float* act, const void* packed, int M, int d, int
     if (top2 && !logits) logits = lg_scratch;              // the runner-up is read off the logits
     if (lm_iso_many(M, d, V)) {
         // the many-row kernel on activations in three bf16 parts: such a call has always computed in fp32, and two
-        // parts would leave the logits 2.3e-6 off.  256 rows x 5120 x 32000: plain product 3.19 ms, this 186 us.
+        // parts would leave the logits 2.3e-6 off.  256 rows x 5120 x 32000: plain product 1.99 ms, this 192 us.
         const size_t off = lm_iso_logits_end(M, V);
         Gemm256Args g; memset(&g, 0, sizeof(g));
         g.W = (const bf16_t*)packed; g.K = d; g.NT = V / 16; g.AF = (bf16_t*)(sc + off); g.planes = 3; g.M = M; g.out = logits; g.ldo = V;
