@@ -351,9 +351,9 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
         for (int qt = 0; qt < QT; ++qt) {
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                float* dst = mine + qt * PART_FLOATS + ((2 * wv + t) * 64 + lane) * 4;
+                float* dst = mine + qt * PART_FLOATS + (2 * wv + t) * 256 + lane * 2;
                 st_agent_f32x2(dst, o2[qt][t][0], o2[qt][t][1]);
-                st_agent_f32x2(dst + 2, o2[qt][t][2], o2[qt][t][3]);
+                st_agent_f32x2(dst + 128, o2[qt][t][2], o2[qt][t][3]);
             }
             if (wv == 0) {
                 st_agent_f32(mine + qt * PART_FLOATS + 2048 + lane, mw[qt]);
@@ -381,10 +381,10 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
                     ls[u] = ld_agent_f32(src + 2112 + lane);
 #pragma unroll
                     for (int t = 0; t < 2; ++t) {
-                        const float* p4 = src + ((2 * wv + t) * 64 + lane) * 4;
+                        const float* p4 = src + (2 * wv + t) * 256 + lane * 2;
                         float v0, v1, v2, v3;
                         ld_agent_f32x2(p4, v0, v1);
-                        ld_agent_f32x2(p4 + 2, v2, v3);
+                        ld_agent_f32x2(p4 + 128, v2, v3);
                         os[u][t] = (f32x4_t){v0, v1, v2, v3};
                     }
                 }

@@ -341,10 +341,10 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
         // squares) meet through memory; the last workgroup to arrive adds them in slice order
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
-            float* mine = a.xpart + ((size_t)blockIdx.x * (8 * NF) + w + 8 * f) * 256 + lane * 4;
+            float* mine = a.xpart + ((size_t)blockIdx.x * (8 * NF) + w + 8 * f) * 256 + lane * 2;
             if (fin[f]) {
                 st_agent_f32x2(mine, v[f][0], v[f][1]);
-                st_agent_f32x2(mine + 2, v[f][2], v[f][3]);
+                st_agent_f32x2(mine + 128, v[f][2], v[f][3]);
             }
         }
         float* sspart = a.xpart + (size_t)gridDim.x * (8 * NF) * 256;       // [workgroup][MT * 16]
@@ -370,10 +370,10 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
             f32x4_t part[8];
 #pragma unroll
             for (int s2 = 0; s2 < 8; ++s2) {
-                const float* src = a.xpart + ((size_t)(owner * ks + (s2 < ks ? s2 : 0)) * (8 * NF) + w + 8 * f) * 256 + lane * 4;
+                const float* src = a.xpart + ((size_t)(owner * ks + (s2 < ks ? s2 : 0)) * (8 * NF) + w + 8 * f) * 256 + lane * 2;
                 float p0, p1, p2, p3;
                 ld_agent_f32x2(src, p0, p1);
-                ld_agent_f32x2(src + 2, p2, p3);
+                ld_agent_f32x2(src + 128, p2, p3);
                 part[s2] = (f32x4_t){p0, p1, p2, p3};
             }
             v[f] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
