@@ -431,13 +431,18 @@ static int forward_plain(fastcot_ctx* c, int lmhead, int R) {
     const StateMap& sm = c->wm.st;
     float* x = (float*)(ws + c->wm.x); float* qkv = (float*)(ws + c->wm.qkv); float* qrot = (float*)(ws + c->wm.qrot);
     float* att = (float*)(ws + c->wm.att); float* h = (float*)(ws + c->wm.h);
-    LAUNCH(c, KK_EMBED, fc_embed(wt + c->mm.emb_off, dt, stp + sm.win, x, M, d, kd.V, c->st));
+    // fp32 models: the first layer takes its residual rows straight from the embedding (one launch less); x is first written
+    // by its O projection
+    const TokenRows emb{(const float*)(wt + c->mm.emb_off), stp + sm.win, kd.V}, none{nullptr, nullptr, 0};
+    const bool gather = dt == FASTCOT_F32 && kd.L > 0;
+    if (!gather) LAUNCH(c, KK_EMBED, fc_embed(wt + c->mm.emb_off, dt, stp + sm.win, x, M, d, kd.V, c->st));
     for (int l = 0; l < kd.L; ++l) {
         const char* lb = wt + c->mm.layers_off + (size_t)l * c->mm.layer_stride;
+        const TokenRows tr = gather && l == 0 ? emb : none;
         LAUNCH(c, KK_QKV, fc_qkv_plain(lb + c->mm.qkv.off, dt, kd, l, x, (const float*)(lb + c->mm.g1_off), qkv, qrot, stp + sm.n,
-                                       (const float*)(ws + c->wm.rope_cos), (const float*)(ws + c->wm.rope_sin), ws + c->wm.kc, ws + c->wm.vc, c->st));
+                                       (const float*)(ws + c->wm.rope_cos), (const float*)(ws + c->wm.rope_sin), ws + c->wm.kc, ws + c->wm.vc, c->st, tr));
         LAUNCH(c, KK_ATTN, fc_attn_plain(qrot, qd, ws + c->wm.kc, ws + c->wm.vc, dt, kd, l, stp + sm.n, 0, att, c->st));
-        LAUNCH(c, KK_O, fc_gemm_plain(lb + c->mm.o.off, dt, qd, c->mm.o.NP, d, att, qd, x, d, M, 1, c->st));
+        LAUNCH(c, KK_O, fc_gemm_plain(lb + c->mm.o.off, dt, qd, c->mm.o.NP, d, att, qd, x, d, M, 1, c->st, nullptr, 0.f, tr));
         LAUNCH(c, KK_GU, fc_swiglu_plain(lb + c->mm.gu.off, dt, d, kd.F, x, d, h, M, (const float*)(lb + c->mm.g2_off), kd.eps, c->st));
         LAUNCH(c, KK_DOWN, fc_gemm_plain(lb + c->mm.down.off, dt, kd.F, c->mm.down.NP, d, h, kd.F, x, d, M, 1, c->st));
     }

@@ -15,14 +15,19 @@ struct PlainGemm {
     const float* X; int32_t ldx;
     float* Y; int32_t ldy, M;
     const float* gain; float eps;
+    const float* emb; const int32_t* tok; int32_t V;   // emb not NULL: row m of the residual stream is still the embedding of token tok[m]
+                                                       // (< V): the inputs X of a product with a norm in front, what an adding one adds to
     KernelDims kd; int32_t layer;
     float* qrot; const int32_t* n_state; const float* cosT; const float* sinT; void* kc; void* vc;
 };
+// residual rows that no launch has written yet: the fp32 embeddings of tokens tok[m] (all NULL / 0: the rows are in memory)
+struct TokenRows { const float* emb; const int32_t* tok; int32_t V; };
 hipError_t fc_gemm_plain(const void* W, int dt, int K, int NP, int N, const float* X, int ldx, float* Y, int ldy,
-                         int M, int accumulate, hipStream_t st, const float* gain = nullptr, float eps = 0.f);
+                         int M, int accumulate, hipStream_t st, const float* gain = nullptr, float eps = 0.f, TokenRows tr = TokenRows{nullptr, nullptr, 0});
 // QKV product of the normed rows, rotary embedding and cache write; qkv keeps the product as it was before the rotation
 hipError_t fc_qkv_plain(const void* W, int dt, const KernelDims& kd, int layer, const float* X, const float* gain, float* qkv, float* qrot,
-                        const int32_t* n_state, const float* cosT, const float* sinT, void* kc, void* vc, hipStream_t st);
+                        const int32_t* n_state, const float* cosT, const float* sinT, void* kc, void* vc, hipStream_t st,
+                        TokenRows tr = TokenRows{nullptr, nullptr, 0});
 // committed lengths from n_state[b], or n_host for every sequence where that is NULL
 hipError_t fc_attn_plain(const float* q, int ldq, const void* kc, const void* vc, int dt, const KernelDims& kd,
                          int layer, const int32_t* n_state, int n_host, float* out, hipStream_t st);

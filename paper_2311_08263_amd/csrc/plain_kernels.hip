@@ -4,6 +4,7 @@
 // i + Dh/2, grouped-query attention with the causal mask of Eq. (2), SwiGLU).  Like the MFMA path a layer is five
 // launches: QKV (norm, rotary embedding and cache write inside), attention, O, gate/up (norm and SwiGLU inside), down.
 #include "kernels.h"
+#include "gemmco.h"      // fc_num_cus
 
 template <int DT> __device__ inline float wat(const void* W, size_t i) {
     if (DT == FASTCOT_F32) return ((const float*)W)[i];
@@ -77,16 +78,59 @@ hipError_t fc_embed(const void* emb, int dt, const int32_t* win, float* x, int M
 }
 
 // ------------------------------------------------------------------ GEMM  Y[m][n] (+)= sum_k norm(X)[m][k] W[k][n]
-// Bound by latency at the sizes it is meant for (256-wide fp32 layers: all weights in L2, a launch is a few load
-// round trips), so K is spread wide and nothing is staged: eight waves, wave w on k-tiles of 32 inputs w, w + 8, ...;
-// lane (column lm, octet g) loads 8 weights of its column and the 8 inputs of every row (the 16 lanes of an octet
-// share the address), and the partial sums meet by two lane exchanges and one LDS round.  A workgroup computes 8 rows
-// x 16 * NC columns: NC = 1 gives the most workgroups; NC = 4 reads the activations once for four tiles.  A norm in
-// front (gain != NULL) costs no pass of its own: the gain multiplies the inputs, the row's 1 / rms the sums.
-// One thread per output with K serial, as it was, took 34-88 us for each product of the 256-wide model; this takes
-// 5-6.6 us.
+// A norm in front (gain != NULL) costs no pass of its own: the gain multiplies the inputs, the row's 1 / rms the sums.
+// K is spread wide and nothing is staged.
+//
+// bf16 weights (k_gemm_plain): eight waves, wave w on k-tiles of 32 inputs w, w + 8, ...; lane (column lm, octet g) loads 8
+// weights of its column and the 8 inputs of every row (the 16 lanes of an octet share the address), and the partial sums meet by
+// two lane exchanges and one LDS round.  A workgroup computes 8 rows x 16 * NC columns: NC = 1 gives the most workgroups;
+// NC = 4 reads the activations once for four tiles.
 enum { PEPI_STORE = 0, PEPI_ADD = 1, PEPI_SWIGLU = 2, PEPI_QKV = 3 };
-template <int DT, int EPI, int NC>
+// One thread of the workgroup finishes an output: product v of row m and column n (16-column tile nt, column c of it) and the value
+// eight columns away; yold, fcos, fsin and pos as plain_request fetched them.
+struct PlainRest { float yold, fcos, fsin; int pos; };
+template <int EPI>
+__device__ inline void plain_request_first(const PlainGemm& a, int m, PlainRest& r, int& tok) {
+    r.pos = 0; tok = 0;
+    if (EPI == PEPI_QKV) r.pos = a.n_state[m / a.kd.W] + m % a.kd.W;
+    if (EPI == PEPI_ADD && a.emb) { tok = a.tok[m]; if (tok < 0 || tok >= a.V) tok = 0; }
+}
+template <int EPI>
+__device__ inline void plain_request(const PlainGemm& a, int m, int n, int c, int tok, PlainRest& r) {
+    r.yold = 0.f; r.fcos = 1.f; r.fsin = 0.f;
+    if (EPI == PEPI_ADD) r.yold = a.emb ? a.emb[(size_t)tok * a.ldy + (n < a.N ? n : 0)] : a.Y[(size_t)m * a.ldy + (n < a.N ? n : 0)];
+    if (EPI == PEPI_QKV) {
+        const int half = a.kd.Dh >> 1, hh = n / a.kd.Dh, i = 8 * ((n % a.kd.Dh) >> 4) + (c & 7), p = r.pos < a.kd.S ? r.pos : 0;
+        if (hh < a.kd.H + a.kd.Hkv) { r.fcos = a.cosT[(size_t)p * half + i]; r.fsin = a.sinT[(size_t)p * half + i]; }
+    }
+}
+template <int DT, int EPI>
+__device__ inline void plain_finish(const PlainGemm& a, int m, int nt, int c, float v, float other, const PlainRest& rest) {
+    const int n = nt * 16 + c;
+    if (EPI == PEPI_STORE) { if (n < a.N) a.Y[(size_t)m * a.ldy + n] = v; }
+    else if (EPI == PEPI_ADD) { if (n < a.N) a.Y[(size_t)m * a.ldy + n] = rest.yold + v; }
+    else if (EPI == PEPI_SWIGLU) {                         // columns 0..7 of a tile: gate of features 8 * nt ..; 8..15: their up values
+        if (c < 8) a.Y[(size_t)m * a.ldy + nt * 8 + c] = v / (1.0f + expf(-v)) * other;
+    } else {
+        // row m = b*W + j sits at absolute position n[b] + j; the product is in packed column order (head_col).
+        // Rotated q goes to qrot in natural order, k heads are rotated and stored to the K cache, v heads stored to
+        // the transposed V cache.
+        const KernelDims& kd = a.kd;
+        const int b = m / kd.W, pos = rest.pos, half = kd.Dh >> 1, hh = n / kd.Dh, cc = n % kd.Dh;
+        a.Y[(size_t)m * a.ldy + n] = v;                    // read by fastcot_debug_read alone
+        if (pos >= kd.S) return;                           // capacity guard: never write outside the cache
+        const size_t plane = (size_t)kd.S * kd.Dh;
+        if (hh < kd.H + kd.Hkv) {
+            const int i = 8 * (cc >> 4) + (c & 7), el = c < 8 ? i : i + half;
+            const float rot = c < 8 ? v * rest.fcos - other * rest.fsin : v * rest.fcos + other * rest.fsin;
+            if (hh < kd.H) a.qrot[(size_t)m * kd.H * kd.Dh + (size_t)hh * kd.Dh + el] = rot;
+            else kvstore<DT>(a.kc, kv_block(kd, a.layer, b, hh - kd.H) + k_index(pos, el, kd.Dh), plane, kd.kvp, rot);
+        } else
+            kvstore<DT>(a.vc, kv_block(kd, a.layer, b, hh - kd.H - kd.Hkv) + v_index(cc, pos, kd.Dh), plane, kd.kvp, v);
+    }
+}
+
+template <int EPI, int NC>
 __global__ __launch_bounds__(512) void k_gemm_plain(PlainGemm a) {
     constexpr int RB = 8;
     __shared__ float part[8][NC][RB][16];
@@ -109,16 +153,10 @@ __global__ __launch_bounds__(512) void k_gemm_plain(PlainGemm a) {
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
             const int nt = nt0 + j < NT ? nt0 + j : NT - 1;
-            if (DT == FASTCOT_F32) {
-                const float* p = (const float*)a.W + (size_t)k0 * a.NP + nt * 16 + lm;
+            const uint4 h = *((const uint4*)a.W + ((size_t)nt * (a.K >> 5) + kt) * 64 + lane);
+            const uint32_t hw[4] = {h.x, h.y, h.z, h.w};
 #pragma unroll
-                for (int e = 0; e < 8; ++e) wv[j][e] = p[(size_t)e * a.NP];
-            } else {
-                const uint4 h = *((const uint4*)a.W + ((size_t)nt * (a.K >> 5) + kt) * 64 + lane);
-                const uint32_t hw[4] = {h.x, h.y, h.z, h.w};
-#pragma unroll
-                for (int p = 0; p < 4; ++p) { wv[j][2 * p] = __uint_as_float(hw[p] << 16); wv[j][2 * p + 1] = __uint_as_float(hw[p] & 0xFFFF0000u); }
-            }
+            for (int p = 0; p < 4; ++p) { wv[j][2 * p] = __uint_as_float(hw[p] << 16); wv[j][2 * p + 1] = __uint_as_float(hw[p] & 0xFFFF0000u); }
         }
         float gv[8];
         if (a.gain) {
@@ -140,9 +178,6 @@ __global__ __launch_bounds__(512) void k_gemm_plain(PlainGemm a) {
     // (one tile per workgroup: two workgroups share a CU instead of two k-tiles of one wave, which would take 175 registers)
 #pragma unroll (NC == 1 ? 1 : 2)
     for (int kt = w; kt < KT; kt += 8) ktile(kt);
-    // K is a multiple of 16: what may be left is half a k-tile, two octets.  The other lanes take no part: zeroed inputs times
-    // some other row's weights would be NaN where those are infinite.
-    if (DT == FASTCOT_F32 && (a.K & 31) && w == (KT & 7) && g < 2) ktile(KT);
     // octets: two exchanges; then each of the four octet groups publishes two rows of the wave's sums
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
@@ -160,7 +195,7 @@ __global__ __launch_bounds__(512) void k_gemm_plain(PlainGemm a) {
     }
     __syncthreads();
     if (tid >= NC * 128) return;
-    const int j = tid >> 7, r = (tid >> 4) & 7, c = tid & 15, m = m0 + r, nt = nt0 + j, n = nt * 16 + c;
+    const int j = tid >> 7, r = (tid >> 4) & 7, c = tid & 15, m = m0 + r, nt = nt0 + j;
     float v = 0.f;
 #pragma unroll
     for (int q = 0; q < 8; ++q) v += part[q][j][r][c];
@@ -172,34 +207,118 @@ __global__ __launch_bounds__(512) void k_gemm_plain(PlainGemm a) {
     }
     const float other = __shfl_xor(v, 8, 64);             // the value 8 columns away: rotary partner, or gate <-> up
     if (m >= a.M || nt >= NT) return;
-    if (EPI == PEPI_STORE) { if (n < a.N) a.Y[(size_t)m * a.ldy + n] = v; }
-    else if (EPI == PEPI_ADD) { if (n < a.N) a.Y[(size_t)m * a.ldy + n] += v; }
-    else if (EPI == PEPI_SWIGLU) {                         // columns 0..7 of a tile: gate of features 8 * nt ..; 8..15: their up values
-        if (c < 8) a.Y[(size_t)m * a.ldy + nt * 8 + c] = v / (1.0f + expf(-v)) * other;
-    } else {
-        // row m = b*W + j sits at absolute position n[b] + j; the product is in packed column order (head_col).
-        // Rotated q goes to qrot in natural order, k heads are rotated and stored to the K cache, v heads stored to
-        // the transposed V cache.
-        const KernelDims& kd = a.kd;
-        const int b = m / kd.W, pos = a.n_state[b] + m % kd.W, half = kd.Dh >> 1, hh = n / kd.Dh, cc = n % kd.Dh;
-        a.Y[(size_t)m * a.ldy + n] = v;                    // read by fastcot_debug_read alone
-        if (pos >= kd.S) return;                           // capacity guard: never write outside the cache
-        const size_t plane = (size_t)kd.S * kd.Dh;
-        if (hh < kd.H + kd.Hkv) {
-            const int i = 8 * (cc >> 4) + (c & 7), el = c < 8 ? i : i + half;
-            const float co = a.cosT[(size_t)pos * half + i], si = a.sinT[(size_t)pos * half + i];
-            const float rot = c < 8 ? v * co - other * si : v * co + other * si;
-            if (hh < kd.H) a.qrot[(size_t)m * kd.H * kd.Dh + (size_t)hh * kd.Dh + el] = rot;
-            else kvstore<DT>(a.kc, kv_block(kd, a.layer, b, hh - kd.H) + k_index(pos, el, kd.Dh), plane, kd.kvp, rot);
-        } else
-            kvstore<DT>(a.vc, kv_block(kd, a.layer, b, hh - kd.H - kd.Hkv) + v_index(cc, pos, kd.Dh), plane, kd.kvp, v);
+    PlainRest rest; int tok;
+    plain_request_first<EPI>(a, m, rest, tok);
+    plain_request<EPI>(a, m, nt * 16 + c, c, tok, rest);
+    plain_finish<FASTCOT_BF16, EPI>(a, m, nt, c, v, other, rest);
+}
+
+// fp32 weights: the fp32 matrix instructions (16 x 16 outputs x 4 inputs, products and sums in fp32).  Bound by latency at the
+// sizes it is meant for (256-wide layers: all weights in L2, a launch is a few load round trips), so the point is few
+// instructions and one round trip: a workgroup computes 16 rows x 16 * NC columns; wave w of eight takes the groups of 16 inputs w,
+// w + 8, ..., U of them requested together; lane (row or column lm, quarter g) holds inputs 4 g .. 4 g + 3 of the group: one
+// 16-byte load of its row and four weights of its column, which are the operands of four instructions.  What the epilogue needs
+// besides the product is requested up front.  (On vector instructions, a lane loading the inputs of all eight rows, a launch's X
+// loads alone kept the CU's load path busy for 0.9 us.)  8 rows of the 256-wide model, traced, that
+// form -> this: QKV 6.1 -> 4.6 us, O 3.8 -> 2.1, gate/up 5.5 -> 4.6, down 8.0 -> 4.7, LM head 4.9 -> 4.1; steps of fp32 models of 96 to 2048
+// inputs and 1 to 128 rows 1.15 to 2.0 times as fast as a whole.
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+template <int EPI, int NC>
+__global__ __launch_bounds__(512) void k_gemm_f32(PlainGemm a) {
+    constexpr int U = NC == 1 ? 6 : 4;
+    __shared__ float part[8][NC][16 * 17];
+    __shared__ float part_ss[8][16];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), lm = lane & 15, g = lane >> 4;
+    const int nt0 = blockIdx.x * NC, m0 = blockIdx.y * 16, NT = a.NP >> 4, GT = a.K >> 4;
+    // the output this thread finishes (the first NC * 256 threads)
+    const int fj = (tid >> 8) % NC, fr = (tid >> 4) & 15, fc = tid & 15, fm = m0 + fr < a.M ? m0 + fr : a.M - 1;
+    const int fnt = nt0 + fj < NT ? nt0 + fj : NT - 1;
+    PlainRest rest; int ftok;
+    plain_request_first<EPI>(a, fm, rest, ftok);
+    const int row = m0 + lm < a.M ? m0 + lm : a.M - 1;     // rows past M repeat the last one, never written
+    const float* xr = a.X + (size_t)row * a.ldx;
+    if (EPI == PEPI_QKV && a.emb) { const int t = a.tok[row]; xr = a.emb + (size_t)(t < 0 || t >= a.V ? 0 : t) * a.ldx; }
+    uint32_t wo[NC];                                       // (weights: a uniform base per input, a fixed 32-bit offset per lane)
+#pragma unroll
+    for (int j = 0; j < NC; ++j) wo[j] = (uint32_t)(4 * g) * (uint32_t)a.NP + (nt0 + j < NT ? nt0 + j : NT - 1) * 16 + lm;
+    f32x4_t acc[NC][4];                                    // (short chains: with one accumulator the sums lose a bit against 64 bits)
+#pragma unroll
+    for (int j = 0; j < NC; ++j) acc[j][0] = acc[j][1] = acc[j][2] = acc[j][3] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    float ss = 0.f;
+    bool first = true;
+    for (int g0 = w; g0 < GT || first; g0 += 8 * U) {      // (waves without a group still request what they finish)
+        float wv[U][NC][4];
+        float4 x[U], gn[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int gi = g0 + 8 * u;
+            if (gi < GT) {
+#pragma unroll
+                for (int j = 0; j < NC; ++j)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) wv[u][j][i] = ((const float*)a.W + (size_t)(gi * 16 + i) * a.NP)[wo[j]];
+                x[u] = *(const float4*)(xr + gi * 16 + 4 * g);
+                if (a.gain) gn[u] = *(const float4*)(a.gain + gi * 16 + 4 * g);
+            }
+        }
+        if (first) plain_request<EPI>(a, fm, fnt * 16 + fc, fc, ftok, rest);
+        first = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (g0 + 8 * u < GT) {
+                float xv[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+                if (a.gain) {
+                    const float gv[4] = {gn[u].x, gn[u].y, gn[u].z, gn[u].w};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) { ss += xv[i] * xv[i]; xv[i] *= gv[i]; }
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < NC; ++j) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[u][j][i], xv[i], acc[j][i], 0, 0, 0);
+            }
+        }
     }
+    // lane: row lm, columns 4 g + e
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+        const f32x4_t s = (acc[j][0] + acc[j][1]) + (acc[j][2] + acc[j][3]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) part[w][j][lm * 17 + 4 * g + e] = s[e];
+    }
+    if (a.gain) {
+        ss += __shfl_xor(ss, 16, 64);
+        ss += __shfl_xor(ss, 32, 64);
+        if (g == 0) part_ss[w][lm] = ss;
+    }
+    __syncthreads();
+    if (tid >= NC * 256) return;
+    float v = 0.f;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v += part[q][fj][fr * 17 + fc];
+    if (a.gain) {
+        float s = 0.f;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s += part_ss[q][fr];
+        v *= 1.0f / sqrtf(s / (float)a.K + a.eps);
+    }
+    const float other = __shfl_xor(v, 8, 64);             // the value 8 columns away: rotary partner, or gate <-> up
+    if (m0 + fr >= a.M || nt0 + fj >= NT) return;
+    plain_finish<FASTCOT_F32, EPI>(a, m0 + fr, nt0 + fj, fc, v, other, rest);
 }
 template <int DT, int EPI> static hipError_t launch_gemm_plain(const PlainGemm& a, hipStream_t st) {
-    const int NT = a.NP >> 4, rb = (a.M + 7) / 8;
-    // four tiles per workgroup only where that leaves several workgroups per CU
-    if ((size_t)NT * rb >= 4096) k_gemm_plain<DT, EPI, 4><<<dim3((NT + 3) / 4, rb), 512, 0, st>>>(a);
-    else k_gemm_plain<DT, EPI, 1><<<dim3(NT, rb), 512, 0, st>>>(a);
+    const int NT = a.NP >> 4;
+    if constexpr (DT == FASTCOT_F32) {
+        const int rb = (a.M + 15) / 16;
+        // two column tiles per workgroup where one would give more than eight workgroups per CU
+        if ((size_t)NT * rb > 2048) k_gemm_f32<EPI, 2><<<dim3((NT + 1) / 2, rb), 512, 0, st>>>(a);
+        else k_gemm_f32<EPI, 1><<<dim3(NT, rb), 512, 0, st>>>(a);
+    } else {
+        const int rb = (a.M + 7) / 8;
+        // four tiles per workgroup only where that leaves several workgroups per CU
+        if ((size_t)NT * rb >= 4096) k_gemm_plain<EPI, 4><<<dim3((NT + 3) / 4, rb), 512, 0, st>>>(a);
+        else k_gemm_plain<EPI, 1><<<dim3(NT, rb), 512, 0, st>>>(a);
+    }
     return hipGetLastError();
 }
 template <int DT> static hipError_t launch_gemm_plain_epi(int epi, const PlainGemm& a, hipStream_t st) {
@@ -216,8 +335,8 @@ static hipError_t gemm_plain_any(int epi, int dt, const PlainGemm& a, hipStream_
     return dt == FASTCOT_F32 ? launch_gemm_plain_epi<FASTCOT_F32>(epi, a, st) : launch_gemm_plain_epi<FASTCOT_BF16>(epi, a, st);
 }
 hipError_t fc_gemm_plain(const void* W, int dt, int K, int NP, int N, const float* X, int ldx, float* Y, int ldy,
-                         int M, int accumulate, hipStream_t st, const float* gain, float eps) {
-    PlainGemm a{}; a.W = W; a.K = K; a.NP = NP; a.N = N; a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy; a.M = M; a.gain = gain; a.eps = eps;
+                         int M, int accumulate, hipStream_t st, const float* gain, float eps, TokenRows tr) {
+    PlainGemm a{}; a.emb = tr.emb; a.tok = tr.tok; a.V = tr.V; a.W = W; a.K = K; a.NP = NP; a.N = N; a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy; a.M = M; a.gain = gain; a.eps = eps;
     return gemm_plain_any(accumulate ? PEPI_ADD : PEPI_STORE, dt, a, st);
 }
 hipError_t fc_swiglu_plain(const void* W, int dt, int K, int F, const float* X, int ldx, float* h, int M, const float* gain,
@@ -226,8 +345,9 @@ hipError_t fc_swiglu_plain(const void* W, int dt, int K, int F, const float* X, 
     return gemm_plain_any(PEPI_SWIGLU, dt, a, st);
 }
 hipError_t fc_qkv_plain(const void* W, int dt, const KernelDims& kd, int layer, const float* X, const float* gain, float* qkv, float* qrot,
-                        const int32_t* n_state, const float* cosT, const float* sinT, void* kc, void* vc, hipStream_t st) {
-    PlainGemm a{}; a.W = W; a.K = kd.d; a.NP = a.N = kd.qkvN; a.X = X; a.ldx = kd.d; a.Y = qkv; a.ldy = kd.qkvN; a.M = kd.M;
+                        const int32_t* n_state, const float* cosT, const float* sinT, void* kc, void* vc, hipStream_t st,
+                        TokenRows tr) {
+    PlainGemm a{}; a.emb = tr.emb; a.tok = tr.tok; a.V = tr.V; a.W = W; a.K = kd.d; a.NP = a.N = kd.qkvN; a.X = X; a.ldx = kd.d; a.Y = qkv; a.ldy = kd.qkvN; a.M = kd.M;
     a.gain = gain; a.eps = kd.eps; a.kd = kd; a.layer = layer; a.qrot = qrot; a.n_state = n_state; a.cosT = cosT; a.sinT = sinT; a.kc = kc; a.vc = vc;
     return gemm_plain_any(PEPI_QKV, dt, a, st);
 }

@@ -96,6 +96,28 @@ def test_windows(env, W):
         assert out["steps"][0] == N
 
 
+@pytest.mark.parametrize("d,H,Hkv,Dh,F,V,B,W,P", [
+    (32, 1, 1, 32, 16, 16, 1, 1, 5),           # fewer groups of inputs than waves, one column tile, one row
+    (96, 3, 1, 32, 80, 48, 1, 15, 20),         # half a row tile empty by one row; 80 inputs
+    (256, 4, 4, 64, 688, 1024, 1, 17, 40),     # a second block of rows with one row
+    (512, 4, 2, 128, 816, 16 * 1031, 1, 17, 12),   # two column tiles per workgroup, the last one alone; heads of 128
+    (128, 4, 1, 32, 1616, 512, 2, 8, 70),      # more groups than a wave takes at once; 8192 logits
+])
+def test_fp32_shapes(d, H, Hkv, Dh, F, V, B, W, P):
+    """The fp32 products at the edges of their tiles and loops, the first layer's rows straight from the embedding: logits,
+    argmax and accept step of three steps against the oracle.  Sums of at most 1616 fp32 products: the bar of the small model."""
+    import paper_2311_08263_amd as fc
+    say(f"fp32 model d={d} heads {H}/{Hkv} x {Dh} F={F} V={V} B={B} W={W} P={P}")
+    shape = synthgen.ModelShape(2, d, H, Hkv, Dh, F, V, dtype="f32")
+    cfg = fc.Config.from_shape(shape, B, P + 3 * W + 32, W)
+    ctx = fc.Context(cfg, fc.load_synth_weights(cfg, shape))
+    prompts = synthgen.prompts(B, P, V, seed=31)
+    lens = [P - 3 * b for b in range(B)]
+    ctx.prefill(prompts, lens, synthgen.buffer_init(B, 3 * W + 8, V, seed=32))
+    r = follow_steps(ctx, oracle.model_from_synth(shape), prompts, lens, 3, TOL, margin=4 * TOL)
+    assert r["rows"] == 3 * B * W
+
+
 def test_ragged_batch_eos_and_cap(env):
     """Sequences of different prompt lengths advance independently; EOS among the accepted tokens
     stops a sequence (approximate EOS does not); max_steps caps the iterations."""
