@@ -368,7 +368,11 @@ __device__ inline float block_sum(float v, float* red) {
 // key r, quarter p of the head elements; two exchanges add the quarters), then 16 head elements x 32 positions
 // (lane = element, octet of positions), and the waves' sums over their blocks meet in LDS.  With a thread per key and
 // a thread per head element walking all keys one by one a 64-row window over 1088 keys and 40 heads took 647 us; now 172 us.
-template <int DT>
+// EARLY (heads of up to 64 elements, launches of at most two workgroups per CU): each wave's first K tile and V block are
+// requested before anything is known of the lengths, so that the launch is not a chain of four round trips; what lies behind the
+// last position is read all the same and not used.  256-wide model, 8 rows x 4 heads, 40 keys: 7.8 -> 5.6 us a launch, same bits.  (Heads of 128: the
+// unrolled copies of the long loop cost long contexts a quarter.)
+template <int DT, bool EARLY>
 __global__ __launch_bounds__(256) void k_attn_plain(const float* q, int ldq, const void* kc, const void* vc, KernelDims kd, int layer,
                                                     const int32_t* n_state, int n_host, float* out) {
     extern __shared__ float sc[];   // [S] scores, [Dh] the query, [4][Dh] sums of the waves, [16] reduction scratch
@@ -376,14 +380,39 @@ __global__ __launch_bounds__(256) void k_attn_plain(const float* q, int ldq, con
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 15, p = lane >> 4;
     const int m = blockIdx.x, h = blockIdx.y, b = m / kd.W, j = m % kd.W;
     int last = (n_state ? n_state[b] : n_host) + j;
-    if (last >= kd.S) last = kd.S - 1;
-    const int kh = h / (kd.H / kd.Hkv), Dh = kd.Dh, G = Dh >> 5, NB = (last >> 5) + 1;
+    const int kh = h / (kd.H / kd.Hkv), Dh = kd.Dh, G = Dh >> 5;
     const size_t kbase = kv_block(kd, layer, b, kh), plane = (size_t)kd.S * Dh;
+    constexpr int EG = EARLY ? 2 : 1;
+    float kv0[EG][8], vv0[2 * EG][8];
+    if (EARLY) {
+        const int nblk = (kd.S + 31) >> 5, kb0 = (w >> 1) < nblk ? w >> 1 : nblk - 1, vb0 = w < nblk ? w : nblk - 1;
+#pragma unroll
+        for (int i = 0; i < EG; ++i)
+            if (i < G) kvload8<DT>(kc, kbase + (size_t)kb0 * 32 * Dh + (size_t)(((w & 1) * 4 + p) * 16 * G + r + 16 * i) * 8, plane, kd.kvp, kv0[i]);
+#pragma unroll
+        for (int i = 0; i < 2 * EG; ++i)
+            if (i < 2 * G) kvload8<DT>(vc, kbase + (size_t)vb0 * 32 * Dh + (size_t)(i * 64 + lane) * 8, plane, kd.kvp, vv0[i]);
+    }
     for (int i = tid; i < Dh; i += 256) qs[i] = q[(size_t)m * ldq + (size_t)h * Dh + i];
+    if (last >= kd.S) last = kd.S - 1;
+    const int NB = (last >> 5) + 1;
     __syncthreads();
     const float scale = 1.0f / sqrtf((float)Dh);
     float mx = -3.0e38f;
-    for (int hb = w; hb < 2 * NB; hb += 4) {               // half block: tile hb % 2 of key block hb / 2
+    if (EARLY && w < 2 * NB) {                             // half block w, as below
+        const int pos = (w >> 1) * 32 + 8 * (r >> 2) + 4 * (w & 1) + (r & 3);
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < EG; ++i)
+            if (i < G)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s += qs[32 * i + 8 * p + e] * kv0[i][e];
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        s *= scale;
+        if (pos <= last) { if (p == 0) sc[pos] = s; mx = fmaxf(mx, s); }
+    }
+    for (int hb = EARLY ? w + 4 : w; hb < 2 * NB; hb += 4) {   // half block: tile hb % 2 of key block hb / 2
         const int pos = (hb >> 1) * 32 + 8 * (r >> 2) + 4 * (hb & 1) + (r & 3);
         float s = 0.f;
 #pragma unroll 4
@@ -405,6 +434,27 @@ __global__ __launch_bounds__(256) void k_attn_plain(const float* q, int ldq, con
     float den = 0.f;
     for (int t = tid; t <= last; t += 256) { const float e = expf(sc[t] - mx); sc[t] = e; den += e; }
     den = block_sum(den, red);                             // (its first barrier also publishes the weights)
+    if constexpr (EARLY) {
+#pragma unroll
+        for (int dt = 0; dt < 2 * EG; ++dt) {
+            if (dt >= 2 * G) break;
+            float acc = 0.f;
+            if (w < NB)                                    // the wave's first block, which is here already
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc += w * 32 + 8 * p + e <= last ? sc[w * 32 + 8 * p + e] * vv0[dt][e] : 0.f;
+#pragma unroll 4
+            for (int blk = w + 4; blk < NB; blk += 4) {
+                float kv[8];
+                kvload8<DT>(vc, kbase + (size_t)blk * 32 * Dh + (size_t)(dt * 64 + lane) * 8, plane, kd.kvp, kv);
+                const int t0 = blk * 32 + 8 * p;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc += t0 + e <= last ? sc[t0 + e] * kv[e] : 0.f;
+            }
+            acc += __shfl_xor(acc, 16, 64);
+            acc += __shfl_xor(acc, 32, 64);
+            if (p == 0) wsum[w * Dh + dt * 16 + r] = acc;
+        }
+    } else
     for (int dt = 0; dt < Dh >> 4; ++dt) {
         float acc = 0.f;
 #pragma unroll 4
@@ -427,13 +477,18 @@ hipError_t fc_attn_plain(const float* q, int ldq, const void* kc, const void* vc
                          int layer, const int32_t* n_state, int n_host, float* out, hipStream_t st) {
     dim3 grid(kd.M, kd.H);
     const size_t sh = ((size_t)kd.S + 5 * kd.Dh + 16) * sizeof(float);
-    const void* fn = dt == FASTCOT_F32 ? (const void*)k_attn_plain<FASTCOT_F32> : (const void*)k_attn_plain<FASTCOT_BF16>;
-    if (sh > 64 * 1024) {                                  // the longest caches: past the default limit of a launch
-        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
-    }
-    if (dt == FASTCOT_F32) k_attn_plain<FASTCOT_F32><<<grid, 256, sh, st>>>(q, ldq, kc, vc, kd, layer, n_state, n_host, out);
-    else k_attn_plain<FASTCOT_BF16><<<grid, 256, sh, st>>>(q, ldq, kc, vc, kd, layer, n_state, n_host, out);
+    auto launch = [&](auto kernel) -> hipError_t {
+        if (sh > 64 * 1024) {                              // the longest caches: past the default limit of a launch
+            const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (e != hipSuccess) return e;
+        }
+        kernel<<<grid, 256, sh, st>>>(q, ldq, kc, vc, kd, layer, n_state, n_host, out);
+        return hipSuccess;
+    };
+    const bool early = kd.Dh <= 64 && kd.M * kd.H <= 2 * fc_num_cus();
+    const hipError_t e = dt == FASTCOT_F32 ? (early ? launch(k_attn_plain<FASTCOT_F32, true>) : launch(k_attn_plain<FASTCOT_F32, false>))
+                                           : (early ? launch(k_attn_plain<FASTCOT_BF16, true>) : launch(k_attn_plain<FASTCOT_BF16, false>));
+    if (e != hipSuccess) return e;
     return hipGetLastError();
 }
 
