@@ -422,7 +422,8 @@ static hipError_t prof_mark(fastcot_ctx* c, int kind) {
         if ((c)->prof_on) HIPCHK(c, prof_mark(c, -1));                             \
     } while (0)
 
-static int forward_plain(fastcot_ctx* c, int lmhead, int R) {
+// accepted (a Jacobi step): set where the accept step was run together with the argmax
+static int forward_plain(fastcot_ctx* c, int lmhead, int R, bool* accepted) {
     const KernelDims kd0 = c->kd;
     KernelDims kd = kd0; kd.W = R; kd.M = c->Bact * R;
     const int dt = c->cfg.dtype, M = kd.M, d = kd.d, qd = kd.H * kd.Dh;
@@ -450,18 +451,22 @@ static int forward_plain(fastcot_ctx* c, int lmhead, int R) {
         float* logits = c->dbg_logits ? c->dbg_logits : (float*)(ws + c->wm.logits);
         LAUNCH(c, KK_LM, fc_gemm_plain(wt + c->mm.lm.off, dt, d, c->mm.lm.NP, kd.V, x, d, logits, kd.V, M, 0, c->st,
                                        (const float*)(wt + c->mm.gf_off), kd.eps));
-        LAUNCH(c, KK_ARGMAX, fc_argmax_plain(logits, M, kd.V, stp + sm.o, (float*)(ws + c->wm.topv), c->st));
+        if (accepted && fc_tail_fits(c->Bact, kd.W, M, kd.V, false)) {
+            LAUNCH(c, KK_ARGMAX, fc_tail_logits(logits, M, kd.V, (float*)(ws + c->wm.topv), stp, sm, c->Bact, kd.W, kd.S, c->st));
+            *accepted = true;
+        } else
+            LAUNCH(c, KK_ARGMAX, fc_argmax_plain(logits, M, kd.V, stp + sm.o, (float*)(ws + c->wm.topv), c->st));
     }
     return 0;
 }
 
 // one forward pass over R rows per sequence (R = 0: the window); step: the pass of a Jacobi step, which computes
 // only the sequences' own rows when they have windows of their own
-static int forward(fastcot_ctx* c, int lmhead, int R = 0, bool step = false) {
+static int forward(fastcot_ctx* c, int lmhead, int R = 0, bool step = false, bool* accepted = nullptr) {
     if (R <= 0) R = c->kd.W;
     const int most = lmhead ? c->kd.Wcap : c->kd.Rcap;
     if (R > most) return fail(c, FASTCOT_ECAPACITY, "pass of %s%ld rows per sequence exceeds the workspace (%ld)", "", (long)R, (long)most);
-    if (c->opt_plain || !fc_fast_supported(c->kd, c->Bact * R)) return forward_plain(c, lmhead, R);
+    if (c->opt_plain || !fc_fast_supported(c->kd, c->Bact * R)) return forward_plain(c, lmhead, R, accepted);
     FastArgs a;
     a.kd = c->kd; a.kd.W = R; a.kd.M = c->Bact * R; a.Bact = c->Bact; a.ctx_len = c->ctx_len + R;
     if (step && c->rows_step > 0) {          // sequences with windows of their own: only those rows
@@ -471,7 +476,7 @@ static int forward(fastcot_ctx* c, int lmhead, int R = 0, bool step = false) {
     }
     a.mm = &c->mm; a.wm = &c->wm; a.weights = c->weights; a.ws = c->ws; a.dbg_logits = c->dbg_logits;
     a.plan = &c->plan; a.st = c->st; a.lmhead = lmhead;
-    a.dbg_stop = c->dbg_stop;
+    a.dbg_stop = c->dbg_stop; a.accept = accepted != nullptr; a.accepted = accepted;
     a.prof = c->prof_on ? c : nullptr;
     a.prof_mark = c->prof_on ? [](void* p, int kind) { return prof_mark((fastcot_ctx*)p, kind); } : nullptr;
     hipError_t e = fc_fast_forward(a);
@@ -480,9 +485,10 @@ static int forward(fastcot_ctx* c, int lmhead, int R = 0, bool step = false) {
 }
 
 static int step_body(fastcot_ctx* c) {
-    int rc = forward(c, 1, 0, true);
+    bool accepted = false;
+    int rc = forward(c, 1, 0, true, &accepted);
     if (rc) return rc;
-    LAUNCH(c, KK_ACCEPT, fc_accept_commit(state_ptr(c), c->wm.st, c->Bact, c->kd.W, c->kd.S, c->st));
+    if (!accepted) LAUNCH(c, KK_ACCEPT, fc_accept_commit(state_ptr(c), c->wm.st, c->Bact, c->kd.W, c->kd.S, c->st));
     return 0;
 }
 

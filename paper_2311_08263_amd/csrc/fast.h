@@ -31,6 +31,8 @@ struct FastArgs {
     void* prof;
     hipError_t (*prof_mark)(void*, int);
     RowMap rm = RowMap{nullptr, nullptr, nullptr};   // packed rows of a step with per-sequence windows (kd.M = their sum, kd.W = the largest)
+    bool accept = false;   // the pass is a Jacobi step: the accept step follows the argmax, in the same launch where that pays ...
+    bool* accepted = nullptr;   // ... and *accepted says whether it did
     int dbg_stop;      // debug: number of stages to run (5 per layer), < 0 = all
     int tune_gi = -1;  // >= 0: launch only GEMM tune_gi (0 QKV, 1 O, 2 gate/up, 3 down, 4 LM head) of layer 0 ...
     int tune_sb = 0;   // ... with this many-batches choice, this batch order and this many K slices per owner

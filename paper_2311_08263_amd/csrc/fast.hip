@@ -283,7 +283,11 @@ hipError_t fc_fast_forward(const FastArgs& a) {
         const int nwin = nwlm;                                // partial winners to reduce
         gi = 4;
         FLAUNCH(KK_LM, gemm(EPI_LMHEAD, wt + mm.lm.off, d, kd.V, x, d, (const float*)(wt + mm.gf_off), a.dbg_logits, kd.V));
-        if (M <= 32)
+        if (a.accept && fc_tail_fits(a.Bact, kd.W, M, nwin, true)) {
+            FLAUNCH(KK_ARGMAX, fc_tail_winners(g.amax_val, (const int32_t*)(g.amax_val + (size_t)nwin * stride), nwin, stride, M, (float*)(ws + wm.topv),
+                                               a.rm, stp, wm.st, a.Bact, kd.W, kd.S, a.st));
+            *a.accepted = true;
+        } else if (M <= 32)
             FLAUNCH(KK_ARGMAX, fc_argmax_final(g.amax_val, (const int32_t*)(g.amax_val + (size_t)nwin * stride), nwin, stride, M, stp + wm.st.o,
                                                (float*)(ws + wm.topv), a.st, a.rm, kd.W));
         else

@@ -42,6 +42,11 @@ hipError_t fc_prefill_advance(int32_t* state, const StateMap& sm, int B, int W, 
                               hipStream_t st);
 hipError_t fc_rewindow(int32_t* state, const StateMap& sm, int B, int W, int S, hipStream_t st);
 hipError_t fc_accept_commit(int32_t* state, const StateMap& sm, int B, int W, int S, hipStream_t st);
+// argmax of a step's rows and the accept step in one launch, where fc_tail_fits (rows M, logits per row or partial winners per row)
+bool fc_tail_fits(int B, int W, int M, int V_or_parts, bool winners);
+hipError_t fc_tail_logits(const float* logits, int M, int V, float* top, int32_t* state, const StateMap& sm, int B, int W, int S, hipStream_t st);
+hipError_t fc_tail_winners(const float* val, const int32_t* idx, int nparts, int stride, int M, float* top, RowMap rm, int32_t* state,
+                           const StateMap& sm, int B, int W, int S, hipStream_t st);
 // sequences b1 and b2 trade slots: state entries and K/V cache (seq_bytes per sequence and layer, layers layer_stride_bytes apart)
 hipError_t fc_swap_sequences(int32_t* state, const StateMap& sm, int b1, int b2, int W, int S, void* kc, void* vc,
                              size_t seq_bytes, int layers, size_t layer_stride_bytes, hipStream_t st);

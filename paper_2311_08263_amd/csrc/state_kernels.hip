@@ -51,7 +51,8 @@ hipError_t fc_prefill_advance(int32_t* state, const StateMap& sm, int B, int W, 
 // n..n+K already.  All W fresh outputs go back to the buffer; the window slides by K+1.
 // One wave per sequence, lane j on window slot j (in rounds of 64 for wider windows): the scans of Eq. 5 and of
 // the EOS rule are ballots, the copies one load and one store per lane.
-__global__ void k_accept_commit(int32_t* st, StateMap sm, int B, int W, int S) {
+// o_all [B][W]: the argmax ids of the step's rows (in memory or LDS).  Called by a whole workgroup.
+__device__ inline void accept_commit(int32_t* st, const StateMap& sm, int B, int W, int S, const int32_t* o_all) {
     __shared__ int not_done;
     if (threadIdx.x == 0) not_done = 0;
     __syncthreads();
@@ -61,7 +62,7 @@ __global__ void k_accept_commit(int32_t* st, StateMap sm, int B, int W, int S) {
     for (int b = wave; b < B; b += nwaves) {
         if (st[sm.done + b]) { if (lane == 0) st[sm.lastK + b] = -1; continue; }
         const int32_t* w = st + sm.win + b * W;
-        const int32_t* o = st + sm.o + b * W;
+        const int32_t* o = o_all + b * W;
         int32_t* buf = st + sm.buf + (size_t)b * S;
         int32_t* out = st + sm.out + (size_t)b * S;
         int n = st[sm.n + b], g = st[sm.g + b], steps = st[sm.steps + b];
@@ -126,6 +127,88 @@ __global__ void k_accept_commit(int32_t* st, StateMap sm, int B, int W, int S) {
     }
     __syncthreads();
     if (threadIdx.x == 0) st[sm.flags + FLAG_ALL_DONE] = (not_done == 0);
+}
+__global__ void k_accept_commit(int32_t* st, StateMap sm, int B, int W, int S) { accept_commit(st, sm, B, W, S, st + sm.o); }
+
+// The end of a small step in one launch: one workgroup of sixteen waves finds every row's argmax and, with the ids still in
+// LDS, runs the accept step.  Two launches cost a kernel boundary more (2-4 us) than one workgroup loses against one per
+// row, as long as there is little to read: see fc_tail_fits.
+#define TAIL_IDS 1024
+__device__ inline bool tail_better(float v, int i, float best, int bi) { return v > best || (v == best && i < bi); }
+// rows of a packed step sit at entry rowb[m] * W + rowj[m] of the ids
+__device__ inline int tail_dst(const RowMap& rm, int m, int W) { return rm.rowb ? rm.rowb[m] * W + rm.rowj[m] : m; }
+
+// from the logits [M][V], a wave per row
+__global__ __launch_bounds__(1024) void k_tail_logits(const float* logits, int M, int V, float* top, int32_t* st, StateMap sm, int B, int W, int S) {
+    __shared__ int32_t ids[TAIL_IDS];
+    const int lane = threadIdx.x & 63;
+    for (int m = threadIdx.x >> 6; m < M; m += 16) {
+        const float* r = logits + (size_t)m * V;
+        float best = -INFINITY; int bi = 0x7fffffff;
+        int i = lane;
+        for (; i + 192 < V; i += 256) {                    // four loads in flight; ascending ids: a later one wins only by value
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = r[i + 64 * u];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) if (tail_better(v[u], i + 64 * u, best, bi)) { best = v[u]; bi = i + 64 * u; }
+        }
+        for (; i < V; i += 64) { const float v = r[i]; if (tail_better(v, i, best, bi)) { best = v; bi = i; } }
+        for (int o = 32; o > 0; o >>= 1) {
+            const float ov = __shfl_xor(best, o, 64); const int oi = __shfl_xor(bi, o, 64);
+            if (tail_better(ov, oi, best, bi)) { best = ov; bi = oi; }
+        }
+        if (lane == 0) { ids[m] = bi == 0x7fffffff ? 0 : bi; st[sm.o + m] = ids[m]; top[m] = best; }     // nothing but NaN: id 0
+    }
+    __syncthreads();
+    accept_commit(st, sm, B, W, S, ids);
+}
+// from the LM head's winners per workgroup, val / idx [nparts][R], R = 16 or 32 rows: lane (row, part), so that a wave's load takes
+// whole lines
+template <int R>
+__global__ __launch_bounds__(1024) void k_tail_winners(const float* val, const int32_t* idx, int nparts, int M, float* top, RowMap rm, int32_t* st,
+                                                       StateMap sm, int B, int W, int S) {
+    __shared__ int32_t ids[TAIL_IDS];
+    __shared__ float bv[16][R];
+    __shared__ int bi[16][R];
+    const int tid = threadIdx.x, m = tid % R, wave = tid >> 6;
+    float best = -INFINITY; int b = 0x7fffffff;
+#pragma unroll 4
+    for (int c = tid / R; c < nparts; c += 1024 / R) {
+        const float v = val[(size_t)c * R + m]; const int i = idx[(size_t)c * R + m];
+        if (tail_better(v, i, best, b)) { best = v; b = i; }
+    }
+#pragma unroll
+    for (int o = R; o < 64; o <<= 1) {
+        const float ov = __shfl_xor(best, o, 64); const int oi = __shfl_xor(b, o, 64);
+        if (tail_better(ov, oi, best, b)) { best = ov; b = oi; }
+    }
+    if ((tid & 63) < R) { bv[wave][m] = best; bi[wave][m] = b; }
+    for (int i = tid; i < B * W; i += 1024) ids[i] = st[sm.o + i];     // entries no row of this step fills keep what they were
+    __syncthreads();
+    if (tid < M) {
+        for (int q = 0; q < 16; ++q) if (tail_better(bv[q][tid], bi[q][tid], best, b)) { best = bv[q][tid]; b = bi[q][tid]; }
+        const int dst = tail_dst(rm, tid, W), id = b == 0x7fffffff ? 0 : b;
+        ids[dst] = id; st[sm.o + dst] = id; top[dst] = best;
+    }
+    __syncthreads();
+    accept_commit(st, sm, B, W, S, ids);
+}
+// Within 8192 logits, or winners of at most 32 rows, one workgroup reads them in the time of a launch.
+bool fc_tail_fits(int B, int W, int M, int V_or_parts, bool winners) {
+    return B * W <= TAIL_IDS && (winners ? M <= 32 && V_or_parts <= 512 : (size_t)M * V_or_parts <= 8192);
+}
+hipError_t fc_tail_logits(const float* logits, int M, int V, float* top, int32_t* state, const StateMap& sm, int B, int W, int S, hipStream_t st) {
+    if (!fc_tail_fits(B, W, M, V, false) || M != B * W) return hipErrorInvalidValue;
+    k_tail_logits<<<1, 1024, 0, st>>>(logits, M, V, top, state, sm, B, W, S);
+    return hipGetLastError();
+}
+hipError_t fc_tail_winners(const float* val, const int32_t* idx, int nparts, int stride, int M, float* top, RowMap rm, int32_t* state,
+                           const StateMap& sm, int B, int W, int S, hipStream_t st) {
+    if (!fc_tail_fits(B, W, M, nparts, true) || (stride != 16 && stride != 32) || M > stride) return hipErrorInvalidValue;
+    if (stride == 16) k_tail_winners<16><<<1, 1024, 0, st>>>(val, idx, nparts, M, top, rm, state, sm, B, W, S);
+    else k_tail_winners<32><<<1, 1024, 0, st>>>(val, idx, nparts, M, top, rm, state, sm, B, W, S);
+    return hipGetLastError();
 }
 // A new window size between steps: the window is rebuilt from the newest exact token and the buffer
 // (the buffer already holds every output of the previous steps, Sec. 4.3 "Cache Update").

@@ -118,6 +118,36 @@ def test_fp32_shapes(d, H, Hkv, Dh, F, V, B, W, P):
     assert r["rows"] == 3 * B * W
 
 
+@pytest.mark.parametrize("dtype,B,W,wins", [("f32", 1, 8, None), ("f32", 5, 13, None), ("bf16", 1, 1, None), ("bf16", 1, 16, None), ("bf16", 2, 9, None),
+                                            ("bf16", 2, 16, None), ("bf16", 4, 12, [3, 12, 1, 7]), ("bf16", 3, 15, [15, 4, 9])])
+def test_equal_logits_take_the_lowest_id(dtype, B, W, wins):
+    """A head of zeros: every logit ties, in every lane, wave and workgroup that looks for the winner, so id 0 it is (R9), also where the
+    accept step runs in the same launch; Eq. 5 on top of it is recomputed."""
+    import paper_2311_08263_amd as fc
+    say(f"ties {dtype} B={B} W={W} windows {wins}")
+    shape = synthgen.ModelShape(1, 256, 2, 2, 128, 512, 112 if dtype == "f32" else 16 * 300, dtype=dtype)
+    cfg = fc.Config.from_shape(shape, B, 128, W)
+
+    def weights():
+        for spec in synthgen.weight_tensors(shape):
+            t = synthgen.weight_array(shape, spec, synthgen.WEIGHT_SEED, as_bf16_bits=dtype == "bf16")
+            yield spec.name, spec.layer, np.zeros_like(t) if spec.name == "wlm" else t
+    ctx = fc.Context(cfg, fc.pack_weights(cfg, weights()))
+    buf = np.zeros((B, 64), dtype=np.int32)
+    buf[:, 2::5] = 7                                       # two slots verify, then one does not
+    ctx.prefill(synthgen.prompts(B, 20, shape.vocab, seed=5), [20] * B, buf)
+    if wins:
+        ctx.set_windows(wins)
+    for _ in range(2):
+        win = ctx.state()["window"].copy()
+        nacc, acc, _ = ctx.step()
+        st = ctx.state()
+        for b in range(B):
+            Wb = wins[b] if wins else W
+            assert (st["o"][b][:Wb] == 0).all()
+            assert nacc[b] == oracle.verify(win[b][:Wb], st["o"][b][:Wb]) + 1 and (acc[b, :nacc[b]] == 0).all()
+
+
 def test_ragged_batch_eos_and_cap(env):
     """Sequences of different prompt lengths advance independently; EOS among the accepted tokens
     stops a sequence (approximate EOS does not); max_steps caps the iterations."""
