@@ -42,6 +42,8 @@ hipError_t fc_prefill_advance(int32_t* state, const StateMap& sm, int B, int W, 
                               hipStream_t st);
 hipError_t fc_rewindow(int32_t* state, const StateMap& sm, int B, int W, int S, hipStream_t st);
 hipError_t fc_accept_commit(int32_t* state, const StateMap& sm, int B, int W, int S, hipStream_t st);
+// g[B], done[B], flags[2] to pinned host memory
+hipError_t fc_report(const int32_t* state, const StateMap& sm, int B, int32_t* host, hipStream_t st);
 // argmax of a step's rows and the accept step in one launch, where fc_tail_fits (rows M, logits per row or partial winners per row)
 bool fc_tail_fits(int B, int W, int M, int V_or_parts, bool winners);
 hipError_t fc_tail_logits(const float* logits, int M, int V, float* top, int32_t* state, const StateMap& sm, int B, int W, int S, hipStream_t st);

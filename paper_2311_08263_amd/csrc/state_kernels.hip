@@ -210,6 +210,16 @@ hipError_t fc_tail_winners(const float* val, const int32_t* idx, int nparts, int
     else k_tail_winners<32><<<1, 1024, 0, st>>>(val, idx, nparts, M, top, rm, state, sm, B, W, S);
     return hipGetLastError();
 }
+// What fastcot_generate looks at between batches of steps, to pinned host memory: g[B], done[B], the two flags.
+__global__ void k_report(const int32_t* st, StateMap sm, int B, int32_t* host) {
+    for (int i = threadIdx.x; i < 2 * B + 2; i += blockDim.x)
+        host[i] = i < B ? st[sm.g + i] : (i < 2 * B ? st[sm.done + i - B] : st[sm.flags + i - 2 * B]);
+}
+hipError_t fc_report(const int32_t* state, const StateMap& sm, int B, int32_t* host, hipStream_t st) {
+    k_report<<<1, 64, 0, st>>>(state, sm, B, host);
+    return hipGetLastError();
+}
+
 // A new window size between steps: the window is rebuilt from the newest exact token and the buffer
 // (the buffer already holds every output of the previous steps, Sec. 4.3 "Cache Update").
 __global__ void k_rewindow(int32_t* st, StateMap sm, int B, int W, int S) {
