@@ -35,7 +35,7 @@ struct fastcot_ctx {
     hipGraphExec_t graph_exec;
     hipGraph_t graph;
     int graph_valid;
-    int graph_one_tile;  // attention form of the captured step (fc_attn_one_tile)
+    int graph_form;      // attention form of the captured step (fc_attn_form)
     int ctx_len, ctx_max;   // committed positions of the longest sequence, at least (prompt, then one per step), and at most
     FastPlan plan;
     // profiling of single launches
@@ -286,7 +286,7 @@ extern "C" int fastcot_init(const fastcot_config* cfg, const void* d_packed, voi
     if (fc_build_maps(cfg, &c->mm, &c->wm, &c->kd) != 0) { delete c; return fail(nullptr, FASTCOT_EINVAL, "invalid configuration: %s", cfg_problem(cfg)); }
     if (workspace_bytes < c->wm.total) { delete c; return fail(nullptr, FASTCOT_ECAPACITY, "workspace too small%s"); }
     c->cfg = *cfg; c->weights = (const char*)d_packed; c->ws = (char*)d_workspace; c->st = (hipStream_t)hip_stream;
-    c->Bact = 0; c->ctx_len = c->ctx_max = 0; c->graph_one_tile = 0; c->prefilled = 0; c->generated = 0; c->buf_len = 0; c->opt_tune = 1; c->opt_compact = 1;
+    c->Bact = 0; c->ctx_len = c->ctx_max = 0; c->graph_form = 0; c->prefilled = 0; c->generated = 0; c->buf_len = 0; c->opt_tune = 1; c->opt_compact = 1;
     c->opt_packed = 1; c->rows_dirty = 1; c->rows_step = 0;
     c->opt_plain = (cfg->dtype == FASTCOT_F32); c->opt_graph = 1; c->dbg_stop = -1; c->dbg_logits = nullptr;
     c->graph_exec = nullptr; c->graph = nullptr; c->graph_valid = 0; c->prof_on = 0; c->prof_used = 0;
@@ -529,17 +529,16 @@ static int enqueue_step(fastcot_ctx* c) {
         c->ctx_len += c->ctx_len < c->ctx_max;
         return rc;
     }
-    // a context that grows past the line between the two attention forms: the step is captured once more
-    int splits;
-    const int one = !c->opt_plain && fc_attn_one_tile(c->kd, c->Bact, c->plan, c->ctx_len + c->kd.W, &splits);
-    if (c->graph_valid && one != c->graph_one_tile) {
+    // a context that grows past a line between attention forms: the step is captured once more
+    const int form = c->opt_plain ? 0 : fc_attn_form(c->kd, c->Bact, c->plan, c->ctx_len + c->kd.W);
+    if (c->graph_valid && form != c->graph_form) {
         HIPCHK(c, hipStreamSynchronize(c->st));        // (the last replay may still run)
         const int dirty = c->rows_dirty;
         drop_graph(c);
         c->rows_dirty = dirty;                         // nobody moved
     }
     if (!c->graph_valid) {
-        c->graph_one_tile = one;
+        c->graph_form = form;
         HIPCHK(c, hipStreamBeginCapture(c->st, hipStreamCaptureModeThreadLocal));
         int rc = step_body(c);
         hipGraph_t g = nullptr;

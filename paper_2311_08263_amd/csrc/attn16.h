@@ -21,6 +21,8 @@ struct AttnArgs {
     int32_t terms;         // bf16 parts of queries and probabilities: 3, or 2 for any other value (see attn16.hip)
     float* part;           // split partials
     int32_t* cnt;          // one arrival counter per (sequence, head), zero between launches
+    int32_t ctx;           // positions of the longest sequence, at least (what the host knows; decides about `rest`)
+    int32_t whole, rest, rest_splits;   // set by fc_attn16: of whole + rest units the last `rest` run in rest_splits key splits; rest = 0: all alike
     int32_t bpw;           // key blocks (of 32) per workgroup that decide how many of the launched splits are used
 };
 
@@ -29,4 +31,6 @@ size_t fc_attn16_part_bytes(int BH, int nsplit, int W);
 // vc, layer, B, H, Hkv, S, W, kvp (1 or 2), n_state, out, ldo, ofrag of the argument block
 int fc_attnp_workgroups(int Bact, int H, int W);
 hipError_t fc_attnp(const AttnArgs& a, int Bact, hipStream_t st);
+// units of a launch that run in *splits key splits while the others stay whole (0: none), see attn16.hip
+int fc_attn16_rest(int W, int subrows, int units, int nsplit, int kvp, int ctx, int* splits);
 hipError_t fc_attn16(const AttnArgs& a, int Bact, int nsplit, hipStream_t st);

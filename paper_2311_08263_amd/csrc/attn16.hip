@@ -16,6 +16,7 @@
 // do not depend on timing.  How many of the launched splits work on a sequence is decided at run
 // time from its length.
 #include "attn16.h"
+#include "gemmco.h"      // fc_num_cus
 #include "xwg.h"
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
@@ -48,6 +49,7 @@ __device__ inline void split8(const float* v, Frag& hi, Frag& lo, Frag& lo2) {
 }
 
 #define NEG_BIG (-1.0e30f)
+#define REST_BLOCKS(two) ((two) ? 56 : 16)   // key blocks times planes from which a unit of the last round is worth cutting, two / one query tiles
 #define PART_FLOATS (8 * 64 * 4 + 128)   // per (bh, split, qt): O^T tiles, then m[64], l[64] per lane
 
 // the bf16 lo operand of eight cached values kept as bf16 hi (h, four words) + 8-bit residual (two words of bytes):
@@ -87,9 +89,17 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
     // K/V heads consecutive indices take different K/V heads: the query heads that share one then follow
     // each other at a stride of Hkv, land on the same XCD when Hkv is a multiple of eight, and fetch the
     // shared planes from memory once instead of once per query head
-    const int bh = blockIdx.x, hr = bh % a.H, G = a.H / a.Hkv, kvh = hr % a.Hkv, h = kvh * G + hr / a.Hkv;
+    // (a launch whose last units are cut in key splits while the others are whole has a grid of one dimension: pieces first, see fc_attn16)
+    int bh = blockIdx.x, sp = blockIdx.y, nsp_max = gridDim.y, slot = bh * nsp_max + sp;
+    if (a.rest > 0) {
+        const int pieces = a.rest * a.rest_splits;
+        nsp_max = bh < pieces ? a.rest_splits : 1;
+        sp = bh < pieces ? bh / a.rest : 0;
+        slot = (bh % a.rest) * a.rest_splits + sp;
+        bh = bh < pieces ? a.whole + bh % a.rest : bh - pieces;
+    }
+    const int hr = bh % a.H, G = a.H / a.Hkv, kvh = hr % a.Hkv, h = kvh * G + hr / a.Hkv;
     const int sub = (bh / a.H) % nsub, b = bh / (a.H * nsub);
-    const int sp = blockIdx.y, nsp_max = gridDim.y;
     const int Wb = a.rstart ? a.rstart[b + 1] - a.rstart[b] : a.W, rbase = a.rstart ? a.rstart[b] : b * a.W;
     const int row0 = SUBR * sub, Wr = Wb - row0 < SUBR ? Wb - row0 : SUBR;        // rows of this unit
     if (Wr <= 0) return;                                     // a sequence with a smaller window of its own
@@ -101,6 +111,8 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
     // longest context; every workgroup of this (sequence, head) derives the same number from n)
     int nsp = (NB + a.bpw - 1) / a.bpw;
     if (nsp > nsp_max) nsp = nsp_max;
+    // a unit of the last round stays whole where its keys are read in less time than its merge costs (see fc_attn16_rest)
+    if (a.rest > 0 && NB * (KVP == 1 ? 1 : 2) < REST_BLOCKS(QT == 2)) nsp = 1;
     if (sp >= nsp) return;
     const int blk0 = (int)(((unsigned)sp * (unsigned)NB) / (unsigned)nsp);
     const int blk1 = (int)(((unsigned)(sp + 1) * (unsigned)NB) / (unsigned)nsp);
@@ -346,7 +358,7 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
         // ---- key splits: partial tiles go to memory with agent-scope stores; the last workgroup to
         // arrive reads all of them back -- every load of the merge is in flight at once (each wave its
         // two tiles of every split), splits folded in index order
-        float* mine = a.part + ((size_t)bh * nsp_max + sp) * QT * PART_FLOATS;
+        float* mine = a.part + (size_t)slot * QT * PART_FLOATS;
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt) {
 #pragma unroll
@@ -376,7 +388,7 @@ __global__ __launch_bounds__(256, QT) void k_attn16(AttnArgs a) {
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     const int s2 = s0 + u < nsp ? s0 + u : nsp - 1;
-                    const float* src = a.part + ((size_t)bh * nsp_max + s2) * QT * PART_FLOATS + qt * PART_FLOATS;
+                    const float* src = a.part + (size_t)(slot - sp + s2) * QT * PART_FLOATS + qt * PART_FLOATS;
                     ms[u] = ld_agent_f32(src + 2048 + lane);
                     ls[u] = ld_agent_f32(src + 2112 + lane);
 #pragma unroll
@@ -506,11 +518,31 @@ size_t fc_attn16_part_bytes(int BH, int nsplit, int W) {      // covers both uni
     return (size_t)BH * tiles * nsplit * PART_FLOATS * 4;
 }
 
-hipError_t fc_attn16(const AttnArgs& a, int Bact, int nsplit, hipStream_t st) {
+// More units than CUs, and one key split each: the CUs that take a unit more than the others decide when the launch ends.  The
+// units past the last full round of the CUs are therefore cut into three to eight key splits, as many as still give every
+// CU at most one, and start first, so that their merges are over long before the whole units.  A launch, whole -> cut, pairs of hi
+// and lo planes: 13B heads, 8 sequences x 16 rows, 1024 positions 71.6 -> 63.0 us, 300 30.4 -> 28.2; 7 sequences, 2000 116.6 -> 94.9;
+// 64 heads on 8, 5 x 16 rows, 2000 69.3 -> 54.2; two query tiles (8 x 32 rows), 1024 73.5 -> 70.7.  Not for two splits (12 x 32 heads 74.7
+// both ways) nor for more pieces than CUs (40 heads x 10 tiles, 144 units in seven 24.9 -> 37.2), nor for short contexts (100
+// positions 11.6 -> 13.5 with one tile, 300 33.3 -> 35.4 with two): by the longest one as the host knows it, and for each unit
+// by its own length.  Returns the number of units cut and their *splits.
+int fc_attn16_rest(int W, int subrows, int units, int nsplit, int kvp, int ctx, int* splits) {
+    const int cus = fc_num_cus(), r = units % cus, two = W > 16 && subrows != 16;
+    *splits = 1;
+    if (nsplit != 1 || units < cus || r == 0 || cus / r < 3 || (ctx + 31) / 32 * (kvp == 1 ? 1 : 2) < REST_BLOCKS(two)) return 0;
+    *splits = cus / r < 8 ? cus / r : 8;
+    return r;
+}
+
+hipError_t fc_attn16(const AttnArgs& a0, int Bact, int nsplit, hipStream_t st) {
+    AttnArgs a = a0;
     const int QT = a.W > 16 && a.subrows != 16 ? 2 : 1, nsub = (a.W + 16 * QT - 1) / (16 * QT);
     if (a.W < 1 || nsplit < 1 || nsplit > FC_MAX_ATTN_SPLITS || Bact * nsub * a.H > FC_MAX_COUNTERS || a.S < 32 || a.S % 32 || a.bpw < 1)
         return hipErrorInvalidValue;
-    dim3 grid(Bact * nsub * a.H, nsplit);
+    const int units = Bact * nsub * a.H;
+    dim3 grid(units, nsplit);
+    a.rest = fc_attn16_rest(a.W, a.subrows, units, nsplit, a.kvp, a.ctx, &a.rest_splits);
+    if (a.rest) { a.whole = units - a.rest; grid = dim3(a.whole + a.rest * a.rest_splits); }
     const size_t l1 = (size_t)4 * PART_FLOATS * 4 + 16, l2 = (size_t)8 * PART_FLOATS * 4 + 16;
     static bool lds_ok = false;                          // two query tiles need more than the default 64 KB
     if (!lds_ok) {

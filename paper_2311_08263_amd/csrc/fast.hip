@@ -149,6 +149,12 @@ bool fc_attn_one_tile(const KernelDims& kd, int Bact, const FastPlan& plan, int 
     return true;
 }
 
+int fc_attn_form(const KernelDims& kd, int Bact, const FastPlan& plan, int ctx_len) {
+    int splits, rest_splits;
+    const int one = fc_attn_one_tile(kd, Bact, plan, ctx_len, &splits), rows = kd.W <= 16 || one ? 16 : 32;
+    return one | (fc_attn16_rest(kd.W, one ? 16 : 0, Bact * kd.H * ((kd.W + rows - 1) / rows), splits, kd.kvp, ctx_len, &rest_splits) ? 2 : 0);
+}
+
 hipError_t fc_fast_forward(const FastArgs& a) {
     const KernelDims& kd = a.kd;
     const ModelMap& mm = *a.mm; const WorkspaceMap& wm = *a.wm;
@@ -256,6 +262,7 @@ hipError_t fc_fast_forward(const FastArgs& a) {
         }
         int attn_splits;
         at.subrows = fc_attn_one_tile(kd, a.Bact, *a.plan, a.ctx_len, &attn_splits) ? 16 : 0;
+        at.ctx = a.ctx_len;
         // passes with many rows per sequence (prompt chunks): one walk over the keys per 128 rows, where that
         // still gives at least half of the CUs a workgroup
         const bool many = a.plan->attn_many == 2 ? kd.W > 32
@@ -374,7 +381,7 @@ hipError_t fc_attn_iso(const float* q, const void* kc, const void* vc, int n, in
     }
     AttnArgs at; memset(&at, 0, sizeof(at));
     at.q = q; at.ldq = H * 128; at.kc = (const bf16_t*)kc; at.vc = (const bf16_t*)vc; at.layer = 0; at.B = 1; at.H = H;
-    at.Hkv = Hkv; at.S = S; at.W = W; at.kvp = 1; at.n_host = n; at.out = out; at.ldo = H * 128;
+    at.Hkv = Hkv; at.S = S; at.W = W; at.kvp = 1; at.n_host = n; at.ctx = n + W; at.out = out; at.ldo = H * 128;
     at.cnt = (int32_t*)(sc + 256); at.bpw = 2;
     at.part = (float*)(sc + ISO_PART_OFF);
     int splits = iso_attn_splits(n + W);

@@ -164,6 +164,20 @@ def test_two_tile_attention_splits(fc, n, W, H, Hkv):
     assert rel(fc.attn_window(q, kc, vc, n), attn64(q, k, v, n)) < 1.5e-5
 
 
+@pytest.mark.parametrize("n,W,H,Hkv", [(511, 1, 257, 257), (3000, 16, 341, 31), (3000, 16, 342, 9), (440, 40, 100, 4), (2000, 113, 40, 40), (600, 64, 66, 66),
+                                       (1750, 20, 300, 4), (2100, 20, 300, 4), (496, 16, 257, 257), (480, 16, 257, 257)])
+def test_attention_cut_last_round(fc, n, W, H, Hkv):
+    """More units than CUs: those past the last full round in three to eight key splits, one unit and as many as are cut at
+    most, one more than that (not cut), one and two query tiles, both sides of the shortest context that is cut."""
+    import torch
+    say(f"attention, cut last round n={n} W={W} H={H}/{Hkv}")
+    q, k, v = attn_inputs(n, W, H, Hkv, 128, torch.bfloat16)
+    kc, vc = fc.kv_scatter(k, v, (n + W + 31) // 32 * 32)
+    out = fc.attn_window(q, kc, vc, n)
+    assert rel(out, attn64(q, k, v, n)) < (1e-6 if W > 32 else 1.5e-5)
+    assert torch.equal(out, fc.attn_window(q, kc, vc, n))
+
+
 def test_one_scratch_for_calls_of_different_shapes(fc):
     """A scratch zeroed once serves any order of shapes it is large enough for."""
     import torch
@@ -361,6 +375,39 @@ def test_attention_form_changes_during_a_run(fc):
             ctx.step()
             torch.cuda.synchronize()
             got.append(dbg.clone())
+        runs.append(got)
+        ctx.close()
+    for a, b, c in zip(*runs):
+        assert torch.equal(a, b)
+        assert rel(a, c) < 1e-4
+
+
+@pytest.mark.parametrize("W,P,longest_first", [(16, 205, 0), (16, 205, 1), (9, 700, 1), (32, 830, 0)])
+def test_attention_cut_last_round_in_steps(fc, W, P, longest_first):
+    """Nine sequences of 32 heads, the last of which runs in key splits once the longest one and its window pass 224 positions (864 with
+    two query tiles): the step before and after that, the cut one the longest or short enough to stay whole, with and
+    without a captured graph and through the plain kernels."""
+    import torch
+    import synthgen
+    shape, B, steps = synthgen.ModelShape(**WIDE_HEADS), 9, 6
+    cfg = fc.Config.from_shape(shape, B, (P + W + 95) // 32 * 32, W)
+    packed = fc.load_synth_weights(cfg, shape)
+    prompts, buf = synthgen.prompts(B, P, shape.vocab, seed=7), synthgen.buffer_init(B, 2 * W + 24, shape.vocab, seed=8)
+    lens = [P - b * (P // 10) if longest_first else P - (B - 1 - b) for b in range(B)]
+    runs = []
+    for opt in ((), (fc.binding.OPT_GRAPH, 0), (fc.binding.OPT_PLAIN_KERNELS, 1)):
+        say(f"attention, cut last round in steps W={W} P={P} longest first {longest_first}, run {opt}")
+        ctx = fc.Context(cfg, packed)
+        if opt:
+            ctx.set_option(*opt)
+        ctx.prefill(prompts, lens, buf)
+        dbg = ctx.debug_logits(True)
+        torch.cuda.synchronize()
+        got = []
+        for _ in range(steps):
+            ctx.step()
+            torch.cuda.synchronize()
+            got.append(dbg[:B * W].clone())
         runs.append(got)
         ctx.close()
     for a, b, c in zip(*runs):
