@@ -87,10 +87,9 @@ hipError_t fc_split3(const float* X, int ldx, int M, int K, bf16_t* AF, hipStrea
     return hipGetLastError();
 }
 
-// Eight residual values of row m (columns c .. c + 7, lane (row lm, octet g4) of k-tile kt): times the gain of the norm
-// that comes next as bf16 hi + lo fragments, and their sum of squares.
-__device__ inline float frag_out8(const f32x4_t& x0, const f32x4_t& x1, const float* gain, int c, bf16_t* AF, size_t tile, int lane) {
-    const f32x4_t g0 = *(const f32x4_t*)(gain + c), g1 = *(const f32x4_t*)(gain + c + 4);
+// Eight residual values (lane (row lm, octet g4) of a k-tile): times g0, g1, the gain of the norm that comes next, as bf16
+// hi + lo fragments, and their sum of squares.
+__device__ inline float frag_out8(const f32x4_t& x0, const f32x4_t& x1, const f32x4_t& g0, const f32x4_t& g1, bf16_t* AF, size_t tile, int lane) {
     uint32_t h[4], l[4];
     pk_bf16_hilo(x0[0] * g0[0], x0[1] * g0[1], h[0], l[0]);
     pk_bf16_hilo(x0[2] * g0[2], x0[3] * g0[3], h[1], l[1]);
@@ -104,45 +103,51 @@ __device__ inline float frag_out8(const f32x4_t& x0, const f32x4_t& x1, const fl
     for (int e = 0; e < 4; ++e) ss += x0[e] * x0[e] + x1[e] * x1[e];
     return ss;
 }
-// partial row sums of squares of a workgroup's 16 rows x 256 columns (lane (row lm, octet g4) of wave w brings ss)
-__device__ inline void ssq_out16(float ss, float (&red)[8][16], int tid, int lane, int w, float* dst) {
-    ss += __shfl_xor(ss, 16, 64);
-    ss += __shfl_xor(ss, 32, 64);
-    if (lane < 16) red[w][lane] = ss;
-    __syncthreads();
-    if (tid < 16) {
-        float t = 0.f;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) t += red[q][tid];
-        dst[tid] = t;
+// A pass over the rows of the residual stream: workgroups of eight rows x 256 columns (grid (row tiles x 2, N / 256)), a wave
+// two rows, a lane eight columns: a row is read in runs of a kilobyte and the eight rows fill whole 128-byte lines of the
+// fragments.  Such passes are bound by the latency of data that other XCDs have just written, so a lane requests all it reads
+// at once.  (With 16 rows x 256 columns to a workgroup, lanes as in the fragments: 77 rows are 80 workgroups instead of 160, a
+// row comes in runs of 128 bytes: reduction of eight K slices of 77 rows x 4096 7.5 us, now 5.3; of three of 256 rows x
+// 5120 9.8, now 8.2.)
+struct RowPass {
+    int m, c, lane; size_t tile;         // row, first column; place in the fragments
+    __device__ inline RowPass(int N) {
+        const int oct = threadIdx.x & 31;
+        m = blockIdx.x * 8 + (threadIdx.x >> 5); c = blockIdx.y * 256 + oct * 8;
+        tile = (size_t)(m >> 4) * (N >> 5) + blockIdx.y * 8 + (oct >> 2); lane = (m & 15) + 16 * (oct & 3);
     }
-}
+    // partial row sums of squares [column block][row], from each lane's ss
+    __device__ inline void ssq_out(float ss, float* ssq) const {
+#pragma unroll
+        for (int s = 1; s <= 16; s <<= 1) ss += __shfl_xor(ss, s, 64);
+        if ((threadIdx.x & 31) == 0) ssq[(size_t)blockIdx.y * (gridDim.x * 8) + m] = ss;
+    }
+};
 
 // Embedding gather of a many-row pass: the residual rows, and in the same pass the first layer's input fragments and
-// row sums of squares.  grid (row tiles, d / 256), wave w on k-tile 8 * blockIdx.y + w.  (As two launches, the gather
-// and a pass that read every row once per 512 workgroups for its norm, 256 rows of 13B: 28 us, now 7 us.)
-__global__ __launch_bounds__(512) void k_embed_split(const bf16_t* emb, const int32_t* win, float* x, int M, int d, int V, RowMap rm, int W,
+// row sums of squares.  (As two launches, the gather and a pass that read every row once per 512 workgroups for its norm,
+// 256 rows of 13B: 28 us, now 7 us.)
+__global__ __launch_bounds__(256) void k_embed_split(const bf16_t* emb, const int32_t* win, float* x, int M, int d, int V, RowMap rm, int W,
                                                      const float* gain, bf16_t* AF, float* ssq) {
-    __shared__ float red[8][16];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, lm = lane & 15, g4 = lane >> 4;
-    const int mt = blockIdx.x, KT = d >> 5, kt = blockIdx.y * 8 + w, m = mt * 16 + lm, c = kt * 32 + 8 * g4;
+    const RowPass r(d);
     float ss = 0.f;
-    if (m < M) {
-        int t = win[rm.rowb ? rm.rowb[m] * W + rm.rowj[m] : m];
+    if (r.m < M) {
+        const f32x4_t g0 = *(const f32x4_t*)(gain + r.c), g1 = *(const f32x4_t*)(gain + r.c + 4);       // (requested before the token is known)
+        int t = win[rm.rowb ? rm.rowb[r.m] * W + rm.rowj[r.m] : r.m];
         if (t < 0 || t >= V) t = 0;
-        const uint4 v = *(const uint4*)(emb + (size_t)t * d + c);
+        const uint4 v = *(const uint4*)(emb + (size_t)t * d + r.c);
         const f32x4_t x0 = {__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xFFFF0000u)};
         const f32x4_t x1 = {__uint_as_float(v.z << 16), __uint_as_float(v.z & 0xFFFF0000u), __uint_as_float(v.w << 16), __uint_as_float(v.w & 0xFFFF0000u)};
-        f32x4_t* o = (f32x4_t*)(x + (size_t)m * d + c);
+        f32x4_t* o = (f32x4_t*)(x + (size_t)r.m * d + r.c);
         o[0] = x0; o[1] = x1;
-        ss = frag_out8(x0, x1, gain, c, AF, (size_t)mt * KT + kt, lane);
+        ss = frag_out8(x0, x1, g0, g1, AF, r.tile, r.lane);
     }
-    ssq_out16(ss, red, tid, lane, w, ssq + (size_t)blockIdx.y * (gridDim.x * 16) + mt * 16);
+    r.ssq_out(ss, ssq);
 }
 hipError_t fc_embed_split(const void* emb, const int32_t* win, float* x, int M, int d, int V, RowMap rm, int W, const float* gain,
                           bf16_t* AF, float* ssq, hipStream_t st) {
     if (M < 1 || d % 256) return hipErrorInvalidValue;
-    k_embed_split<<<dim3((M + 15) / 16, d / 256), 512, 0, st>>>((const bf16_t*)emb, win, x, M, d, V, rm, W, gain, AF, ssq);
+    k_embed_split<<<dim3((M + 15) / 16 * 2, d / 256), 256, 0, st>>>((const bf16_t*)emb, win, x, M, d, V, rm, W, gain, AF, ssq);
     return hipGetLastError();
 }
 
@@ -536,29 +541,29 @@ __global__ __launch_bounds__(512, 1) void k_gemm256(Gemm256Args a) {
 }
 
 // out[m][n] += part[0][m][n] + part[1][m][n] + ... (slice order: the result does not depend on timing), and in the same
-// pass the input of the next GEMM: the new residual rows times the next norm's gain as bf16 hi + lo B-fragments, plus partial row sums of squares (the consumer applies the norm's row scale
-// in its epilogue).  grid (row tiles, N / 256); wave w of a workgroup converts k-tile 8 * blockIdx.y + w; lane
-// (row lm, octet g4) as in the fragment.  Rows past M of the last row tile are not written.
-__global__ __launch_bounds__(512) void k_resid_reduce_split(const float* part, int sk, int M, int N, float* out, int ldo,
+// pass the input of the next GEMM: the new residual rows times the next norm's gain as bf16 hi + lo B-fragments, plus partial
+// row sums of squares (the consumer applies the norm's row scale in its epilogue).  Rows past M of the last row tile are not written.
+template <int SK>
+__global__ __launch_bounds__(256) void k_resid_reduce_split(const float* part, int M, int N, float* out, int ldo,
                                                             const float* gain, bf16_t* AF, float* ssq) {
-    __shared__ float red[8][16];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int lm = lane & 15, g4 = lane >> 4;
-    const int mt = blockIdx.x, KT = N >> 5, kt = blockIdx.y * 8 + w, MP = gridDim.x * 16;
-    const int m = mt * 16 + lm, c = kt * 32 + 8 * g4;
+    const RowPass r(N);
     float ss = 0.f;
-    if (m < M) {
-        f32x4_t s0 = *(const f32x4_t*)(part + (size_t)m * N + c), s1 = *(const f32x4_t*)(part + (size_t)m * N + c + 4);
-        for (int k = 1; k < sk; ++k) {
-            s0 = s0 + *(const f32x4_t*)(part + ((size_t)k * M + m) * N + c);
-            s1 = s1 + *(const f32x4_t*)(part + ((size_t)k * M + m) * N + c + 4);
+    if (r.m < M) {
+        f32x4_t p0[SK], p1[SK];
+#pragma unroll
+        for (int k = 0; k < SK; ++k) {
+            const f32x4_t* p = (const f32x4_t*)(part + ((size_t)k * M + r.m) * N + r.c);
+            p0[k] = p[0]; p1[k] = p[1];
         }
-        f32x4_t* o = (f32x4_t*)(out + (size_t)m * ldo + c);
-        const f32x4_t x0 = o[0] + s0, x1 = o[1] + s1;
+        f32x4_t* o = (f32x4_t*)(out + (size_t)r.m * ldo + r.c);
+        const f32x4_t o0 = o[0], o1 = o[1], g0 = *(const f32x4_t*)(gain + r.c), g1 = *(const f32x4_t*)(gain + r.c + 4);
+#pragma unroll
+        for (int k = 1; k < SK; ++k) { p0[0] = p0[0] + p0[k]; p1[0] = p1[0] + p1[k]; }
+        const f32x4_t x0 = o0 + p0[0], x1 = o1 + p1[0];
         o[0] = x0; o[1] = x1;
-        ss = frag_out8(x0, x1, gain, c, AF, (size_t)mt * KT + kt, lane);
+        ss = frag_out8(x0, x1, g0, g1, AF, r.tile, r.lane);
     }
-    ssq_out16(ss, red, tid, lane, w, ssq + (size_t)blockIdx.y * MP + mt * 16);
+    r.ssq_out(ss, ssq);
 }
 
 // K slices for a matrix with few columns: as many as give every CU at most one workgroup (measured at 256 rows,
@@ -651,6 +656,10 @@ hipError_t fc_gemm256(int epi, const Gemm256Args& a0, hipStream_t st) {
     const dim3 grid((unsigned)((units + 7) / 8 * 8 * nrb));
     const hipError_t e = p.rt == 3 ? launch256_rt<3>(p, epi, a, grid, st) : launch256_rt<4>(p, epi, a, grid, st);
     if (e != hipSuccess || a.sk == 1) return e;
-    k_resid_reduce_split<<<dim3((a.M + 15) / 16, a.NT * 16 / 256), 512, 0, st>>>(a.part, a.sk, a.M, a.NT * 16, a.out, a.ldo, a.rf_gain, a.rf_AF, a.rf_ssq);
+    const dim3 rgrid((a.M + 15) / 16 * 2, a.NT * 16 / 256);
+#define REDUCE(SK) case SK: k_resid_reduce_split<SK><<<rgrid, 256, 0, st>>>(a.part, a.M, a.NT * 16, a.out, a.ldo, a.rf_gain, a.rf_AF, a.rf_ssq); break;
+    switch (a.sk) { REDUCE(2) REDUCE(3) REDUCE(4) REDUCE(5) REDUCE(6) REDUCE(7) REDUCE(8) }
+#undef REDUCE
+    static_assert(FC_GEMM256_MAX_SK == 8, "a case per number of slices");
     return hipGetLastError();
 }

@@ -415,6 +415,33 @@ def test_attention_cut_last_round_in_steps(fc, W, P, longest_first):
         assert rel(a, c) < 1e-4
 
 
+@pytest.mark.parametrize("W,F", [(33, 768), (40, 1024), (41, 1280), (47, 1536), (48, 1792), (49, 2048), (63, 512), (65, 2048)])
+def test_reduction_of_k_slices(fc, W, F):
+    """Many-row residual products in two to eight K slices (F / 256 of them), rows that fill the eight-row workgroups of their
+    reduction and that do not: logits of a prompt and a step through the matrix-core and the plain kernels (activations as
+    hi + lo pairs in one and fp32 in the other, 2^-17 per product)."""
+    import torch
+    import synthgen
+    shape = synthgen.ModelShape(2, 512, 4, 4, 128, F, 1040, init_std=0.05)
+    cfg = fc.Config.from_shape(shape, 1, 256, W)
+    packed = fc.load_synth_weights(cfg, shape)
+    prompts, buf = synthgen.prompts(1, W + 2, shape.vocab, seed=7), synthgen.buffer_init(1, 2 * W + 8, shape.vocab, seed=8)
+    out = []
+    for plain in (0, 1):
+        say(f"reduction of K slices W={W} F={F} plain={plain}")
+        ctx = fc.Context(cfg, packed)
+        if plain:
+            ctx.set_option(fc.binding.OPT_PLAIN_KERNELS, 1)
+        ctx.prefill(prompts, [W + 2], buf)
+        dbg = ctx.debug_logits(True)
+        torch.cuda.synchronize()
+        ctx.step()
+        torch.cuda.synchronize()
+        out.append(dbg[:W].clone())
+        ctx.close()
+    assert rel(out[0], out[1]) < 1e-4
+
+
 @pytest.fixture(scope="module")
 def wide_model(fc):
     """One layer whose QKV, gate/up and LM head have more column tiles than 8 * (CUs / 8 / row blocks) * 16."""
