@@ -35,15 +35,19 @@ void fc_fast_plan(const KernelDims& kd, FastPlan* p) {
     // measured on the 7B shape: one workgroup per CU
     for (int i = 0; i < 5; ++i) { p->nw[i] = fc_gemmco_grid(nts[i]); p->ks[i] = 1; }
     if (nts[1] < 512) {                  // O projection with fewer than two n-tiles per CU
-        // measured at the 7B shape: two K slices per owner (16.6 us against 17.6 us for one)
+        // two K slices per owner, four where a wave is left with four k-tiles.  Since the partial tiles travel in whole
+        // lines a step of eight 4096-wide layers takes with two / four slices 891 / 881 us (16 rows), 885 / 881 (8 rows), 853 /
+        // 852 (1 row); of eight 2048-wide layers 495 / 497 (16 rows).
         const int G = p->nw[1], K = kd.H * kd.Dh;
         if (G % 2 == 0 && G / 2 <= nts[1] && (nts[1] + G / 2 - 1) / (G / 2) <= 8 && K >= 2048) p->ks[1] = 2;
+        if (p->ks[1] == 2 && G % 4 == 0 && (nts[1] + G / 4 - 1) / (G / 4) <= 8 && K >= 4096) p->ks[1] = 4;
     }
     // down projection: K is long and the columns few, so every workgroup would read far more activation
     // bytes than weight bytes; K slices per owner cut that (measured at the 7B shape)
     if (kd.F >= 2 * kd.d && kd.F >= 4096 && p->nw[3] % 4 == 0 && p->nw[3] / 4 <= nts[3] && (nts[3] + p->nw[3] / 4 - 1) / (p->nw[3] / 4) <= 8) p->ks[3] = 4;
     p->co_single = 2;    // measured (7B and 70B shapes): down and LM head 2-4 % faster with two batches in flight, QKV and O slower
     for (int i = 0; i < 5; ++i) { p->co_sb[0][i] = !(i == 3 || i == 4); p->co_sb[1][i] = 0; p->co_rot[0][i] = i >= 2; p->co_rot[1][i] = 1; }
+    if (p->ks[1] == 4) { p->co_rot[0][1] = 1; p->co_sb[0][1] = 0; }       // (one batch in flight, or in plain order: 5-9 us slower than the above)
     // Measured per shape (steps of up to 16 rows, every combination of K slices per owner x batch order x batches
     // in flight timed on the shape's own matrices, the fastest recorded here): {K slices, rotated order, batches in
     // flight} for QKV, O, gate/up, down, LM head.  Everything that fixes the order of the fp32 additions comes from
@@ -52,7 +56,7 @@ void fc_fast_plan(const KernelDims& kd, FastPlan* p) {
     // first triple as below): 7B QKV 33.5 -> 31.7 us, O 20.4 -> 16.9 us, down 31.0 -> 29.4 us; 70B gate/up 183.9 -> 171.9 us.
     struct Row { int d, F, H, Hkv; int ks[5], rot[5], sb[5]; int ks2[5], rot2[5], sb2[5]; };
     static const Row table[] = {
-        {4096, 11008, 32, 32, {1, 2, 1, 8, 1}, {0, 0, 1, 1, 1}, {2, 2, 1, 0, 0}, {1, 4, 1, 4, 1}, {1, 1, 1, 1, 1}, {1, 0, 0, 0, 0}},      // Llama-2-7B shape
+        {4096, 11008, 32, 32, {1, 4, 1, 8, 1}, {0, 1, 1, 1, 1}, {2, 0, 1, 0, 0}, {1, 4, 1, 4, 1}, {1, 1, 1, 1, 1}, {1, 0, 0, 0, 0}},      // Llama-2-7B shape
         {5120, 13824, 40, 40, {1, 4, 1, 4, 1}, {1, 0, 1, 1, 1}, {0, 1, 0, 1, 0}, {0, 0, 0, 0, 0}, {1, 1, 1, 1, 1}, {0, 0, 0, 0, 0}},      // 13B shape
         {8192, 28672, 64, 8, {2, 4, 1, 4, 1}, {1, 1, 0, 1, 1}, {1, 1, 0, 0, 0}, {0, 2, 0, 0, 0}, {1, 1, 0, 1, 1}, {0, 0, 0, 0, 0}},       // 70B shape
     };
@@ -77,6 +81,7 @@ void fc_fast_plan(const KernelDims& kd, FastPlan* p) {
         const int own = G2 > 0 ? G2 / p->ks[i] : 0;
         if (own < 1 || (nts[i] + own - 1) / own > most) G2 = fc_gemmco_grid(nts[i], most);
         int k2 = p->ks[i];
+        if (i == 1 && k2 == 2) k2 = 4;       // (twice the activations: slices pay earlier; eight 2048-wide layers, 24 / 32 rows, two -> four slices 564 / 595 -> 557 / 584 us)
         while (k2 > 1 && (G2 % k2 || G2 / k2 > nts[i] || (nts[i] + G2 / k2 - 1) / (G2 / k2) > most)) k2 >>= 1;
         const int kt = mine ? mine->ks2[i] : 0;          // the table's own value for this class, where it fits
         if (kt >= 1 && i < 4 && G2 % kt == 0 && G2 / kt >= 1 && G2 / kt <= nts[i] && (nts[i] + G2 / kt - 1) / (G2 / kt) <= most && kin[i] / 256 >= kt) k2 = kt;
