@@ -301,7 +301,8 @@ extern "C" int fastcot_init(const fastcot_config* cfg, const void* d_packed, voi
             cs[(size_t)p * half + i] = (float)cos(ang); sn[(size_t)p * half + i] = (float)sin(ang);
         }
 #define INITCHK(call) do { hipError_t e_ = (call); if (e_ != hipSuccess) { int rc_ = fail(nullptr, FASTCOT_EHIP, "HIP error '%s' in init line %ld", hipGetErrorString(e_), __LINE__); if (c->pinned) (void)hipHostFree(c->pinned); delete c; return rc_; } } while (0)
-    INITCHK(hipHostMalloc((void**)&c->pinned, 4096 * 4, hipHostMallocDefault));
+    // two words per sequence and the flags: the report kernel writes there, past the block it would fault
+    INITCHK(hipHostMalloc((void**)&c->pinned, std::max<size_t>(4096, 2 * (size_t)c->kd.B + 8) * 4, hipHostMallocDefault));
     INITCHK(hipMemcpyAsync(c->ws + c->wm.rope_cos, cs.data(), cs.size() * 4, hipMemcpyHostToDevice, c->st));
     INITCHK(hipMemcpyAsync(c->ws + c->wm.rope_sin, sn.data(), sn.size() * 4, hipMemcpyHostToDevice, c->st));
     INITCHK(hipMemsetAsync(c->ws + c->wm.state, 0, (size_t)c->wm.st.words * 4, c->st));

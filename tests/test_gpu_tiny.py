@@ -148,6 +148,29 @@ def test_equal_logits_take_the_lowest_id(dtype, B, W, wins):
             assert nacc[b] == oracle.verify(win[b][:Wb], st["o"][b][:Wb]) + 1 and (acc[b, :nacc[b]] == 0).all()
 
 
+@pytest.mark.parametrize("B", [2047, 2048, 2100])
+def test_report_of_more_sequences_than_a_fixed_block_holds(B):
+    """generate and answer look at two words per sequence through pinned host memory: batches whose words fill 4096, and more.  Every
+    fifth prompt is the same, so every fifth sequence is what a batch of five makes of it (sums per row, the same in any batch)."""
+    import paper_2311_08263_amd as fc
+    say(f"report of {B} sequences")
+    shape = synthgen.ModelShape(1, 32, 1, 1, 32, 32, 64, dtype="f32")
+    P, W, N, few = 4, 1, 3, 5
+    prompts, buf = synthgen.prompts(few, P, shape.vocab, seed=41), synthgen.buffer_init(few, 16, shape.vocab, seed=42)
+    out = []
+    for n in (few, B):
+        cfg = fc.Config.from_shape(shape, n, 32, W)
+        ctx = fc.Context(cfg, fc.load_synth_weights(cfg, shape))
+        idx = np.arange(n) % few
+        ctx.prefill(prompts[idx], [P] * n, buf[idx])
+        g = ctx.generate(N)
+        assert (g["len"] == N).all() and (g["steps"] == N).all()
+        out.append((g["ids"], ctx.answer([1, 2], 3)["ids"]))
+        ctx.close()
+    for small, large in zip(*out):
+        assert (large == small[np.arange(B) % few]).all()
+
+
 def test_ragged_batch_eos_and_cap(env):
     """Sequences of different prompt lengths advance independently; EOS among the accepted tokens
     stops a sequence (approximate EOS does not); max_steps caps the iterations."""
