@@ -221,7 +221,8 @@ enum { FASTCOT_OPT_PLAIN_KERNELS = 1, FASTCOT_OPT_GRAPH = 2, FASTCOT_OPT_KV_PLAN
  * FASTCOT_PLAN_SB + g: weight batches in flight per wave: 0 two, 1 one, 2 the wave's whole K slice up front.
  * FASTCOT_PLAN_ROT + g: 1 = every wave walks its K batches in an order rotated by workgroup and wave.
  * FASTCOT_PLAN_CO_SINGLE: 0 / 1 = two / one batch in flight for every GEMM, 2 (default) = per GEMM (PLAN_SB).
- * FASTCOT_PLAN_ATTN_SPLITS: key-range splits the attention launch provides (1..16).
+ * FASTCOT_PLAN_ATTN_SPLITS: key-range splits the attention launch provides (1..16), the same for every unit of it.  (Unset,
+ * a launch of more units than compute units may run the last ones in key splits while the others stay whole.)
  * FASTCOT_PLAN_ATTN_BLOCKS: key blocks of 32 positions per attention workgroup: of the launched splits,
  * ceil(blocks / value) work on a sequence, the rest exit.
  * FASTCOT_PLAN_ATTN_MANY_ROWS: which passes use the attention kernel for many rows per sequence (workgroups of

@@ -21,7 +21,7 @@ struct AttnArgs {
     int32_t terms;         // bf16 parts of queries and probabilities: 3, or 2 for any other value (see attn16.hip)
     float* part;           // split partials
     int32_t* cnt;          // one arrival counter per (sequence, head), zero between launches
-    int32_t ctx;           // positions of the longest sequence, at least (what the host knows; decides about `rest`)
+    int32_t ctx;           // positions of the longest sequence, at least (what the host knows; decides about `rest`: 0 = none)
     int32_t whole, rest, rest_splits;   // set by fc_attn16: of whole + rest units the last `rest` run in rest_splits key splits; rest = 0: all alike
     int32_t bpw;           // key blocks (of 32) per workgroup that decide how many of the launched splits are used
 };

@@ -7,6 +7,7 @@
 
 struct FastPlan {
     int32_t attn_splits;
+    int32_t attn_cut;  // units past the last full round of CUs may run in key splits (fc_attn16_rest); 0: every unit in attn_splits splits, as asked for
     int32_t attn_bpw;  // key blocks of 32 per attention workgroup (decides at run time how many of the splits work)
     int32_t attn_many; // many-row attention kernel (attnp.hip): 0 never, 1 where it gives half of the CUs a workgroup, 2 for every pass of more than 32 rows per sequence
     int32_t co_single; // column-owner GEMM: 1 = one weight batch in flight per wave, 0 = two, 2 = chosen per GEMM

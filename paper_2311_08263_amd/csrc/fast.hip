@@ -28,6 +28,7 @@ void fc_fast_plan(const KernelDims& kd, FastPlan* p) {
     // 24.3 us; batch 8 x 40 heads: 1 split 75 us, 2 splits 102 us)
     while (sp > 1 && kd.B * kd.H * sp > fc_num_cus()) --sp;
     p->attn_splits = sp < 1 ? 1 : sp;
+    p->attn_cut = 1;
     p->attn_bpw = 2;
     p->attn_many = 1;
     // column-owner kernel: workgroups per GEMM (one per CU where the matrix allows)
@@ -157,7 +158,7 @@ bool fc_attn_one_tile(const KernelDims& kd, int Bact, const FastPlan& plan, int 
 int fc_attn_form(const KernelDims& kd, int Bact, const FastPlan& plan, int ctx_len) {
     int splits, rest_splits;
     const int one = fc_attn_one_tile(kd, Bact, plan, ctx_len, &splits), rows = kd.W <= 16 || one ? 16 : 32;
-    return one | (fc_attn16_rest(kd.W, one ? 16 : 0, Bact * kd.H * ((kd.W + rows - 1) / rows), splits, kd.kvp, ctx_len, &rest_splits) ? 2 : 0);
+    return one | (fc_attn16_rest(kd.W, one ? 16 : 0, Bact * kd.H * ((kd.W + rows - 1) / rows), splits, kd.kvp, plan.attn_cut ? ctx_len : 0, &rest_splits) ? 2 : 0);
 }
 
 hipError_t fc_fast_forward(const FastArgs& a) {
@@ -267,7 +268,7 @@ hipError_t fc_fast_forward(const FastArgs& a) {
         }
         int attn_splits;
         at.subrows = fc_attn_one_tile(kd, a.Bact, *a.plan, a.ctx_len, &attn_splits) ? 16 : 0;
-        at.ctx = a.ctx_len;
+        at.ctx = a.plan->attn_cut ? a.ctx_len : 0;
         // passes with many rows per sequence (prompt chunks): one walk over the keys per 128 rows, where that
         // still gives at least half of the CUs a workgroup
         const bool many = a.plan->attn_many == 2 ? kd.W > 32

@@ -415,6 +415,31 @@ def test_attention_cut_last_round_in_steps(fc, W, P, longest_first):
         assert rel(a, c) < 1e-4
 
 
+def test_splits_option_counts_for_every_unit(fc):
+    """Nine equal sequences, one in key splits by default: with the number of splits set, 1 included, all nine are computed alike, to
+    the last bit."""
+    import torch
+    import synthgen
+    shape, B, W, P = synthgen.ModelShape(**WIDE_HEADS), 9, 16, 300
+    cfg = fc.Config.from_shape(shape, B, 448, W)
+    packed = fc.load_synth_weights(cfg, shape)
+    prompts, buf = synthgen.prompts(1, P, shape.vocab, seed=7).repeat(B, 0), synthgen.buffer_init(1, 2 * W + 24, shape.vocab, seed=8).repeat(B, 0)
+    alike = []
+    for splits in (0, 1, 2):
+        say(f"splits of the attention launch: {splits}")
+        ctx = fc.Context(cfg, packed)
+        if splits:
+            ctx.set_option(fc.binding.PLAN_ATTN_SPLITS, splits)
+        ctx.prefill(prompts, [P] * B, buf)
+        dbg = ctx.debug_logits(True)
+        ctx.step()
+        torch.cuda.synchronize()
+        lg = dbg.view(B, W, -1)
+        alike.append([bool(torch.equal(lg[b], lg[0])) for b in range(B)])
+        ctx.close()
+    assert alike[0] == [True] * 8 + [False] and all(alike[1]) and all(alike[2])
+
+
 @pytest.mark.parametrize("W,F", [(33, 768), (40, 1024), (41, 1280), (47, 1536), (48, 1792), (49, 2048), (63, 512), (65, 2048)])
 def test_reduction_of_k_slices(fc, W, F):
     """Many-row residual products in two to eight K slices (F / 256 of them), rows that fill the eight-row workgroups of their
