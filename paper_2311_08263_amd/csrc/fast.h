@@ -47,7 +47,7 @@ void fc_fast_plan(const KernelDims& kd, FastPlan* plan);
 hipError_t fc_fast_forward(const FastArgs& a);
 // true: a pass of kd.W rows per sequence runs its attention as workgroups of one query tile, with *splits key splits
 bool fc_attn_one_tile(const KernelDims& kd, int Bact, const FastPlan& plan, int ctx_len, int* splits);
-// which of the attention launch's forms such a pass takes (one query tile, cut last units): a captured step stays valid while this is the same
+// which of the attention launch's forms such a pass takes (one query tile, cut last units, many rows): a captured step stays valid while this is the same
 int fc_attn_form(const KernelDims& kd, int Bact, const FastPlan& plan, int ctx_len);
 // Times every column-owner GEMM of the pass shape a.kd (at most 32 rows) with one and with two weight batches in
 // flight per wave or the wave's whole K slice at once and records the fastest in the plan.  Only that choice is

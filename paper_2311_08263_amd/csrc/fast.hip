@@ -155,7 +155,15 @@ bool fc_attn_one_tile(const KernelDims& kd, int Bact, const FastPlan& plan, int 
     return true;
 }
 
+// passes with many rows per sequence (prompt chunks): one walk over the keys per 128 rows, where that still gives at least half
+// of the CUs a workgroup
+static bool attn_many_rows(const KernelDims& kd, int Bact, const FastPlan& plan) {
+    if (kd.kvp == 3) return false;
+    return plan.attn_many == 2 ? kd.W > 32 : (plan.attn_many == 1 && kd.W >= 64 && 2 * fc_attnp_workgroups(Bact, kd.H, kd.W) >= fc_num_cus());
+}
+
 int fc_attn_form(const KernelDims& kd, int Bact, const FastPlan& plan, int ctx_len) {
+    if (attn_many_rows(kd, Bact, plan)) return 4;            // (one form for every length)
     int splits, rest_splits;
     const int one = fc_attn_one_tile(kd, Bact, plan, ctx_len, &splits), rows = kd.W <= 16 || one ? 16 : 32;
     return one | (fc_attn16_rest(kd.W, one ? 16 : 0, Bact * kd.H * ((kd.W + rows - 1) / rows), splits, kd.kvp, plan.attn_cut ? ctx_len : 0, &rest_splits) ? 2 : 0);
@@ -269,11 +277,7 @@ hipError_t fc_fast_forward(const FastArgs& a) {
         int attn_splits;
         at.subrows = fc_attn_one_tile(kd, a.Bact, *a.plan, a.ctx_len, &attn_splits) ? 16 : 0;
         at.ctx = a.plan->attn_cut ? a.ctx_len : 0;
-        // passes with many rows per sequence (prompt chunks): one walk over the keys per 128 rows, where that
-        // still gives at least half of the CUs a workgroup
-        const bool many = a.plan->attn_many == 2 ? kd.W > 32
-                                                  : (a.plan->attn_many == 1 && kd.W >= 64 && 2 * fc_attnp_workgroups(a.Bact, kd.H, kd.W) >= fc_num_cus());
-        if (many && kd.kvp != 3)
+        if (attn_many_rows(kd, a.Bact, *a.plan))
             FLAUNCH(KK_ATTN, fc_attnp(at, a.Bact, a.st));
         else
         FLAUNCH(KK_ATTN, fc_attn16(at, a.Bact, attn_splits, a.st));

@@ -67,3 +67,37 @@ def test_null_arguments_are_rejected_without_a_gpu():
     assert L.fastcot_pack_weights(ctypes.byref(cfg), None, None, None) == -1
     assert L.fastcot_canonical_offset(ctypes.byref(cfg), 3, 99) == ctypes.c_size_t(-1).value
     assert L.fastcot_kernel_name(4) == b"attention"
+
+
+class _Dims(ctypes.Structure):              # KernelDims and FastPlan of the library's headers
+    _fields_ = [(n, ctypes.c_int32) for n in "L d H Hkv Dh F V B S W M Wcap Rcap qkvN".split()] + [("eps", ctypes.c_float)] + \
+               [(n, ctypes.c_int32) for n in "esz kvp actq kvq".split()]
+
+
+class _Plan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in "attn_splits attn_cut attn_bpw attn_many co_single".split()] + \
+               [(n, ctypes.c_int32 * k) for n, k in (("co_sb", 10), ("co_rot", 10), ("ks", 5), ("nw2", 5), ("ks2", 5), ("nw", 5))]
+
+
+def _attention_form(B, H, W, kvp, many, ctx_len):
+    """Form of a step's attention launch, by which a captured step is kept or captured once more (256 CUs without a GPU)."""
+    L = ctypes.CDLL(binding._build.SO)
+    plan, form = L["_Z12fc_fast_planRK10KernelDimsP8FastPlan"], L["_Z12fc_attn_formRK10KernelDimsiRK8FastPlani"]
+    kd = _Dims(2, H * 128, H, H, 128, H * 256, 1024, B, 4096, W, B * W, W, W, 3 * H * 128, 1e-5, 2, kvp, 0, 0)
+    p = _Plan()
+    plan(ctypes.byref(kd), ctypes.byref(p))
+    p.attn_many = many
+    assert p.attn_bpw == 2 and p.co_single == 2           # (the fields above are where the library has them)
+    return form(ctypes.byref(kd), B, ctypes.byref(p), ctx_len)
+
+
+def test_attention_form_of_a_captured_step():
+    """A step keeps its graph while its launches stay what they are: the many-row kernel has one form for every context, the other
+    one changes where its last units are first cut."""
+    binding.lib()
+    lengths = range(100, 3000, 50)
+    for B, H, W in ((7, 40, 64), (9, 32, 64), (9, 32, 128)):
+        assert len({_attention_form(B, H, W, 2, 1, n) for n in lengths}) == 1
+    assert len({_attention_form(7, 40, 64, 2, 0, n) for n in lengths}) == 2
+    assert len({_attention_form(7, 40, 64, 3, 1, n) for n in lengths}) == 2
+    assert len({_attention_form(9, 32, 16, 2, 1, n) for n in lengths}) == 2
