@@ -133,7 +133,7 @@ __global__ void k_accept_commit(int32_t* st, StateMap sm, int B, int W, int S) {
 // The end of a small step in one launch: one workgroup of sixteen waves finds every row's argmax and, with the ids still in
 // LDS, runs the accept step.  Two launches cost a kernel boundary more (2-4 us) than one workgroup loses against one per
 // row, as long as there is little to read: see fc_tail_fits.
-#define TAIL_IDS 1024
+#define TAIL_IDS 1024                                      // one per thread
 __device__ inline bool tail_better(float v, int i, float best, int bi) { return v > best || (v == best && i < bi); }
 // rows of a packed step sit at entry rowb[m] * W + rowj[m] of the ids
 __device__ inline int tail_dst(const RowMap& rm, int m, int W) { return rm.rowb ? rm.rowb[m] * W + rm.rowj[m] : m; }
@@ -194,9 +194,15 @@ __global__ __launch_bounds__(1024) void k_tail_winners(const float* val, const i
     __syncthreads();
     accept_commit(st, sm, B, W, S, ids);
 }
-// Within 8192 logits, or winners of at most 32 rows, one workgroup reads them in the time of a launch.
+// What a wave walks decides: per row a fixed part and a round per 256 logits.  A step of a small one-layer model, two launches ->
+// one, us: up to 16 rows (a wave each) 1 x 2048 logits 32.4 -> 31.4, 16 x 2048 33.0 -> 32.3, 1 x 4096 34.1 -> 34.2, 16 x 4096 34.6 ->
+// 35.2, 1 x 8192 39.6 -> 41.2; two rows a wave 32 x 256 31.1 -> 30.6, 32 x 512 31.1 -> 31.4; 64 x 64 31.1 -> 32.1, 512 x 16 40 -> 63.
+// Winners, 16 / 32 columns of them: 64 parts 56.2 -> 55.0 / 54.4 -> 53.1, 256 parts 56.4 -> 56.1 / 55.0 -> 55.4, 512 parts 61.2 ->
+// 62.0 / 64.6 -> 67.1.
 bool fc_tail_fits(int B, int W, int M, int V_or_parts, bool winners) {
-    return B * W <= TAIL_IDS && (winners ? M <= 32 && V_or_parts <= 512 : (size_t)M * V_or_parts <= 8192);
+    if (B * W > TAIL_IDS) return false;
+    if (winners) return M <= 32 && V_or_parts * (M > 16 ? 32 : 16) <= 4096;
+    return (M + 15) / 16 * (5 + (V_or_parts + 255) / 256) <= 13;
 }
 hipError_t fc_tail_logits(const float* logits, int M, int V, float* top, int32_t* state, const StateMap& sm, int B, int W, int S, hipStream_t st) {
     if (!fc_tail_fits(B, W, M, V, false) || M != B * W) return hipErrorInvalidValue;

@@ -101,3 +101,18 @@ def test_attention_form_of_a_captured_step():
     assert len({_attention_form(7, 40, 64, 2, 0, n) for n in lengths}) == 2
     assert len({_attention_form(7, 40, 64, 3, 1, n) for n in lengths}) == 2
     assert len({_attention_form(9, 32, 16, 2, 1, n) for n in lengths}) == 2
+
+
+def test_end_of_a_step_in_one_launch_where_that_is_faster():
+    """Rows and logits, or rows and partial winners, on both sides of the lines: one workgroup loses where a wave has much to walk."""
+    fits = ctypes.CDLL(binding._build.SO)["_Z12fc_tail_fitsiiiib"]
+    fits.argtypes, fits.restype = [ctypes.c_int32] * 4 + [ctypes.c_bool], ctypes.c_bool
+    for M, V in ((1, 2048), (8, 1024), (16, 2048), (17, 256), (32, 256)):
+        assert fits(1, M, M, V, False)
+    for M, V in ((1, 2064), (1, 8192), (8, 4096), (16, 4096), (17, 272), (32, 512), (33, 16), (64, 128), (512, 16)):
+        assert not fits(1, M, M, V, False)
+    for M, parts in ((1, 256), (16, 256), (17, 128), (32, 128)):
+        assert fits(2, M, M, parts, True)
+    for M, parts in ((1, 512), (16, 257), (17, 129), (32, 256), (33, 16)):
+        assert not fits(2, M, M, parts, True)
+    assert fits(4, 256, 10, 64, True) and not fits(4, 257, 10, 64, True)
