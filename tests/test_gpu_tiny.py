@@ -118,34 +118,55 @@ def test_fp32_shapes(d, H, Hkv, Dh, F, V, B, W, P):
     assert r["rows"] == 3 * B * W
 
 
-@pytest.mark.parametrize("dtype,B,W,wins", [("f32", 1, 8, None), ("f32", 5, 13, None), ("bf16", 1, 1, None), ("bf16", 1, 16, None), ("bf16", 2, 9, None),
-                                            ("bf16", 2, 16, None), ("bf16", 4, 12, [3, 12, 1, 7]), ("bf16", 3, 15, [15, 4, 9])])
-def test_equal_logits_take_the_lowest_id(dtype, B, W, wins):
-    """A head of zeros: every logit ties, in every lane, wave and workgroup that looks for the winner, so id 0 it is (R9), also where the
-    accept step runs in the same launch; Eq. 5 on top of it is recomputed."""
+@pytest.mark.parametrize("dtype,B,W,V,wins", [
+    ("f32", 1, 1, 2048, None), ("f32", 1, 1, 2064, None), ("f32", 1, 8, 1024, None), ("f32", 1, 16, 2048, None), ("f32", 1, 16, 2064, None),
+    ("f32", 2, 9, 256, None), ("f32", 2, 16, 256, None), ("f32", 2, 16, 272, None), ("f32", 5, 13, 112, None),
+    ("bf16", 1, 1, 4096, None), ("bf16", 1, 16, 4800, None), ("bf16", 1, 16, 65536, None), ("bf16", 2, 9, 2048, None), ("bf16", 2, 16, 2048, None),
+    ("bf16", 2, 16, 2064, None), ("bf16", 4, 12, 2048, [3, 12, 1, 7]), ("bf16", 3, 15, 2048, [15, 4, 9]), ("bf16", 3, 15, 4800, [15, 4, 9]),
+    ("bf16", 4, 12, 4800, [3, 2, 1, 7]), ("bf16", 4, 257, 1024, [3, 2, 1, 7])])
+def test_equal_logits_take_the_lowest_id(dtype, B, W, V, wins):
+    """Heads whose columns are unit vectors: a logit is one element of the normed row, without any rounding of its own, and ids that share
+    an element tie exactly.  Each of 23 elements has its ids all over the vocabulary (neighbours, lanes, the loads of a wave, waves and
+    workgroups apart, the last ones), the lowest never 0 and different for each, so rows have different winners.  Both sides of the lines up
+    to which the accept step runs in the same launch, dense and packed rows; Eq. 5 on top of it is recomputed."""
     import paper_2311_08263_amd as fc
-    say(f"ties {dtype} B={B} W={W} windows {wins}")
-    shape = synthgen.ModelShape(1, 256, 2, 2, 128, 512, 112 if dtype == "f32" else 16 * 300, dtype=dtype)
-    cfg = fc.Config.from_shape(shape, B, 128, W)
+    say(f"ties {dtype} B={B} W={W} V={V} windows {wins}")
+    shape = synthgen.ModelShape(1, 256, 2, 2, 128, 512, V, dtype=dtype, init_std=0.1)
+    cfg = fc.Config.from_shape(shape, B, max(128, 3 * W), W)
+    rng = np.random.RandomState(V + W)
+    head, groups = np.zeros((256, V), dtype=np.float32), 23
+    low = rng.choice(np.arange(1, V // 2), groups, replace=False)
+    for k, i in enumerate(low):
+        for j in (i, i + 1, i + 64, i + 256, i + V // 2, V - 1 - k):
+            if i <= j < V and not head[:, j].any():
+                head[11 * k, j] = 1.0
 
     def weights():
         for spec in synthgen.weight_tensors(shape):
             t = synthgen.weight_array(shape, spec, synthgen.WEIGHT_SEED, as_bf16_bits=dtype == "bf16")
-            yield spec.name, spec.layer, np.zeros_like(t) if spec.name == "wlm" else t
+            if spec.name == "wlm":
+                t = (head.view(np.uint32) >> 16).astype(t.dtype) if dtype == "bf16" else head
+            yield spec.name, spec.layer, t
     ctx = fc.Context(cfg, fc.pack_weights(cfg, weights()))
-    buf = np.zeros((B, 64), dtype=np.int32)
-    buf[:, 2::5] = 7                                       # two slots verify, then one does not
-    ctx.prefill(synthgen.prompts(B, 20, shape.vocab, seed=5), [20] * B, buf)
+    ctx.prefill(synthgen.prompts(B, 20, V, seed=5), [20] * B, synthgen.buffer_init(B, 2 * W + 24, V, seed=6))
     if wins:
         ctx.set_windows(wins)
-    for _ in range(2):
-        win = ctx.state()["window"].copy()
+    dbg, tied, winners, rows = ctx.debug_logits(True), 0, set(), 0
+    for _ in range(5):
+        win, rs = ctx.state()["window"].copy(), ctx.step_rows()
         nacc, acc, _ = ctx.step()
-        st = ctx.state()
+        st, lg = ctx.state(), dbg.cpu().numpy()
         for b in range(B):
             Wb = wins[b] if wins else W
-            assert (st["o"][b][:Wb] == 0).all()
-            assert nacc[b] == oracle.verify(win[b][:Wb], st["o"][b][:Wb]) + 1 and (acc[b, :nacc[b]] == 0).all()
+            r = lg[rs[b]:rs[b] + Wb]
+            want = r.argmax(-1)                            # the first of the largest
+            tied += int(((r == r.max(-1, keepdims=True)).sum(-1) > 1).sum())
+            rows += Wb
+            winners.update(want.tolist())
+            assert (st["o"][b][:Wb] == want).all()
+            K = oracle.verify(win[b][:Wb], want)
+            assert st["K"][b] == K and nacc[b] == K + 1 and (acc[b, :K + 1] == want[:K + 1]).all()
+    assert tied > 0.7 * rows and 0 not in winners and len(winners) >= min(rows // 2, 6)
 
 
 @pytest.mark.parametrize("B", [2047, 2048, 2100])
