@@ -368,10 +368,13 @@ __device__ inline float block_sum(float v, float* red) {
 // key r, quarter p of the head elements; two exchanges add the quarters), then 16 head elements x 32 positions
 // (lane = element, octet of positions), and the waves' sums over their blocks meet in LDS.  With a thread per key and
 // a thread per head element walking all keys one by one a 64-row window over 1088 keys and 40 heads took 647 us; now 172 us.
-// EARLY (heads of up to 64 elements, launches of at most two workgroups per CU): each wave's first K tile and V block are
+// EARLY (heads of up to 64 elements, launches of at most two workgroups per CU, bf16 caches of at most 128 positions): each wave's first K tile and V block are
 // requested before anything is known of the lengths, so that the launch is not a chain of four round trips; what lies behind the
-// last position is read all the same and not used.  256-wide model, 8 rows x 4 heads, 40 keys: 7.8 -> 5.6 us a launch, same bits.  (Heads of 128: the
-// unrolled copies of the long loop cost long contexts a quarter.)
+// last position is read all the same and not used, same bits.  fp32 caches, 8 rows x 32 heads of 64, plain -> EARLY: 0 to 32 keys 6.2 -> 5.6 us,
+// 200 9.9 -> 9.9, 2000 73.3 -> 72.1, 15800 525 -> 521.  bf16 caches gain while a wave has no block but its first one (128
+// positions) and lose after that: 32 keys 6.9 -> 6.5 us, 127 7.6 -> 7.1, 152 10.4 -> 10.7, 700 25.0 -> 25.4; so only in caches that
+// hold no more.  (Heads of 128: the unrolled copies of the long loop cost long contexts a quarter.  Four workgroups per CU: 6-8 % at 32 keys, 1 % at 2000.)
+#define EARLY_BF16_KEYS 128
 template <int DT, bool EARLY>
 __global__ __launch_bounds__(256) void k_attn_plain(const float* q, int ldq, const void* kc, const void* vc, KernelDims kd, int layer,
                                                     const int32_t* n_state, int n_host, float* out) {
@@ -485,7 +488,7 @@ hipError_t fc_attn_plain(const float* q, int ldq, const void* kc, const void* vc
         kernel<<<grid, 256, sh, st>>>(q, ldq, kc, vc, kd, layer, n_state, n_host, out);
         return hipSuccess;
     };
-    const bool early = kd.Dh <= 64 && kd.M * kd.H <= 2 * fc_num_cus();
+    const bool early = kd.Dh <= 64 && kd.M * kd.H <= 2 * fc_num_cus() && (dt == FASTCOT_F32 || kd.S <= EARLY_BF16_KEYS);
     const hipError_t e = dt == FASTCOT_F32 ? (early ? launch(k_attn_plain<FASTCOT_F32, true>) : launch(k_attn_plain<FASTCOT_F32, false>))
                                            : (early ? launch(k_attn_plain<FASTCOT_BF16, true>) : launch(k_attn_plain<FASTCOT_BF16, false>));
     if (e != hipSuccess) return e;

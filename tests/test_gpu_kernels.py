@@ -58,6 +58,21 @@ def test_plain_attention(fc, n, W, H, Hkv, Dh, f32):
     assert rel(out, attn64(q, k, v, n)) < 2e-6
 
 
+@pytest.mark.parametrize("f32", [0, 1])
+@pytest.mark.parametrize("S,n,W,H,Hkv,Dh", [(32, 0, 1, 3, 1, 32), (128, 125, 3, 4, 2, 64), (128, 96, 8, 64, 64, 32), (128, 3, 16, 33, 33, 64), (160, 3, 8, 4, 4, 64),
+                                            (160, 150, 10, 4, 2, 32), (640, 127, 1, 512, 8, 64), (640, 600, 2, 257, 257, 32)])
+def test_plain_attention_with_its_first_blocks_requested_early(fc, f32, S, n, W, H, Hkv, Dh):
+    """Heads of 32 and 64 on both sides of the lines: caches of up to 128 positions and larger ones, up to two workgroups per CU and
+    more; what lies behind the last position is infinite or NaN.  Bound as above."""
+    import torch
+    say(f"plain attention, early blocks S={S} n={n} W={W} H={H}/{Hkv} Dh={Dh} f32={f32}")
+    q, k, v = attn_inputs(n, W, H, Hkv, Dh, torch.float32 if f32 else torch.bfloat16)
+    kp, vp = (torch.full((S, Hkv, Dh), float("nan"), dtype=k.dtype, device="cuda") for _ in range(2))
+    vp[n + W::2] = float("inf")
+    kp[:n + W], vp[:n + W] = k, v
+    assert rel(fc.attn_window(q, *fc.kv_scatter(kp, vp, S), n), attn64(q, k, v, n)) < 2e-6
+
+
 @pytest.mark.parametrize("n,W,H,Hkv", [(0, 33, 2, 2), (1024, 64, 40, 40), (37, 48, 8, 2), (4000, 49, 4, 1), (5, 300, 3, 3), (777, 96, 64, 8)])
 def test_wide_window_attention(fc, n, W, H, Hkv):
     """More than 32 rows: units of 16 rows with three-part queries and probabilities, with and without key splits,
