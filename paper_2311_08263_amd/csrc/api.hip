@@ -360,18 +360,21 @@ extern "C" int fastcot_set_option(fastcot_ctx* c, int32_t option, int32_t value)
     } else if (option == FASTCOT_OPT_COMPACT) c->opt_compact = value != 0;
     else if (option == FASTCOT_OPT_AUTOTUNE) { c->opt_tune = value != 0; c->tuned_rows[0] = c->tuned_rows[1] = 0; }
     else if (option >= FASTCOT_PLAN_NW && option < FASTCOT_PLAN_NW + 5) {
-        const int gi = option - FASTCOT_PLAN_NW, NT = nts[gi], ks = c->plan.ks[gi] > 1 ? c->plan.ks[gi] : 1;
+        const int gi = option - FASTCOT_PLAN_NW, NT = nts[gi];
+        int ks = c->plan.ks[gi] > 1 ? c->plan.ks[gi] : 1;
         if (value < 1 || value > NT || (NT + value - 1) / value > 8)
             return fail(c, FASTCOT_EINVAL, "workgroups of the column-owner GEMM: NT/8 .. NT%s");
-        if (value % ks || value / ks > NT || (NT + value / ks - 1) / (value / ks) > 12)
+        auto fits = [&](int k) { return value % k == 0 && value / k >= 1 && value / k <= NT && (NT + value / k - 1) / (value / k) <= 12; };
+        if (c->plan.ks_rule[gi]) { ks = c->plan.ks_rule[gi]; if (!fits(ks)) ks /= 2; }     // (slices nobody asked for do not refuse a grid)
+        if (!fits(ks))
             return fail(c, FASTCOT_EINVAL, "workgroups of the column-owner GEMM do not fit its K slices per owner%s");
-        c->plan.nw[gi] = value; c->opt_tune = 0;
+        c->plan.nw[gi] = value; c->plan.ks[gi] = ks; c->opt_tune = 0;
     } else if (option >= FASTCOT_PLAN_KS && option < FASTCOT_PLAN_KS + 4) {
         const int gi = option - FASTCOT_PLAN_KS, NT = nts[gi], nw = c->plan.nw[gi], K = Ks[gi];
         if (value < 1 || value > 8 || K / 256 < value) return fail(c, FASTCOT_EINVAL, "K slices per owner out of range%s");
         if (nw % value || nw / value > NT || nw / value < 1 || (NT + nw / value - 1) / (nw / value) > 12)
             return fail(c, FASTCOT_EINVAL, "K slices per owner do not fit the workgroup count of that GEMM%s");
-        c->plan.ks[gi] = value; c->opt_tune = 0;
+        c->plan.ks[gi] = value; c->plan.ks_rule[gi] = 0; c->opt_tune = 0;
         // steps of 17..32 rows (two row tiles per workgroup, at most 8 n-tiles): the same value where it fits
         const int nw2 = c->plan.nw2[gi];
         if (nw2 > 0 && nw2 % value == 0 && nw2 / value >= 1 && nw2 / value <= NT && (NT + nw2 / value - 1) / (nw2 / value) <= 8)

@@ -17,6 +17,7 @@ struct FastPlan {
     int32_t ks[5];     // column-owner GEMM: K slices per owner (residual GEMMs only; 1 elsewhere)
     int32_t nw2[5], ks2[5];   // the same for passes of 17..32 rows (two row tiles per workgroup)
     int32_t nw[5];     // column-owner GEMM: workgroups for QKV, O, gate/up, down, LM head
+    int32_t ks_rule[5];   // K slices a rule over sizes chose where a workgroup count set later may go with half as many; 0: as they are
 };
 struct FastArgs {
     KernelDims kd;     // kd.M = rows of this pass

@@ -48,16 +48,16 @@ void fc_fast_plan(const KernelDims& kd, FastPlan* p) {
     if (kd.F >= 2 * kd.d && kd.F >= 4096 && p->nw[3] % 4 == 0 && p->nw[3] / 4 <= nts[3] && (nts[3] + p->nw[3] / 4 - 1) / (p->nw[3] / 4) <= 8) p->ks[3] = 4;
     p->co_single = 2;    // measured (7B and 70B shapes): down and LM head 2-4 % faster with two batches in flight, QKV and O slower
     for (int i = 0; i < 5; ++i) { p->co_sb[0][i] = !(i == 3 || i == 4); p->co_sb[1][i] = 0; p->co_rot[0][i] = i >= 2; p->co_rot[1][i] = 1; }
-    if (p->ks[1] == 4) { p->co_rot[0][1] = 1; p->co_sb[0][1] = 0; }       // (one batch in flight, or in plain order: 5-9 us slower than the above)
+    if (p->ks[1] == 4) { p->ks_rule[1] = 4; p->co_rot[0][1] = 1; p->co_sb[0][1] = 0; }       // (one batch in flight, or in plain order: 5-9 us slower than the above)
     // Measured per shape (steps of up to 16 rows, every combination of K slices per owner x batch order x batches
     // in flight timed on the shape's own matrices, the fastest recorded here): {K slices, rotated order, batches in
-    // flight} for QKV, O, gate/up, down, LM head.  Everything that fixes the order of the fp32 additions comes from
+    // flight} for QKV, O, gate/up, down, LM head; 0 K slices: what the rules above say.  Everything that fixes the order of the fp32 additions comes from
     // this table or the rules above, never from a timing at run time, so that every process computes the same bits.
     // The second triple is the same for steps of 17..32 rows (measured at 32 rows; 0 K slices = derived from the
     // first triple as below): 7B QKV 33.5 -> 31.7 us, O 20.4 -> 16.9 us, down 31.0 -> 29.4 us; 70B gate/up 183.9 -> 171.9 us.
     struct Row { int d, F, H, Hkv; int ks[5], rot[5], sb[5]; int ks2[5], rot2[5], sb2[5]; };
     static const Row table[] = {
-        {4096, 11008, 32, 32, {1, 4, 1, 8, 1}, {0, 1, 1, 1, 1}, {2, 0, 1, 0, 0}, {1, 4, 1, 4, 1}, {1, 1, 1, 1, 1}, {1, 0, 0, 0, 0}},      // Llama-2-7B shape
+        {4096, 11008, 32, 32, {1, 0, 1, 8, 1}, {0, 1, 1, 1, 1}, {2, 0, 1, 0, 0}, {1, 4, 1, 4, 1}, {1, 1, 1, 1, 1}, {1, 0, 0, 0, 0}},      // Llama-2-7B shape
         {5120, 13824, 40, 40, {1, 4, 1, 4, 1}, {1, 0, 1, 1, 1}, {0, 1, 0, 1, 0}, {0, 0, 0, 0, 0}, {1, 1, 1, 1, 1}, {0, 0, 0, 0, 0}},      // 13B shape
         {8192, 28672, 64, 8, {2, 4, 1, 4, 1}, {1, 1, 0, 1, 1}, {1, 1, 0, 0, 0}, {0, 2, 0, 0, 0}, {1, 1, 0, 1, 1}, {0, 0, 0, 0, 0}},       // 70B shape
     };
@@ -65,8 +65,8 @@ void fc_fast_plan(const KernelDims& kd, FastPlan* p) {
     for (const Row& r : table) {
         if (r.d != kd.d || r.F != kd.F || r.H != kd.H || r.Hkv != kd.Hkv || kd.Dh != 128) continue;
         for (int i = 0; i < 5; ++i) {
-            const int G = p->nw[i], ks = r.ks[i], own = G / ks;
-            if (G % ks == 0 && own >= 1 && own <= nts[i] && (nts[i] + own - 1) / own <= 12 && kin0(kd, i) / 256 >= ks) p->ks[i] = ks;
+            const int G = p->nw[i], ks = r.ks[i], own = ks ? G / ks : 0;
+            if (ks && G % ks == 0 && own >= 1 && own <= nts[i] && (nts[i] + own - 1) / own <= 12 && kin0(kd, i) / 256 >= ks) { p->ks[i] = ks; p->ks_rule[i] = 0; }
             p->co_rot[0][i] = r.rot[i]; p->co_sb[0][i] = r.sb[i];
             p->co_rot[1][i] = r.rot2[i]; p->co_sb[1][i] = r.sb2[i];
         }

@@ -76,7 +76,7 @@ class _Dims(ctypes.Structure):              # KernelDims and FastPlan of the lib
 
 class _Plan(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int32) for n in "attn_splits attn_cut attn_bpw attn_many co_single".split()] + \
-               [(n, ctypes.c_int32 * k) for n, k in (("co_sb", 10), ("co_rot", 10), ("ks", 5), ("nw2", 5), ("ks2", 5), ("nw", 5))]
+               [(n, ctypes.c_int32 * k) for n, k in (("co_sb", 10), ("co_rot", 10), ("ks", 5), ("nw2", 5), ("ks2", 5), ("nw", 5), ("ks_rule", 5))]
 
 
 def _attention_form(B, H, W, kvp, many, ctx_len):

@@ -455,6 +455,38 @@ def test_splits_option_counts_for_every_unit(fc):
     assert alike[0] == [True] * 8 + [False] and all(alike[1]) and all(alike[2])
 
 
+def test_workgroups_of_the_o_projection(fc):
+    """Grids that go with four K slices of 4096 inputs, or with two where four do not fit; odd ones and those that leave an owner too many
+    tiles stay refused, and so does what does not fit slices that were asked for.  Logits against the plain kernels."""
+    import torch
+    import synthgen
+    shape, W, P = synthgen.ModelShape(1, 512, 32, 32, 128, 512, 1040, init_std=0.05), 8, 20
+    cfg = fc.Config.from_shape(shape, 1, 96, W)
+    packed = fc.load_synth_weights(cfg, shape)
+    prompts, buf = synthgen.prompts(1, P, shape.vocab, seed=7), synthgen.buffer_init(1, 2 * W + 8, shape.vocab, seed=8)
+    O = fc.binding.PLAN_NW + 1
+
+    def logits(*opts):
+        say(f"workgroups of the O projection {opts}")
+        ctx = fc.Context(cfg, packed)
+        for o in opts:
+            ctx.set_option(*o)
+        ctx.prefill(prompts, [P], buf)
+        dbg = ctx.debug_logits(True)
+        ctx.step()
+        torch.cuda.synchronize()
+        out = dbg[:W].clone()
+        ctx.close()
+        return out
+    plain, default = logits((fc.binding.OPT_PLAIN_KERNELS, 1)), logits()
+    for nw in (6, 8, 12, 30, 32):
+        assert rel(logits((O, nw)), plain) < 1e-4
+    assert torch.equal(logits((O, 30), (O, 32)), default)
+    for refused in (((O, 31),), ((O, 4),), ((fc.binding.PLAN_KS + 1, 4), (O, 30))):
+        with pytest.raises(fc.FastcotError):
+            logits(*refused)
+
+
 @pytest.mark.parametrize("W,F", [(33, 768), (40, 1024), (41, 1280), (47, 1536), (48, 1792), (49, 2048), (63, 512), (65, 2048)])
 def test_reduction_of_k_slices(fc, W, F):
     """Many-row residual products in two to eight K slices (F / 256 of them), rows that fill the eight-row workgroups of their
