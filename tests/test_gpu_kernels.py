@@ -179,13 +179,19 @@ def test_two_tile_attention_splits(fc, n, W, H, Hkv):
     assert rel(fc.attn_window(q, kc, vc, n), attn64(q, k, v, n)) < 1.5e-5
 
 
-@pytest.mark.parametrize("n,W,H,Hkv", [(511, 1, 257, 257), (3000, 16, 341, 31), (3000, 16, 342, 9), (440, 40, 100, 4), (2000, 113, 40, 40), (600, 64, 66, 66),
-                                       (1750, 20, 300, 4), (2100, 20, 300, 4), (496, 16, 257, 257), (480, 16, 257, 257)])
-def test_attention_cut_last_round(fc, n, W, H, Hkv):
-    """More units than CUs: those past the last full round in three to eight key splits, one unit and as many as are cut at
-    most, one more than that (not cut), one and two query tiles, both sides of the shortest context that is cut."""
+@pytest.mark.parametrize("n,W,H,Hkv,splits", [(511, 1, 257, 257, 8), (3000, 16, 341, 31, 3), (3000, 16, 342, 9, 1), (440, 40, 100, 4, 1), (441, 40, 100, 4, 5),
+                                              (2000, 113, 40, 40, 4), (600, 64, 66, 66, 8), (1740, 20, 300, 4, 1), (1741, 20, 300, 4, 5), (2100, 20, 300, 4, 5),
+                                              (464, 16, 257, 257, 1), (465, 16, 257, 257, 8)])
+def test_attention_cut_last_round(fc, n, W, H, Hkv, splits):
+    """More units than CUs (256): those past the last full round in three to eight key splits, one unit and as many as are cut at
+    most, one more than that (not cut), one and two query tiles, the longest context that is not cut and the shortest that is."""
+    import ctypes
     import torch
     say(f"attention, cut last round n={n} W={W} H={H}/{Hkv}")
+    got = ctypes.c_int32(0)
+    units = H * ((W + 15) // 16 if W > 32 else 1)
+    rest = fc.lib()["_Z14fc_attn16_restiiiiiiPi"](W, 16 if W > 32 else 0, units, 1, 1, n + W, ctypes.byref(got))
+    assert (got.value, rest) == (splits, units % 256 if splits > 1 else 0)
     q, k, v = attn_inputs(n, W, H, Hkv, 128, torch.bfloat16)
     kc, vc = fc.kv_scatter(k, v, (n + W + 31) // 32 * 32)
     out = fc.attn_window(q, kc, vc, n)
@@ -428,6 +434,43 @@ def test_attention_cut_last_round_in_steps(fc, W, P, longest_first):
     for a, b, c in zip(*runs):
         assert torch.equal(a, b)
         assert rel(a, c) < 1e-4
+
+
+@pytest.mark.parametrize("W,wins,planes", [(16, [16, 3, 9, 16, 1, 12, 5, 16, 2], 1), (16, [16, 3, 9, 16, 1, 12, 5, 16, 2], 3), (16, [1, 3, 9, 2, 1, 12, 5, 4, 16], 2),
+                                           (20, [3, 20, 16, 17, 1, 20, 8, 20, 5], 1), (20, [3, 20, 16, 17, 1, 20, 8, 5, 20], 2), (20, [3, 20, 16, 17, 1, 20, 8, 20, 5], 3),
+                                           (40, [40, 3, 33, 40, 5], 2), (40, [5, 3, 32, 20, 40], 1), (40, [40, 16, 3, 17, 33], 3)])
+def test_attention_cut_last_round_of_packed_rows(fc, W, wins, planes):
+    """Cut units of sequences with windows of their own (units with few rows, and second units without any), one to three cache planes:
+    against whole units.  One layer, so both runs cache the same bits and differ by the order in which fp32 partial results of the
+    attention are added."""
+    import ctypes
+    import torch
+    import synthgen
+    shape, B = synthgen.ModelShape(**WIDE_HEADS), len(wins)
+    P = (600 if W == 16 else 1800) if planes == 1 else (300 if W == 16 else 900)
+    cfg = fc.Config.from_shape(shape, B, P + 160, W)
+    packed = fc.load_synth_weights(cfg, shape)
+    units, got = 32 * B * (2 if W > 32 else 1), ctypes.c_int32(0)
+    assert fc.lib()["_Z14fc_attn16_restiiiiiiPi"](W, 0, units, 1, planes, P, ctypes.byref(got)) == units - 256 and got.value > 2
+    prompts, buf = synthgen.prompts(B, P, shape.vocab, seed=7), synthgen.buffer_init(B, 2 * W + 24, shape.vocab, seed=8)
+    out = []
+    for opt in ((), (fc.binding.OPT_GRAPH, 0), (fc.binding.PLAN_ATTN_SPLITS, 1)):
+        say(f"cut last round, packed rows W={W} windows {wins} planes {planes} {opt}")
+        ctx = fc.Context(cfg, packed)
+        ctx.set_option(fc.binding.OPT_KV_PLANES, planes)
+        if opt:
+            ctx.set_option(*opt)
+        ctx.prefill(prompts, [P - b for b in range(B)], buf)
+        ctx.set_windows(wins)
+        rows = int(ctx.step_rows()[-1])
+        assert rows == sum(wins)
+        dbg = ctx.debug_logits(True)
+        ctx.step()
+        torch.cuda.synchronize()
+        out.append(dbg[:rows].clone())
+        ctx.close()
+    assert torch.equal(out[0], out[1])
+    assert 0 < rel(out[0], out[2]) < 1e-5
 
 
 def test_splits_option_counts_for_every_unit(fc):
