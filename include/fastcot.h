@@ -244,7 +244,9 @@ int fastcot_step_times(fastcot_ctx* ctx, float* ms, int32_t cap, int32_t* n_step
 
 /* Runs `iters` forward passes of the current state (no accept, state unchanged), launching
  * kernels one by one with a HIP event pair around each, and reports per kernel kind the mean
- * duration of one launch in ms and the launches per step.  kinds: see fastcot_kernel_name(); kind
+ * duration of one launch in ms and the launches per step.  The pass ends with the argmax as a launch of its own (kind
+ * "argmax"; "accept_commit" stays at zero): where a Jacobi step runs argmax and accept step in one launch, that launch is not among
+ * those reported.  "embed" stays at zero for fp32 models, whose first layer reads the embedding rows itself.  kinds: see fastcot_kernel_name(); kind
  * "empty_kernel" is the same event pair around a kernel that does nothing (what the pair itself adds).
  * Host outputs sized FASTCOT_N_KERNEL_KINDS. */
 enum { FASTCOT_N_KERNEL_KINDS = 16 };

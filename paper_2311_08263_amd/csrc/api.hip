@@ -842,7 +842,8 @@ extern "C" int fastcot_generate(fastcot_ctx* c, int32_t max_new, int32_t max_ste
             if (ev) HIPCHK(c, hipEventRecord(ev, c->st));
             ++total_steps;
         }
-        // one small launch that writes to host memory: as three copies this look cost the device 50 us
+        // one small launch that writes to host memory: as three copies a look took 5 us more (small fp32 model, 32 tokens, 16
+        // looks: 2465 -> 2385 us)
         HIPCHK(c, fc_report(stp, sm, B, c->pinned, c->st));
         HIPCHK(c, hipStreamSynchronize(c->st));
         all_done = c->pinned[2 * B + FLAG_ALL_DONE] != 0;
@@ -986,7 +987,6 @@ extern "C" int fastcot_answer(fastcot_ctx* c, const int32_t* trigger_ids, int32_
             if (rc) return rc;
             HIPCHK(c, fc_accept_commit(stp, sm, B, 1, S, c->st));
         }
-        // one small launch that writes to host memory: as three copies this look cost the device 50 us
         HIPCHK(c, fc_report(stp, sm, B, c->pinned, c->st));
         HIPCHK(c, hipStreamSynchronize(c->st));
         all_done = c->pinned[2 * B + FLAG_ALL_DONE] != 0;

@@ -50,7 +50,8 @@ __device__ inline void split8(const float* v, Frag& hi, Frag& lo, Frag& lo2) {
 
 #define NEG_BIG (-1.0e30f)
 #define REST_BLOCKS(two) ((two) ? 56 : 16)   // key blocks times planes from which a unit of the last round is worth cutting, two / one query tiles
-#define PART_FLOATS (8 * 64 * 4 + 128)   // per (bh, split, qt): O^T tiles, then m[64], l[64] per lane
+#define PART_FLOATS (8 * 64 * 4 + 128)   // per split of a unit and query tile: O^T tiles, then m[64], l[64] per lane.  Units lie by number with all the
+                                         // launch's splits, or, where only the last units are cut, by their number among those
 
 // the bf16 lo operand of eight cached values kept as bf16 hi (h, four words) + 8-bit residual (two words of bytes):
 // value - hi = byte * 2^-15 * 2^(exponent of hi), exact in bf16

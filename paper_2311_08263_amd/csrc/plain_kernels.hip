@@ -1,5 +1,6 @@
-// Plain kernels: fp32 arithmetic, no matrix cores.  They run fp32 models (the small parity configuration) and
-// bf16 shapes the MFMA kernels do not cover, and serve as the on-device cross-check of the MFMA kernels.  Each
+// Plain kernels: fp32 arithmetic.  They run fp32 models (the small parity configuration) and bf16 shapes the bf16
+// matrix-core kernels do not cover, and serve as the on-device cross-check of those.  Products of fp32 weights run on the fp32
+// matrix instructions (k_gemm_f32); products of bf16 weights, the cross-check, and attention stay on vector instructions.  Each
 // follows the model definition the benchmark configurations fix (RMSNorm, rotary embedding pairing i with
 // i + Dh/2, grouped-query attention with the causal mask of Eq. (2), SwiGLU).  Like the MFMA path a layer is five
 // launches: QKV (norm, rotary embedding and cache write inside), attention, O, gate/up (norm and SwiGLU inside), down.
