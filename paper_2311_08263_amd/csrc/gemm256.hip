@@ -12,7 +12,8 @@
 // 8192^3 reaches 1135, of 16384^3 1358 on the same card): power and the bytes that move.  The same loop takes 98 us with
 // matrix instructions alone, 93 us with LDS reads, 125 us with the weight loads, and on all-zero data 126 us complete and
 // 84 us with matrix instructions alone.  Without effect: software-pipelined LDS reads, activations loaded straight into
-// LDS, weights two stages further ahead, another order of the k-tiles per wave; slower: 128-row tiles in every form tried
+// LDS, weights two stages further ahead, another order of the k-tiles per wave (the order of the matrix instructions has one:
+// MFMA_TILE); slower: 128-row tiles in every form tried
 // (weights through LDS, shared by two row halves, 128 accumulator registers per wave), 8 x 2 tiles per wave.
 // Matrices with few columns (O and down projections) are also split along K so that the launch fills the chip; the
 // slices store partial tiles and k_resid_reduce_split adds them to the residual stream in slice order.
@@ -154,7 +155,7 @@ hipError_t fc_embed_split(const void* emb, const int32_t* win, float* x, int M, 
 // ------------------------------------------------------------------ the GEMM
 // Eight waves per workgroup, RT row tiles per row block (4, or 3 where that pads fewer rows: 65..96 rows are two blocks of
 // 48 instead of two of 64), each wave RT x (up to CW) output tiles of 16 x 16.  Two forms:
-//  KSPLIT: two groups of four waves take the even and the odd k-tiles of every stage for the same up to 4 * CW column
+//  KSPLIT: two groups of four waves take the first and the second pair of k-tiles of every stage for the same up to 4 * CW column
 //    tiles and add their accumulators through LDS at the end; used where the launch has at most one workgroup per CU.
 //    The weights of a wave's next four k-tiles (two stages) travel ahead.
 //  else: the eight waves own neighbouring column tiles (up to 8 * CW) and share the activation stage.
@@ -172,7 +173,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm256(Gemm256Args a) {
     __shared__ float rowpart[8][16 * RT];
     constexpr int SL = RT * NPL / 2;                     // 16-byte stage loads per thread
     constexpr int CWV = KSPLIT ? 4 : 8;                  // waves a column block is dealt to
-    const int tid = threadIdx.x, lane = tid & 63, w8 = tid >> 6, w = w8 & 3, kg = w8 >> 2;
+    const int tid = threadIdx.x, lane = tid & 63, w8 = __builtin_amdgcn_readfirstlane(tid >> 6), w = w8 & 3, kg = w8 >> 2;
     const int lm = lane & 15, g4 = lane >> 4;
     const int KT = a.K >> 5, NS = KT >> 2, MT = (a.M + 15) >> 4;
     // id -> (XCD x, sequence number q on that XCD) -> row block q % nrb of unit 8 * (q / nrb) + x
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm256(Gemm256Args a) {
     // stage copy: wave w8 copies fragments w8, w8 + 8, ... of the stage's 4 * RT * NPL.  Addresses are a uniform 64-bit
     // base (scalar registers, advanced per stage) plus a per-thread 32-bit byte offset fixed for the whole kernel:
     // no 64-bit vector arithmetic in the loop.
-    const char* AFb = (const char*)a.AF;
+    const __amdgpu_buffer_rsrc_t Ar = __builtin_amdgcn_make_buffer_rsrc((void*)a.AF, 0, (uint32_t)MT * KT * NPL * 1024, 0x00020000);
     uint32_t aoff[SL];
 #pragma unroll
     for (int i = 0; i < SL; ++i) {
@@ -212,26 +213,29 @@ __global__ __launch_bounds__(512, 1) void k_gemm256(Gemm256Args a) {
         aoff[i] = ((((uint32_t)mt * KT + ktl) * NPL + part) * 64 + lane) * 16;
     }
     auto stage_load = [&](u32x4_t (&r)[SL], int s) {
-        const char* base = AFb + (size_t)s * (4096 * NPL);    // 4 k-tiles x parts x 1 KB
 #pragma unroll
-        for (int i = 0; i < SL; ++i) r[i] = *(const u32x4_t*)(base + aoff[i]);
+        for (int i = 0; i < SL; ++i) r[i] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(Ar, aoff[i], s * (4096 * NPL), 0));   // 4 k-tiles x parts x 1 KB
     };
     auto stage_store = [&](const u32x4_t (&r)[SL], int buf) {
 #pragma unroll
         for (int i = 0; i < SL; ++i) lds[buf * STG + (w8 + 8 * i) * 64 + lane] = r[i];
     };
-    const char* Wb = (const char*)a.W;
+    // Weights: a descriptor of the matrix and a scalar offset per pair of k-tiles, a 32-bit offset per lane fixed for the whole
+    // kernel (as a base pointer plus offset the compiler kept 64-bit vector addresses, since the loads of a pair stand in
+    // several blocks).
+    const __amdgpu_buffer_rsrc_t Wr = __builtin_amdgcn_make_buffer_rsrc((void*)a.W, 0, (uint32_t)a.NT * KT * 1024, 0x00020000);
     uint32_t woff[CW];
 #pragma unroll
     for (int j = 0; j < CW; ++j) {
-        const int nt = nt0 + j < ntend ? nt0 + j : (ntend > nt0 ? ntend - 1 : cb0);     // no tile of its own: one that is being read anyway
-        woff[j] = ((uint32_t)nt * KT * 64 + lane) * 16;
+        const uint32_t nt = nt0 + j < ntend ? nt0 + j : (ntend > nt0 ? ntend - 1 : cb0);     // no tile of its own: one that is being read anyway
+        woff[j] = (nt * KT * 64 + lane) * 16;
     }
-    auto wload = [&](u32x4_t (&wt)[CW], int kt) {
-        const int kc = kt < 4 * s_hi ? kt : 4 * s_hi - 1;     // past the end of the slice: its last k-tile again (never used, no new line)
-        const char* base = Wb + (size_t)kc * 1024;
+    struct Pair { Frag t[2]; };
+    auto wload = [&](Pair& w, int j, int pair) {
+        const int pc = pair < 2 * s_hi ? pair : 2 * s_hi - 1;     // past the end of the slice: its last pair again (never used, no new line)
 #pragma unroll
-        for (int j = 0; j < CW; ++j) wt[j] = *(const u32x4_t*)(base + woff[j]);   // plain loads: the row blocks of a column block share these lines in L2
+        for (int t = 0; t < 2; ++t)                               // (not past the caches: the row blocks of a column block share these lines in L2)
+            w.t[t].u = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(Wr, woff[j], pc * 2048 + t * 1024, 0));
     };
 
     f32x4_t acc[CW][RT];
@@ -241,10 +245,12 @@ __global__ __launch_bounds__(512, 1) void k_gemm256(Gemm256Args a) {
         for (int m = 0; m < RT; ++m) acc[j][m] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 
     u32x4_t sr[SL];
-    u32x4_t W0[CW], W1[CW], W2[CW], W3[CW];              // KSPLIT: k-tiles kg and kg + 2 of a stage and of the next
+    Pair P0[CW], P1[CW];                                 // the two pairs of a stage; KSPLIT: pair kg of a stage and of the next
     stage_load(sr, s_lo);
-    if (!KSPLIT) { wload(W0, 4 * s_lo); wload(W1, 4 * s_lo + 1); wload(W2, 4 * s_lo + 2); wload(W3, 4 * s_lo + 3); }
-    else { wload(W0, 4 * s_lo + kg); wload(W1, 4 * s_lo + kg + 2); wload(W2, 4 * s_lo + kg + 4); wload(W3, 4 * s_lo + kg + 6); }
+#pragma unroll
+    for (int j = 0; j < CW; ++j) wload(P0[j], j, 2 * s_lo + (KSPLIT ? kg : 0));
+#pragma unroll
+    for (int j = 0; j < CW; ++j) wload(P1[j], j, 2 * s_lo + (KSPLIT ? 2 + kg : 1));
     stage_store(sr, 0);
     if (EPI != EPI_RESID && a.ssq) {
         // row statistics of the rows (activations that come without their norm scale): wave w adds every
@@ -258,22 +264,52 @@ __global__ __launch_bounds__(512, 1) void k_gemm256(Gemm256Args a) {
     }
     __syncthreads();
 
-#define MFMA_COL(WSET, J)                                                                           \
+// One accumulator: the NPL parts of one k-tile of row tile M.  The order of the matrix instructions is fixed (nothing of them
+// passes the scheduling barrier, everything else does): power bounds this loop, and instructions in a row that add to
+// the same accumulator take less of it.  16 x 16 x 32 alone on random data, TFLOP/s issued: another accumulator every
+// instruction (the order the compiler takes, which puts dependent instructions apart) 1780-1850, two in a row 1890-1940, four
+// 1940-1990, eight 2010-2030; 32 x 32 x 16 1650-1710 in any order.
+#define MFMA_TILE(W, J, AP, M)                                                                      \
     do {                                                                                            \
-        Frag wf; wf.u = WSET[J];                                                                    \
-        _Pragma("unroll") for (int m = 0; m < RT; ++m)                                              \
-            _Pragma("unroll") for (int p = 0; p < NPL; ++p)                                         \
-                acc[J][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf.v, ap[m][p].v, acc[J][m], 0, 0, 0); \
+        _Pragma("unroll") for (int p = 0; p < NPL; ++p) {                                           \
+            acc[J][M] = __builtin_amdgcn_mfma_f32_16x16x32_bf16((W).v, AP[M][p].v, acc[J][M], 0, 0, 0); \
+            __builtin_amdgcn_sched_barrier(0x3F6);                                                  \
+        }                                                                                           \
     } while (0)
+#define READ_AP(AP, KTL)                                                                            \
+    _Pragma("unroll") for (int m = 0; m < RT; ++m)                                                  \
+        _Pragma("unroll") for (int p = 0; p < NPL; ++p) AP[m][p].u = lds[buf * STG + (((KTL) * RT + m) * NPL + p) * 64 + lane]
+// Pair U of the stage, from registers WSET: a column tile's two k-tiles row tile by row tile (four instructions in a row to
+// an accumulator), then its next weights are requested: requests are spread over the pair and a weight has almost two pairs'
+// time to arrive.  (A k-tile at a time for all columns, then all their requests, in the compiler's order: 7B prompt of
+// 2048 7211 -> 6870 us, 13B step of 256 rows 1800 -> 1746, isolated LM head of 256 rows 196 -> 190, 77 rows 822 -> 814; the
+// requests alone gave 1.3 % of the prompt and nothing of the 13B step.)  Three parts of an activation leave registers for one k-tile's only.
 #define STEP(WSET, U, AHEAD)                                                                        \
     do {                                                                                            \
-        Frag ap[RT][NPL];                                                                           \
-        _Pragma("unroll") for (int m = 0; m < RT; ++m)                                              \
-            _Pragma("unroll") for (int p = 0; p < NPL; ++p) ap[m][p].u = lds[buf * STG + (((U) * RT + m) * NPL + p) * 64 + lane]; \
-        _Pragma("unroll") for (int j = 0; j < CW - 1; ++j) MFMA_COL(WSET, j);                       \
-        if (full) MFMA_COL(WSET, CW - 1);                                                           \
-        wload(WSET, 4 * s + (U) + (AHEAD));                                                         \
-        __builtin_amdgcn_sched_barrier(0);   /* keep these loads here, a stage or two ahead of their use */ \
+        const int next = 2 * s + (U) + (AHEAD);                                                     \
+        if (NPL == 2) {                                                                             \
+            Frag a0[RT][NPL], a1[RT][NPL];                                                          \
+            READ_AP(a0, 2 * (U)); READ_AP(a1, 2 * (U) + 1);                                         \
+            _Pragma("unroll") for (int j = 0; j < CW; ++j) {                                        \
+                if (j < CW - 1 || full) {                                                           \
+                    _Pragma("unroll") for (int m = 0; m < RT; ++m) { MFMA_TILE(WSET[j].t[0], j, a0, m); MFMA_TILE(WSET[j].t[1], j, a1, m); } \
+                }                                                                                   \
+                wload(WSET[j], j, next);                                                            \
+                __builtin_amdgcn_sched_barrier(0);                                                  \
+            }                                                                                       \
+        } else {                                                                                    \
+            _Pragma("unroll") for (int t = 0; t < 2; ++t) {                                         \
+                Frag ap[RT][NPL];                                                                   \
+                READ_AP(ap, 2 * (U) + t);                                                           \
+                _Pragma("unroll") for (int j = 0; j < CW; ++j) {                                    \
+                    if (j < CW - 1 || full) {                                                       \
+                        _Pragma("unroll") for (int m = 0; m < RT; ++m) MFMA_TILE(WSET[j].t[t], j, ap, m); \
+                    }                                                                               \
+                    if (t == 1) wload(WSET[j], j, next);                                            \
+                    __builtin_amdgcn_sched_barrier(0);                                              \
+                }                                                                                   \
+            }                                                                                       \
+        }                                                                                           \
     } while (0)
 
     int buf = 0, s = s_lo;
@@ -284,25 +320,22 @@ __global__ __launch_bounds__(512, 1) void k_gemm256(Gemm256Args a) {
     while (s < s_hi) {
         STAGE_BEGIN();
         if (!KSPLIT) {
-            STEP(W0, 0, 4);
-            STEP(W1, 1, 4);
-            STEP(W2, 2, 4);
-            STEP(W3, 3, 4);
+            STEP(P0, 0, 2);
+            STEP(P1, 1, 2);
         } else {
-            STEP(W0, kg, 8);
-            STEP(W1, kg + 2, 8);
+            STEP(P0, kg, 4);
             STAGE_END();
             if (s >= s_hi) break;
             STAGE_BEGIN();
-            STEP(W2, kg, 8);
-            STEP(W3, kg + 2, 8);
+            STEP(P1, kg, 4);
         }
         STAGE_END();
     }
 #undef STAGE_BEGIN
 #undef STAGE_END
 #undef STEP
-#undef MFMA_COL
+#undef READ_AP
+#undef MFMA_TILE
 
     if (KSPLIT) {
         // the two k-groups meet: each publishes the part of its accumulators that the other group will finish (group 0
