@@ -67,7 +67,11 @@ typedef struct fastcot_ctx fastcot_ctx;
  * activations, token buffers, counters) for a configuration.  0 on an invalid configuration.
  * The activations are sized for the largest pass: a step of max_batch * window rows, or a prompt chunk (Sec. 4.1, the
  * first forward): up to 1024 rows in all for bf16 models of the shapes the matrix-core kernels cover, for other models
- * up to 128 rows per sequence within 512 in all, but at least 16 per sequence.  Logits are sized for a step's rows. */
+ * up to 128 rows per sequence within 512 in all, but at least 16 per sequence.  Logits are sized for a step's rows.
+ * For bf16 models of the matrix-core shapes the workspace also holds a copy of the weights in 13 bits each, from which passes of up to
+ * 32 rows read them (7B shape: 10 GiB; of models whose weights and copies would pass 208 GiB, the matrices that fit): a context's first
+ * fastcot_prefill makes it, and a later one makes it again where fastcot_pack_tensor or fastcot_pack_weights wrote to the packed
+ * weights in between. */
 size_t fastcot_weight_bytes(const fastcot_config* cfg);
 size_t fastcot_workspace_bytes(const fastcot_config* cfg);
 
@@ -193,12 +197,8 @@ int fastcot_debug_logits(fastcot_ctx* ctx, float* d_logits);
  * FASTCOT_OPT_COMPACT = 1 (default): whenever fastcot_generate finds finished sequences at one of its checks,
  * they trade slots (state and K/V cache) with unfinished ones so that the following steps run only the
  * unfinished sequences' rows; the order is restored before it returns.  0: finished sequences keep their rows.
- * FASTCOT_OPT_AUTOTUNE = 1 (default): at the first fastcot_prefill of a step shape with at most 32 rows, the
- * column-owner GEMMs that walk K in plain order (QKV, O) are timed on the model's own matrices with one / two
- * weight batches in flight or the whole K slice requested up front, and the fastest is kept.  The choice moves
- * loads, not additions: logits are the same bits whichever wins, in every process.  Everything that fixes the
- * order of the fp32 additions (K slices per owner, batch order) is chosen from the model shape alone.  Setting
- * any FASTCOT_PLAN_* value turns the measurement off: explicit choices win.
+ * FASTCOT_OPT_AUTOTUNE: accepted and without effect.  (The first fastcot_prefill used to time launches of the column-owner GEMMs;
+ * everything about them now follows from the shape, and logits are the same bits in every process.)
  * FASTCOT_OPT_KV_EMULATE (bf16 models, matrix-core kernels; a precision study, not a storage mode): value =
  * K mode + 16 * V mode; before a K (V) value is cached it is rounded as a narrower storage format would round it
  * (mode 0 as computed, 1 bf16, 2 fp16, 3 the upper 24 bits of fp32) and then kept in the two planes as usual, so
@@ -218,9 +218,10 @@ enum { FASTCOT_OPT_PLAIN_KERNELS = 1, FASTCOT_OPT_GRAPH = 2, FASTCOT_OPT_KV_PLAN
  * FASTCOT_PLAN_NW + g: workgroups of GEMM g (each owns at most 8 tiles of 16 columns over all of K).
  * FASTCOT_PLAN_KS + g (g < 4): workgroups per column owner, each taking 1/value of K (1..8); their partial tiles
  * meet through memory and the last to arrive adds them in slice order.  The workgroup count must be a multiple.
- * FASTCOT_PLAN_SB + g: weight batches in flight per wave: 0 two, 1 one, 2 the wave's whole K slice up front.
- * FASTCOT_PLAN_ROT + g: 1 = every wave walks its K batches in an order rotated by workgroup and wave.
- * FASTCOT_PLAN_CO_SINGLE: 0 / 1 = two / one batch in flight for every GEMM, 2 (default) = per GEMM (PLAN_SB).
+ * FASTCOT_PLAN_SB + g: pairs of k-tiles under way per wave: 0 two, 1 one (more where a workgroup owns one or two n-tiles), 2 (default)
+ * by the n-tiles a workgroup owns.
+ * FASTCOT_PLAN_ROT + g: 1 = every wave walks its part of K in an order rotated by workgroup and wave (default 0).
+ * FASTCOT_PLAN_CO_SINGLE: 0 / 1 = two / one pair under way for every GEMM, 2 (default) = per GEMM (PLAN_SB).
  * FASTCOT_PLAN_ATTN_SPLITS: key-range splits the attention launch provides (1..16), the same for every unit of it.  (Unset,
  * a launch of more units than compute units may run the last ones in key splits while the others stay whole.)
  * FASTCOT_PLAN_ATTN_BLOCKS: key blocks of 32 positions per attention workgroup: of the launched splits,
@@ -295,7 +296,8 @@ int fastcot_stream_read_chain(const void* d_src, size_t src_bytes, const uint64_
                               void* d_sink16, void* hip_stream);
 
 /* LM head fused with argmax (Eq. 1/2, lowest id on ties): act device fp32 [M][d] (already
- * normalised), packed W_lm as written by fastcot_lmhead_pack from canonical bf16 [d][V] (finite weights);
+ * normalised), packed W_lm as written by fastcot_lmhead_pack from canonical bf16 [d][V] (finite weights; where d is a multiple of 256 a copy in
+ * 13 bits a weight follows the plain tiles, which is what calls of up to 32 rows read);
  * ids device int32 [M], top device fp32 [M] (the winning logit); d_top2 nullable fp32 [M], the largest logit
  * among all other ids (top - top2 is the margin of the decision; asking for it makes the call write the
  * logits, to d_logits or to the scratch); d_logits nullable fp32 [M][V].

@@ -23,8 +23,6 @@ struct fastcot_ctx {
     int Bact;            // sequences of the current run
     int prefilled, generated;
     int opt_compact;     // fastcot_generate moves finished sequences out of the way so that later steps run fewer rows
-    int opt_tune;        // measure the plan's per-GEMM choices at prefill
-    int tuned_rows[2];   // rows per step the plan's per-GEMM choices were last measured for (up to 16 / 17..32 rows)
     int last_eos;        // eos_id of the last fastcot_generate (-1 = none)
     int buf_len;
     int opt_plain, opt_graph, dbg_stop;
@@ -47,6 +45,8 @@ struct fastcot_ctx {
     std::vector<hipEvent_t> step_ev;
     std::vector<float> step_ms;
     int32_t* pinned;     // small pinned host block for polling
+    int coded;           // the coded copies of the weights are there, of the weights with this stamp
+    uint64_t coded_stamp;
     char err[512];
 };
 
@@ -96,31 +96,34 @@ int fc_build_maps(const fastcot_config* c, ModelMap* mm, WorkspaceMap* wm, Kerne
     if (!valid_cfg(c)) return FASTCOT_EINVAL;
     const size_t esz = c->dtype == FASTCOT_F32 ? 4 : 2;
     const int d = c->d_model, qd = c->n_heads * c->head_dim, kvd = c->n_kv_heads * c->head_dim, F = c->d_ffn;
-    auto fused = [&](size_t& cur, int K, int N) {
-        FusedMat f; f.off = cur; f.K = K; f.N = N; f.NP = (N + 15) & ~15;
-        cur = FC_ALIGN(cur + (size_t)K * f.NP * esz);
-        return f;
-    };
-    if (mm) {
-        size_t cur = 0;
-        mm->qkv = fused(cur, d, qd + 2 * kvd);
-        mm->o = fused(cur, qd, d);
-        mm->gu = fused(cur, d, 2 * F);
-        mm->down = fused(cur, F, d);
-        mm->g1_off = cur; cur = FC_ALIGN(cur + (size_t)d * 4);
-        mm->g2_off = cur; cur = FC_ALIGN(cur + (size_t)d * 4);
-        mm->layer_stride = cur;
-        size_t top = 0;
-        mm->emb_off = top; top = FC_ALIGN(top + (size_t)c->vocab * d * esz);
-        mm->lm = fused(top, d, c->vocab);
-        mm->gf_off = top; top = FC_ALIGN(top + (size_t)d * 4);
-        mm->layers_off = top;
-        mm->total = top + (size_t)c->n_layers * mm->layer_stride;
-    }
     KernelDims k;
     k.L = c->n_layers; k.d = d; k.H = c->n_heads; k.Hkv = c->n_kv_heads; k.Dh = c->head_dim; k.F = F;
     k.V = c->vocab; k.B = c->max_batch; k.S = (c->max_seq + 31) & ~31; k.W = c->window;
     k.qkvN = qd + 2 * kvd; k.eps = c->rms_eps; k.esz = (int)esz; k.kvp = c->dtype == FASTCOT_BF16 ? 2 : 1; k.kvq = 0; k.actq = 0;
+    auto fused = [&](size_t& cur, int K, int N) {
+        FusedMat f; f.off = cur; f.K = K; f.N = N; f.NP = (N + 15) & ~15; f.coded = 0;
+        cur = FC_ALIGN(cur + (size_t)K * f.NP * esz);
+        return f;
+    };
+    ModelMap m;
+    {
+        size_t cur = 0;
+        m.qkv = fused(cur, d, qd + 2 * kvd);
+        m.o = fused(cur, qd, d);
+        m.gu = fused(cur, d, 2 * F);
+        m.down = fused(cur, F, d);
+        m.g1_off = cur; cur = FC_ALIGN(cur + (size_t)d * 4);
+        m.g2_off = cur; cur = FC_ALIGN(cur + (size_t)d * 4);
+        m.layer_stride = cur;
+        size_t top = 0;
+        m.emb_off = top; top = FC_ALIGN(top + (size_t)c->vocab * d * esz);
+        m.lm = fused(top, d, c->vocab);
+        m.gf_off = top; top = FC_ALIGN(top + (size_t)d * 4);
+        m.layers_off = top;
+        m.stamp_off = top + (size_t)c->n_layers * m.layer_stride;
+        m.total = m.stamp_off + 256;
+        if (mm) *mm = m;
+    }
     // prefill runs the same kernels over chunks of the prompt; where the matrix-core path covers the
     // shape a chunk is up to 1024 rows per sequence (at most 1024 rows in all), else one window
     k.Wcap = k.W; k.M = k.B * k.W;
@@ -171,6 +174,18 @@ int fc_build_maps(const fastcot_config* c, ModelMap* mm, WorkspaceMap* wm, Kerne
         s.words = w;
         wm->st = s;
         wm->state = take((size_t)w * 4);
+        // Coded copies for the kernels of up to 32 rows: 13/16 of a matrix each, so where all of them would take weights and
+        // workspace past 208 GiB of the 288 GB a GPU has (70B shapes: 129 GiB of weights, 104 of copies), those that fit, the
+        // matrices in the order of what a step spends on them.
+        const FusedMat* mats[5] = {&m.qkv, &m.o, &m.gu, &m.down, &m.lm};
+        const int order[5] = {2, 3, 4, 0, 1};
+        for (int i = 0; i < 5; ++i) wm->code[i] = wm->code_stride[i] = 0;
+        for (int i : order) {
+            const size_t each = FC_ALIGN(wc_bytes(mats[i]->K, mats[i]->NP / 16)), all = each * (i == 4 ? 1 : (size_t)k.L);
+            if (!fc_fast_supported(k, 1) || !all || m.total + cur + all > ((size_t)208 << 30)) continue;
+            wm->code_stride[i] = each;
+            wm->code[i] = take(all);
+        }
         wm->total = cur;
     }
     return 0;
@@ -186,6 +201,18 @@ extern "C" size_t fastcot_workspace_bytes(const fastcot_config* cfg) {
 }
 
 // ------------------------------------------------------------------ weight packing
+// canonical layout of a whole model: element count and element size of a tensor
+static size_t canon_elems(const KernelDims& kd, int t) {
+    const size_t d = kd.d, qd = (size_t)kd.H * kd.Dh, kvd = (size_t)kd.Hkv * kd.Dh, F = kd.F, V = kd.V;
+    switch (t) {
+        case FASTCOT_T_EMB: case FASTCOT_T_WLM: return V * d;
+        case FASTCOT_T_GF: case FASTCOT_T_G1: case FASTCOT_T_G2: return d;
+        case FASTCOT_T_WQ: case FASTCOT_T_WO: return d * qd;
+        case FASTCOT_T_WK: case FASTCOT_T_WV: return d * kvd;
+        case FASTCOT_T_WG: case FASTCOT_T_WU: case FASTCOT_T_WD: return d * F;
+    }
+    return 0;
+}
 extern "C" int fastcot_pack_tensor(const fastcot_config* cfg, int32_t tensor, int32_t layer, const void* src,
                                    void* d_packed, void* hip_stream) {
     ModelMap mm; KernelDims kd;
@@ -218,22 +245,11 @@ extern "C" int fastcot_pack_tensor(const fastcot_config* cfg, int32_t tensor, in
         case FASTCOT_T_WD: e = fc_pack(src, dt, kd.F, d, lbase, mm.down, 0, 0, st); break;
         default: return fail(nullptr, FASTCOT_EINVAL, "unknown tensor id%s");
     }
+    if (e == hipSuccess) e = fc_stamp(base + mm.stamp_off, gain ? nullptr : src, canon_elems(kd, tensor) * (size_t)kd.esz / 2, (uint32_t)(tensor + 16 * (per_layer ? layer + 1 : 0)), st);
     if (e != hipSuccess) return fail(nullptr, FASTCOT_EHIP, "pack launch failed: %s", hipGetErrorString(e));
     return 0;
 }
 
-// canonical layout of a whole model: element count and element size of a tensor
-static size_t canon_elems(const KernelDims& kd, int t) {
-    const size_t d = kd.d, qd = (size_t)kd.H * kd.Dh, kvd = (size_t)kd.Hkv * kd.Dh, F = kd.F, V = kd.V;
-    switch (t) {
-        case FASTCOT_T_EMB: case FASTCOT_T_WLM: return V * d;
-        case FASTCOT_T_GF: case FASTCOT_T_G1: case FASTCOT_T_G2: return d;
-        case FASTCOT_T_WQ: case FASTCOT_T_WO: return d * qd;
-        case FASTCOT_T_WK: case FASTCOT_T_WV: return d * kvd;
-        case FASTCOT_T_WG: case FASTCOT_T_WU: case FASTCOT_T_WD: return d * F;
-    }
-    return 0;
-}
 static size_t canon_bytes(const KernelDims& kd, int t) {
     const bool gain = t == FASTCOT_T_GF || t == FASTCOT_T_G1 || t == FASTCOT_T_G2;
     return FC_ALIGN(canon_elems(kd, t) * (gain ? 4 : (size_t)kd.esz));
@@ -286,11 +302,11 @@ extern "C" int fastcot_init(const fastcot_config* cfg, const void* d_packed, voi
     if (fc_build_maps(cfg, &c->mm, &c->wm, &c->kd) != 0) { delete c; return fail(nullptr, FASTCOT_EINVAL, "invalid configuration: %s", cfg_problem(cfg)); }
     if (workspace_bytes < c->wm.total) { delete c; return fail(nullptr, FASTCOT_ECAPACITY, "workspace too small%s"); }
     c->cfg = *cfg; c->weights = (const char*)d_packed; c->ws = (char*)d_workspace; c->st = (hipStream_t)hip_stream;
-    c->Bact = 0; c->ctx_len = c->ctx_max = 0; c->graph_form = 0; c->prefilled = 0; c->generated = 0; c->buf_len = 0; c->opt_tune = 1; c->opt_compact = 1;
+    c->Bact = 0; c->ctx_len = c->ctx_max = 0; c->graph_form = 0; c->prefilled = 0; c->generated = 0; c->buf_len = 0; c->opt_compact = 1;
     c->opt_packed = 1; c->rows_dirty = 1; c->rows_step = 0;
     c->opt_plain = (cfg->dtype == FASTCOT_F32); c->opt_graph = 1; c->dbg_stop = -1; c->dbg_logits = nullptr;
     c->graph_exec = nullptr; c->graph = nullptr; c->graph_valid = 0; c->prof_on = 0; c->prof_used = 0;
-    c->pinned = nullptr; c->err[0] = 0;
+    c->pinned = nullptr; c->err[0] = 0; c->coded = 0; c->coded_stamp = 0;
     fc_fast_plan(c->kd, &c->plan);
     // rotary table: cos/sin of pos * base^(-2i/Dh), evaluated in double on the host
     const int half = c->kd.Dh / 2;
@@ -358,7 +374,7 @@ extern "C" int fastcot_set_option(fastcot_ctx* c, int32_t option, int32_t value)
         if (c->cfg.dtype != FASTCOT_BF16 || value < 0 || value > 31) return fail(c, FASTCOT_EINVAL, "activation format emulation: a mask of the five GEMMs, bf16 models only%s");
         c->kd.actq = value;
     } else if (option == FASTCOT_OPT_COMPACT) c->opt_compact = value != 0;
-    else if (option == FASTCOT_OPT_AUTOTUNE) { c->opt_tune = value != 0; c->tuned_rows[0] = c->tuned_rows[1] = 0; }
+    else if (option == FASTCOT_OPT_AUTOTUNE) {}      // (nothing is measured any more)
     else if (option >= FASTCOT_PLAN_NW && option < FASTCOT_PLAN_NW + 5) {
         const int gi = option - FASTCOT_PLAN_NW, NT = nts[gi];
         int ks = c->plan.ks[gi] > 1 ? c->plan.ks[gi] : 1;
@@ -368,25 +384,25 @@ extern "C" int fastcot_set_option(fastcot_ctx* c, int32_t option, int32_t value)
         if (c->plan.ks_rule[gi]) { ks = c->plan.ks_rule[gi]; if (!fits(ks)) ks /= 2; }     // (slices nobody asked for do not refuse a grid)
         if (!fits(ks))
             return fail(c, FASTCOT_EINVAL, "workgroups of the column-owner GEMM do not fit its K slices per owner%s");
-        c->plan.nw[gi] = value; c->plan.ks[gi] = ks; c->opt_tune = 0;
+        c->plan.nw[gi] = value; c->plan.ks[gi] = ks;
     } else if (option >= FASTCOT_PLAN_KS && option < FASTCOT_PLAN_KS + 4) {
         const int gi = option - FASTCOT_PLAN_KS, NT = nts[gi], nw = c->plan.nw[gi], K = Ks[gi];
         if (value < 1 || value > 8 || K / 256 < value) return fail(c, FASTCOT_EINVAL, "K slices per owner out of range%s");
         if (nw % value || nw / value > NT || nw / value < 1 || (NT + nw / value - 1) / (nw / value) > 12)
             return fail(c, FASTCOT_EINVAL, "K slices per owner do not fit the workgroup count of that GEMM%s");
-        c->plan.ks[gi] = value; c->plan.ks_rule[gi] = 0; c->opt_tune = 0;
+        c->plan.ks[gi] = value; c->plan.ks_rule[gi] = 0;
         // steps of 17..32 rows (two row tiles per workgroup, at most 8 n-tiles): the same value where it fits
         const int nw2 = c->plan.nw2[gi];
         if (nw2 > 0 && nw2 % value == 0 && nw2 / value >= 1 && nw2 / value <= NT && (NT + nw2 / value - 1) / (nw2 / value) <= 8)
             c->plan.ks2[gi] = value;
     } else if (option >= FASTCOT_PLAN_SB && option < FASTCOT_PLAN_SB + 5) {
-        if (value < 0 || value > 2) return fail(c, FASTCOT_EINVAL, "weight batches in flight: 0 (two), 1 (one) or 2 (whole slice up front)%s");
-        c->plan.co_sb[0][option - FASTCOT_PLAN_SB] = c->plan.co_sb[1][option - FASTCOT_PLAN_SB] = value; c->opt_tune = 0;
+        if (value < 0 || value > 2) return fail(c, FASTCOT_EINVAL, "pairs of k-tiles under way per wave: 0 (two), 1 (one) or 2 (by the tiles a workgroup owns)%s");
+        c->plan.co_sb[0][option - FASTCOT_PLAN_SB] = c->plan.co_sb[1][option - FASTCOT_PLAN_SB] = value;
     } else if (option >= FASTCOT_PLAN_ROT && option < FASTCOT_PLAN_ROT + 5) {
-        c->plan.co_rot[0][option - FASTCOT_PLAN_ROT] = c->plan.co_rot[1][option - FASTCOT_PLAN_ROT] = value != 0; c->opt_tune = 0;
+        c->plan.co_rot[0][option - FASTCOT_PLAN_ROT] = c->plan.co_rot[1][option - FASTCOT_PLAN_ROT] = value != 0;
     } else if (option == FASTCOT_PLAN_CO_SINGLE) {
         if (value < 0 || value > 2) return fail(c, FASTCOT_EINVAL, "buffering of the column-owner GEMM: 0, 1 or 2%s");
-        c->plan.co_single = value; c->opt_tune = 0;
+        c->plan.co_single = value;
     } else if (option == FASTCOT_PLAN_ATTN_SPLITS) {
         if (value < 1 || value > FC_MAX_ATTN_SPLITS) return fail(c, FASTCOT_EINVAL, "attention splits out of range%s");
         c->plan.attn_splits = value; c->plan.attn_cut = 0;
@@ -563,6 +579,29 @@ static int enqueue_step(fastcot_ctx* c) {
 // becomes slot 0 of the first window).  Enqueues only.  (The plain path took a window's rows per pass: a prompt of 32
 // tokens of the 256-wide model with window 8 was four passes of eleven launches, 379 us; one
 // pass 163 us.)
+// The coded copies of the weights (wcode.h), made by a context's first prefill and again by one that finds other weights packed since:
+// 7B shape, 6.5 GB of tiles a millisecond.  A look at the stamp takes about 10 us.
+static int code_weights(fastcot_ctx* c) {
+    bool any = false;
+    for (int i = 0; i < 5; ++i) any = any || c->wm.code[i];
+    if (!any) return 0;
+    HIPCHK(c, fc_stamp_read(c->weights + c->mm.stamp_off, c->pinned, c->st));
+    HIPCHK(c, hipStreamSynchronize(c->st));
+    const uint64_t stamp = *(const uint64_t*)c->pinned;
+    if (c->coded && c->coded_stamp == stamp) return 0;
+    c->coded = 0;
+    const FusedMat* mats[5] = {&c->mm.qkv, &c->mm.o, &c->mm.gu, &c->mm.down, &c->mm.lm};
+    for (int i = 0; i < 5; ++i) {
+        if (!c->wm.code[i]) continue;
+        for (int l = 0; l < (i == 4 ? 1 : c->kd.L); ++l) {
+            const char* base = i == 4 ? c->weights : c->weights + c->mm.layers_off + (size_t)l * c->mm.layer_stride;
+            HIPCHK(c, fc_code(base + mats[i]->off, c->ws + c->wm.code[i] + (size_t)l * c->wm.code_stride[i], mats[i]->K, mats[i]->NP / 16, 0, mats[i]->NP / 16, c->st));
+        }
+    }
+    c->coded = 1; c->coded_stamp = stamp;
+    return 0;
+}
+
 static int prefill_passes(fastcot_ctx* c, int B, int maxlen) {
     const KernelDims& kd = c->kd; const StateMap& sm = c->wm.st;
     int32_t* stp = state_ptr(c);
@@ -630,20 +669,7 @@ extern "C" int fastcot_prefill(fastcot_ctx* c, int32_t B, const int32_t* prompts
     HIPCHK(c, hipMemsetAsync(stp + sm.wseq, 0, (size_t)kd.B * 4, c->st));
     if (B != c->Bact) drop_graph(c);
     c->Bact = B; c->buf_len = buf_len; c->prefilled = 0; c->generated = 0;
-    // the plan's per-GEMM choices are measured once per step shape, on this model's own matrices (the buffers
-    // hold nothing yet that the passes below do not overwrite)
-    {
-        const int rows = B * kd.W, cls = rows > 16;
-        if (c->opt_tune && !c->opt_plain && c->plan.co_single == 2 && rows <= 32 && c->tuned_rows[cls] != rows &&
-            fc_fast_supported(kd, rows)) {
-            FastArgs a;
-            a.kd = kd; a.kd.M = rows; a.Bact = B; a.mm = &c->mm; a.wm = &c->wm; a.weights = c->weights; a.ws = c->ws;
-            a.dbg_logits = nullptr; a.plan = &c->plan; a.st = c->st; a.lmhead = 1; a.dbg_stop = -1; a.prof = nullptr; a.prof_mark = nullptr;
-            HIPCHK(c, fc_fast_tune(a, &c->plan));
-            c->tuned_rows[cls] = rows;
-            drop_graph(c);
-        }
-    }
+    { int rc = code_weights(c); if (rc) return rc; }
     { int rc = prefill_passes(c, B, maxlen); if (rc) return rc; }
     HIPCHK(c, hipStreamSynchronize(c->st));
     c->prefilled = 1;

@@ -61,11 +61,20 @@ __device__ inline float kv_round(float v, int mode) {
 // fp32 models keep it row-major [K][NP].  bf16 models keep it in MFMA fragment order: the
 // 16-column x 32-row tile (nt, kt) is 64 lanes x 8 values, lane = (col % 16) + 16 * ((row % 32) / 8),
 // value = row % 8, tiles ordered [nt][kt]; one wave reads a tile with one 16-byte load per lane.
+// The coded copy of such a matrix (wcode.h; a model's are part of the workspace, that of an isolated LM head follows its tiles): the
+// weights of every pair of k-tiles in 13 bits each [nt][K / 64], a byte per pair (holds weights that 13 bits do not), a byte per
+// column (its base).
 struct FusedMat {
     size_t off;     // byte offset inside the packed weights
     int32_t K, N;   // logical rows, logical columns
     int32_t NP;     // padded columns
+    int32_t coded;  // its coded copy follows
 };
+#define WC_PAIR 1664
+__host__ __device__ inline size_t wc_off(int32_t K, int32_t NT) { return (size_t)NT * K * 32; }
+__host__ __device__ inline size_t wc_flag_off(int32_t K, int32_t NT) { return (size_t)NT * (K >> 6) * WC_PAIR; }          // from the copy's start
+__host__ __device__ inline size_t wc_base_off(int32_t K, int32_t NT) { return (size_t)NT * (K >> 6) * (WC_PAIR + 1); }
+__host__ __device__ inline size_t wc_bytes(int32_t K, int32_t NT) { return wc_base_off(K, NT) + (size_t)NT * 16; }
 __host__ __device__ inline size_t frag_index(int32_t K, int32_t k, int32_t n) {
     int32_t KT = K >> 5;
     int32_t nt = n >> 4, kt = k >> 5;
@@ -99,6 +108,7 @@ struct ModelMap {
     size_t emb_off;              // [V][d] row-major, model dtype
     FusedMat lm;                 // absolute offset
     size_t gf_off;
+    size_t stamp_off;            // 64 bits that change with every tensor packed
     size_t total;
 };
 
@@ -124,6 +134,7 @@ struct WorkspaceMap {
     size_t x, qkv, qrot, att, h, logits, topv;
     size_t gemm_part, gemm_cnt, attn_part, attn_cnt, amax_part;
     size_t state;
+    size_t code[5], code_stride[5];   // coded copies of QKV, O, gate/up, down (layer l at code + l * stride) and the LM head; 0: none
     size_t total;
     size_t gemm_part_bytes, attn_part_bytes;
     StateMap st;

@@ -10,10 +10,9 @@ struct FastPlan {
     int32_t attn_cut;  // units past the last full round of CUs may run in key splits (fc_attn16_rest); 0: every unit in attn_splits splits, as asked for
     int32_t attn_bpw;  // key blocks of 32 per attention workgroup (decides at run time how many of the splits work)
     int32_t attn_many; // many-row attention kernel (attnp.hip): 0 never, 1 where it gives half of the CUs a workgroup, 2 for every pass of more than 32 rows per sequence
-    int32_t co_single; // column-owner GEMM: 1 = one weight batch in flight per wave, 0 = two, 2 = chosen per GEMM
-    int32_t co_sb[2][5];   // the per-GEMM choice (1 = one batch, 0 = two, 2 = whole slice) for up to 16 rows [0] and 17..32 rows [1]: defaults
-                           // from the 7B shape, replaced by fc_fast_tune's measurement on the actual shape
-    int32_t co_rot[2][5];  // per-GEMM: walk the K batches in a per-wave rotated order (same defaults / measurement)
+    int32_t co_single; // column-owner GEMM: pairs of k-tiles under way per wave for every GEMM as co_sb below; 2 = per GEMM (co_sb)
+    int32_t co_sb[2][5];   // ... for up to 16 rows [0] and 17..32 rows [1]: 0 two, 1 one, 2 by the n-tiles a workgroup owns
+    int32_t co_rot[2][5];  // per GEMM: walk the pairs in an order rotated by workgroup and wave (0: in order)
     int32_t ks[5];     // column-owner GEMM: K slices per owner (residual GEMMs only; 1 elsewhere)
     int32_t nw2[5], ks2[5];   // the same for passes of 17..32 rows (two row tiles per workgroup)
     int32_t nw[5];     // column-owner GEMM: workgroups for QKV, O, gate/up, down, LM head
@@ -36,9 +35,6 @@ struct FastArgs {
     bool accept = false;   // the pass is a Jacobi step: the accept step follows the argmax, in the same launch where that pays ...
     bool* accepted = nullptr;   // ... and *accepted says whether it did
     int dbg_stop;      // debug: number of stages to run (5 per layer), < 0 = all
-    int tune_gi = -1;  // >= 0: launch only GEMM tune_gi (0 QKV, 1 O, 2 gate/up, 3 down, 4 LM head) of layer 0 ...
-    int tune_sb = 0;   // ... with this many-batches choice, this batch order and this many K slices per owner
-    int tune_rot = 0, tune_ks = 1;   // (timing runs of fc_fast_tune; results are scratch)
 };
 
 // true when the MFMA path covers this shape (else the caller uses the plain kernels)
@@ -50,12 +46,6 @@ hipError_t fc_fast_forward(const FastArgs& a);
 bool fc_attn_one_tile(const KernelDims& kd, int Bact, const FastPlan& plan, int ctx_len, int* splits);
 // which of the attention launch's forms such a pass takes (one query tile, cut last units, many rows): a captured step stays valid while this is the same
 int fc_attn_form(const KernelDims& kd, int Bact, const FastPlan& plan, int ctx_len);
-// Times every column-owner GEMM of the pass shape a.kd (at most 32 rows) with one and with two weight batches in
-// flight per wave or the wave's whole K slice at once and records the fastest in the plan.  Only that choice is
-// measured: it moves loads, not additions, so the results are the same bits whichever wins.  Overwrites activations and layer 0's first cache rows:
-// call it before a prefill.  Synchronises the stream.
-hipError_t fc_fast_tune(FastArgs a, FastPlan* plan);
-
 // isolation launchers (same kernels as the step)
 size_t fc_attn_iso_scratch_bytes(int W, int H, int Dh);
 hipError_t fc_attn_iso(const float* q, const void* kc, const void* vc, int n, int W, int H, int Hkv, int Dh, int S,

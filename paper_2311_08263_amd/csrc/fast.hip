@@ -13,9 +13,6 @@ bool fc_fast_supported(const KernelDims& kd, int rows) {
            (kd.H * kd.Dh) % 256 == 0 && kd.S % 32 == 0 && kd.V % 16 == 0;
 }
 
-// inputs (K) of GEMM i: QKV, O, gate/up, down, LM head
-static int kin0(const KernelDims& kd, int i) { return i == 1 ? kd.H * kd.Dh : (i == 3 ? kd.F : kd.d); }
-
 void fc_fast_plan(const KernelDims& kd, FastPlan* p) {
     memset(p, 0, sizeof(*p));
     // at most 8 key splits: the last workgroup to arrive folds up to 8 partial results in one round of loads
@@ -35,43 +32,24 @@ void fc_fast_plan(const KernelDims& kd, FastPlan* p) {
     const int nts[5] = {kd.qkvN / 16, kd.d / 16, 2 * kd.F / 16, kd.d / 16, kd.V / 16};
     // measured on the 7B shape: one workgroup per CU
     for (int i = 0; i < 5; ++i) { p->nw[i] = fc_gemmco_grid(nts[i]); p->ks[i] = 1; }
-    if (nts[1] < 512) {                  // O projection with fewer than two n-tiles per CU
-        // two K slices per owner, four where a wave is left with four k-tiles.  Since the partial tiles travel in whole
-        // lines a step of eight 4096-wide layers takes with two / four slices 891 / 881 us (16 rows), 885 / 881 (8 rows), 853 /
-        // 852 (1 row); of eight 2048-wide layers 495 / 497 (16 rows).
+    // K slices per owner cut the activations a workgroup reads and cost a meeting of the slices in memory.
+    if (nts[1] <= 512) {                 // O projection with at most two n-tiles per CU
+        // two K slices per owner, four from 4096 inputs on (steps of up to 16 rows with one / two / four slices, us: eight
+        // 4096-wide layers 874 / 874 / 869, six 5120-wide 895 / 888 / 886, two 8192-wide 647 / 642 / 644, eight 2048-wide 526 / 519 / 522)
         const int G = p->nw[1], K = kd.H * kd.Dh;
         if (G % 2 == 0 && G / 2 <= nts[1] && (nts[1] + G / 2 - 1) / (G / 2) <= 8 && K >= 2048) p->ks[1] = 2;
         if (p->ks[1] == 2 && G % 4 == 0 && (nts[1] + G / 4 - 1) / (G / 4) <= 8 && K >= 4096) p->ks[1] = 4;
     }
     // down projection: K is long and the columns few, so every workgroup would read far more activation
-    // bytes than weight bytes; K slices per owner cut that (measured at the 7B shape)
+    // bytes than weight bytes (one / two / four / eight slices, us: eight layers of the 7B shape 903 / 862 / 850 / 859, six of 13B
+    // 935 / 876 / 859 / 881, two of 70B 678 / 648 / 642)
     if (kd.F >= 2 * kd.d && kd.F >= 4096 && p->nw[3] % 4 == 0 && p->nw[3] / 4 <= nts[3] && (nts[3] + p->nw[3] / 4 - 1) / (p->nw[3] / 4) <= 8) p->ks[3] = 4;
-    p->co_single = 2;    // measured (7B and 70B shapes): down and LM head 2-4 % faster with two batches in flight, QKV and O slower
-    for (int i = 0; i < 5; ++i) { p->co_sb[0][i] = !(i == 3 || i == 4); p->co_sb[1][i] = 0; p->co_rot[0][i] = i >= 2; p->co_rot[1][i] = 1; }
-    if (p->ks[1] == 4) { p->ks_rule[1] = 4; p->co_rot[0][1] = 1; p->co_sb[0][1] = 0; }       // (one batch in flight, or in plain order: 5-9 us slower than the above)
-    // Measured per shape (steps of up to 16 rows, every combination of K slices per owner x batch order x batches
-    // in flight timed on the shape's own matrices, the fastest recorded here): {K slices, rotated order, batches in
-    // flight} for QKV, O, gate/up, down, LM head; 0 K slices: what the rules above say.  Everything that fixes the order of the fp32 additions comes from
-    // this table or the rules above, never from a timing at run time, so that every process computes the same bits.
-    // The second triple is the same for steps of 17..32 rows (measured at 32 rows; 0 K slices = derived from the
-    // first triple as below): 7B QKV 33.5 -> 31.7 us, O 20.4 -> 16.9 us, down 31.0 -> 29.4 us; 70B gate/up 183.9 -> 171.9 us.
-    struct Row { int d, F, H, Hkv; int ks[5], rot[5], sb[5]; int ks2[5], rot2[5], sb2[5]; };
-    static const Row table[] = {
-        {4096, 11008, 32, 32, {1, 0, 1, 8, 1}, {0, 1, 1, 1, 1}, {2, 0, 1, 0, 0}, {1, 4, 1, 4, 1}, {1, 1, 1, 1, 1}, {1, 0, 0, 0, 0}},      // Llama-2-7B shape
-        {5120, 13824, 40, 40, {1, 4, 1, 4, 1}, {1, 0, 1, 1, 1}, {0, 1, 0, 1, 0}, {0, 0, 0, 0, 0}, {1, 1, 1, 1, 1}, {0, 0, 0, 0, 0}},      // 13B shape
-        {8192, 28672, 64, 8, {2, 4, 1, 4, 1}, {1, 1, 0, 1, 1}, {1, 1, 0, 0, 0}, {0, 2, 0, 0, 0}, {1, 1, 0, 1, 1}, {0, 0, 0, 0, 0}},       // 70B shape
-    };
-    const Row* mine = nullptr;
-    for (const Row& r : table) {
-        if (r.d != kd.d || r.F != kd.F || r.H != kd.H || r.Hkv != kd.Hkv || kd.Dh != 128) continue;
-        for (int i = 0; i < 5; ++i) {
-            const int G = p->nw[i], ks = r.ks[i], own = ks ? G / ks : 0;
-            if (ks && G % ks == 0 && own >= 1 && own <= nts[i] && (nts[i] + own - 1) / own <= 12 && kin0(kd, i) / 256 >= ks) { p->ks[i] = ks; p->ks_rule[i] = 0; }
-            p->co_rot[0][i] = r.rot[i]; p->co_sb[0][i] = r.sb[i];
-            p->co_rot[1][i] = r.rot2[i]; p->co_sb[1][i] = r.sb2[i];
-        }
-        mine = &r;
-    }
+    // QKV with few columns over many inputs (grouped K/V heads): two 8192-wide layers of 24 rows 736 -> 726 us, of 16 rows the same; with
+    // heads of their own slices lose (eight 4096-wide layers 853 -> 871)
+    if (kd.d >= 8192 && nts[0] < 3 * fc_num_cus() && p->nw[0] % 2 == 0 && (nts[0] + p->nw[0] / 2 - 1) / (p->nw[0] / 2) <= 8) p->ks[0] = 2;
+    p->co_single = 2;
+    for (int i = 0; i < 5; ++i) p->co_sb[0][i] = p->co_sb[1][i] = 2;
+    if (p->ks[1] == 4) p->ks_rule[1] = 4;
     // 17..32 rows (two row tiles per workgroup, up to 16 output tiles): the same grids where the partial tiles
     // fit the LDS, K slices halved until they divide the grid
     const int kin[5] = {kd.d, kd.H * kd.Dh, kd.d, kd.F, kd.d};
@@ -84,8 +62,6 @@ void fc_fast_plan(const KernelDims& kd, FastPlan* p) {
         int k2 = p->ks[i];
         if (i == 1 && k2 == 2) k2 = 4;       // (twice the activations: slices pay earlier; eight 2048-wide layers, 24 / 32 rows, two -> four slices 564 / 595 -> 557 / 584 us)
         while (k2 > 1 && (G2 % k2 || G2 / k2 > nts[i] || (nts[i] + G2 / k2 - 1) / (G2 / k2) > most)) k2 >>= 1;
-        const int kt = mine ? mine->ks2[i] : 0;          // the table's own value for this class, where it fits
-        if (kt >= 1 && i < 4 && G2 % kt == 0 && G2 / kt >= 1 && G2 / kt <= nts[i] && (nts[i] + G2 / kt - 1) / (G2 / kt) <= most && kin[i] / 256 >= kt) k2 = kt;
         p->nw2[i] = G2; p->ks2[i] = k2;
     }
 }
@@ -189,7 +165,7 @@ hipError_t fc_fast_forward(const FastArgs& a) {
     GemmCoArgs co; memset(&co, 0, sizeof(co));
     co.M = M; co.eps = kd.eps; co.n_state = g.n_state; co.cosT = g.cosT; co.sinT = g.sinT; co.kc = g.kc; co.vc = g.vc;
     co.H = kd.H; co.Hkv = kd.Hkv; co.B = kd.B; co.S = kd.S; co.Wn = kd.W; co.kvp = kd.kvp; co.kvq = kd.kvq;
-    co.amax_val = g.amax_val; co.single_buffer = 1; co.rm = a.rm;
+    co.amax_val = g.amax_val; co.single_buffer = 2; co.rm = a.rm;
     Gemm256Args big; memset(&big, 0, sizeof(big));
     big.M = M; big.n_state = g.n_state; big.cosT = g.cosT; big.sinT = g.sinT; big.kc = g.kc; big.vc = g.vc;
     big.H = kd.H; big.Hkv = kd.Hkv; big.B = kd.B; big.S = kd.S; big.Wn = kd.W; big.kvp = kd.kvp; big.kvq = kd.kvq;
@@ -209,18 +185,17 @@ hipError_t fc_fast_forward(const FastArgs& a) {
     const int lm_ncb = fc_gemm256_plan(M, kd.V / 16, 1, 2).ncb;
     big.amax_val = g.amax_val; big.amax_idx = (int32_t*)(g.amax_val + (size_t)lm_ncb * big.amax_stride);
     int gi = 0;        // which GEMM of the plan
-    auto gemm = [&](int epi, const void* W, int K, int N, const float* X, int ldx, const float* gain,
-                    float* out, int ldo) {
+    auto gemm = [&](int epi, const char* base, const FusedMat& fm, const float* X, const float* gain, float* out, int ldo) {
+        const char* W = base + fm.off;
+        const int K = fm.K, N = fm.N, ldx = fm.K;
         // workgroups of the column-owner kernel and its K slices per owner
         const int nw = M <= 16 ? a.plan->nw[gi] : (M <= 32 ? a.plan->nw2[gi] : 0);
-        const int ksl = a.tune_gi >= 0 ? a.tune_ks : (M <= 16 ? a.plan->ks[gi] : a.plan->ks2[gi]);
+        const int ksl = M <= 16 ? a.plan->ks[gi] : a.plan->ks2[gi];
         if (nw > 0) {
-            co.W = (const bf16_t*)W; co.K = K; co.NT = N / 16; co.X = X; co.ldx = ldx; co.gain = gain; co.out = out; co.ldo = ldo;
+            co.W = (const bf16_t*)W; co.C = wm.code[gi] ? ws + wm.code[gi] + (size_t)g.layer * wm.code_stride[gi] : nullptr; co.K = K; co.NT = N / 16; co.X = X; co.ldx = ldx; co.gain = gain; co.out = out; co.ldo = ldo;
             co.layer = g.layer; co.ks = epi != EPI_LMHEAD ? ksl : 1; co.hi_only = (kd.actq >> gi) & 1;
-            // one or two weight batches in flight per wave: which is faster depends on the GEMM and on the shape
-            // (7B: two for down and LM head; 13B: two for QKV and gate/up, one for down), so it is a plan entry
-            co.single_buffer = a.tune_gi >= 0 ? a.tune_sb : (a.plan->co_single == 2 ? a.plan->co_sb[M > 16][gi] : a.plan->co_single);
-            co.rotate = a.tune_gi >= 0 ? a.tune_rot : a.plan->co_rot[M > 16][gi];
+            co.single_buffer = a.plan->co_single == 2 ? a.plan->co_sb[M > 16][gi] : a.plan->co_single;
+            co.rotate = a.plan->co_rot[M > 16][gi];
             co.xpart = (float*)(ws + wm.gemm_part); co.xcnt = (int32_t*)(ws + wm.gemm_cnt);
             co.amax_idx = (int32_t*)(co.amax_val + (size_t)nw * (M > 16 ? 32 : 16));
             return fc_gemmco(epi, co, nw, a.st);
@@ -244,18 +219,6 @@ hipError_t fc_fast_forward(const FastArgs& a) {
         return hipErrorInvalidValue;       // every plan gives the column-owner kernel a grid
     };
 
-    if (a.tune_gi >= 0) {            // timing run of one GEMM (layer 0 weights, whatever the buffers hold)
-        const char* lb = wt + mm.layers_off;
-        g.layer = 0; gi = a.tune_gi;
-        switch (gi) {
-            case 0: return gemm(EPI_QKV, lb + mm.qkv.off, d, kd.qkvN, x, d, (const float*)(lb + mm.g1_off), q, qd);
-            case 1: return gemm(EPI_RESID, lb + mm.o.off, qd, d, att, qd, nullptr, x, d);
-            case 2: return gemm(EPI_SWIGLU, lb + mm.gu.off, d, 2 * kd.F, x, d, (const float*)(lb + mm.g2_off), h, kd.F);
-            case 3: return gemm(EPI_RESID, lb + mm.down.off, kd.F, d, h, kd.F, nullptr, x, d);
-            case 4: return gemm(EPI_LMHEAD, wt + mm.lm.off, d, kd.V, x, d, (const float*)(wt + mm.gf_off), nullptr, kd.V);
-        }
-        return hipErrorInvalidValue;
-    }
     if (M > 32)
         FLAUNCH(KK_EMBED, fc_embed_split(wt + mm.emb_off, stp + wm.st.win, x, M, d, kd.V, a.rm, kd.W,
                                          (const float*)(kd.L > 0 ? wt + mm.layers_off + mm.g1_off : wt + mm.gf_off), af_x, ssq, a.st));
@@ -268,7 +231,7 @@ hipError_t fc_fast_forward(const FastArgs& a) {
         g.layer = l; at.layer = l;
         DBG_STOP();
         gi = 0;
-        FLAUNCH(KK_QKV, gemm(EPI_QKV, lb + mm.qkv.off, d, kd.qkvN, x, d, (const float*)(lb + mm.g1_off), q, qd));
+        FLAUNCH(KK_QKV, gemm(EPI_QKV, lb, mm.qkv, x, (const float*)(lb + mm.g1_off), q, qd));
         DBG_STOP();
         if (M > 32) {                  // the many-row O projection reads fragments: attention writes them itself
             at.ofrag = af_att;
@@ -284,22 +247,22 @@ hipError_t fc_fast_forward(const FastArgs& a) {
         DBG_STOP();
         gi = 1;
         next_gain = (const float*)(lb + mm.g2_off);
-        FLAUNCH(KK_O, gemm(EPI_RESID, lb + mm.o.off, qd, d, att, qd, nullptr, x, d));
+        FLAUNCH(KK_O, gemm(EPI_RESID, lb, mm.o, att, nullptr, x, d));
         DBG_STOP();
         gi = 2;
-        FLAUNCH(KK_GU, gemm(EPI_SWIGLU, lb + mm.gu.off, d, 2 * kd.F, x, d, (const float*)(lb + mm.g2_off), h, kd.F));
+        FLAUNCH(KK_GU, gemm(EPI_SWIGLU, lb, mm.gu, x, (const float*)(lb + mm.g2_off), h, kd.F));
         DBG_STOP();
         gi = 3;
         next_gain = l + 1 < kd.L ? (const float*)(wt + mm.layers_off + (size_t)(l + 1) * mm.layer_stride + mm.g1_off) : (const float*)(wt + mm.gf_off);
-        FLAUNCH(KK_DOWN, gemm(EPI_RESID, lb + mm.down.off, kd.F, d, h, kd.F, nullptr, x, d));
+        FLAUNCH(KK_DOWN, gemm(EPI_RESID, lb, mm.down, h, nullptr, x, d));
     }
     if (a.dbg_stop >= 0 && nstage >= a.dbg_stop) return hipSuccess;
     if (a.lmhead) {
         const int stride = M > 16 ? 32 : 16;
         const int nwlm = M <= 16 ? a.plan->nw[4] : (M <= 32 ? a.plan->nw2[4] : 0);
         const int nwin = nwlm;                                // partial winners to reduce
-        gi = 4;
-        FLAUNCH(KK_LM, gemm(EPI_LMHEAD, wt + mm.lm.off, d, kd.V, x, d, (const float*)(wt + mm.gf_off), a.dbg_logits, kd.V));
+        gi = 4; g.layer = 0;
+        FLAUNCH(KK_LM, gemm(EPI_LMHEAD, wt, mm.lm, x, (const float*)(wt + mm.gf_off), a.dbg_logits, kd.V));
         if (a.accept && fc_tail_fits(a.Bact, kd.W, M, nwin, true)) {
             FLAUNCH(KK_ARGMAX, fc_tail_winners(g.amax_val, (const int32_t*)(g.amax_val + (size_t)nwin * stride), nwin, stride, M, (float*)(ws + wm.topv),
                                                a.rm, stp, wm.st, a.Bact, kd.W, kd.S, a.st));
@@ -312,60 +275,6 @@ hipError_t fc_fast_forward(const FastArgs& a) {
                                                stp + wm.st.o, (float*)(ws + wm.topv), a.st, a.rm, kd.W));
     }
     return hipSuccess;
-}
-
-hipError_t fc_fast_tune(FastArgs a, FastPlan* plan) {
-    const int M = a.kd.M;
-    if (M < 1 || M > 32) return hipSuccess;
-    const int cls = M > 16;
-    a.prof = nullptr; a.prof_mark = nullptr; a.dbg_stop = -1; a.plan = plan;
-    hipEvent_t e0, e1;
-    hipError_t e = hipEventCreate(&e0);
-    if (e != hipSuccess) return e;
-    if ((e = hipEventCreate(&e1)) != hipSuccess) { (void)hipEventDestroy(e0); return e; }
-    // mean of 5 launches after 2 untimed ones; hipErrorInvalidValue from the first launch = the launcher
-    // rejected the combination (nothing ran)
-    auto measure = [&](float* ms) -> hipError_t {
-        hipError_t r = fc_fast_forward(a);
-        if (r != hipSuccess) return r;
-        r = fc_fast_forward(a);
-        if (r == hipSuccess) r = hipEventRecord(e0, a.st);
-        for (int i = 0; i < 5 && r == hipSuccess; ++i) r = fc_fast_forward(a);
-        if (r == hipSuccess) r = hipEventRecord(e1, a.st);
-        if (r == hipSuccess) r = hipEventSynchronize(e1);
-        if (r == hipSuccess) r = hipEventElapsedTime(ms, e0, e1);
-        return r;
-    };
-    // Only the number of weight batches in flight is measured, and only for the GEMMs that walk their batches in
-    // plain order: there it changes when loads are issued, never the order in which a wave adds its k-tiles, so
-    // every choice gives the same bits.  The K slices per owner and the batch order do change the order of the
-    // fp32 additions, and so does the batch size of a GEMM that walks its batches in rotated order: all of those
-    // stay as fc_fast_plan fixed them from the shape.  Two processes therefore compute identical logits whatever
-    // their timings were.
-    for (int gi = 0; gi < 5 && e == hipSuccess; ++gi) {
-        const int nw = cls ? plan->nw2[gi] : plan->nw[gi];
-        if (nw <= 0) continue;                      // not a column-owner launch
-        float best = 1e30f;
-        int best_sb = plan->co_sb[cls][gi];
-        const int rot = plan->co_rot[cls][gi], ks = cls ? plan->ks2[gi] : plan->ks[gi];
-        if (rot) continue;
-        a.tune_gi = gi; a.tune_ks = ks; a.tune_rot = rot;
-        for (int sb = 0; sb < 3 && e == hipSuccess; ++sb) {      // two batches, one batch, the whole slice at once
-            a.tune_sb = sb;
-            float t = 1e30f;
-            for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {
-                float ms = 0.f;
-                const hipError_t r = measure(&ms);
-                if (r == hipErrorInvalidValue) { t = 1e30f; break; }
-                e = r;
-                if (e == hipSuccess && ms < t) t = ms;
-            }
-            if (e == hipSuccess && t < best) { best = t; best_sb = sb; }
-        }
-        if (e == hipSuccess) plan->co_sb[cls][gi] = best_sb;
-    }
-    (void)hipEventDestroy(e0); (void)hipEventDestroy(e1);
-    return e;
 }
 
 // ------------------------------------------------------------------ isolation launchers
@@ -469,11 +378,8 @@ hipError_t fc_lmhead_iso(const float* act, const void* packed, int M, int d, int
     }
     GemmCoArgs co; memset(&co, 0, sizeof(co));
     const int nwg = lm_iso_grid(M, d, V), stride = M > 16 ? 32 : 16;
-    co.W = (const bf16_t*)packed; co.K = d; co.NT = V / 16; co.X = act; co.ldx = d; co.M = M; co.out = logits; co.ldo = V;
-    // two batches in flight, every wave in an order of its own: the weights are read once and nothing is reused, so
-    // what counts is requests under way on every channel.  A call, one batch in plain order -> this: 4096 x 32000 with 16
-    // rows 48.4 -> 44.8 us; 3-20 % over 2048..8192 x 8000..51200 and 1..32 rows (8192 x 51200: 140.5 -> 134.2 us with 16).
-    co.single_buffer = 0; co.rotate = 1;
+    co.W = (const bf16_t*)packed; co.C = (const char*)packed + wc_off(d, V / 16); co.K = d; co.NT = V / 16; co.X = act; co.ldx = d; co.M = M; co.out = logits; co.ldo = V;
+    co.single_buffer = 2;
     co.amax_val = (float*)sc;
     co.amax_idx = (int32_t*)(co.amax_val + (size_t)nwg * stride);
     hipError_t e = fc_gemmco(EPI_LMHEAD, co, nwg, st);

@@ -6,6 +6,7 @@ enum { EPI_RESID = 0, EPI_SWIGLU = 1, EPI_QKV = 2, EPI_LMHEAD = 3 };
 
 struct GemmCoArgs {
     const bf16_t* W;       // fused matrix in fragment order
+    const char* C;         // its coded copy (wcode.h), or NULL
     int32_t K, NT;         // inputs (multiple of 256), n-tiles
     const float* X;        // activations fp32 [M][ldx]
     int32_t ldx, M;        // M <= 32 rows
@@ -23,9 +24,9 @@ struct GemmCoArgs {
                            // workgroup's share of the row sums of squares [workgroup][16 or 32]
     int32_t* xcnt;         // ks > 1: one arrival counter per owner, zero between launches
     int32_t hi_only;       // precision study: the activations enter as plain bf16 (their lo halves dropped)
-    int32_t rotate;        // walk the K batches in a per-wave rotated order (spreads the streams over the memory channels)
-    int32_t single_buffer; // weights in flight per wave: 1 = one batch, 0 = two batches, 2 = the wave's whole K slice requested up front
-                           // (QKV and residual GEMMs, up to 16 rows, slices of at most 16 k-tiles per wave; else rejected)
+    int32_t rotate;        // walk the pairs of k-tiles in a per-wave rotated order (a measurement aid: in order is as fast or faster everywhere)
+    int32_t gain_wave;     // set by the launch: floats of the gain a wave keeps in LDS
+    int32_t single_buffer; // pairs of k-tiles under way per wave: 0 two, 1 one, 2 by the n-tiles a workgroup owns
 };
 
 // G workgroups = G / ks owners x ks K slices; owner i owns n-tiles [i*NT/owners, (i+1)*NT/owners), at most
@@ -36,6 +37,7 @@ int fc_gemmco_grid(int NT, int most = 8);
 // norm in front, the gain vector (K floats) fit the LDS of a CU
 int fc_gemmco_most(int M, int K, bool gain);
 int fc_num_cus();      // compute units of the current device
+hipError_t fc_gemmco_coded(int epi, const GemmCoArgs& a, int G, hipStream_t st);      // (through fc_gemmco)
 hipError_t fc_gemmco(int epi, const GemmCoArgs& a, int G, hipStream_t st);
 // reduction of the LM head's per-workgroup winners [nparts][stride] to one id and value per row (lowest id on ties)
 // (with a row map the result of row m goes to entry rowb[m] * W + rowj[m] of ids and top)

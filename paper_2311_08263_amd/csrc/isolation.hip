@@ -127,7 +127,7 @@ extern "C" int fastcot_attn_window_noalloc(const float* d_q, const void* d_k_cac
 
 extern "C" size_t fastcot_lmhead_packed_bytes(int32_t d, int32_t V) {
     if (d <= 0 || V <= 0 || d % 32 || V % 16) return 0;
-    return (size_t)d * V * 2;
+    return (size_t)d * V * 2 + (d % 256 ? 0 : wc_bytes(d, V / 16));
 }
 extern "C" size_t fastcot_lmhead_scratch_bytes(int32_t M, int32_t d, int32_t V) {
     if (M <= 0 || d <= 0 || V <= 0) return 0;
@@ -135,7 +135,7 @@ extern "C" size_t fastcot_lmhead_scratch_bytes(int32_t M, int32_t d, int32_t V) 
 }
 extern "C" int fastcot_lmhead_pack(const void* src, int32_t d, int32_t V, void* d_packed, void* hip_stream) {
     if (!src || !d_packed || d <= 0 || V <= 0 || d % 32 || V % 16) return FASTCOT_EINVAL;
-    FusedMat fm; fm.off = 0; fm.K = d; fm.N = V; fm.NP = V;
+    FusedMat fm; fm.off = 0; fm.K = d; fm.N = V; fm.NP = V; fm.coded = d % 256 == 0;
     hipError_t e = fc_pack(src, FASTCOT_BF16, d, V, d_packed, fm, 0, 0, (hipStream_t)hip_stream);
     return e == hipSuccess ? 0 : FASTCOT_EHIP;
 }

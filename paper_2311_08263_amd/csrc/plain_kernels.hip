@@ -5,6 +5,7 @@
 // i + Dh/2, grouped-query attention with the causal mask of Eq. (2), SwiGLU).  Like the MFMA path a layer is five
 // launches: QKV (norm, rotary embedding and cache write inside), attention, O, gate/up (norm and SwiGLU inside), down.
 #include "kernels.h"
+#include "wcode.h"
 #include "gemmco.h"      // fc_num_cus
 
 template <int DT> __device__ inline float wat(const void* W, size_t i) {
@@ -526,22 +527,116 @@ hipError_t fc_argmax_plain(const float* logits, int M, int V, int32_t* ids, floa
 // ------------------------------------------------------------------ packing
 // canonical [rows][cols] -> fused matrix columns; mode selects the column map: 0 natural at col_off,
 // 1 / 2 gate / up interleave, 3 + Dh rotary-pair order inside heads of Dh columns (q and k heads).
-template <int DT>
-__global__ void k_pack(const void* src, int rows, int cols, void* dst, FusedMat fm, int col_off, int mode) {
+__device__ inline int pack_col(int c, int col_off, int mode) { return mode == 0 ? col_off + c : (mode <= 2 ? gu_col(c, mode - 1) : qkv_col(col_off + c, mode - 3, 0x7fffffff)); }
+__global__ void k_pack_f32(const float* src, int rows, int cols, float* dst, int NP, int col_off, int mode) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (size_t)rows * cols) return;
-    int k = (int)(i / cols), c = (int)(i % cols);
-    int n = mode == 0 ? col_off + c : (mode <= 2 ? gu_col(c, mode - 1) : qkv_col(col_off + c, mode - 3, 0x7fffffff));
-    char* base = (char*)dst + fm.off;
-    if (DT == FASTCOT_F32) ((float*)base)[(size_t)k * fm.NP + n] = ((const float*)src)[i];
-    else ((bf16_t*)base)[frag_index(fm.K, k, n)] = ((const bf16_t*)src)[i];
+    const int k = (int)(i / cols), c = (int)(i % cols);
+    dst[(size_t)k * NP + pack_col(c, col_off, mode)] = src[i];
+}
+// bf16: a thread takes eight rows of a column, which are a lane's 16 bytes of the fragment: rows are read in runs of the workgroup's
+// columns, sixteen neighbouring columns are written as 256 bytes.
+__global__ void k_pack_bf16(const bf16_t* src, int rows, int cols, bf16_t* dst, int K, int col_off, int mode) {
+    const int c = blockIdx.x * 64 + (threadIdx.x & 63), k = (blockIdx.y * 4 + (threadIdx.x >> 6)) * 8;
+    if (c >= cols || k >= rows) return;
+    uint32_t v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = src[(size_t)(k + e) * cols + c];
+    *(u32x4_t*)(dst + frag_index(K, k, pack_col(c, col_off, mode))) = (u32x4_t){v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
+}
+// The coded copy (wcode.h) of n-tiles nt0, nt0 + 1, ... from their plain tiles: a workgroup an n-tile, its eight waves all of K twice, for
+// the columns' largest exponents and for the codes.
+__global__ __launch_bounds__(512) void k_code(const char* W, char* C, int K, int NT, int nt0) {
+    __shared__ uint32_t top[8][16];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, lm = lane & 15, nt = nt0 + blockIdx.x, PT = K >> 6;
+    const u32x4_t* src = (const u32x4_t*)W + (size_t)nt * PT * 128 + lane;
+    uint32_t hi = 0;
+#pragma unroll 4
+    for (int t = w; t < 2 * PT; t += 8) {
+        const u32x4_t v = src[(size_t)t * 64];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { const uint32_t a = (v[i] >> 8) & 0x7Fu, b = (v[i] >> 24) & 0x7Fu; hi = max(hi, max(a, b)); }
+    }
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, 16, 64));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, 32, 64));
+    if (lane < 16) top[w][lane] = hi;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) hi = max(hi, top[q][lm]);
+    const uint32_t base = hi > 15 ? hi - 15 : 0;
+    if (tid < 16) C[wc_base_off(K, NT) + (size_t)nt * 16 + tid] = (char)base;
+    for (int p = w; p < PT; p += 8) {
+        u32x4_t l; u32x2_t n; uint32_t s = 0, out = 0;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const u32x4_t v = src[(size_t)(2 * p + t) * 64];
+            n[t] = 0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                uint32_t lw = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t x = (v[2 * h + (j >> 1)] >> (16 * (j & 1))) & 0xFFFFu, e = (x >> 8) & 0x7Fu;
+                    const bool in = e == 0 || e > base;              // (e - base <= 15: no exponent is above the largest)
+                    out |= !in;
+                    lw |= (x & 0xFFu) << (8 * j);
+                    n[t] |= (in && e ? e - base : 0u) << (8 * j + 4 * h);
+                    s |= (x >> 15) << (2 * t + h + ((j & 1) << 3) + ((j >> 1) << 2));
+                }
+                l[2 * t + h] = lw;
+            }
+        }
+        char* at = C + ((size_t)nt * PT + p) * WC_PAIR;
+        *(u32x4_t*)(at + lane * 16) = l;
+        *(u32x2_t*)(at + 1024 + lane * 8) = n;
+        *(uint16_t*)(at + 1536 + lane * 2) = (uint16_t)s;
+        const bool any = __ballot(out != 0) != 0;
+        if (lane == 0) C[wc_flag_off(K, NT) + (size_t)nt * PT + p] = (char)any;
+    }
+}
+hipError_t fc_code(const void* W, void* C, int K, int NT, int nt0, int cnt, hipStream_t st) {
+    if (K < 256 || K % 256 || nt0 < 0 || cnt < 1 || nt0 + cnt > NT) return hipErrorInvalidValue;
+    k_code<<<cnt, 512, 0, st>>>((const char*)W, (char*)C, K, NT, nt0);
+    return hipGetLastError();
 }
 hipError_t fc_pack(const void* src, int dt, int rows, int cols, void* dst_base, const FusedMat& fm, int col_off,
                    int mode, hipStream_t st) {
-    size_t n = (size_t)rows * cols;
-    unsigned blocks = (unsigned)((n + 255) / 256);
-    if (dt == FASTCOT_F32) k_pack<FASTCOT_F32><<<blocks, 256, 0, st>>>(src, rows, cols, dst_base, fm, col_off, mode);
-    else k_pack<FASTCOT_BF16><<<blocks, 256, 0, st>>>(src, rows, cols, dst_base, fm, col_off, mode);
+    char* dst = (char*)dst_base + fm.off;
+    if (dt == FASTCOT_F32) {
+        const size_t n = (size_t)rows * cols;
+        k_pack_f32<<<(unsigned)((n + 255) / 256), 256, 0, st>>>((const float*)src, rows, cols, (float*)dst, fm.NP, col_off, mode);
+        return hipGetLastError();
+    }
+    if (rows % 32) return hipErrorInvalidValue;
+    k_pack_bf16<<<dim3((cols + 63) / 64, (rows / 8 + 3) / 4), 256, 0, st>>>((const bf16_t*)src, rows, cols, (bf16_t*)dst, fm.K, col_off, mode);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess && fm.coded ? fc_code(dst, dst + wc_off(fm.K, fm.NP / 16), fm.K, fm.NP / 16, 0, fm.NP / 16, st) : e;
+}
+// The stamp of a packed model: a sum over the tensors packed into it of odd numbers made from the tensor's number and some 4096 of its
+// words, so that a context can see that its coded copies are of other weights: packing anything again changes the stamp, and
+// the same tensors give the same stamp in any order.
+__device__ inline unsigned long long stamp_mix(unsigned long long x) {
+    x = (x ^ (x >> 31)) * 6364136223846793005ull;
+    return (x ^ (x >> 29)) * 2862933555777941757ull;
+}
+__global__ __launch_bounds__(256) void k_stamp(unsigned long long* s, const uint16_t* src, size_t words, uint32_t tag) {
+    __shared__ unsigned long long part[256];
+    unsigned long long h = 0;
+    const size_t step = words > 4096 ? words / 4096 : 1;
+    for (size_t i = threadIdx.x; i * step < words; i += 256) h += stamp_mix(((unsigned long long)i << 32) | src[i * step]);
+    part[threadIdx.x] = h;
+    __syncthreads();
+    if (threadIdx.x) return;
+    for (int q = 1; q < 256; ++q) h += part[q];
+    *s += stamp_mix(h + tag) | 1;
+}
+__global__ void k_stamp_read(const unsigned long long* s, unsigned long long* host) { *host = *s; }
+hipError_t fc_stamp(void* stamp, const void* src, size_t words, uint32_t tag, hipStream_t st) {
+    k_stamp<<<1, 256, 0, st>>>((unsigned long long*)stamp, (const uint16_t*)src, src ? words : 0, tag);
+    return hipGetLastError();
+}
+hipError_t fc_stamp_read(const void* stamp, void* host, hipStream_t st) {
+    k_stamp_read<<<1, 1, 0, st>>>((const unsigned long long*)stamp, (unsigned long long*)host);
     return hipGetLastError();
 }
 

@@ -1,0 +1,134 @@
+"""Coded copies of the weights: the kernels that read them compute with every weight as it was packed.
+
+A row with a single 1 picks one row of W out of the product: every other term is an exact zero, so the logits are W's row itself."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fc():
+    import paper_2311_08263_amd as m
+    return m
+
+
+def special(w, kind, seed):
+    """Weights outside their columns' windows: few (flagged pairs taken one by one), many (whole walks over the plain tiles), columns of
+    zeros, tiny or huge ones, a column whose largest weight leaves all others outside; zeros, which have a code of their own."""
+    import torch
+    g = torch.Generator(device="cuda"); g.manual_seed(seed)
+    d, V = w.shape
+    if kind == "few":
+        for i in range(6):
+            w[(i * 7919 + 5) % d, (i * 104729 + 3) % V] = 2.0 ** -60
+        w[d - 1, V - 1] = -0.0; w[0, 0] = 2.0 ** -100
+    elif kind == "many":
+        w[torch.rand(d, V, generator=g, device="cuda") < 0.5] = 2.0 ** -60
+    elif kind == "zeros":
+        w[torch.rand(d, V, generator=g, device="cuda") < 0.5] = 0.0
+        w[torch.rand(d, V, generator=g, device="cuda") < 0.01] = -0.0
+    elif kind == "columns":
+        w[:, 0] = 0.0; w[:, 15] = 0.0; w[3, 15] = 1.5
+        w[:, 5] *= 2.0 ** -120; w[:, 6] *= 2.0 ** 120; w[:, 7] = -w[:, 7].abs(); w[0, 8] = 2.0 ** 126
+        for c, e in ((9, -29), (10, -30), (11, -31), (12, -32)):  # the last exponents inside the window and the first ones outside
+            w[:, c] = 2.0 ** e; w[1, c] = 1.9921875
+    return w
+
+
+@pytest.mark.parametrize("kind", ["none", "few", "many", "zeros", "columns"])
+@pytest.mark.parametrize("M,d,V", [(16, 256, 16), (16, 512, 592), (5, 768, 4112), (32, 1024, 2000), (17, 256, 8208)])
+def test_every_weight_comes_out_as_it_went_in(fc, kind, M, d, V):
+    """One to eight n-tiles per workgroup, waves of no, one and two pairs of k-tiles, one and two row tiles."""
+    import torch
+    say(f"coded weights {kind} M={M} d={d} V={V}")
+    g = torch.Generator(device="cuda"); g.manual_seed(7)
+    w = special((0.02 * torch.randn(d, V, generator=g, device="cuda")).bfloat16(), kind, 11)
+    packed = fc.lmhead_pack(w)
+    scratch = torch.zeros(fc.lib().fastcot_lmhead_scratch_bytes(M, d, V), dtype=torch.uint8, device="cuda")
+    for k0 in range(0, d, M):
+        act = torch.zeros(M, d, device="cuda")
+        rows = torch.arange(k0, min(k0 + M, d), device="cuda")
+        act[torch.arange(len(rows), device="cuda"), rows] = 1.0
+        _, _, logits = fc.lmhead_argmax(act, packed, V, True, scratch)
+        assert torch.equal(logits[:len(rows)], w[rows].float()), k0
+
+
+def tensors(shape, kind, seed):
+    import torch
+    L, d, H, Hkv, F, V = shape
+    g = torch.Generator(device="cuda"); g.manual_seed(seed)
+    def t(r, c, s): return (s * torch.randn(r, c, generator=g, device="cuda")).bfloat16()
+    emb = t(V, d, 1.0)
+    yield "emb", 0, emb
+    yield "wlm", 0, special(t(d, V, 0.02), kind, seed)
+    for l in range(L):
+        for n, r, c in (("wq", d, H * 128), ("wk", d, Hkv * 128), ("wv", d, Hkv * 128), ("wo", H * 128, d), ("wg", d, F), ("wu", d, F), ("wd", F, d)):
+            yield n, l, special(t(r, c, 0.02 if n not in ("wo", "wd") else 0.01), kind, seed + l)
+
+
+def pack(fc, cfg, items, packed=None):
+    import torch
+    L, st = fc.lib(), torch.cuda.current_stream().cuda_stream
+    if packed is None:
+        packed = torch.zeros(L.fastcot_weight_bytes(ctypes.byref(cfg)), dtype=torch.uint8, device="cuda")
+    for n, l, t in items:
+        assert L.fastcot_pack_tensor(ctypes.byref(cfg), fc.binding.T[n], l, t.data_ptr(), packed.data_ptr(), st) == 0
+    for n, l in [("gf", 0)] + [(g, l) for g in ("g1", "g2") for l in range(cfg.n_layers)]:
+        assert L.fastcot_pack_tensor(ctypes.byref(cfg), fc.binding.T[n], l, None, packed.data_ptr(), st) == 0
+    torch.cuda.synchronize()
+    return packed
+
+
+def first_logits(ctx, prompts, buf, rows):
+    logits = ctx.debug_logits(True)
+    ctx.prefill(prompts, [prompts.shape[1]] * prompts.shape[0], buf)
+    ctx.step()
+    return logits[:rows].clone()
+
+
+@pytest.mark.parametrize("kind", ["none", "few", "many", "zeros"])
+@pytest.mark.parametrize("B,W", [(1, 1), (1, 16), (2, 12)])
+def test_steps_on_coded_weights(fc, kind, B, W):
+    """Every product of a step (K slices, flagged pairs, plain walks) against the plain kernels on the plain tiles: fp32 arithmetic there,
+    activations of 17 bits here, so logits that differ by a few 2^-17 of their size per product (nine in a row; 1e-4 is ten times that)."""
+    import torch
+    say(f"step on coded weights {kind} B={B} W={W}")
+    shape = (2, 4096, 32, 8, 8192, 1008) if W == 16 else (2, 512, 4, 2, 768, 1008)
+    L, d, H, Hkv, F, V = shape
+    cfg = fc.Config(L, d, H, Hkv, 128, F, V, 1e-5, 1e4, 1, B, 128, W)
+    packed = pack(fc, cfg, tensors(shape, kind, 3))
+    r = np.random.RandomState(5)
+    prompts, buf = r.randint(0, V, (B, 21)).astype(np.int32), r.randint(0, V, (B, 3 * W)).astype(np.int32)
+    out = []
+    for plain in (0, 1):
+        ctx = fc.Context(cfg, packed)
+        if plain:
+            ctx.set_option(fc.binding.OPT_PLAIN_KERNELS, 1)
+        out.append(first_logits(ctx, prompts, buf, B * W))
+        ctx.close() if hasattr(ctx, "close") else None
+    a, b = out[0].double(), out[1].double()
+    assert float(torch.linalg.norm(a - b) / torch.linalg.norm(b)) < 1e-4
+
+
+def test_weights_packed_again_are_coded_again(fc):
+    """A prefill after other weights were packed computes with those, as a context that never saw the first ones does."""
+    import torch
+    say("weights packed again")
+    shape = (2, 512, 4, 2, 768, 1008)
+    L, d, H, Hkv, F, V = shape
+    cfg = fc.Config(L, d, H, Hkv, 128, F, V, 1e-5, 1e4, 1, 1, 128, 8)
+    r = np.random.RandomState(5)
+    prompts, buf = r.randint(0, V, (1, 21)).astype(np.int32), r.randint(0, V, (1, 24)).astype(np.int32)
+    packed = pack(fc, cfg, tensors(shape, "none", 3))
+    ctx = fc.Context(cfg, packed)
+    first = first_logits(ctx, prompts, buf, 8)
+    assert torch.equal(first, first_logits(ctx, prompts, buf, 8))
+    pack(fc, cfg, tensors(shape, "few", 9), packed)
+    again = first_logits(ctx, prompts, buf, 8)
+    fresh = first_logits(fc.Context(cfg, pack(fc, cfg, tensors(shape, "few", 9))), prompts, buf, 8)
+    assert not torch.equal(first, again) and torch.equal(again, fresh)
