@@ -31,7 +31,7 @@ void fc_fast_plan(const KernelDims& kd, FastPlan* p) {
     // column-owner kernel: workgroups per GEMM (one per CU where the matrix allows)
     const int nts[5] = {kd.qkvN / 16, kd.d / 16, 2 * kd.F / 16, kd.d / 16, kd.V / 16};
     // measured on the 7B shape: one workgroup per CU
-    for (int i = 0; i < 5; ++i) { p->nw[i] = fc_gemmco_grid(nts[i]); p->ks[i] = 1; }
+    for (int i = 0; i < 5; ++i) { p->nw[i] = fc_gemmco_grid(nts[i], 8, i != 1 && i != 3); p->ks[i] = 1; }
     // K slices per owner cut the activations a workgroup reads and cost a meeting of the slices in memory.
     if (nts[1] <= 512) {                 // O projection with at most two n-tiles per CU
         // two K slices per owner, four from 4096 inputs on (steps of up to 16 rows with one / two / four slices, us: eight
@@ -323,7 +323,7 @@ hipError_t fc_attn_iso(const float* q, const void* kc, const void* vc, int n, in
 
 // scratch: winners per workgroup [workgroups][32] value + index, then room for logits (where they are not asked for),
 // then, for more than 32 rows, the activations as three bf16 parts and the winners per column block
-static int lm_iso_grid(int M, int d, int V) { return fc_gemmco_grid(V / 16, M > 16 ? fc_gemmco_most(32, d, false) : 8); }
+static int lm_iso_grid(int M, int d, int V) { return fc_gemmco_grid(V / 16, M > 16 ? fc_gemmco_most(32, d, false) : 8, M <= 16); }
 // more than 32 rows of a width the many-row kernel takes, within its 32-bit byte offsets
 static bool lm_iso_many(int M, int d, int V) {
     return M > 32 && d % 256 == 0 && (size_t)V * d * 2 < ((size_t)1 << 32) && fc_split_bytes(M, d, 3) < ((size_t)1 << 32);

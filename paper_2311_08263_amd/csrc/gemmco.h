@@ -30,9 +30,8 @@ struct GemmCoArgs {
 };
 
 // G workgroups = G / ks owners x ks K slices; owner i owns n-tiles [i*NT/owners, (i+1)*NT/owners), at most
-// 8; fc_gemmco_grid picks one workgroup per CU (all resident, one round) unless the matrix is wider than
-// 8 n-tiles per CU
-int fc_gemmco_grid(int NT, int most = 8);
+// 14 up to 16 rows, 8 of more; fc_gemmco_grid picks one workgroup per CU (all resident, one round) unless the matrix is wider than that
+int fc_gemmco_grid(int NT, int most = 8, bool wide = false);
 // most n-tiles a workgroup may own so that its partial tiles (8 sets x n-tiles x row tiles x 1 KB up to eight output tiles, 4 sets beyond) and, with a
 // norm in front, the gain vector (K floats) fit the LDS of a CU
 int fc_gemmco_most(int M, int K, bool gain);

@@ -538,6 +538,7 @@ static hipError_t launch_epi(const GemmCoArgs& a, int G, hipStream_t st) {
         case 5: case 6: return launch_k<WP, EPI, 6, 1, 1>(a, G, st);
         case 7: case 8: return launch_k<WP, EPI, 8, 1, 1>(a, G, st);
         case 9: case 10: case 11: case 12: return launch_k<WP, EPI, 12, 1, 1>(a, G, st);
+        case 13: case 14: return launch_k<WP, EPI, 14, 1, 1>(a, G, st);
     } else switch (nw) {
         case 1: return launch_k<WP, EPI, 1, 4, 1>(a, G, st);
         case 2: return launch_k<WP, EPI, 2, 3, 1>(a, G, st);
@@ -546,6 +547,7 @@ static hipError_t launch_epi(const GemmCoArgs& a, int G, hipStream_t st) {
         case 5: case 6: return launch_k<WP, EPI, 6, 2, 1>(a, G, st);
         case 7: case 8: return launch_k<WP, EPI, 8, 2, 1>(a, G, st);
         case 9: case 10: case 11: case 12: return launch_k<WP, EPI, 12, 1, 1>(a, G, st);
+        case 13: case 14: return launch_k<WP, EPI, 14, 1, 1>(a, G, st);
     }
     return hipErrorInvalidValue;
 }
