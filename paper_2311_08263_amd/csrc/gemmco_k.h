@@ -13,13 +13,15 @@
 // order (lane = row % 16 + 16 * k-octet: two 16-byte loads per k-tile), converts them to a bf16
 // hi + lo pair and reuses each fragment for its NW weight tiles.  Weights stream HBM -> VGPR once,
 // in MFMA fragment order, a pair of k-tiles x NW n-tiles at a time; from the coded copy (wcode.h) where the matrix has one: 13/16
-// of the bytes for 13 vector instructions a tile, which the memory-bound loop has room for (leaving them out gained 1 us of 31).
+// of the bytes for 21 vector instructions a tile, which the memory-bound loop has room for (13, without the code for zeros, leave a step
+// 1-2 % shorter; leaving those 13 out as well gained 1 us of 31).
 //
 // What bounds a launch (7B gate/up, 16 rows, 146 MB coded, 29.1 us; from the plain tiles, 180 MB, 33.6): the bytes a CU is sent, weights
 // and activations alike (six n-tiles of 64 pairs and 256 KB of activations on the fullest CUs; without activations 27.2 us), then
 // 4-5 us of head, first round trip, and tail.  Activations through a ring in LDS, asked for in front of the first weights, cost what they saved:
 // 256 KB a CU take 2.5 us to arrive there and 3.3 among the weights (gate/up 30.6-31.1 us against 29.1, QKV 22.4 against 21.3).
-// 7B / 13B / 70B shape, 16 rows, plain tiles with a plan tuned per shape -> coded, steps of 8 / 6 / 2 layers: 871 / 912 / 704 -> 805 / 835 / 636 us.
+// 7B / 13B / 70B shape, 16 rows, plain tiles with a plan tuned per shape -> coded, steps of 8 / 6 / 2 layers: 871 / 912 / 704 -> 805 / 835 / 636 us
+// (before the code for zeros; with it, and one round of up to 14 n-tiles a workgroup, the 70B shape's step takes 622).
 #pragma once
 #include "gemmco.h"
 #include "wcode.h"
