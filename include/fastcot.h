@@ -71,7 +71,7 @@ typedef struct fastcot_ctx fastcot_ctx;
  * For bf16 models of the matrix-core shapes the workspace also holds a copy of the weights in 13 bits each, from which passes of up to
  * 32 rows read them (7B shape: 10 GiB; of models whose weights and copies would pass 208 GiB, the matrices that fit): a context's first
  * fastcot_prefill makes it, and a later one makes it again where fastcot_pack_tensor or fastcot_pack_weights wrote to the packed
- * weights in between. */
+ * weights in between, or a whole packed buffer was copied over them; until then passes read the packed weights themselves. */
 size_t fastcot_weight_bytes(const fastcot_config* cfg);
 size_t fastcot_workspace_bytes(const fastcot_config* cfg);
 
@@ -96,8 +96,9 @@ size_t fastcot_canonical_offset(const fastcot_config* cfg, int32_t tensor, int32
 int fastcot_pack_weights(const fastcot_config* cfg, const void* d_canonical, void* d_packed, void* hip_stream);
 
 /* Creates a context over packed weights and a zero-initialised-or-not workspace (the library
- * initialises what it needs, synchronously).  Both device buffers must stay alive and untouched
- * by the caller until fastcot_free. */
+ * initialises what it needs, synchronously).  Both device buffers must stay alive until fastcot_free and are written by the library alone
+ * meanwhile: weights may be packed again (no call on the context in progress), the whole packed buffer may be replaced by a copy of another one of
+ * the same configuration; single bytes of it changed in another way may go unnoticed. */
 int fastcot_init(const fastcot_config* cfg, const void* d_packed, void* d_workspace, size_t workspace_bytes,
                  void* hip_stream, fastcot_ctx** out);
 void fastcot_free(fastcot_ctx* ctx);

@@ -5,7 +5,10 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <time.h>
+#include <unistd.h>
 #include <algorithm>
+#include <atomic>
 #include <vector>
 #include "kernels.h"
 #include "fast.h"
@@ -45,8 +48,6 @@ struct fastcot_ctx {
     std::vector<hipEvent_t> step_ev;
     std::vector<float> step_ms;
     int32_t* pinned;     // small pinned host block for polling
-    int coded;           // the coded copies of the weights are there, of the weights with this stamp
-    uint64_t coded_stamp;
     char err[512];
 };
 
@@ -179,6 +180,7 @@ int fc_build_maps(const fastcot_config* c, ModelMap* mm, WorkspaceMap* wm, Kerne
         // matrices in the order of what a step spends on them.
         const FusedMat* mats[5] = {&m.qkv, &m.o, &m.gu, &m.down, &m.lm};
         const int order[5] = {2, 3, 4, 0, 1};
+        wm->code_record = take(8);
         for (int i = 0; i < 5; ++i) wm->code[i] = wm->code_stride[i] = 0;
         for (int i : order) {
             const size_t each = FC_ALIGN(wc_bytes(mats[i]->K, mats[i]->NP / 16)), all = each * (i == 4 ? 1 : (size_t)k.L);
@@ -213,6 +215,20 @@ static size_t canon_elems(const KernelDims& kd, int t) {
     }
     return 0;
 }
+// a number that no other packing call adds to a stamp, of this process or of another one (packed weights may be copied between buffers
+// and kept in files, and the stamp with them)
+static uint64_t pack_nonce() {
+    static std::atomic<uint64_t> calls{0};
+    static const uint64_t seed = [] {
+        timespec t = {0, 0};
+        (void)clock_gettime(CLOCK_REALTIME, &t);
+        return ((uint64_t)t.tv_sec * 1000000000ull + (uint64_t)t.tv_nsec) ^ ((uint64_t)getpid() << 40);
+    }();
+    uint64_t x = seed + calls.fetch_add(1) * 0x9E3779B97F4A7C15ull;       // (the mixing steps are splitmix64's)
+    x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
+    x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+    return (x ^ (x >> 31)) | 1;
+}
 extern "C" int fastcot_pack_tensor(const fastcot_config* cfg, int32_t tensor, int32_t layer, const void* src,
                                    void* d_packed, void* hip_stream) {
     ModelMap mm; KernelDims kd;
@@ -245,7 +261,8 @@ extern "C" int fastcot_pack_tensor(const fastcot_config* cfg, int32_t tensor, in
         case FASTCOT_T_WD: e = fc_pack(src, dt, kd.F, d, lbase, mm.down, 0, 0, st); break;
         default: return fail(nullptr, FASTCOT_EINVAL, "unknown tensor id%s");
     }
-    if (e == hipSuccess) e = fc_stamp(base + mm.stamp_off, gain ? nullptr : src, canon_elems(kd, tensor) * (size_t)kd.esz / 2, (uint32_t)(tensor + 16 * (per_layer ? layer + 1 : 0)), st);
+    // matrices of models that can have coded copies
+    if (e == hipSuccess && !gain && tensor != FASTCOT_T_EMB && fc_fast_supported(kd, 1)) e = fc_stamp(base + mm.stamp_off, pack_nonce(), st);
     if (e != hipSuccess) return fail(nullptr, FASTCOT_EHIP, "pack launch failed: %s", hipGetErrorString(e));
     return 0;
 }
@@ -306,7 +323,7 @@ extern "C" int fastcot_init(const fastcot_config* cfg, const void* d_packed, voi
     c->opt_packed = 1; c->rows_dirty = 1; c->rows_step = 0;
     c->opt_plain = (cfg->dtype == FASTCOT_F32); c->opt_graph = 1; c->dbg_stop = -1; c->dbg_logits = nullptr;
     c->graph_exec = nullptr; c->graph = nullptr; c->graph_valid = 0; c->prof_on = 0; c->prof_used = 0;
-    c->pinned = nullptr; c->err[0] = 0; c->coded = 0; c->coded_stamp = 0;
+    c->pinned = nullptr; c->err[0] = 0;
     fc_fast_plan(c->kd, &c->plan);
     // rotary table: cos/sin of pos * base^(-2i/Dh), evaluated in double on the host
     const int half = c->kd.Dh / 2;
@@ -324,6 +341,7 @@ extern "C" int fastcot_init(const fastcot_config* cfg, const void* d_packed, voi
     INITCHK(hipMemsetAsync(c->ws + c->wm.state, 0, (size_t)c->wm.st.words * 4, c->st));
     INITCHK(hipMemsetAsync(c->ws + c->wm.gemm_cnt, 0, FC_MAX_COUNTERS * 4, c->st));
     INITCHK(hipMemsetAsync(c->ws + c->wm.attn_cnt, 0, FC_MAX_COUNTERS * 4, c->st));
+    INITCHK(fc_stamp_keep(c->weights + c->mm.stamp_off, c->ws + c->wm.code_record, 0, c->st));      // no coded copies yet
     INITCHK(hipMemsetAsync(c->ws + c->wm.kc, 0, c->wm.rope_cos - c->wm.kc, c->st));   // whole KV cache
     INITCHK(hipStreamSynchronize(c->st));
 #undef INITCHK
@@ -575,21 +593,20 @@ static int enqueue_step(fastcot_ctx* c) {
 }
 
 // ------------------------------------------------------------------ prefill
-// Passes of R rows per sequence over prompt tokens 0 .. maxlen-2 of the first B slots (the last prompt token
-// becomes slot 0 of the first window).  Enqueues only.  (The plain path took a window's rows per pass: a prompt of 32
-// tokens of the 256-wide model with window 8 was four passes of eleven launches, 379 us; one
-// pass 163 us.)
-// The coded copies of the weights (wcode.h), made by a context's first prefill and again by one that finds other weights packed since:
-// 7B shape, 6.5 GB of tiles a millisecond.  A look at the stamp takes about 10 us.
+// The coded copies of the weights (wcode.h), made by a context's first prefill and again by one that finds other weights packed since.
+// A look at stamp and record takes about 10 us.  (Steps between the packing and that prefill read the plain tiles: the
+// kernels compare stamp and record themselves.)
 static int code_weights(fastcot_ctx* c) {
     bool any = false;
     for (int i = 0; i < 5; ++i) any = any || c->wm.code[i];
     if (!any) return 0;
-    HIPCHK(c, fc_stamp_read(c->weights + c->mm.stamp_off, c->pinned, c->st));
+    const char* stamp = c->weights + c->mm.stamp_off;
+    char* record = c->ws + c->wm.code_record;
+    HIPCHK(c, fc_stamp_read(stamp, record, c->pinned, c->st));
     HIPCHK(c, hipStreamSynchronize(c->st));
-    const uint64_t stamp = *(const uint64_t*)c->pinned;
-    if (c->coded && c->coded_stamp == stamp) return 0;
-    c->coded = 0;
+    const uint64_t* seen = (const uint64_t*)c->pinned;
+    if (seen[0] == seen[1]) return 0;
+    HIPCHK(c, fc_stamp_keep(stamp, record, 0, c->st));
     const FusedMat* mats[5] = {&c->mm.qkv, &c->mm.o, &c->mm.gu, &c->mm.down, &c->mm.lm};
     for (int i = 0; i < 5; ++i) {
         if (!c->wm.code[i]) continue;
@@ -598,10 +615,14 @@ static int code_weights(fastcot_ctx* c) {
             HIPCHK(c, fc_code(base + mats[i]->off, c->ws + c->wm.code[i] + (size_t)l * c->wm.code_stride[i], mats[i]->K, mats[i]->NP / 16, 0, mats[i]->NP / 16, c->st));
         }
     }
-    c->coded = 1; c->coded_stamp = stamp;
+    HIPCHK(c, fc_stamp_keep(stamp, record, 1, c->st));
     return 0;
 }
 
+// Passes of R rows per sequence over prompt tokens 0 .. maxlen-2 of the first B slots (the last prompt token
+// becomes slot 0 of the first window).  Enqueues only.  (The plain path took a window's rows per pass: a prompt of 32
+// tokens of the 256-wide model with window 8 was four passes of eleven launches, 379 us; one
+// pass 163 us.)
 static int prefill_passes(fastcot_ctx* c, int B, int maxlen) {
     const KernelDims& kd = c->kd; const StateMap& sm = c->wm.st;
     int32_t* stp = state_ptr(c);

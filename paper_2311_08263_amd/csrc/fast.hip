@@ -166,6 +166,7 @@ hipError_t fc_fast_forward(const FastArgs& a) {
     co.M = M; co.eps = kd.eps; co.n_state = g.n_state; co.cosT = g.cosT; co.sinT = g.sinT; co.kc = g.kc; co.vc = g.vc;
     co.H = kd.H; co.Hkv = kd.Hkv; co.B = kd.B; co.S = kd.S; co.Wn = kd.W; co.kvp = kd.kvp; co.kvq = kd.kvq;
     co.amax_val = g.amax_val; co.single_buffer = 2; co.rm = a.rm;
+    co.stamp = (const uint64_t*)(wt + mm.stamp_off); co.record = (const uint64_t*)(ws + wm.code_record);
     Gemm256Args big; memset(&big, 0, sizeof(big));
     big.M = M; big.n_state = g.n_state; big.cosT = g.cosT; big.sinT = g.sinT; big.kc = g.kc; big.vc = g.vc;
     big.H = kd.H; big.Hkv = kd.Hkv; big.B = kd.B; big.S = kd.S; big.Wn = kd.W; big.kvp = kd.kvp; big.kvq = kd.kvq;
@@ -192,7 +193,8 @@ hipError_t fc_fast_forward(const FastArgs& a) {
         const int nw = M <= 16 ? a.plan->nw[gi] : (M <= 32 ? a.plan->nw2[gi] : 0);
         const int ksl = M <= 16 ? a.plan->ks[gi] : a.plan->ks2[gi];
         if (nw > 0) {
-            co.W = (const bf16_t*)W; co.C = wm.code[gi] ? ws + wm.code[gi] + (size_t)g.layer * wm.code_stride[gi] : nullptr; co.K = K; co.NT = N / 16; co.X = X; co.ldx = ldx; co.gain = gain; co.out = out; co.ldo = ldo;
+            co.W = (const bf16_t*)W; co.K = K; co.NT = N / 16; co.X = X; co.ldx = ldx; co.gain = gain; co.out = out; co.ldo = ldo;
+            co.C = wm.code[gi] ? ws + wm.code[gi] + (size_t)g.layer * wm.code_stride[gi] : nullptr;
             co.layer = g.layer; co.ks = epi != EPI_LMHEAD ? ksl : 1; co.hi_only = (kd.actq >> gi) & 1;
             co.single_buffer = a.plan->co_single == 2 ? a.plan->co_sb[M > 16][gi] : a.plan->co_single;
             co.rotate = a.plan->co_rot[M > 16][gi];
@@ -379,6 +381,7 @@ hipError_t fc_lmhead_iso(const float* act, const void* packed, int M, int d, int
     GemmCoArgs co; memset(&co, 0, sizeof(co));
     const int nwg = lm_iso_grid(M, d, V), stride = M > 16 ? 32 : 16;
     co.W = (const bf16_t*)packed; co.C = (const char*)packed + wc_off(d, V / 16); co.K = d; co.NT = V / 16; co.X = act; co.ldx = d; co.M = M; co.out = logits; co.ldo = V;
+    co.stamp = co.record = (const uint64_t*)packed;        // (the copy was packed with the tiles)
     co.single_buffer = 2;
     co.amax_val = (float*)sc;
     co.amax_idx = (int32_t*)(co.amax_val + (size_t)nwg * stride);

@@ -7,6 +7,8 @@ enum { EPI_RESID = 0, EPI_SWIGLU = 1, EPI_QKV = 2, EPI_LMHEAD = 3 };
 struct GemmCoArgs {
     const bf16_t* W;       // fused matrix in fragment order
     const char* C;         // its coded copy (wcode.h), or NULL
+    const uint64_t* stamp;     // with a copy: stamp of the packed weights and record of the copies; where they differ, weights were packed after
+    const uint64_t* record;    // the copies were made, and the plain tiles are read
     int32_t K, NT;         // inputs (multiple of 256), n-tiles
     const float* X;        // activations fp32 [M][ldx]
     int32_t ldx, M;        // M <= 32 rows

@@ -83,7 +83,9 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
     auto tile_no = [&](int j) { return nt0 + j < nt_last ? nt0 + j : nt_last; };
     uint32_t base4[NW], flag[NW];
     const uint8_t* flags = (const uint8_t*)a.C + wc_flag_off(a.K, a.NT);
+    u32x2_t mark;                                        // lane 0: stamp, lane 1: record (a vector load, in the row of the flags: scalar ones cost 0.15 us a launch)
     if constexpr (CODED) {
+        mark = *(const u32x2_t*)(lane & 1 ? a.record : a.stamp);
         const uint8_t* bases = (const uint8_t*)a.C + wc_base_off(a.K, a.NT);
         const int p = p_begin + lane < PT ? p_begin + lane : PT - 1;
 #pragma unroll
@@ -242,8 +244,9 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
                 for (int p = p_begin + 64 + lane; p < p_begin + n; p += 64) any |= flags[(size_t)tile_no(j) * PT + p];
         flagged = __ballot(any != 0);
         // Flagged pairs are left out of the walk over the copy and taken from the plain tiles behind it, one after the other;
-        // where a wave has more than two of them, it walks the plain tiles instead.
-        if (__builtin_expect(__popcll(flagged) > 2, 0)) {
+        // where a wave has more than two of them, or the copy is not of these weights, it walks the plain tiles instead.
+        const uint32_t stale = (__builtin_amdgcn_readlane(mark[0], 0) ^ __builtin_amdgcn_readlane(mark[0], 1)) | (__builtin_amdgcn_readlane(mark[1], 0) ^ __builtin_amdgcn_readlane(mark[1], 1));
+        if (__builtin_expect(stale || __popcll(flagged) > 2, 0)) {
             constexpr int DP = NW * MT * D <= 12 ? D : 1;
             Pair<WPlain, NW, MT> bp[DP];
 #pragma unroll

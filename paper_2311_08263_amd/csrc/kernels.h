@@ -58,9 +58,11 @@ hipError_t fc_pack(const void* src, int dt, int rows, int cols, void* dst_base, 
                    int mode /*0 natural, 1 gate, 2 up, 3 + Dh: q/k heads of Dh*/, hipStream_t st);
 // the coded copy at C of n-tiles nt0 .. nt0 + cnt - 1 of a matrix of K inputs and NT n-tiles
 hipError_t fc_code(const void* W, void* C, int K, int NT, int nt0, int cnt, hipStream_t st);
-// a tensor of `words` 16-bit words (src may be NULL) joins a packed model's stamp; the stamp to host memory
-hipError_t fc_stamp(void* stamp, const void* src, size_t words, uint32_t tag, hipStream_t st);
-hipError_t fc_stamp_read(const void* stamp, void* host, hipStream_t st);
+// a packing call joins a packed model's stamp; the record of coded copies takes the stamp over (made = 0: there are no copies); stamp and
+// record (a 64-bit word each) to host memory
+hipError_t fc_stamp(void* stamp, uint64_t nonce, hipStream_t st);
+hipError_t fc_stamp_keep(const void* stamp, void* record, int made, hipStream_t st);
+hipError_t fc_stamp_read(const void* stamp, const void* record, void* host, hipStream_t st);
 hipError_t fc_fill_f32(float* dst, size_t n, float v, hipStream_t st);
 hipError_t fc_copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t st);
 hipError_t fc_kv_scatter(const void* k, const void* v, int S_in, int Hkv, int Dh, int S, int dt, void* kc, void* vc,

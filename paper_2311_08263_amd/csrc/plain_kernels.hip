@@ -612,31 +612,22 @@ hipError_t fc_pack(const void* src, int dt, int rows, int cols, void* dst_base, 
     const hipError_t e = hipGetLastError();
     return e == hipSuccess && fm.coded ? fc_code(dst, dst + wc_off(fm.K, fm.NP / 16), fm.K, fm.NP / 16, 0, fm.NP / 16, st) : e;
 }
-// The stamp of a packed model: a sum over the tensors packed into it of odd numbers made from the tensor's number and some 4096 of its
-// words, so that a context can see that its coded copies are of other weights: packing anything again changes the stamp, and
-// the same tensors give the same stamp in any order.
-__device__ inline unsigned long long stamp_mix(unsigned long long x) {
-    x = (x ^ (x >> 31)) * 6364136223846793005ull;
-    return (x ^ (x >> 29)) * 2862933555777941757ull;
-}
-__global__ __launch_bounds__(256) void k_stamp(unsigned long long* s, const uint16_t* src, size_t words, uint32_t tag) {
-    __shared__ unsigned long long part[256];
-    unsigned long long h = 0;
-    const size_t step = words > 4096 ? words / 4096 : 1;
-    for (size_t i = threadIdx.x; i * step < words; i += 256) h += stamp_mix(((unsigned long long)i << 32) | src[i * step]);
-    part[threadIdx.x] = h;
-    __syncthreads();
-    if (threadIdx.x) return;
-    for (int q = 1; q < 256; ++q) h += part[q];
-    *s += stamp_mix(h + tag) | 1;
-}
-__global__ void k_stamp_read(const unsigned long long* s, unsigned long long* host) { *host = *s; }
-hipError_t fc_stamp(void* stamp, const void* src, size_t words, uint32_t tag, hipStream_t st) {
-    k_stamp<<<1, 256, 0, st>>>((unsigned long long*)stamp, (const uint16_t*)src, src ? words : 0, tag);
+// The stamp of a packed model: every packing call adds a number of its own, so that copies made of the weights before can be told from
+// copies of the weights that are there.  (Tensors may be packed on several streams: the sum is atomic.)
+__global__ void k_stamp(unsigned long long* s, unsigned long long nonce) { atomicAdd(s, nonce); }
+// The record of a set of coded copies: the stamp of the weights they were made from, its complement while there are none.
+__global__ void k_stamp_keep(const unsigned long long* s, unsigned long long* record, int made) { *record = made ? *s : ~*s; }
+__global__ void k_stamp_read(const unsigned long long* s, const unsigned long long* record, unsigned long long* host) { host[0] = *s; host[1] = *record; }
+hipError_t fc_stamp(void* stamp, uint64_t nonce, hipStream_t st) {
+    k_stamp<<<1, 1, 0, st>>>((unsigned long long*)stamp, nonce);
     return hipGetLastError();
 }
-hipError_t fc_stamp_read(const void* stamp, void* host, hipStream_t st) {
-    k_stamp_read<<<1, 1, 0, st>>>((const unsigned long long*)stamp, (unsigned long long*)host);
+hipError_t fc_stamp_keep(const void* stamp, void* record, int made, hipStream_t st) {
+    k_stamp_keep<<<1, 1, 0, st>>>((const unsigned long long*)stamp, (unsigned long long*)record, made);
+    return hipGetLastError();
+}
+hipError_t fc_stamp_read(const void* stamp, const void* record, void* host, hipStream_t st) {
+    k_stamp_read<<<1, 1, 0, st>>>((const unsigned long long*)stamp, (const unsigned long long*)record, (unsigned long long*)host);
     return hipGetLastError();
 }
 

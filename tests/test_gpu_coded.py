@@ -132,3 +132,89 @@ def test_weights_packed_again_are_coded_again(fc):
     again = first_logits(ctx, prompts, buf, 8)
     fresh = first_logits(fc.Context(cfg, pack(fc, cfg, tensors(shape, "few", 9))), prompts, buf, 8)
     assert not torch.equal(first, again) and torch.equal(again, fresh)
+
+
+def _unsampled_change(items):
+    """The same tensors with weights of wo and the LM head changed in all columns but the first."""
+    for n, l, t in items:
+        if n in ("wo", "wlm"):
+            t = t.clone(); t[:, 1:] *= -1
+        yield n, l, t
+
+
+@pytest.mark.parametrize("how", ["packed over zeros", "copied over"])
+def test_every_new_set_of_weights_is_noticed(fc, how):
+    """Other weights in the same buffer, packed after clearing it or copied over as a whole packed image: the next prefill and its
+    step are those of a context that never saw the first ones, whichever weights differ."""
+    import torch
+    say(f"other weights {how}")
+    shape = (1, 4096, 32, 8, 512, 1008)
+    L, d, H, Hkv, F, V = shape
+    cfg = fc.Config(L, d, H, Hkv, 128, F, V, 1e-5, 1e4, 1, 1, 128, 8)
+    r = np.random.RandomState(5)
+    prompts, buf = r.randint(0, V, (1, 21)).astype(np.int32), r.randint(0, V, (1, 24)).astype(np.int32)
+    packed, other = pack(fc, cfg, tensors(shape, "none", 3)), pack(fc, cfg, _unsampled_change(tensors(shape, "none", 3)))
+    ctx = fc.Context(cfg, packed)
+    first = first_logits(ctx, prompts, buf, 8)
+    if how == "copied over":
+        packed.copy_(other)
+        torch.cuda.synchronize()
+    else:
+        packed.zero_()
+        torch.cuda.synchronize()
+        pack(fc, cfg, _unsampled_change(tensors(shape, "none", 3)), packed)
+    again = first_logits(ctx, prompts, buf, 8)
+    assert torch.equal(again, first_logits(fc.Context(cfg, other), prompts, buf, 8)) and not torch.equal(first, again)
+
+
+@pytest.mark.parametrize("graph", [0, 1])
+def test_steps_between_packing_and_prefill(fc, graph):
+    """A step after other weights were packed computes with those, also as a replay captured before; against the plain kernels on the same
+    cache (nine products in a row, 1e-4 as above)."""
+    import torch
+    say(f"weights packed between steps graph={graph}")
+    shape = (2, 512, 4, 2, 768, 1008)
+    L, d, H, Hkv, F, V = shape
+    cfg = fc.Config(L, d, H, Hkv, 128, F, V, 1e-5, 1e4, 1, 1, 128, 8)
+    r = np.random.RandomState(5)
+    prompts, buf = r.randint(0, V, (1, 21)).astype(np.int32), r.randint(0, V, (1, 64)).astype(np.int32)
+    packed = pack(fc, cfg, tensors(shape, "none", 3))
+    ctx = fc.Context(cfg, packed)
+    ctx.set_option(fc.binding.OPT_GRAPH, graph)
+    logits = ctx.debug_logits(True)
+    ctx.prefill(prompts, [21], buf)
+    ctx.step()
+    pack(fc, cfg, tensors(shape, "few", 9), packed)
+    n, win = ctx.state()["n"][0], ctx.state()["window"]
+    ctx.step()
+    got = logits[:8].clone()
+    plain = fc.Context(cfg, pack(fc, cfg, tensors(shape, "none", 3)))
+    plain.set_option(fc.binding.OPT_PLAIN_KERNELS, 1)
+    ref = plain.debug_logits(True)
+    plain.prefill(prompts, [21], buf)
+    plain.step()
+    assert plain.state()["n"][0] == n and (plain.state()["window"] == win).all()
+    pack(fc, cfg, tensors(shape, "few", 9), plain.packed)
+    plain.step()
+    a, b = got.double(), ref[:8].double()
+    assert float(torch.linalg.norm(a - b) / torch.linalg.norm(b)) < 1e-4
+
+
+def test_contexts_that_share_a_workspace_in_turn(fc):
+    """Two contexts of one configuration over different weights, one workspace, used one after the other, each from its own prefill on."""
+    import ctypes as ct
+    import torch
+    say("shared workspace")
+    shape = (2, 512, 4, 2, 768, 1008)
+    L, d, H, Hkv, F, V = shape
+    cfg = fc.Config(L, d, H, Hkv, 128, F, V, 1e-5, 1e4, 1, 1, 128, 8)
+    r = np.random.RandomState(5)
+    prompts, buf = r.randint(0, V, (1, 21)).astype(np.int32), r.randint(0, V, (1, 24)).astype(np.int32)
+    a, b = fc.Context(cfg, pack(fc, cfg, tensors(shape, "none", 3))), fc.Context(cfg, pack(fc, cfg, tensors(shape, "none", 4)))
+    want = [first_logits(c, prompts, buf, 8) for c in (a, b)]
+    lib, h = fc.lib(), ct.c_void_p()
+    assert lib.fastcot_init(ct.byref(cfg), b.packed.data_ptr(), a.workspace.data_ptr(), a.workspace.numel(), b.stream.cuda_stream, ct.byref(h)) == 0
+    lib.fastcot_free(b.h); b.h = h; b.workspace = a.workspace
+    for _ in range(2):
+        for c, w in zip((a, b), want):
+            assert torch.equal(first_logits(c, prompts, buf, 8), w)
