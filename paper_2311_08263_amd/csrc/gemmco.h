@@ -2,7 +2,7 @@
 #pragma once
 #include "fast.h"
 
-enum { EPI_RESID = 0, EPI_SWIGLU = 1, EPI_QKV = 2, EPI_LMHEAD = 3 };
+enum { EPI_RESID = 0, EPI_SWIGLU = 1, EPI_QKV = 2, EPI_LMHEAD = 3, EPI_LMHEAD_BARE = 4 };       // (fc_gemmco takes an LM head without a norm in front as the last)
 
 struct GemmCoArgs {
     const bf16_t* W;       // fused matrix in fragment order

@@ -44,7 +44,7 @@ hipError_t fc_gemmco(int epi, const GemmCoArgs& a, int G, hipStream_t st) {
     if (a.M < 1 || a.M > 32 || a.K % 256 || a.NT < 1 || G < 1 || ks > 8 || G % ks || G / ks > a.NT ||
         (a.NT + G / ks - 1) / (G / ks) > most || a.K / 256 < ks)
         return hipErrorInvalidValue;
-    if (epi == EPI_RESID && a.gain) return hipErrorInvalidValue;          // (no norm in front of an adding product)
+    if (epi != EPI_LMHEAD && (a.gain != nullptr) != co_gained(epi)) return hipErrorInvalidValue;          // (no norm in front of an adding product, one in front of the others)
     if (ks > 1 && (epi == EPI_LMHEAD || !a.xpart || !a.xcnt || G / ks > FC_MAX_COUNTERS)) return hipErrorInvalidValue;
     return a.C ? fc_gemmco_coded(epi, a, G, st) : launch_co<WPlain>(epi, a, G, st);
 }

@@ -38,6 +38,7 @@ __device__ inline uint32_t rne16(float f) {
 }
 __device__ inline float up16(uint32_t b) { return __uint_as_float(b << 16); }
 
+constexpr bool co_gained(int epi) { return epi != EPI_RESID && epi != EPI_LMHEAD_BARE; }       // a norm in front
 // A pair of k-tiles of a wave: its weights for the wave's n-tiles, its activation octets.
 template <typename WP, int NW, int MT> struct Pair { float4 x[2][MT][2]; WP w[NW]; };
 
@@ -59,7 +60,7 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
     float* lds_gain = (float*)(lds_ami + 8 * 16) + w * a.gain_wave;      // this wave's part of the gain [pairs][64]
     auto part_of = [&](int wave) { return (f32x4_t*)lds + (SETS == 8 ? wave : wave & 3) * (TW * 64); };
     // workgroup i owns n-tiles [i*NT/G, (i+1)*NT/G): at most NW of them
-    const int ks = (EPI != EPI_LMHEAD && a.ks > 1) ? a.ks : 1;
+    const int ks = (EPI != EPI_LMHEAD && EPI != EPI_LMHEAD_BARE && a.ks > 1) ? a.ks : 1;
     const int G = gridDim.x / ks, owner = blockIdx.x / ks, slice = blockIdx.x % ks;
     const int nt0 = (int)(((unsigned)owner * (unsigned)a.NT) / (unsigned)G);
     const int nt1 = (int)(((unsigned)(owner + 1) * (unsigned)a.NT) / (unsigned)G);
@@ -115,8 +116,7 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
 
     f32x4_t acc[NW][MT];
     float ss[MT];
-    constexpr bool GAINED = EPI != EPI_RESID;            // the gain of a norm in front comes from LDS (ones without a norm)
-    const bool gained = GAINED && a.gain != nullptr;
+    constexpr bool GAINED = co_gained(EPI), LMHEAD = EPI == EPI_LMHEAD || EPI == EPI_LMHEAD_BARE;       // (gain: from LDS)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         ss[mt] = 0.f;
@@ -218,10 +218,10 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
         }
     }
 
-    // The gain of this wave's part of K goes through its part of LDS (ones where there is no norm).  It is requested before the
+    // The gain of this wave's part of K goes through its part of LDS.  It is requested before the
     // weights: its store to LDS would otherwise wait for every weight load in front of it.
     f32x4_t gr[4];
-    auto gain_at = [&](int q) { const int k = p_begin * 64 + q * 256 + lane * 4; return *(const f32x4_t*)((a.gain ? a.gain : a.X) + (k < a.K ? k : 0)); };
+    auto gain_at = [&](int q) { const int k = p_begin * 64 + q * 256 + lane * 4; return *(const f32x4_t*)(a.gain + (k < a.K ? k : 0)); };
     if (GAINED) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) gr[q] = gain_at(q);
@@ -230,10 +230,10 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
 #pragma unroll
     for (int d = 0; d < D; ++d) load(b[d], d);
     if (GAINED) {
-        const f32x4_t one = {1.f, 1.f, 1.f, 1.f};
+        auto mine = [&](int q) { return q * 256 + lane * 4 < n * 64; };
 #pragma unroll
-        for (int q = 0; q < 4; ++q) if (4 * q < n) *(f32x4_t*)(lds_gain + q * 256 + lane * 4) = gained ? gr[q] : one;
-        for (int q = 4; 4 * q < n; ++q) *(f32x4_t*)(lds_gain + q * 256 + lane * 4) = gained ? gain_at(q) : one;
+        for (int q = 0; q < 4; ++q) if (mine(q)) *(f32x4_t*)(lds_gain + q * 256 + lane * 4) = gr[q];
+        for (int q = 4; 4 * q < n; ++q) if (mine(q)) *(f32x4_t*)(lds_gain + q * 256 + lane * 4) = gain_at(q);
     }
     if constexpr (CODED) {
         uint32_t any = 0;
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
     bool fin[NF];
     f32x4_t v[NF];
     float rs = 1.0f, ssrow = 0.f;
-    if (gained) {
+    if (GAINED) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) ssrow += lds_ss[(q * MT + tm) * 16 + lm];
         rs = 1.0f / sqrtf(ssrow / (float)a.K + a.eps);
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
             if (ks == 1) v[f] *= rs;
         }
     }
-    if (EPI != EPI_LMHEAD && ks > 1) {
+    if (!LMHEAD && ks > 1) {
         // partial tiles of the ks slices (and, with a norm in front, each slice's share of the row sums of
         // squares) meet through memory; the last workgroup to arrive adds them in slice order
 #pragma unroll
@@ -341,14 +341,14 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
             }
         }
         float* sspart = a.xpart + (size_t)gridDim.x * (8 * NF) * 256;       // [workgroup][MT * 16]
-        if (gained && w < MT && g4 == 0) st_agent_f32(sspart + (size_t)blockIdx.x * (MT * 16) + tm * 16 + lm, ssrow);
+        if (GAINED && w < MT && g4 == 0) st_agent_f32(sspart + (size_t)blockIdx.x * (MT * 16) + tm * 16 + lm, ssrow);
         wait_vmem_done();
         __syncthreads();
         int* flag = (int*)lds_ss;
         if (tid == 0) *flag = arrive_agent(a.xcnt + owner);
         __syncthreads();
         if (*flag != ks - 1) return;
-        if (gained) {
+        if (GAINED) {
             float s = 0.f;
 #pragma unroll
             for (int s2 = 0; s2 < 8; ++s2) {
@@ -458,14 +458,14 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
                     }
                 }
             }
-        } else if (EPI == EPI_LMHEAD) {
+        } else if (LMHEAD) {
             const int n0 = nt * 16 + 4 * g4;
             if (a.out && m < a.M) *(f32x4_t*)(a.out + (size_t)m * a.ldo + n0) = vv;
 #pragma unroll
             for (int r = 0; r < 4; ++r) if (vv[r] > best || (vv[r] == best && n0 + r < bi)) { best = vv[r]; bi = n0 + r; }
         }
     }
-    if (EPI == EPI_LMHEAD) {
+    if (LMHEAD) {
 #pragma unroll
         for (int o = 16; o <= 32; o <<= 1) {
             const float ov = __shfl_xor(best, o, 64); const int oi = __shfl_xor(bi, o, 64);
@@ -491,14 +491,14 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
 // LDS of a launch: the partial tiles (in two rounds of four sets where there are more than eight), row sums and winners, the waves' parts of the gain
 static size_t co_lds_plan(GemmCoArgs& a, int nw, int mt, bool gain) {
     const int ks = a.ks > 1 ? a.ks : 1, PT = a.K >> 6, pairs = ((PT + ks - 1) / ks + 7) / 8;        // most pairs of a wave
-    a.gain_wave = gain ? (pairs + 3) / 4 * 256 : 0;
+    a.gain_wave = gain ? pairs * 64 : 0;
     return (size_t)(nw * mt <= 8 ? 8 : 4) * nw * mt * 1024 + (size_t)(8 * mt * 16 + 2 * 8 * 16) * 4 + (size_t)a.gain_wave * 32 + 64;
 }
 
 template <typename WP, int EPI, int NW, int D, int MT>
 static hipError_t launch_k(const GemmCoArgs& a0, int G, hipStream_t st) {
     GemmCoArgs a = a0;
-    const size_t lds = co_lds_plan(a, NW, MT, EPI != EPI_RESID);
+    const size_t lds = co_lds_plan(a, NW, MT, co_gained(EPI));
     if (lds > 150 * 1024) return hipErrorInvalidValue;
     static bool raised = false;
     if (!raised) {
@@ -562,7 +562,7 @@ static hipError_t launch_co(int epi, const GemmCoArgs& a, int G, hipStream_t st)
         case EPI_RESID: return launch_epi<WP, EPI_RESID>(a, G, st);
         case EPI_SWIGLU: return launch_epi<WP, EPI_SWIGLU>(a, G, st);
         case EPI_QKV: return launch_epi<WP, EPI_QKV>(a, G, st);
-        case EPI_LMHEAD: return launch_epi<WP, EPI_LMHEAD>(a, G, st);
+        case EPI_LMHEAD: return a.gain ? launch_epi<WP, EPI_LMHEAD>(a, G, st) : launch_epi<WP, EPI_LMHEAD_BARE>(a, G, st);
     }
     return hipErrorInvalidValue;
 }

@@ -218,3 +218,41 @@ def test_contexts_that_share_a_workspace_in_turn(fc):
     for _ in range(2):
         for c, w in zip((a, b), want):
             assert torch.equal(first_logits(c, prompts, buf, 8), w)
+
+
+@pytest.mark.parametrize("M,d,V", [(16, 20736, 24592), (32, 20736, 24592), (16, 23552, 53264), (1, 35072, 48), (32, 35072, 48)])
+def test_isolated_lm_head_of_many_inputs(fc, M, d, V):
+    """An LM head without a norm in front keeps no gain in LDS, so the number of its inputs is not limited by that: seven, fourteen and one
+    n-tile per workgroup, waves of up to 69 pairs."""
+    import torch
+    say(f"LM head of many inputs M={M} d={d} V={V}")
+    g = torch.Generator(device="cuda"); g.manual_seed(7)
+    w = special((0.02 * torch.randn(d, V, generator=g, device="cuda", dtype=torch.float32)).bfloat16(), "few", 11)
+    packed = fc.lmhead_pack(w)
+    scratch = torch.zeros(fc.lib().fastcot_lmhead_scratch_bytes(M, d, V), dtype=torch.uint8, device="cuda")
+    for k0 in (0, 7 * 7919 % d, d - M):
+        act = torch.zeros(M, d, device="cuda")
+        rows = torch.arange(k0, min(k0 + M, d), device="cuda")
+        act[torch.arange(len(rows), device="cuda"), rows] = 1.0
+        _, _, logits = fc.lmhead_argmax(act, packed, V, True, scratch)
+        assert torch.equal(logits[:len(rows)], w[rows].float()), k0
+
+
+def test_model_of_the_most_inputs(fc):
+    """21504 inputs, the most whose norm gain fits the LDS beside the partial tiles of seven or eight n-tiles (the LM head here); against the
+    plain kernels as above."""
+    import torch
+    say("model of 21504 inputs")
+    shape = (1, 21504, 2, 2, 256, 24592)
+    L, d, H, Hkv, F, V = shape
+    cfg = fc.Config(L, d, H, Hkv, 128, F, V, 1e-5, 1e4, 1, 1, 64, 16)
+    packed = pack(fc, cfg, tensors(shape, "none", 3))
+    r = np.random.RandomState(5)
+    prompts, buf = r.randint(0, V, (1, 9)).astype(np.int32), r.randint(0, V, (1, 48)).astype(np.int32)
+    out = []
+    for plain in (0, 1):
+        ctx = fc.Context(cfg, packed)
+        ctx.set_option(fc.binding.OPT_PLAIN_KERNELS, plain)
+        out.append(first_logits(ctx, prompts, buf, 16).double())
+        ctx.close()
+    assert float(torch.linalg.norm(out[0] - out[1]) / torch.linalg.norm(out[1])) < 1e-4
