@@ -216,7 +216,7 @@ enum { FASTCOT_OPT_PLAIN_KERNELS = 1, FASTCOT_OPT_GRAPH = 2, FASTCOT_OPT_KV_PLAN
 /* Launch-plan values, also set through fastcot_set_option.  They are measurement aids: defaults are chosen from
  * the model shape, and which values exist may change with the kernels.  The five GEMMs are numbered QKV, O,
  * gate/up, down, LM head.
- * FASTCOT_PLAN_NW + g: workgroups of GEMM g (each owns at most 8 tiles of 16 columns over all of K).
+ * FASTCOT_PLAN_NW + g: workgroups of GEMM g (each owns at most 14 tiles of 16 columns over all of K), for passes of up to 16 rows.
  * FASTCOT_PLAN_KS + g (g < 4): workgroups per column owner, each taking 1/value of K (1..8); their partial tiles
  * meet through memory and the last to arrive adds them in slice order.  The workgroup count must be a multiple.
  * FASTCOT_PLAN_SB + g: pairs of k-tiles under way per wave: 0 two, 1 one (more where a workgroup owns one or two n-tiles), 2 (default)

@@ -11,7 +11,7 @@
 #include <atomic>
 #include <vector>
 #include "kernels.h"
-#include "fast.h"
+#include "gemmco.h"
 
 static thread_local char g_err[512] = "";
 
@@ -376,6 +376,11 @@ extern "C" int fastcot_set_option(fastcot_ctx* c, int32_t option, int32_t value)
     if (!c) return fail(nullptr, FASTCOT_EINVAL, "ctx is NULL%s");
     const int nts[5] = {c->kd.qkvN / 16, c->kd.d / 16, 2 * c->kd.F / 16, c->kd.d / 16, c->kd.V / 16};
     const int Ks[5] = {c->kd.d, c->kd.H * c->kd.Dh, c->kd.d, c->kd.F, c->kd.d};
+    // a grid and its K slices are taken where a launch of them is (models without the matrix-core kernels: by the tiles per owner alone)
+    auto fits = [&](int rows, int gi, int G, int ks) {
+        if (G < 1 || G % ks || G / ks > nts[gi] || (nts[gi] + G / ks - 1) / (G / ks) > (rows <= 16 ? 14 : 8)) return false;
+        return !fc_fast_supported(c->kd, 1) || fc_gemmco_fits(rows, Ks[gi], nts[gi], G, ks, gi != 1 && gi != 3);
+    };
     if (option == FASTCOT_OPT_PLAIN_KERNELS) {
         if (!value && c->cfg.dtype == FASTCOT_F32) return fail(c, FASTCOT_EINVAL, "fp32 models only have the plain kernels%s");
         c->opt_plain = value != 0;
@@ -396,23 +401,20 @@ extern "C" int fastcot_set_option(fastcot_ctx* c, int32_t option, int32_t value)
     else if (option >= FASTCOT_PLAN_NW && option < FASTCOT_PLAN_NW + 5) {
         const int gi = option - FASTCOT_PLAN_NW, NT = nts[gi];
         int ks = c->plan.ks[gi] > 1 ? c->plan.ks[gi] : 1;
-        if (value < 1 || value > NT || (NT + value - 1) / value > 8)
-            return fail(c, FASTCOT_EINVAL, "workgroups of the column-owner GEMM: NT/8 .. NT%s");
-        auto fits = [&](int k) { return value % k == 0 && value / k >= 1 && value / k <= NT && (NT + value / k - 1) / (value / k) <= 12; };
-        if (c->plan.ks_rule[gi]) { ks = c->plan.ks_rule[gi]; if (!fits(ks)) ks /= 2; }     // (slices nobody asked for do not refuse a grid)
-        if (!fits(ks))
+        if (value < 1 || value > NT || (NT + value - 1) / value > 14)
+            return fail(c, FASTCOT_EINVAL, "workgroups of the column-owner GEMM: NT/14 .. NT%s");
+        if (c->plan.ks_rule[gi]) { ks = c->plan.ks_rule[gi]; if (!fits(16, gi, value, ks)) ks /= 2; }     // (slices nobody asked for do not refuse a grid)
+        if (!fits(16, gi, value, ks))
             return fail(c, FASTCOT_EINVAL, "workgroups of the column-owner GEMM do not fit its K slices per owner%s");
         c->plan.nw[gi] = value; c->plan.ks[gi] = ks;
     } else if (option >= FASTCOT_PLAN_KS && option < FASTCOT_PLAN_KS + 4) {
-        const int gi = option - FASTCOT_PLAN_KS, NT = nts[gi], nw = c->plan.nw[gi], K = Ks[gi];
-        if (value < 1 || value > 8 || K / 256 < value) return fail(c, FASTCOT_EINVAL, "K slices per owner out of range%s");
-        if (nw % value || nw / value > NT || nw / value < 1 || (NT + nw / value - 1) / (nw / value) > 12)
+        const int gi = option - FASTCOT_PLAN_KS;
+        if (value < 1 || value > 8 || Ks[gi] / 256 < value) return fail(c, FASTCOT_EINVAL, "K slices per owner out of range%s");
+        if (!fits(16, gi, c->plan.nw[gi], value))
             return fail(c, FASTCOT_EINVAL, "K slices per owner do not fit the workgroup count of that GEMM%s");
         c->plan.ks[gi] = value; c->plan.ks_rule[gi] = 0;
         // steps of 17..32 rows (two row tiles per workgroup, at most 8 n-tiles): the same value where it fits
-        const int nw2 = c->plan.nw2[gi];
-        if (nw2 > 0 && nw2 % value == 0 && nw2 / value >= 1 && nw2 / value <= NT && (NT + nw2 / value - 1) / (nw2 / value) <= 8)
-            c->plan.ks2[gi] = value;
+        if (fits(32, gi, c->plan.nw2[gi], value)) c->plan.ks2[gi] = value;
     } else if (option >= FASTCOT_PLAN_SB && option < FASTCOT_PLAN_SB + 5) {
         if (value < 0 || value > 2) return fail(c, FASTCOT_EINVAL, "pairs of k-tiles under way per wave: 0 (two), 1 (one) or 2 (by the tiles a workgroup owns)%s");
         c->plan.co_sb[0][option - FASTCOT_PLAN_SB] = c->plan.co_sb[1][option - FASTCOT_PLAN_SB] = value;

@@ -37,6 +37,8 @@ int fc_gemmco_grid(int NT, int most = 8, bool wide = false);
 // most n-tiles a workgroup may own so that its partial tiles (8 sets x n-tiles x row tiles x 1 KB up to eight output tiles, 4 sets beyond) and, with a
 // norm in front, the gain vector (K floats) fit the LDS of a CU
 int fc_gemmco_most(int M, int K, bool gain);
+// whether M rows run on G workgroups with ks K slices per owner: everything above and what a launch of it needs
+bool fc_gemmco_fits(int M, int K, int NT, int G, int ks, bool gain);
 int fc_num_cus();      // compute units of the current device
 hipError_t fc_gemmco_coded(int epi, const GemmCoArgs& a, int G, hipStream_t st);      // (through fc_gemmco)
 hipError_t fc_gemmco(int epi, const GemmCoArgs& a, int G, hipStream_t st);

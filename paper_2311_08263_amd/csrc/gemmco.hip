@@ -34,18 +34,26 @@ int fc_gemmco_most(int M, int K, bool gain) {
     const int inst[6] = {8, 6, 4, 3, 2, 1};
     for (int i = 0; i < 6; ++i) {
         GemmCoArgs a; a.K = K; a.ks = 1;
-        if (co_lds_plan(a, inst[i], M > 16 ? 2 : 1, gain) <= 150 * 1024) return inst[i];
+        if (co_lds_plan(a, inst[i], M > 16 ? 2 : 1, gain) <= CO_LDS_MOST) return inst[i];
     }
     return 1;
 }
 
+bool fc_gemmco_fits(int M, int K, int NT, int G, int ks, bool gain) {
+    if (M < 1 || M > 32 || K < 256 || K % 256 || NT < 1 || G < 1 || ks < 1 || ks > 8 || G % ks || G / ks > NT || K / 256 < ks) return false;
+    const int inst[8] = {1, 2, 3, 4, 6, 8, 12, 14}, own = (NT + G / ks - 1) / (G / ks), most = M <= 16 ? 14 : 8;
+    if (own > most || (ks > 1 && G / ks > FC_MAX_COUNTERS)) return false;
+    int nw = own;
+    for (int i = 7; i >= 0; --i) if (inst[i] >= own) nw = inst[i];
+    GemmCoArgs a; a.K = K; a.ks = ks;
+    return co_lds_plan(a, nw, M > 16 ? 2 : 1, gain) <= CO_LDS_MOST;
+}
+
 hipError_t fc_gemmco(int epi, const GemmCoArgs& a, int G, hipStream_t st) {
-    const int ks = a.ks > 1 ? a.ks : 1, most = a.M <= 16 ? 14 : 8;
-    if (a.M < 1 || a.M > 32 || a.K % 256 || a.NT < 1 || G < 1 || ks > 8 || G % ks || G / ks > a.NT ||
-        (a.NT + G / ks - 1) / (G / ks) > most || a.K / 256 < ks)
-        return hipErrorInvalidValue;
+    const int ks = a.ks > 1 ? a.ks : 1;
+    if (!fc_gemmco_fits(a.M, a.K, a.NT, G, ks, a.gain != nullptr)) return hipErrorInvalidValue;
     if (epi != EPI_LMHEAD && (a.gain != nullptr) != co_gained(epi)) return hipErrorInvalidValue;          // (no norm in front of an adding product, one in front of the others)
-    if (ks > 1 && (epi == EPI_LMHEAD || !a.xpart || !a.xcnt || G / ks > FC_MAX_COUNTERS)) return hipErrorInvalidValue;
+    if (ks > 1 && (epi == EPI_LMHEAD || !a.xpart || !a.xcnt)) return hipErrorInvalidValue;
     return a.C ? fc_gemmco_coded(epi, a, G, st) : launch_co<WPlain>(epi, a, G, st);
 }
 

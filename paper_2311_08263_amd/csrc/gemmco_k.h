@@ -489,6 +489,7 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
 }
 
 // LDS of a launch: the partial tiles (in two rounds of four sets where there are more than eight), row sums and winners, the waves' parts of the gain
+static constexpr size_t CO_LDS_MOST = 150 * 1024;
 static size_t co_lds_plan(GemmCoArgs& a, int nw, int mt, bool gain) {
     const int ks = a.ks > 1 ? a.ks : 1, PT = a.K >> 6, pairs = ((PT + ks - 1) / ks + 7) / 8;        // most pairs of a wave
     a.gain_wave = gain ? pairs * 64 : 0;
@@ -499,10 +500,10 @@ template <typename WP, int EPI, int NW, int D, int MT>
 static hipError_t launch_k(const GemmCoArgs& a0, int G, hipStream_t st) {
     GemmCoArgs a = a0;
     const size_t lds = co_lds_plan(a, NW, MT, co_gained(EPI));
-    if (lds > 150 * 1024) return hipErrorInvalidValue;
+    if (lds > CO_LDS_MOST) return hipErrorInvalidValue;
     static bool raised = false;
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_gemmco<WP, EPI, NW, D, MT>, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
+        hipError_t e = hipFuncSetAttribute((const void*)k_gemmco<WP, EPI, NW, D, MT>, hipFuncAttributeMaxDynamicSharedMemorySize, CO_LDS_MOST);
         if (e != hipSuccess) return e;
         raised = true;
     }

@@ -256,3 +256,34 @@ def test_model_of_the_most_inputs(fc):
         out.append(first_logits(ctx, prompts, buf, 16).double())
         ctx.close()
     assert float(torch.linalg.norm(out[0] - out[1]) / torch.linalg.norm(out[1])) < 1e-4
+
+
+def test_plan_options_take_what_a_launch_takes(fc):
+    """Gate/up of 13.5 n-tiles per CU: its own grid (one round of 14) and slice count are accepted, other grids up to 14 tiles too, 15 are not;
+    one K slice computes the default's bits, other grids the same logits."""
+    import torch
+    shape = (1, 256, 2, 2, 27648, 1008)
+    L, d, H, Hkv, F, V = shape
+    cfg = fc.Config(L, d, H, Hkv, 128, F, V, 1e-5, 1e4, 1, 1, 128, 16)
+    packed = pack(fc, cfg, tensors(shape, "none", 3))
+    r = np.random.RandomState(5)
+    prompts, buf = r.randint(0, V, (1, 21)).astype(np.int32), r.randint(0, V, (1, 48)).astype(np.int32)
+    NW, KS, NT = fc.binding.PLAN_NW + 2, fc.binding.PLAN_KS + 2, 2 * F // 16
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+
+    def logits(*opts):
+        say(f"gate/up plan {opts}")
+        ctx = fc.Context(cfg, packed)
+        for o in opts:
+            ctx.set_option(*o)
+        out = first_logits(ctx, prompts, buf, 16).double()
+        ctx.close()
+        return out
+    default, fewest = logits(), (NT + 13) // 14
+    for same in (((KS, 1),), ((NW, cus),), ((NW, 2 * cus), (NW, cus), (KS, 1))):
+        assert torch.equal(logits(*same), default)
+    for other in (((NW, 2 * cus),), ((NW, fewest),)):
+        assert float(torch.linalg.norm(logits(*other) - default) / torch.linalg.norm(default)) < 1e-5
+    for refused in (((NW, fewest - 1),), ((NW, NT + 1),), ((KS, 2),), ((KS, 9),)):
+        with pytest.raises(fc.FastcotError):
+            logits(*refused)
