@@ -5,10 +5,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
-#include <time.h>
-#include <unistd.h>
 #include <algorithm>
-#include <atomic>
 #include <vector>
 #include "kernels.h"
 #include "gemmco.h"
@@ -122,7 +119,7 @@ int fc_build_maps(const fastcot_config* c, ModelMap* mm, WorkspaceMap* wm, Kerne
         m.gf_off = top; top = FC_ALIGN(top + (size_t)d * 4);
         m.layers_off = top;
         m.stamp_off = top + (size_t)c->n_layers * m.layer_stride;
-        m.total = m.stamp_off + 256;
+        m.total = FC_ALIGN(m.stamp_off + 8 * (size_t)(2 + 7 * c->n_layers));
         if (mm) *mm = m;
     }
     // prefill runs the same kernels over chunks of the prompt; where the matrix-core path covers the
@@ -215,20 +212,6 @@ static size_t canon_elems(const KernelDims& kd, int t) {
     }
     return 0;
 }
-// a number that no other packing call adds to a stamp, of this process or of another one (packed weights may be copied between buffers
-// and kept in files, and the stamp with them)
-static uint64_t pack_nonce() {
-    static std::atomic<uint64_t> calls{0};
-    static const uint64_t seed = [] {
-        timespec t = {0, 0};
-        (void)clock_gettime(CLOCK_REALTIME, &t);
-        return ((uint64_t)t.tv_sec * 1000000000ull + (uint64_t)t.tv_nsec) ^ ((uint64_t)getpid() << 40);
-    }();
-    uint64_t x = seed + calls.fetch_add(1) * 0x9E3779B97F4A7C15ull;       // (the mixing steps are splitmix64's)
-    x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
-    x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
-    return (x ^ (x >> 31)) | 1;
-}
 extern "C" int fastcot_pack_tensor(const fastcot_config* cfg, int32_t tensor, int32_t layer, const void* src,
                                    void* d_packed, void* hip_stream) {
     ModelMap mm; KernelDims kd;
@@ -242,27 +225,27 @@ extern "C" int fastcot_pack_tensor(const fastcot_config* cfg, int32_t tensor, in
     char* lbase = base + mm.layers_off + (size_t)(per_layer ? layer : 0) * mm.layer_stride;
     const bool gain = tensor == FASTCOT_T_GF || tensor == FASTCOT_T_G1 || tensor == FASTCOT_T_G2;
     if (!src && !gain) return fail(nullptr, FASTCOT_EINVAL, "d_canonical is NULL%s");
+    void* stamp = fc_fast_supported(kd, 1) ? base + mm.stamp_off : nullptr;       // (of models that can have coded copies)
+    const int part = tensor == FASTCOT_T_WLM ? 1 : 2 + 7 * layer + (tensor - FASTCOT_T_WQ);
     hipError_t e = hipSuccess;
     switch (tensor) {
         case FASTCOT_T_EMB: e = fc_copy_bytes(base + mm.emb_off, src, (size_t)kd.V * d * kd.esz, st); break;
-        case FASTCOT_T_WLM: e = fc_pack(src, dt, d, kd.V, base, mm.lm, 0, 0, st); break;
+        case FASTCOT_T_WLM: e = fc_pack(src, dt, d, kd.V, base, mm.lm, 0, 0, st, stamp, part); break;
         case FASTCOT_T_GF: case FASTCOT_T_G1: case FASTCOT_T_G2: {
             float* dst = (float*)(tensor == FASTCOT_T_GF ? base + mm.gf_off
                                   : lbase + (tensor == FASTCOT_T_G1 ? mm.g1_off : mm.g2_off));
             e = src ? fc_copy_bytes(dst, src, (size_t)d * 4, st) : fc_fill_f32(dst, d, 1.0f, st);
             break;
         }
-        case FASTCOT_T_WQ: e = fc_pack(src, dt, d, qd, lbase, mm.qkv, 0, 3 + kd.Dh, st); break;
-        case FASTCOT_T_WK: e = fc_pack(src, dt, d, kvd, lbase, mm.qkv, qd, 3 + kd.Dh, st); break;
-        case FASTCOT_T_WV: e = fc_pack(src, dt, d, kvd, lbase, mm.qkv, qd + kvd, 0, st); break;
-        case FASTCOT_T_WO: e = fc_pack(src, dt, qd, d, lbase, mm.o, 0, 0, st); break;
-        case FASTCOT_T_WG: e = fc_pack(src, dt, d, kd.F, lbase, mm.gu, 0, 1, st); break;
-        case FASTCOT_T_WU: e = fc_pack(src, dt, d, kd.F, lbase, mm.gu, 0, 2, st); break;
-        case FASTCOT_T_WD: e = fc_pack(src, dt, kd.F, d, lbase, mm.down, 0, 0, st); break;
+        case FASTCOT_T_WQ: e = fc_pack(src, dt, d, qd, lbase, mm.qkv, 0, 3 + kd.Dh, st, stamp, part); break;
+        case FASTCOT_T_WK: e = fc_pack(src, dt, d, kvd, lbase, mm.qkv, qd, 3 + kd.Dh, st, stamp, part); break;
+        case FASTCOT_T_WV: e = fc_pack(src, dt, d, kvd, lbase, mm.qkv, qd + kvd, 0, st, stamp, part); break;
+        case FASTCOT_T_WO: e = fc_pack(src, dt, qd, d, lbase, mm.o, 0, 0, st, stamp, part); break;
+        case FASTCOT_T_WG: e = fc_pack(src, dt, d, kd.F, lbase, mm.gu, 0, 1, st, stamp, part); break;
+        case FASTCOT_T_WU: e = fc_pack(src, dt, d, kd.F, lbase, mm.gu, 0, 2, st, stamp, part); break;
+        case FASTCOT_T_WD: e = fc_pack(src, dt, kd.F, d, lbase, mm.down, 0, 0, st, stamp, part); break;
         default: return fail(nullptr, FASTCOT_EINVAL, "unknown tensor id%s");
     }
-    // matrices of models that can have coded copies
-    if (e == hipSuccess && !gain && tensor != FASTCOT_T_EMB && fc_fast_supported(kd, 1)) e = fc_stamp(base + mm.stamp_off, pack_nonce(), st);
     if (e != hipSuccess) return fail(nullptr, FASTCOT_EHIP, "pack launch failed: %s", hipGetErrorString(e));
     return 0;
 }
@@ -604,17 +587,16 @@ static int code_weights(fastcot_ctx* c) {
     if (!any) return 0;
     const char* stamp = c->weights + c->mm.stamp_off;
     char* record = c->ws + c->wm.code_record;
-    HIPCHK(c, fc_stamp_read(stamp, record, c->pinned, c->st));
+    HIPCHK(c, fc_stamp_look(stamp, record, c->pinned, c->st));
     HIPCHK(c, hipStreamSynchronize(c->st));
-    const uint64_t* seen = (const uint64_t*)c->pinned;
-    if (seen[0] == seen[1]) return 0;
+    if (!c->pinned[0]) return 0;
     HIPCHK(c, fc_stamp_keep(stamp, record, 0, c->st));
     const FusedMat* mats[5] = {&c->mm.qkv, &c->mm.o, &c->mm.gu, &c->mm.down, &c->mm.lm};
     for (int i = 0; i < 5; ++i) {
         if (!c->wm.code[i]) continue;
         for (int l = 0; l < (i == 4 ? 1 : c->kd.L); ++l) {
             const char* base = i == 4 ? c->weights : c->weights + c->mm.layers_off + (size_t)l * c->mm.layer_stride;
-            HIPCHK(c, fc_code(base + mats[i]->off, c->ws + c->wm.code[i] + (size_t)l * c->wm.code_stride[i], mats[i]->K, mats[i]->NP / 16, 0, mats[i]->NP / 16, c->st));
+            HIPCHK(c, fc_code(base + mats[i]->off, c->ws + c->wm.code[i] + (size_t)l * c->wm.code_stride[i], mats[i]->K, mats[i]->NP / 16, c->st));
         }
     }
     HIPCHK(c, fc_stamp_keep(stamp, record, 1, c->st));

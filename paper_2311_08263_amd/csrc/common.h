@@ -108,7 +108,7 @@ struct ModelMap {
     size_t emb_off;              // [V][d] row-major, model dtype
     FusedMat lm;                 // absolute offset
     size_t gf_off;
-    size_t stamp_off;            // 64 bits that change with every matrix packed
+    size_t stamp_off;            // the stamp of the packed matrices (64 bits), then each one's part of it: LM head, WQ, WK, WV, WO, WG, WU, WD layer by layer
     size_t total;
 };
 
@@ -135,7 +135,7 @@ struct WorkspaceMap {
     size_t gemm_part, gemm_cnt, attn_part, attn_cnt, amax_part;
     size_t state;
     size_t code[5], code_stride[5];   // coded copies of QKV, O, gate/up, down (layer l at code + l * stride) and the LM head; 0: none
-    size_t code_record;               // the stamp of the weights the copies were made from (64 bits; its complement: there are none yet)
+    size_t code_record;               // the stamp (ModelMap) of the weights the copies were made from; its complement: there are none yet
     size_t total;
     size_t gemm_part_bytes, attn_part_bytes;
     StateMap st;

@@ -86,7 +86,7 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
     const uint8_t* flags = (const uint8_t*)a.C + wc_flag_off(a.K, a.NT);
     u32x2_t mark;                                        // lane 0: stamp, lane 1: record (a vector load, in the row of the flags: scalar ones cost 0.15 us a launch)
     if constexpr (CODED) {
-        mark = *(const u32x2_t*)(lane & 1 ? a.record : a.stamp);
+        mark = *(const u32x2_t*)((lane & 1 ? a.record : a.stamp));
         const uint8_t* bases = (const uint8_t*)a.C + wc_base_off(a.K, a.NT);
         const int p = p_begin + lane < PT ? p_begin + lane : PT - 1;
 #pragma unroll

@@ -55,14 +55,12 @@ hipError_t fc_swap_sequences(int32_t* state, const StateMap& sm, int b1, int b2,
 
 // ---- weight packing
 hipError_t fc_pack(const void* src, int dt, int rows, int cols, void* dst_base, const FusedMat& fm, int col_off,
-                   int mode /*0 natural, 1 gate, 2 up, 3 + Dh: q/k heads of Dh*/, hipStream_t st);
-// the coded copy at C of n-tiles nt0 .. nt0 + cnt - 1 of a matrix of K inputs and NT n-tiles
-hipError_t fc_code(const void* W, void* C, int K, int NT, int nt0, int cnt, hipStream_t st);
-// a packing call joins a packed model's stamp; the record of coded copies takes the stamp over (made = 0: there are no copies); stamp and
-// record (a 64-bit word each) to host memory
-hipError_t fc_stamp(void* stamp, uint64_t nonce, hipStream_t st);
+                   int mode /*0 natural, 1 gate, 2 up, 3 + Dh: q/k heads of Dh*/, hipStream_t st, void* stamp = nullptr /*of the packed model, bf16*/, int tensor = 0 /*its own part of it*/);
+// the coded copy at C of a matrix of K inputs and NT n-tiles
+hipError_t fc_code(const void* W, void* C, int K, int NT, hipStream_t st);
+// the record of coded copies takes a packed model's stamp over (made = 0: there are no copies); whether they differ, to host memory
 hipError_t fc_stamp_keep(const void* stamp, void* record, int made, hipStream_t st);
-hipError_t fc_stamp_read(const void* stamp, const void* record, void* host, hipStream_t st);
+hipError_t fc_stamp_look(const void* stamp, const void* record, int* host, hipStream_t st);
 hipError_t fc_fill_f32(float* dst, size_t n, float v, hipStream_t st);
 hipError_t fc_copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t st);
 hipError_t fc_kv_scatter(const void* k, const void* v, int S_in, int Hkv, int Dh, int S, int dt, void* kc, void* vc,

@@ -534,21 +534,49 @@ __global__ void k_pack_f32(const float* src, int rows, int cols, float* dst, int
     const int k = (int)(i / cols), c = (int)(i % cols);
     dst[(size_t)k * NP + pack_col(c, col_off, mode)] = src[i];
 }
-// bf16: a thread takes eight rows of a column, which are a lane's 16 bytes of the fragment: rows are read in runs of the workgroup's
-// columns, sixteen neighbouring columns are written as 256 bytes.
-__global__ void k_pack_bf16(const bf16_t* src, int rows, int cols, bf16_t* dst, int K, int col_off, int mode) {
-    const int c = blockIdx.x * 64 + (threadIdx.x & 63), k = (blockIdx.y * 4 + (threadIdx.x >> 6)) * 8;
-    if (c >= cols || k >= rows) return;
-    uint32_t v[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = src[(size_t)(k + e) * cols + c];
-    *(u32x4_t*)(dst + frag_index(K, k, pack_col(c, col_off, mode))) = (u32x4_t){v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
+// bf16: a thread takes eight rows of a column at a time, which are a lane's 16 bytes of the fragment: rows are read in runs of the workgroup's
+// columns, sixteen neighbouring columns are written as 256 bytes.  stamp (or NULL) and stamp[tensor] take the hash of what was packed; a workgroup
+// takes many rows so that few of them add to it.
+__global__ void k_stamp_clear(unsigned long long* stamp, int tensor) {       // (tensors may be packed on several streams)
+    atomicAdd(stamp, 0ull - stamp[tensor]);
+    stamp[tensor] = 0;
 }
-// The coded copy (wcode.h) of n-tiles nt0, nt0 + 1, ... from their plain tiles: a workgroup an n-tile, its eight waves all of K twice, for
+__device__ inline unsigned long long stamp_mix(unsigned long long x) {
+    x = (x ^ (x >> 31)) * 6364136223846793005ull;
+    x = (x ^ (x >> 29)) * 2862933555777941757ull;
+    return x ^ (x >> 32);
+}
+__global__ __launch_bounds__(1024) void k_pack_bf16(const bf16_t* src, int rows, int cols, bf16_t* dst, int K, int col_off, int mode, unsigned long long* stamp, int tensor) {
+    __shared__ unsigned long long part[16];
+    const int c = blockIdx.x * 64 + (threadIdx.x & 63);
+    unsigned long long h = 0;
+    if (c < cols) {
+        const int n = pack_col(c, col_off, mode);
+        const unsigned long long salt = (unsigned long long)tensor << 40;
+        for (int k = (blockIdx.y * 16 + (threadIdx.x >> 6)) * 8; k < rows; k += gridDim.y * 128) {
+            uint32_t v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = src[(size_t)(k + e) * cols + c];
+            const u32x4_t w = {v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
+            const size_t at = frag_index(K, k, n);
+            *(u32x4_t*)(dst + at) = w;
+            h += stamp_mix((w[0] | ((unsigned long long)w[1] << 32)) + stamp_mix(salt + at)) + stamp_mix((w[2] | ((unsigned long long)w[3] << 32)) + stamp_mix(salt + at + 4));
+        }
+    }
+    if (!stamp) return;
+    for (int o = 32; o > 0; o >>= 1) h += __shfl_xor(h, o, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = h;
+    __syncthreads();
+    if (threadIdx.x >= 2) return;
+    h = 0;
+    for (int q = 0; q < 16; ++q) h += part[q];
+    atomicAdd(stamp + threadIdx.x * tensor, h);
+}
+// The coded copy (wcode.h) of a matrix from its plain tiles: a workgroup an n-tile, its eight waves all of K twice, for
 // the columns' largest exponents and for the codes.
-__global__ __launch_bounds__(512) void k_code(const char* W, char* C, int K, int NT, int nt0) {
+__global__ __launch_bounds__(512) void k_code(const char* W, char* C, int K, int NT) {
     __shared__ uint32_t top[8][16];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, lm = lane & 15, nt = nt0 + blockIdx.x, PT = K >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, lm = lane & 15, nt = blockIdx.x, PT = K >> 6;
     const u32x4_t* src = (const u32x4_t*)W + (size_t)nt * PT * 128 + lane;
     uint32_t hi = 0;
 #pragma unroll 4
@@ -594,13 +622,13 @@ __global__ __launch_bounds__(512) void k_code(const char* W, char* C, int K, int
         if (lane == 0) C[wc_flag_off(K, NT) + (size_t)nt * PT + p] = (char)any;
     }
 }
-hipError_t fc_code(const void* W, void* C, int K, int NT, int nt0, int cnt, hipStream_t st) {
-    if (K < 256 || K % 256 || nt0 < 0 || cnt < 1 || nt0 + cnt > NT) return hipErrorInvalidValue;
-    k_code<<<cnt, 512, 0, st>>>((const char*)W, (char*)C, K, NT, nt0);
+hipError_t fc_code(const void* W, void* C, int K, int NT, hipStream_t st) {
+    if (K < 256 || K % 256 || NT < 1) return hipErrorInvalidValue;
+    k_code<<<NT, 512, 0, st>>>((const char*)W, (char*)C, K, NT);
     return hipGetLastError();
 }
 hipError_t fc_pack(const void* src, int dt, int rows, int cols, void* dst_base, const FusedMat& fm, int col_off,
-                   int mode, hipStream_t st) {
+                   int mode, hipStream_t st, void* stamp, int tensor) {
     char* dst = (char*)dst_base + fm.off;
     if (dt == FASTCOT_F32) {
         const size_t n = (size_t)rows * cols;
@@ -608,26 +636,22 @@ hipError_t fc_pack(const void* src, int dt, int rows, int cols, void* dst_base, 
         return hipGetLastError();
     }
     if (rows % 32) return hipErrorInvalidValue;
-    k_pack_bf16<<<dim3((cols + 63) / 64, (rows / 8 + 3) / 4), 256, 0, st>>>((const bf16_t*)src, rows, cols, (bf16_t*)dst, fm.K, col_off, mode);
+    if (stamp) k_stamp_clear<<<1, 1, 0, st>>>((unsigned long long*)stamp, tensor);
+    const int runs = (rows / 8 + 15) / 16, strips = (cols + 63) / 64, per = strips < 1024 ? 1024 / strips : 1;
+    k_pack_bf16<<<dim3(strips, runs < per ? runs : per), 1024, 0, st>>>((const bf16_t*)src, rows, cols, (bf16_t*)dst, fm.K, col_off, mode, (unsigned long long*)stamp, tensor);
     const hipError_t e = hipGetLastError();
-    return e == hipSuccess && fm.coded ? fc_code(dst, dst + wc_off(fm.K, fm.NP / 16), fm.K, fm.NP / 16, 0, fm.NP / 16, st) : e;
+    return e == hipSuccess && fm.coded ? fc_code(dst, dst + wc_off(fm.K, fm.NP / 16), fm.K, fm.NP / 16, st) : e;
 }
-// The stamp of a packed model: every packing call adds a number of its own, so that copies made of the weights before can be told from
-// copies of the weights that are there.  (Tensors may be packed on several streams: the sum is atomic.)
-__global__ void k_stamp(unsigned long long* s, unsigned long long nonce) { atomicAdd(s, nonce); }
-// The record of a set of coded copies: the stamp of the weights they were made from, its complement while there are none.
-__global__ void k_stamp_keep(const unsigned long long* s, unsigned long long* record, int made) { *record = made ? *s : ~*s; }
-__global__ void k_stamp_read(const unsigned long long* s, const unsigned long long* record, unsigned long long* host) { host[0] = *s; host[1] = *record; }
-hipError_t fc_stamp(void* stamp, uint64_t nonce, hipStream_t st) {
-    k_stamp<<<1, 1, 0, st>>>((unsigned long long*)stamp, nonce);
-    return hipGetLastError();
-}
+// A packed model's stamp is the sum of hashes over all its matrices, each of every 8 bytes of it and their place (k_pack_bf16): a coded
+// copy's record (the stamp of the weights it was made from, its complement while there is no copy) shows whether it is of the weights that are there.
+__global__ void k_stamp_keep(const unsigned long long* stamp, unsigned long long* record, int made) { *record = made ? *stamp : ~*stamp; }
+__global__ void k_stamp_look(const unsigned long long* stamp, const unsigned long long* record, int* host) { *host = *stamp != *record; }
 hipError_t fc_stamp_keep(const void* stamp, void* record, int made, hipStream_t st) {
     k_stamp_keep<<<1, 1, 0, st>>>((const unsigned long long*)stamp, (unsigned long long*)record, made);
     return hipGetLastError();
 }
-hipError_t fc_stamp_read(const void* stamp, const void* record, void* host, hipStream_t st) {
-    k_stamp_read<<<1, 1, 0, st>>>((const unsigned long long*)stamp, (const unsigned long long*)record, (unsigned long long*)host);
+hipError_t fc_stamp_look(const void* stamp, const void* record, int* host, hipStream_t st) {
+    k_stamp_look<<<1, 1, 0, st>>>((const unsigned long long*)stamp, (const unsigned long long*)record, host);
     return hipGetLastError();
 }
 
