@@ -68,12 +68,17 @@ typedef struct fastcot_ctx fastcot_ctx;
  * The activations are sized for the largest pass: a step of max_batch * window rows, or a prompt chunk (Sec. 4.1, the
  * first forward): up to 1024 rows in all for bf16 models of the shapes the matrix-core kernels cover, for other models
  * up to 128 rows per sequence within 512 in all, but at least 16 per sequence.  Logits are sized for a step's rows.
- * For bf16 models of the matrix-core shapes the workspace also holds a copy of the weights in 13 bits each, from which passes of up to
- * 32 rows read them (7B shape: 10 GiB; of models whose weights and copies would pass 208 GiB, the matrices that fit): a context's first
- * fastcot_prefill makes it, and a later one makes it again where fastcot_pack_tensor or fastcot_pack_weights wrote to the packed
- * weights in between, or a whole packed buffer was copied over them; until then passes read the packed weights themselves. */
+ * For bf16 models of the matrix-core shapes the workspace also has room for a copy of the weights in 13 bits each, from which passes of
+ * up to 32 rows read them (7B shape: 10 GiB; where weights and workspace would pass 208 GiB, as many matrices as fit).  The copy is made in
+ * front of the first step of at most 32 rows (by fastcot_prefill, where the steps have so few), and again after a
+ * fastcot_prefill that finds that fastcot_pack_tensor or fastcot_pack_weights wrote to the packed weights in between, or that a whole packed
+ * buffer was copied over them; until then passes read the packed weights themselves.
+ * fastcot_workspace_bytes_min is the workspace without that room: fastcot_init takes any size from there on, and copies what fits.  Passes
+ * read the other matrices as they were packed: slower (7B step of 16 rows 11 %), with the same results save for the order in which
+ * some products are added (matrices of which 13 bits do not hold every weight). */
 size_t fastcot_weight_bytes(const fastcot_config* cfg);
 size_t fastcot_workspace_bytes(const fastcot_config* cfg);
+size_t fastcot_workspace_bytes_min(const fastcot_config* cfg);
 
 /* Rearranges one tensor from the canonical layout into its place inside the packed weights.
  * d_canonical: device pointer, elements of cfg->dtype (gains: fp32); NULL for a gain tensor

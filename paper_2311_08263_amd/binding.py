@@ -48,6 +48,7 @@ class Config(ctypes.Structure):
 SYMBOLS = {
     "fastcot_weight_bytes": (sz, [ctypes.POINTER(Config)]),
     "fastcot_workspace_bytes": (sz, [ctypes.POINTER(Config)]),
+    "fastcot_workspace_bytes_min": (sz, [ctypes.POINTER(Config)]),
     "fastcot_pack_tensor": (ctypes.c_int, [ctypes.POINTER(Config), i32, i32, vp, vp, vp]),
     "fastcot_init": (ctypes.c_int, [ctypes.POINTER(Config), vp, vp, sz, vp, ctypes.POINTER(vp)]),
     "fastcot_free": (None, [vp]),
@@ -186,15 +187,24 @@ def load_synth_weights(cfg: Config, shape, seed: Optional[int] = None):
 
 # ---------------------------------------------------------------------------- context
 class Context:
-    def __init__(self, cfg: Config, packed):
+    def __init__(self, cfg: Config, packed, workspace_bytes: Optional[int] = None):
+        """workspace_bytes: from fastcot_workspace_bytes_min on; by default room for the coded copies of the weights, and the least
+        where the GPU has no memory left for them."""
         torch = _torch()
         self.cfg = cfg
         self.packed = packed
         L = lib()
-        wbytes = L.fastcot_workspace_bytes(ctypes.byref(cfg))
+        wbytes = workspace_bytes or L.fastcot_workspace_bytes(ctypes.byref(cfg))
         if wbytes == 0:
             raise FastcotError(-1, "invalid configuration")
-        self.workspace = torch.empty(wbytes, dtype=torch.uint8, device="cuda")
+        try:
+            self.workspace = torch.empty(wbytes, dtype=torch.uint8, device="cuda")
+        except torch.cuda.OutOfMemoryError:
+            least = L.fastcot_workspace_bytes_min(ctypes.byref(cfg))
+            if workspace_bytes or least >= wbytes:
+                raise
+            wbytes = least
+            self.workspace = torch.empty(wbytes, dtype=torch.uint8, device="cuda")
         torch.cuda.synchronize()                     # packing ran on torch's current stream
         self.stream = torch.cuda.Stream()            # a capturable stream of its own, default priority
         self.h = vp()

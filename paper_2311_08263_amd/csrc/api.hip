@@ -45,6 +45,7 @@ struct fastcot_ctx {
     std::vector<hipEvent_t> step_ev;
     std::vector<float> step_ms;
     int32_t* pinned;     // small pinned host block for polling
+    int looked, coded;   // coded copies: looked at since the last prefill; made at some time (code_weights)
     char err[512];
 };
 
@@ -89,6 +90,28 @@ static const char* cfg_problem(const fastcot_config* c) {
     return nullptr;
 }
 static int valid_cfg(const fastcot_config* c) { return cfg_problem(c) == nullptr; }
+
+// Coded copies for the kernels of up to 32 rows, 13/16 of a matrix each, in a workspace of at most `room` bytes: the kinds of matrices
+// that fit with all their layers in the order of what a step spends on them, then as many layers of the others as fit.
+// (fastcot_workspace_bytes gives weights and workspace 208 GiB of the 288 GB a GPU has.  70B shapes: 129 GiB of weights, 104 of copies,
+// of which down gets those of a few layers.)
+static void place_copies(const ModelMap& m, const KernelDims& k, WorkspaceMap* wm, size_t room) {
+    const FusedMat* mats[5] = {&m.qkv, &m.o, &m.gu, &m.down, &m.lm};
+    const int order[5] = {2, 3, 4, 0, 1};
+    size_t cur = wm->base_total;
+    for (int i = 0; i < 5; ++i) { wm->code[i] = wm->code_stride[i] = 0; wm->code_layers[i] = 0; }
+    for (int some = 0; some < 2 && fc_fast_supported(k, 1); ++some)
+        for (int i : order) {
+            const size_t each = FC_ALIGN(wc_bytes(mats[i]->K, mats[i]->NP / 16));
+            const int all = i == 4 ? 1 : k.L;
+            const size_t fit = room > cur ? (room - cur) / each : 0;
+            if (wm->code_layers[i] || (!some && fit < (size_t)all)) continue;
+            wm->code[i] = cur; wm->code_stride[i] = each;
+            wm->code_layers[i] = fit < (size_t)all ? (int)fit : all;
+            cur += (size_t)wm->code_layers[i] * each;
+        }
+    wm->total = cur;
+}
 
 int fc_build_maps(const fastcot_config* c, ModelMap* mm, WorkspaceMap* wm, KernelDims* kd) {
     if (!valid_cfg(c)) return FASTCOT_EINVAL;
@@ -172,20 +195,10 @@ int fc_build_maps(const fastcot_config* c, ModelMap* mm, WorkspaceMap* wm, Kerne
         s.words = w;
         wm->st = s;
         wm->state = take((size_t)w * 4);
-        // Coded copies for the kernels of up to 32 rows: 13/16 of a matrix each, so where all of them would take weights and
-        // workspace past 208 GiB of the 288 GB a GPU has (70B shapes: 129 GiB of weights, 104 of copies), those that fit, the
-        // matrices in the order of what a step spends on them.
-        const FusedMat* mats[5] = {&m.qkv, &m.o, &m.gu, &m.down, &m.lm};
-        const int order[5] = {2, 3, 4, 0, 1};
         wm->code_record = take(8);
-        for (int i = 0; i < 5; ++i) wm->code[i] = wm->code_stride[i] = 0;
-        for (int i : order) {
-            const size_t each = FC_ALIGN(wc_bytes(mats[i]->K, mats[i]->NP / 16)), all = each * (i == 4 ? 1 : (size_t)k.L);
-            if (!fc_fast_supported(k, 1) || !all || m.total + cur + all > ((size_t)208 << 30)) continue;
-            wm->code_stride[i] = each;
-            wm->code[i] = take(all);
-        }
-        wm->total = cur;
+        wm->base_total = cur;
+        const size_t most = (size_t)208 << 30;
+        place_copies(m, k, wm, most > m.total ? most - m.total : 0);
     }
     return 0;
 }
@@ -197,6 +210,10 @@ extern "C" size_t fastcot_weight_bytes(const fastcot_config* cfg) {
 extern "C" size_t fastcot_workspace_bytes(const fastcot_config* cfg) {
     WorkspaceMap wm;
     return fc_build_maps(cfg, nullptr, &wm, nullptr) == 0 ? wm.total : 0;
+}
+extern "C" size_t fastcot_workspace_bytes_min(const fastcot_config* cfg) {
+    WorkspaceMap wm;
+    return fc_build_maps(cfg, nullptr, &wm, nullptr) == 0 ? wm.base_total : 0;
 }
 
 // ------------------------------------------------------------------ weight packing
@@ -300,13 +317,14 @@ extern "C" int fastcot_init(const fastcot_config* cfg, const void* d_packed, voi
     fastcot_ctx* c = new (std::nothrow) fastcot_ctx();
     if (!c) return fail(nullptr, FASTCOT_ENOMEM, "out of host memory%s");
     if (fc_build_maps(cfg, &c->mm, &c->wm, &c->kd) != 0) { delete c; return fail(nullptr, FASTCOT_EINVAL, "invalid configuration: %s", cfg_problem(cfg)); }
-    if (workspace_bytes < c->wm.total) { delete c; return fail(nullptr, FASTCOT_ECAPACITY, "workspace too small%s"); }
+    if (workspace_bytes < c->wm.base_total) { delete c; return fail(nullptr, FASTCOT_ECAPACITY, "workspace too small%s"); }
+    if (workspace_bytes < c->wm.total) place_copies(c->mm, c->kd, &c->wm, workspace_bytes);
     c->cfg = *cfg; c->weights = (const char*)d_packed; c->ws = (char*)d_workspace; c->st = (hipStream_t)hip_stream;
     c->Bact = 0; c->ctx_len = c->ctx_max = 0; c->graph_form = 0; c->prefilled = 0; c->generated = 0; c->buf_len = 0; c->opt_compact = 1;
     c->opt_packed = 1; c->rows_dirty = 1; c->rows_step = 0;
     c->opt_plain = (cfg->dtype == FASTCOT_F32); c->opt_graph = 1; c->dbg_stop = -1; c->dbg_logits = nullptr;
     c->graph_exec = nullptr; c->graph = nullptr; c->graph_valid = 0; c->prof_on = 0; c->prof_used = 0;
-    c->pinned = nullptr; c->err[0] = 0;
+    c->pinned = nullptr; c->err[0] = 0; c->looked = c->coded = 0;
     fc_fast_plan(c->kd, &c->plan);
     // rotary table: cos/sin of pos * base^(-2i/Dh), evaluated in double on the host
     const int half = c->kd.Dh / 2;
@@ -483,6 +501,32 @@ static int forward_plain(fastcot_ctx* c, int lmhead, int R, bool* accepted) {
     return 0;
 }
 
+// The coded copies of the weights (wcode.h): looked at in front of the first step since a prefill that reads them (up to 32 rows, not
+// on the plain kernels), made where they are not there or of other weights.  7B shape 13.2 GB of tiles, 7 ms; a look about
+// 10 us.  (Steps between a packing and the next prefill read the plain tiles: the kernels compare stamp and record themselves.  Contexts whose
+// steps have more rows never make them.)
+static int code_weights(fastcot_ctx* c, int rows) {
+    bool any = false;
+    for (int i = 0; i < 5; ++i) any = any || c->wm.code_layers[i];
+    if (c->looked || !any || c->opt_plain || rows > 32) return 0;
+    const char* stamp = c->weights + c->mm.stamp_off;
+    char* record = c->ws + c->wm.code_record;
+    HIPCHK(c, fc_stamp_look(stamp, record, c->pinned, c->st));
+    HIPCHK(c, hipStreamSynchronize(c->st));
+    if (c->pinned[0]) {
+        HIPCHK(c, fc_stamp_keep(stamp, record, 0, c->st));
+        const FusedMat* mats[5] = {&c->mm.qkv, &c->mm.o, &c->mm.gu, &c->mm.down, &c->mm.lm};
+        for (int i = 0; i < 5; ++i)
+            for (int l = 0; l < c->wm.code_layers[i]; ++l) {
+                const char* base = i == 4 ? c->weights : c->weights + c->mm.layers_off + (size_t)l * c->mm.layer_stride;
+                HIPCHK(c, fc_code(base + mats[i]->off, c->ws + c->wm.code[i] + (size_t)l * c->wm.code_stride[i], mats[i]->K, mats[i]->NP / 16, c->st));
+            }
+        HIPCHK(c, fc_stamp_keep(stamp, record, 1, c->st));
+    }
+    c->looked = c->coded = 1;
+    return 0;
+}
+
 // one forward pass over R rows per sequence (R = 0: the window); step: the pass of a Jacobi step, which computes
 // only the sequences' own rows when they have windows of their own
 static int forward(fastcot_ctx* c, int lmhead, int R = 0, bool step = false, bool* accepted = nullptr) {
@@ -497,7 +541,7 @@ static int forward(fastcot_ctx* c, int lmhead, int R = 0, bool step = false, boo
         a.kd.M = c->rows_step;
         a.rm = RowMap{stp + sm.rowb, stp + sm.rowj, stp + sm.rstart};
     }
-    a.mm = &c->mm; a.wm = &c->wm; a.weights = c->weights; a.ws = c->ws; a.dbg_logits = c->dbg_logits;
+    a.mm = &c->mm; a.wm = &c->wm; a.weights = c->weights; a.ws = c->ws; a.coded = c->coded != 0; a.dbg_logits = c->dbg_logits;
     a.plan = &c->plan; a.st = c->st; a.lmhead = lmhead;
     a.dbg_stop = c->dbg_stop; a.accept = accepted != nullptr; a.accepted = accepted;
     a.prof = c->prof_on ? c : nullptr;
@@ -544,8 +588,10 @@ static int rebuild_rows(fastcot_ctx* c) {
     return 0;
 }
 
+static int step_rows(const fastcot_ctx* c) { return c->rows_step > 0 ? c->rows_step : c->Bact * c->kd.W; }
 static int enqueue_step(fastcot_ctx* c) {
     if (c->rows_dirty) { int rc = rebuild_rows(c); if (rc) return rc; }
+    { int rc = code_weights(c, step_rows(c)); if (rc) return rc; }        // (in front of a capture)
     // the legacy default stream cannot be captured: launch kernel by kernel there
     if (!c->opt_graph || c->prof_on || c->st == nullptr) {
         const int rc = step_body(c);
@@ -578,31 +624,6 @@ static int enqueue_step(fastcot_ctx* c) {
 }
 
 // ------------------------------------------------------------------ prefill
-// The coded copies of the weights (wcode.h), made by a context's first prefill and again by one that finds other weights packed since.
-// A look at stamp and record takes about 10 us.  (Steps between the packing and that prefill read the plain tiles: the
-// kernels compare stamp and record themselves.)
-static int code_weights(fastcot_ctx* c) {
-    bool any = false;
-    for (int i = 0; i < 5; ++i) any = any || c->wm.code[i];
-    if (!any) return 0;
-    const char* stamp = c->weights + c->mm.stamp_off;
-    char* record = c->ws + c->wm.code_record;
-    HIPCHK(c, fc_stamp_look(stamp, record, c->pinned, c->st));
-    HIPCHK(c, hipStreamSynchronize(c->st));
-    if (!c->pinned[0]) return 0;
-    HIPCHK(c, fc_stamp_keep(stamp, record, 0, c->st));
-    const FusedMat* mats[5] = {&c->mm.qkv, &c->mm.o, &c->mm.gu, &c->mm.down, &c->mm.lm};
-    for (int i = 0; i < 5; ++i) {
-        if (!c->wm.code[i]) continue;
-        for (int l = 0; l < (i == 4 ? 1 : c->kd.L); ++l) {
-            const char* base = i == 4 ? c->weights : c->weights + c->mm.layers_off + (size_t)l * c->mm.layer_stride;
-            HIPCHK(c, fc_code(base + mats[i]->off, c->ws + c->wm.code[i] + (size_t)l * c->wm.code_stride[i], mats[i]->K, mats[i]->NP / 16, c->st));
-        }
-    }
-    HIPCHK(c, fc_stamp_keep(stamp, record, 1, c->st));
-    return 0;
-}
-
 // Passes of R rows per sequence over prompt tokens 0 .. maxlen-2 of the first B slots (the last prompt token
 // becomes slot 0 of the first window).  Enqueues only.  (The plain path took a window's rows per pass: a prompt of 32
 // tokens of the 256-wide model with window 8 was four passes of eleven launches, 379 us; one
@@ -674,7 +695,8 @@ extern "C" int fastcot_prefill(fastcot_ctx* c, int32_t B, const int32_t* prompts
     HIPCHK(c, hipMemsetAsync(stp + sm.wseq, 0, (size_t)kd.B * 4, c->st));
     if (B != c->Bact) drop_graph(c);
     c->Bact = B; c->buf_len = buf_len; c->prefilled = 0; c->generated = 0;
-    { int rc = code_weights(c); if (rc) return rc; }
+    c->looked = 0;
+    { int rc = code_weights(c, B * kd.W); if (rc) return rc; }            // for the steps (and a short prompt with them)
     { int rc = prefill_passes(c, B, maxlen); if (rc) return rc; }
     HIPCHK(c, hipStreamSynchronize(c->st));
     c->prefilled = 1;
@@ -1006,6 +1028,7 @@ extern "C" int fastcot_answer(fastcot_ctx* c, const int32_t* trigger_ids, int32_
     int32_t zeros[8] = {0};
     HIPCHK(c, hipMemcpy(stp + sm.flags, zeros, sizeof(zeros), hipMemcpyHostToDevice));
     c->prefilled = 0;        // the windowed state is gone: the next run starts with fastcot_prefill
+    { int rc = code_weights(c, B); if (rc) return rc; }
     // greedy decoding, one row per sequence and step; as many steps at a time as every unfinished sequence
     // still needs at least
     std::vector<int32_t> g2(B, 0), d2(B, 0);
@@ -1060,8 +1083,9 @@ extern "C" int fastcot_profile_step(fastcot_ctx* c, int32_t iters, float* mean_m
     if (!c->prefilled) return fail(c, FASTCOT_ESTATE, "fastcot_profile_step before fastcot_prefill%s");
     double sum[FASTCOT_N_KERNEL_KINDS] = {0}; long cnt[FASTCOT_N_KERNEL_KINDS] = {0};
     for (int it = 0; it < iters; ++it) {
-        c->prof_on = 1; c->prof_used = 0;
         int rc = c->rows_dirty ? rebuild_rows(c) : 0;
+        if (!rc) rc = code_weights(c, step_rows(c));
+        c->prof_on = 1; c->prof_used = 0;
         if (!rc) rc = forward(c, 1, 0, true);
         // what an event pair itself adds to a launch: the same pair around a kernel that does nothing
         if (!rc) {

@@ -134,7 +134,9 @@ struct WorkspaceMap {
     size_t x, qkv, qrot, att, h, logits, topv;
     size_t gemm_part, gemm_cnt, attn_part, attn_cnt, amax_part;
     size_t state;
-    size_t code[5], code_stride[5];   // coded copies of QKV, O, gate/up, down (layer l at code + l * stride) and the LM head; 0: none
+    size_t base_total;                // everything but the copies
+    size_t code[5], code_stride[5];   // coded copies of QKV, O, gate/up, down (layer l at code + l * stride) and the LM head
+    int32_t code_layers[5];           // ... of the first so many layers (the LM head: 1 or 0)
     size_t code_record;               // the stamp (ModelMap) of the weights the copies were made from; its complement: there are none yet
     size_t total;
     size_t gemm_part_bytes, attn_part_bytes;

@@ -34,6 +34,7 @@ struct FastArgs {
     RowMap rm = RowMap{nullptr, nullptr, nullptr};   // packed rows of a step with per-sequence windows (kd.M = their sum, kd.W = the largest)
     bool accept = false;   // the pass is a Jacobi step: the accept step follows the argmax, in the same launch where that pays ...
     bool* accepted = nullptr;   // ... and *accepted says whether it did
+    bool coded = false;    // the coded copies of the weights have been made
     int dbg_stop;      // debug: number of stages to run (5 per layer), < 0 = all
 };
 

@@ -194,7 +194,7 @@ hipError_t fc_fast_forward(const FastArgs& a) {
         const int ksl = M <= 16 ? a.plan->ks[gi] : a.plan->ks2[gi];
         if (nw > 0) {
             co.W = (const bf16_t*)W; co.K = K; co.NT = N / 16; co.X = X; co.ldx = ldx; co.gain = gain; co.out = out; co.ldo = ldo;
-            co.C = wm.code[gi] ? ws + wm.code[gi] + (size_t)g.layer * wm.code_stride[gi] : nullptr;
+            co.C = a.coded && g.layer < wm.code_layers[gi] ? ws + wm.code[gi] + (size_t)g.layer * wm.code_stride[gi] : nullptr;
             co.layer = g.layer; co.ks = epi != EPI_LMHEAD ? ksl : 1; co.hi_only = (kd.actq >> gi) & 1;
             co.single_buffer = a.plan->co_single == 2 ? a.plan->co_sb[M > 16][gi] : a.plan->co_single;
             co.rotate = a.plan->co_rot[M > 16][gi];

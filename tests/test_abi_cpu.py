@@ -116,3 +116,23 @@ def test_end_of_a_step_in_one_launch_where_that_is_faster():
     for M, parts in ((1, 512), (16, 257), (17, 129), (32, 256), (33, 16)):
         assert not fits(2, M, M, parts, True)
     assert fits(4, 256, 10, 64, True) and not fits(4, 257, 10, 64, True)
+
+
+def test_workspaces_with_and_without_copies_of_the_weights():
+    """Copies in 13 bits a weight of every matrix; of the 70B shape, where weights and workspace may have 208 GiB, as many layers as
+    fit; none for fp32 models."""
+    L = binding.lib()
+
+    def sizes(name, B=1, S=640, W=16):
+        c = binding.Config.from_shape(synthgen.SHAPES[name], B, S, W)
+        return L.fastcot_weight_bytes(ctypes.byref(c)), L.fastcot_workspace_bytes_min(ctypes.byref(c)), L.fastcot_workspace_bytes(ctypes.byref(c))
+    for name in ("7b", "13b"):
+        _, least, full = sizes(name)
+        streamed = synthgen.SHAPES[name].n_params_streamed() * 13 / 8
+        assert streamed < full - least < streamed * 1.01
+    s = synthgen.SHAPES["70b"]
+    for B, S in ((1, 640), (8, 4096)):
+        weights, least, full = sizes("70b", B, S)
+        assert least < full and 0 <= (208 << 30) - weights - full < s.d_ffn * s.d_model * 13 / 8 * 1.01
+    assert sizes("70b", 32, 8192)[1] == sizes("70b", 32, 8192)[2]
+    assert sizes("tiny")[1] == sizes("tiny")[2]

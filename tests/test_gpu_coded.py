@@ -287,3 +287,75 @@ def test_plan_options_take_what_a_launch_takes(fc):
     for refused in (((NW, fewest - 1),), ((NW, NT + 1),), ((KS, 2),), ((KS, 9),)):
         with pytest.raises(fc.FastcotError):
             logits(*refused)
+
+
+SMALL = (2, 512, 4, 2, 768, 1008)
+
+
+def small_cfg(fc, B, W):
+    L, d, H, Hkv, F, V = SMALL
+    return fc.Config(L, d, H, Hkv, 128, F, V, 1e-5, 1e4, 1, B, 128, W)
+
+
+def sizes(fc, cfg):
+    return fc.lib().fastcot_workspace_bytes_min(ctypes.byref(cfg)), fc.lib().fastcot_workspace_bytes(ctypes.byref(cfg))
+
+
+def test_workspaces_without_room_for_every_copy(fc, monkeypatch):
+    """From the least workspace on any size does, with the same logits (weights of this kind have no pairs of their own place in the order of
+    additions); less is refused; without memory for the copies a context takes the least."""
+    import torch
+    cfg = small_cfg(fc, 1, 8)
+    packed, (least, full) = pack(fc, cfg, tensors(SMALL, "none", 3)), sizes(fc, cfg)
+    r = np.random.RandomState(5)
+    prompts, buf = r.randint(0, 1008, (1, 21)).astype(np.int32), r.randint(0, 1008, (1, 24)).astype(np.int32)
+    want = first_logits(fc.Context(cfg, packed), prompts, buf, 8)
+    for n in (least, least + 1, least + (full - least) // 3, (least + full) // 2, full - 1, full + 4096):
+        say(f"workspace of {n} bytes, {least} to {full}")
+        ctx = fc.Context(cfg, packed, n)
+        assert ctx.workspace.numel() == n and torch.equal(first_logits(ctx, prompts, buf, 8), want)
+    with pytest.raises(fc.FastcotError):
+        fc.Context(cfg, packed, least - 1)
+    empty = torch.empty
+
+    def short(n, *a, **k):
+        if n == full:
+            raise torch.cuda.OutOfMemoryError("no room")
+        return empty(n, *a, **k)
+    monkeypatch.setattr(torch, "empty", short)
+    ctx = fc.Context(cfg, packed)
+    assert ctx.workspace.numel() == least and torch.equal(first_logits(ctx, prompts, buf, 8), want)
+
+
+@pytest.mark.parametrize("B,W,plain", [(1, 8, 0), (1, 8, 1), (3, 12, 0)])
+def test_copies_are_made_where_steps_read_them(fc, B, W, plain):
+    """Steps of up to 32 rows by the matrix-core kernels: made by the prefill; the plain kernels and steps of more rows: never; made by the
+    first step that has few rows because its sequences have windows of their own."""
+    import torch
+    say(f"copies made B={B} W={W} plain={plain}")
+    cfg = small_cfg(fc, B, W)
+    packed, (least, full) = pack(fc, cfg, tensors(SMALL, "none", 3)), sizes(fc, cfg)
+    r = np.random.RandomState(5)
+    prompts, buf = r.randint(0, 1008, (B, 21)).astype(np.int32), r.randint(0, 1008, (B, 5 * W)).astype(np.int32)
+    ctx = fc.Context(cfg, packed)
+    ctx.set_option(fc.binding.OPT_PLAIN_KERNELS, plain)
+    ctx.workspace[least:] = 0x5A
+    torch.cuda.synchronize()
+    ctx.prefill(prompts, [21] * B, buf)
+    if plain or B * W > 32:
+        ctx.step()
+        assert bool((ctx.workspace[least:] == 0x5A).all())
+    else:
+        assert float((ctx.workspace[least:] != 0x5A).float().mean()) > 0.9
+    if B * W > 32:
+        ctx.set_windows([4] * B)
+        logits = ctx.debug_logits(True)
+        ctx.step()
+        assert float((ctx.workspace[least:] != 0x5A).float().mean()) > 0.9
+        got = logits[:4 * B].clone()
+        ref = fc.Context(cfg, packed, least)
+        ref.prefill(prompts, [21] * B, buf)
+        ref.step(); ref.set_windows([4] * B)
+        logits = ref.debug_logits(True)
+        ref.step()
+        assert torch.equal(got, logits[:4 * B])
