@@ -74,8 +74,7 @@ typedef struct fastcot_ctx fastcot_ctx;
  * fastcot_prefill that finds that fastcot_pack_tensor or fastcot_pack_weights wrote to the packed weights in between, or that a whole packed
  * buffer was copied over them; until then passes read the packed weights themselves.
  * fastcot_workspace_bytes_min is the workspace without that room: fastcot_init takes any size from there on, and copies what fits.  Passes
- * read the other matrices as they were packed: slower (7B step of 16 rows 11 %), with the same results save for the order in which
- * some products are added (matrices of which 13 bits do not hold every weight). */
+ * read the other matrices as they were packed: slower (7B step of 16 rows 10 %), with the same products in another order of additions. */
 size_t fastcot_weight_bytes(const fastcot_config* cfg);
 size_t fastcot_workspace_bytes(const fastcot_config* cfg);
 size_t fastcot_workspace_bytes_min(const fastcot_config* cfg);
@@ -204,7 +203,7 @@ int fastcot_debug_logits(fastcot_ctx* ctx, float* d_logits);
  * they trade slots (state and K/V cache) with unfinished ones so that the following steps run only the
  * unfinished sequences' rows; the order is restored before it returns.  0: finished sequences keep their rows.
  * FASTCOT_OPT_AUTOTUNE: accepted and without effect.  (The first fastcot_prefill used to time launches of the column-owner GEMMs;
- * everything about them now follows from the shape, and logits are the same bits in every process.)
+ * everything about them now follows from the shape and the size of the workspace, and logits are the same bits in every process.)
  * FASTCOT_OPT_KV_EMULATE (bf16 models, matrix-core kernels; a precision study, not a storage mode): value =
  * K mode + 16 * V mode; before a K (V) value is cached it is rounded as a narrower storage format would round it
  * (mode 0 as computed, 1 bf16, 2 fp16, 3 the upper 24 bits of fp32) and then kept in the two planes as usual, so
@@ -226,7 +225,8 @@ enum { FASTCOT_OPT_PLAIN_KERNELS = 1, FASTCOT_OPT_GRAPH = 2, FASTCOT_OPT_KV_PLAN
  * meet through memory and the last to arrive adds them in slice order.  The workgroup count must be a multiple.
  * FASTCOT_PLAN_SB + g: pairs of k-tiles under way per wave: 0 two, 1 one (more where a workgroup owns one or two n-tiles), 2 (default)
  * by the n-tiles a workgroup owns.
- * FASTCOT_PLAN_ROT + g: 1 = every wave walks its part of K in an order rotated by workgroup and wave (default 0).
+ * FASTCOT_PLAN_ROT + g: 1 = every wave walks its part of K in an order rotated by workgroup and wave, 0 = in order (unset: by what it reads,
+ * the copies in order).
  * FASTCOT_PLAN_CO_SINGLE: 0 / 1 = two / one pair under way for every GEMM, 2 (default) = per GEMM (PLAN_SB).
  * FASTCOT_PLAN_ATTN_SPLITS: key-range splits the attention launch provides (1..16), the same for every unit of it.  (Unset,
  * a launch of more units than compute units may run the last ones in key splits while the others stay whole.)

@@ -12,7 +12,7 @@ struct FastPlan {
     int32_t attn_many; // many-row attention kernel (attnp.hip): 0 never, 1 where it gives half of the CUs a workgroup, 2 for every pass of more than 32 rows per sequence
     int32_t co_single; // column-owner GEMM: pairs of k-tiles under way per wave for every GEMM as co_sb below; 2 = per GEMM (co_sb)
     int32_t co_sb[2][5];   // ... for up to 16 rows [0] and 17..32 rows [1]: 0 two, 1 one, 2 by the n-tiles a workgroup owns
-    int32_t co_rot[2][5];  // per GEMM: walk the pairs in an order rotated by workgroup and wave (0: in order)
+    int32_t co_rot[2][5];  // per GEMM: walk the pairs in an order rotated by workgroup and wave: 0 no, 1 yes, 2 plain tiles of up to eight n-tiles per workgroup
     int32_t ks[5];     // column-owner GEMM: K slices per owner (residual GEMMs only; 1 elsewhere)
     int32_t nw2[5], ks2[5];   // the same for passes of 17..32 rows (two row tiles per workgroup)
     int32_t nw[5];     // column-owner GEMM: workgroups for QKV, O, gate/up, down, LM head

@@ -48,7 +48,7 @@ void fc_fast_plan(const KernelDims& kd, FastPlan* p) {
     // heads of their own slices lose (eight 4096-wide layers 853 -> 871)
     if (kd.d >= 8192 && nts[0] < 3 * fc_num_cus() && p->nw[0] % 2 == 0 && (nts[0] + p->nw[0] / 2 - 1) / (p->nw[0] / 2) <= 8) p->ks[0] = 2;
     p->co_single = 2;
-    for (int i = 0; i < 5; ++i) p->co_sb[0][i] = p->co_sb[1][i] = 2;
+    for (int i = 0; i < 5; ++i) p->co_sb[0][i] = p->co_sb[1][i] = p->co_rot[0][i] = p->co_rot[1][i] = 2;
     if (p->ks[1] == 4) p->ks_rule[1] = 4;
     // 17..32 rows (two row tiles per workgroup, up to 16 output tiles): the same grids where the partial tiles
     // fit the LDS, K slices halved until they divide the grid
@@ -382,7 +382,7 @@ hipError_t fc_lmhead_iso(const float* act, const void* packed, int M, int d, int
     const int nwg = lm_iso_grid(M, d, V), stride = M > 16 ? 32 : 16;
     co.W = (const bf16_t*)packed; co.C = (const char*)packed + wc_off(d, V / 16); co.K = d; co.NT = V / 16; co.X = act; co.ldx = d; co.M = M; co.out = logits; co.ldo = V;
     co.stamp = co.record = (const uint64_t*)packed;        // (the copy was packed with the tiles)
-    co.single_buffer = 2;
+    co.single_buffer = co.rotate = 2;
     co.amax_val = (float*)sc;
     co.amax_idx = (int32_t*)(co.amax_val + (size_t)nwg * stride);
     hipError_t e = fc_gemmco(EPI_LMHEAD, co, nwg, st);

@@ -26,7 +26,7 @@ struct GemmCoArgs {
                            // workgroup's share of the row sums of squares [workgroup][16 or 32]
     int32_t* xcnt;         // ks > 1: one arrival counter per owner, zero between launches
     int32_t hi_only;       // precision study: the activations enter as plain bf16 (their lo halves dropped)
-    int32_t rotate;        // walk the pairs of k-tiles in a per-wave rotated order (a measurement aid: in order is as fast or faster everywhere)
+    int32_t rotate;        // walk the pairs of k-tiles in a per-wave rotated order: 0 no, 1 yes, 2 by a rule (fc_gemmco)
     int32_t gain_wave;     // set by the launch: floats of the gain a wave keeps in LDS
     int32_t single_buffer; // pairs of k-tiles under way per wave: 0 two, 1 one, 2 by the n-tiles a workgroup owns
 };

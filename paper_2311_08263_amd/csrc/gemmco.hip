@@ -54,7 +54,14 @@ hipError_t fc_gemmco(int epi, const GemmCoArgs& a, int G, hipStream_t st) {
     if (!fc_gemmco_fits(a.M, a.K, a.NT, G, ks, a.gain != nullptr)) return hipErrorInvalidValue;
     if (epi != EPI_LMHEAD && (a.gain != nullptr) != co_gained(epi)) return hipErrorInvalidValue;          // (no norm in front of an adding product, one in front of the others)
     if (ks > 1 && (epi == EPI_LMHEAD || !a.xpart || !a.xcnt)) return hipErrorInvalidValue;
-    return a.C ? fc_gemmco_coded(epi, a, G, st) : launch_co<WPlain>(epi, a, G, st);
+    // Plain tiles of up to eight n-tiles per workgroup are walked in rotated order: the slices of different workgroups start at addresses that
+    // differ by multiples of K * 32 bytes, in step they would all sit on the same memory channels.  us a launch in order / rotated, 16 rows:
+    // down of the 7B / 13B / 70B shape 24.6 / 22.3, 30.6 / 31.0, 78.6 / 75.2 (24 rows 86.4 / 79.3), O 13.2 / 12.7, 16.4 / 16.3, 31.4 / 28.0, QKV
+    // 23.2 / 23.0, 33.5 / 32.1, 37 / 35.8, gate/up 36.6 / 36.5, 54 / 50.4, LM head 49.1 / 45.1, 55.7 / 56.5, 86.8 / 83.0; with 14 n-tiles per workgroup
+    // (70B gate/up) 141.3 / 143.3.  Coded pairs are 1664 bytes, so that the slices fall on different channels by themselves: as fast or faster in order.
+    GemmCoArgs b = a;
+    if (a.rotate == 2) b.rotate = !a.C && (a.NT + G / ks - 1) / (G / ks) <= 8;
+    return b.C ? fc_gemmco_coded(epi, b, G, st) : launch_co<WPlain>(epi, b, G, st);
 }
 
 // reduction of the LM head's per-workgroup winners: lowest id on ties

@@ -69,8 +69,7 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
     const int s_lo = (int)((unsigned)PT * (unsigned)slice / (unsigned)ks), s_len = (int)((unsigned)PT * (unsigned)(slice + 1) / (unsigned)ks) - s_lo;
     const int p_begin = s_lo + ((w * s_len) >> 3), n = ((s_lo + (((w + 1) * s_len) >> 3))) - p_begin;
     // With a.rotate every wave walks its pairs in a rotated order that differs from wave to wave and
-    // workgroup to workgroup: the slices of different workgroups start at addresses that differ by multiples
-    // of K * 32 bytes, so in step they would all sit on the same memory channels.
+    // workgroup to workgroup (fc_gemmco).
     const int rot = (a.rotate && n > 0) ? (int)(((unsigned)blockIdx.x * 7u + (unsigned)w * 3u) % (unsigned)n) : 0;
     auto pair_no = [&](int i) { const int r = i + rot; return p_begin + (r >= n ? r - n : r); };      // i < n
     uint32_t xoff[MT];                                  // byte offsets of this lane's rows and octet; rows past M repeat a valid row, never written

@@ -302,8 +302,8 @@ def sizes(fc, cfg):
 
 
 def test_workspaces_without_room_for_every_copy(fc, monkeypatch):
-    """From the least workspace on any size does, with the same logits (weights of this kind have no pairs of their own place in the order of
-    additions); less is refused; without memory for the copies a context takes the least."""
+    """From the least workspace on any size does, with the same logits but for the order of additions (fp32 sums of 17-bit activations times
+    weights: 1e-5 as between grids); less is refused; without memory for the copies a context takes the least."""
     import torch
     cfg = small_cfg(fc, 1, 8)
     packed, (least, full) = pack(fc, cfg, tensors(SMALL, "none", 3)), sizes(fc, cfg)
@@ -313,7 +313,8 @@ def test_workspaces_without_room_for_every_copy(fc, monkeypatch):
     for n in (least, least + 1, least + (full - least) // 3, (least + full) // 2, full - 1, full + 4096):
         say(f"workspace of {n} bytes, {least} to {full}")
         ctx = fc.Context(cfg, packed, n)
-        assert ctx.workspace.numel() == n and torch.equal(first_logits(ctx, prompts, buf, 8), want)
+        got = first_logits(ctx, prompts, buf, 8)
+        assert ctx.workspace.numel() == n and float(torch.linalg.norm(got - want) / torch.linalg.norm(want)) < 1e-5
     with pytest.raises(fc.FastcotError):
         fc.Context(cfg, packed, least - 1)
     empty = torch.empty
@@ -324,7 +325,8 @@ def test_workspaces_without_room_for_every_copy(fc, monkeypatch):
         return empty(n, *a, **k)
     monkeypatch.setattr(torch, "empty", short)
     ctx = fc.Context(cfg, packed)
-    assert ctx.workspace.numel() == least and torch.equal(first_logits(ctx, prompts, buf, 8), want)
+    got = first_logits(ctx, prompts, buf, 8)
+    assert ctx.workspace.numel() == least and torch.equal(got, first_logits(fc.Context(cfg, packed, least), prompts, buf, 8))
 
 
 @pytest.mark.parametrize("B,W,plain", [(1, 8, 0), (1, 8, 1), (3, 12, 0)])
@@ -358,4 +360,4 @@ def test_copies_are_made_where_steps_read_them(fc, B, W, plain):
         ref.step(); ref.set_windows([4] * B)
         logits = ref.debug_logits(True)
         ref.step()
-        assert torch.equal(got, logits[:4 * B])
+        assert float(torch.linalg.norm(got - logits[:4 * B]) / torch.linalg.norm(got)) < 1e-5
