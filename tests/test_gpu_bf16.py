@@ -120,7 +120,7 @@ def test_three_byte_kv_cache(fc, shape, B, W, P, plain):
 
 @pytest.mark.parametrize("W", [16, 24])
 def test_without_autotune(fc, W):
-    """The plan's defaults (no timing runs at prefill) pass the same bar as the measured plan."""
+    """The option that used to switch timing runs at prefill off is still accepted and has no effect: same bar as everywhere, bits of the default."""
     shape, B, P, N = SMALL, 2, 37, 48
     say(f"bf16 follow without autotune W={W}")
     S = ((P + N + 2 * W + 31) // 32) * 32
@@ -132,6 +132,16 @@ def test_without_autotune(fc, W):
     ctx.prefill(prompts, lens, buf)
     r = follow_steps(ctx, om, prompts, lens, 4, TOL)
     assert r["max_err"] < 2e-3
+    logits = []
+    for off in (0, 1):
+        ctx = fc.Context(ctx.cfg, ctx.packed)
+        if off:
+            ctx.set_option(fc.binding.OPT_AUTOTUNE, 0)
+        ctx.prefill(prompts, lens, buf)
+        dbg = ctx.debug_logits(True)
+        ctx.step()
+        logits.append(dbg.clone())
+    assert bool((logits[0] == logits[1]).all())
 
 
 def test_fast_path_matches_plain_path_and_oracle_stream(fc):
@@ -315,9 +325,8 @@ def test_deterministic_replay(fc):
 @pytest.mark.parametrize("shape,B,W", [(synthgen.small_variant(synthgen.SHAPES["7b"], n_layers=3), 1, 16),
                                        (synthgen.small_variant(synthgen.SHAPES["13b"], n_layers=2), 1, 32)])
 def test_fresh_contexts_give_identical_bits(fc, shape, B, W):
-    """Same inputs, same logits bits, same verified counts and lengths in any context: three contexts, each
-    measuring its own launch plan at its first prefill (the measurement may come out differently each time; it
-    only moves loads)."""
+    """Same inputs, same logits bits, same verified counts and lengths in any context: three contexts, the second and third with two and
+    with one pair of k-tiles under way in every product of up to 32 rows (that only moves loads)."""
     import torch
     P, N = 70, 32
     S = ((P + N + 2 * W + 31) // 32) * 32
@@ -329,6 +338,8 @@ def test_fresh_contexts_give_identical_bits(fc, shape, B, W):
     for variant in range(3):
         say(f"fresh context {variant}: d={shape.d_model} W={W}")
         ctx = fc.Context(cfg, packed)
+        if variant:
+            ctx.set_option(fc.binding.PLAN_CO_SINGLE, variant - 1)
         ctx.prefill(prompts, [P] * B, buf)
         dbg = ctx.debug_logits(True)
         steps = []

@@ -17,8 +17,17 @@ def fc():
     return m
 
 
+def edge_rows(d):
+    """Rows of two pairs of wave 0, of three of wave 1 and, where it has them, of the first and the 65th pair of wave 3 (no K slices)."""
+    PT = d // 64
+    begin = [w * PT // 8 for w in range(9)]
+    pairs = [(0, 0), (0, 1), (1, 0), (1, 1), (1, 2)] + ([(3, 0), (3, 64)] if begin[4] - begin[3] > 64 else [])
+    return [64 * (begin[w] + i) + 9 * (w + 1) for w, i in pairs]
+
+
 def special(w, kind, seed):
-    """Weights outside their columns' windows: few (flagged pairs taken one by one), many (whole walks over the plain tiles), columns of
+    """Weights outside their columns' windows: few (flagged pairs taken one by one), edge (two flagged pairs of a wave are taken one by one, three
+    are not; where waves have more than 64 pairs, the first and the 65th share a bit), many (whole walks over the plain tiles), columns of
     zeros, tiny or huge ones, a column whose largest weight leaves all others outside; zeros, which have a code of their own."""
     import torch
     g = torch.Generator(device="cuda"); g.manual_seed(seed)
@@ -27,6 +36,9 @@ def special(w, kind, seed):
         for i in range(6):
             w[(i * 7919 + 5) % d, (i * 104729 + 3) % V] = 2.0 ** -60
         w[d - 1, V - 1] = -0.0; w[0, 0] = 2.0 ** -100
+    elif kind == "edge":
+        for k in edge_rows(d):
+            w[k, k // 64 % 8] = 2.0 ** -60
     elif kind == "many":
         w[torch.rand(d, V, generator=g, device="cuda") < 0.5] = 2.0 ** -60
     elif kind == "zeros":
@@ -43,7 +55,7 @@ def special(w, kind, seed):
 @pytest.mark.parametrize("kind", ["none", "few", "many", "zeros", "columns"])
 @pytest.mark.parametrize("M,d,V", [(16, 256, 16), (16, 512, 592), (5, 768, 4112), (32, 1024, 2000), (17, 256, 8208)])
 def test_every_weight_comes_out_as_it_went_in(fc, kind, M, d, V):
-    """One to eight n-tiles per workgroup, waves of no, one and two pairs of k-tiles, one and two row tiles."""
+    """One to three n-tiles per workgroup (256 CUs), waves of no, one and two pairs of k-tiles, one and two row tiles; every row."""
     import torch
     say(f"coded weights {kind} M={M} d={d} V={V}")
     g = torch.Generator(device="cuda"); g.manual_seed(7)
@@ -51,6 +63,26 @@ def test_every_weight_comes_out_as_it_went_in(fc, kind, M, d, V):
     packed = fc.lmhead_pack(w)
     scratch = torch.zeros(fc.lib().fastcot_lmhead_scratch_bytes(M, d, V), dtype=torch.uint8, device="cuda")
     for k0 in range(0, d, M):
+        act = torch.zeros(M, d, device="cuda")
+        rows = torch.arange(k0, min(k0 + M, d), device="cuda")
+        act[torch.arange(len(rows), device="cuda"), rows] = 1.0
+        _, _, logits = fc.lmhead_argmax(act, packed, V, True, scratch)
+        assert torch.equal(logits[:len(rows)], w[rows].float()), k0
+
+
+@pytest.mark.parametrize("kind", ["few", "edge", "many", "columns"])
+@pytest.mark.parametrize("M,d,V", [(16, 4096, 16 * 1000), (5, 4096, 16 * 1300), (16, 4096, 16 * 1800), (16, 4096, 16 * 2900), (16, 4096, 16 * 3400), (24, 4096, 16 * 1000),
+                                   (32, 4096, 16 * 1300), (17, 4096, 16 * 1800), (16, 33280, 16 * 20), (32, 33280, 16 * 300)])
+def test_weights_of_wide_workgroups(fc, kind, M, d, V):
+    """Four, six, eight, twelve and fourteen n-tiles per workgroup (256 CUs) up to 16 rows, four, six and eight of more, waves of eight pairs; waves
+    of 65 pairs.  The rows that hold weights outside the windows, the first and the last ones."""
+    import torch
+    say(f"wide workgroups {kind} M={M} d={d} V={V}")
+    g = torch.Generator(device="cuda"); g.manual_seed(7)
+    w = special((0.02 * torch.randn(d, V, generator=g, device="cuda")).bfloat16(), kind, 11)
+    packed = fc.lmhead_pack(w)
+    scratch = torch.zeros(fc.lib().fastcot_lmhead_scratch_bytes(M, d, V), dtype=torch.uint8, device="cuda")
+    for k0 in sorted({k // M * M for k in [0, 1, 3, d - 1] + [(i * 7919 + 5) % d for i in range(6)] + edge_rows(d)}):
         act = torch.zeros(M, d, device="cuda")
         rows = torch.arange(k0, min(k0 + M, d), device="cuda")
         act[torch.arange(len(rows), device="cuda"), rows] = 1.0
@@ -113,6 +145,36 @@ def test_steps_on_coded_weights(fc, kind, B, W):
         ctx.close() if hasattr(ctx, "close") else None
     a, b = out[0].double(), out[1].double()
     assert float(torch.linalg.norm(a - b) / torch.linalg.norm(b)) < 1e-4
+
+
+@pytest.mark.parametrize("kind", ["few", "many"])
+@pytest.mark.parametrize("W", [16, 24])
+@pytest.mark.parametrize("copies", [0, 1])
+def test_orders_of_a_walk(fc, kind, W, copies):
+    """Pairs of k-tiles under way (two, one) move loads and no bits; a walk in rotated order, or in order where it is rotated by default, moves
+    additions alone (fp32 sums, 1e-5), with K slices, flagged pairs and plain walks, over the copies and without them."""
+    import torch
+    shape = (2, 4096, 32, 8, 8192, 1008)
+    L, d, H, Hkv, F, V = shape
+    cfg = fc.Config(L, d, H, Hkv, 128, F, V, 1e-5, 1e4, 1, 1, 128, W)
+    packed = pack(fc, cfg, tensors(shape, kind, 3))
+    r = np.random.RandomState(5)
+    prompts, buf = r.randint(0, V, (1, 21)).astype(np.int32), r.randint(0, V, (1, 3 * W)).astype(np.int32)
+
+    def logits(*opts):
+        say(f"order of a walk {kind} W={W} copies={copies} {opts}")
+        ctx = fc.Context(cfg, packed, None if copies else sizes(fc, cfg)[0])
+        for o in opts:
+            ctx.set_option(*o)
+        out = first_logits(ctx, prompts, buf, W)
+        ctx.close()
+        return out
+    default = logits()
+    for n in (0, 1):
+        assert torch.equal(logits((fc.binding.PLAN_CO_SINGLE, n)), default)
+        other = logits(*[(fc.binding.PLAN_ROT + g, n) for g in range(5)])
+        assert float(torch.linalg.norm(other - default) / torch.linalg.norm(default)) < 1e-5
+        assert torch.equal(other, default) == (n == 1 - copies)
 
 
 def test_weights_packed_again_are_coded_again(fc):
