@@ -24,9 +24,9 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 matrix cores, published
 # HBM bytes per launch of the dominant kernel from rocprofv3 FETCH_SIZE + WRITE_SIZE, scaled by a plain
-# copy kernel of known size (profiles/hbm_traffic_7b_w16.md, hbm_traffic_13b_b8_w32.md); None where no counter
-# run exists
-MEASURED_TRAFFIC = {("7b", "gemm_gate_up"): 183.5e6, ("13b", "gemm_gate_up"): 400.1e6, ("70b", "gemm_gate_up"): 945.8e6}
+# copy kernel of known size (profiles/hbm_traffic_*.md); None where no counter run exists.  Steps of up to 32 rows read a lossless copy of
+# the weights in 13 bits each, so their traffic is less than the bytes_per_launch (2 per weight) that achieved and frac are stated in
+MEASURED_TRAFFIC = {("7b", "gemm_gate_up"): 150.35e6, ("13b", "gemm_gate_up"): 339.8e6, ("70b", "gemm_gate_up"): 770.6e6}
 WORKLOADS = {
     # name: (shape, batch, prompt, window, new tokens)
     "7b": ("7b", 1, 256, 16, 256),
@@ -443,7 +443,7 @@ def main():
     dom = max(cands, key=lambda t: t[1] * t[2])
     achieved = dom[3] / (dom[1] * 1e-3) / 1e9
     roofline = {"bound": "hbm", "kernel": dom[0], "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": MEASURED_TRAFFIC.get((args.workload, dom[0])),
+                "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None if args.plain else MEASURED_TRAFFIC.get((args.workload, dom[0])),
                 "bytes_per_launch": dom[3], "avg_launch_ms": round(dom[1], 5),
                 "step_algorithmic_bytes": int(alg), "step_frac": round(step_gbs / HBM_PEAK_GBS, 4)}
     if B * W > 32 and not args.plain:
@@ -453,9 +453,12 @@ def main():
         flops = 2.0 * B * W * dom[3] / esz
         tf = flops / (dom[1] * 1e-3) / 1e12
         roofline = {"bound": "mfma", "kernel": dom[0], "achieved": round(tf, 1), "peak": MFMA_BF16_PEAK_TFLOPS,
-                    "unit": "TFLOP/s", "frac": round(tf / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": MEASURED_TRAFFIC.get((args.workload, dom[0])),
+                    "unit": "TFLOP/s", "frac": round(tf / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": None if args.plain else MEASURED_TRAFFIC.get((args.workload, dom[0])),
                     "flops_per_launch": flops, "issued_flops_per_launch": 2 * flops, "avg_launch_ms": round(dom[1], 5),
                     "step_algorithmic_bytes": int(alg), "step_hbm_frac": round(step_gbs / HBM_PEAK_GBS, 4)}
+
+    if roofline["traffic"]:
+        roofline["traffic_frac"] = round(roofline["traffic"] / (dom[1] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)     # bytes really moved, of 8 TB/s
 
     # launch durations above are HIP-event intervals, which start when the previous event completes: they
     # contain the launch latency that a profiler's begin-to-end duration leaves out.  The same pair around an
