@@ -32,20 +32,25 @@ void fc_fast_plan(const KernelDims& kd, FastPlan* p) {
     const int nts[5] = {kd.qkvN / 16, kd.d / 16, 2 * kd.F / 16, kd.d / 16, kd.V / 16};
     // measured on the 7B shape: one workgroup per CU
     for (int i = 0; i < 5; ++i) { p->nw[i] = fc_gemmco_grid(nts[i], 8, i != 1 && i != 3); p->ks[i] = 1; }
-    // K slices per owner cut the activations a workgroup reads and cost a meeting of the slices in memory.
+    // K slices per owner cut the activations a workgroup reads and cost a meeting of the slices in memory.  (Contexts of one plan differ by up
+    // to 1 % with where their copies lie, at some widths by 5: the lines are drawn where several shapes agree, not at the best of each.)
     if (nts[1] <= 512) {                 // O projection with at most two n-tiles per CU
-        // two K slices per owner, four from 4096 inputs on (steps of up to 16 rows with one / two / four slices, us: eight
-        // 4096-wide layers 874 / 874 / 869, six 5120-wide 895 / 888 / 886, two 8192-wide 647 / 642 / 644, eight 2048-wide 526 / 519 / 522)
+        // two K slices per owner, four from 4096 inputs on.  Steps with one / two / four slices, us, 16 rows: eight 4096-wide layers 736 / 729 /
+        // 720, with grouped K/V heads 806 / 796 / 776, four 6144-wide 594 / 592 / 581, six 5120-wide 723 / 705 / 716, two 8192-wide 561 / 552 /
+        // 551, three 9216-wide 923 / 914 / 912; one row 659 / 661 / 663, 696 / 721 / 716, 542 / 533 / 538, 641 / 628 / 641, 504 / 507 / 508,
+        // 833 / 830 / 839: what sixteen rows gain a single one nearly loses.  Twelve 2048-wide layers 687 / 670 / 659, 585 / 594 / 610.
         const int G = p->nw[1], K = kd.H * kd.Dh;
         if (G % 2 == 0 && G / 2 <= nts[1] && (nts[1] + G / 2 - 1) / (G / 2) <= 8 && K >= 2048) p->ks[1] = 2;
         if (p->ks[1] == 2 && G % 4 == 0 && (nts[1] + G / 4 - 1) / (G / 4) <= 8 && K >= 4096) p->ks[1] = 4;
     }
     // down projection: K is long and the columns few, so every workgroup would read far more activation
     // bytes than weight bytes (one / two / four / eight slices, us: eight layers of the 7B shape 903 / 862 / 850 / 859, six of 13B
-    // 935 / 876 / 859 / 881, two of 70B 678 / 648 / 642)
+    // 935 / 876 / 859 / 881, two of 70B 678 / 648 / 642; two / four of 24 rows, two 8192-wide layers 676 / 655, eight 4096-wide 888 / 845)
     if (kd.F >= 2 * kd.d && kd.F >= 4096 && p->nw[3] % 4 == 0 && p->nw[3] / 4 <= nts[3] && (nts[3] + p->nw[3] / 4 - 1) / (p->nw[3] / 4) <= 8) p->ks[3] = 4;
-    // QKV with few columns over many inputs (grouped K/V heads): two 8192-wide layers of 24 rows 736 -> 726 us, of 16 rows the same; with
-    // heads of their own slices lose (eight 4096-wide layers 853 -> 871)
+    // QKV with few columns over many inputs (grouped K/V heads), one -> two slices, us, 24 / 16 rows / one row: two 8192-wide layers 678 -> 671, 557 -> 552,
+    // 507 -> 509, three 9216-wide 1131 -> 1116, 933 -> 925, 836 -> 833.  Narrower layers of 24 rows would gain more (four 6144-wide 681 -> 651, six 5120-wide
+    // 849 -> 819) and lose with one row (547 -> 551, 647 -> 650, eight 4096-wide 702 -> 713); with heads of their own slices lose (4096-wide 724 -> 736,
+    // 663 -> 681)
     if (kd.d >= 8192 && nts[0] < 3 * fc_num_cus() && p->nw[0] % 2 == 0 && (nts[0] + p->nw[0] / 2 - 1) / (p->nw[0] / 2) <= 8) p->ks[0] = 2;
     p->co_single = 2;
     for (int i = 0; i < 5; ++i) p->co_sb[0][i] = p->co_sb[1][i] = p->co_rot[0][i] = p->co_rot[1][i] = 2;

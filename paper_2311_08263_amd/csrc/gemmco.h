@@ -1,4 +1,4 @@
-// Argument block and launcher of the column-owner weight-streaming GEMM (see gemmco.hip).
+// Argument block and launcher of the column-owner weight-streaming GEMM (gemmco_k.h).
 #pragma once
 #include "fast.h"
 

@@ -17,8 +17,8 @@ int fc_num_cus() { return num_cus(); }
 // grid: one workgroup per CU unless that would give a workgroup more than `most` n-tiles (at most 8: with two
 // row tiles a workgroup then finishes 16 output tiles, whose partial sums take 64 KB of LDS).
 // wide (up to 16 rows): one round also of 12 to 14 n-tiles per CU.  The second round costs a head and a tail and reads the activations
-// once more; one pair of 14 tiles per wave keeps the loads as busy as two of eight.  us, two rounds / one: LM heads of 16 rows,
-// 51200 columns, 2048 / 4096 / 8192 inputs 41.7 / 37.6, 68.6 / 61.4, 122.5 / 111.7; two layers of the 70B shape (gate/up 14
+// once more; one pair of 14 tiles per wave keeps the loads as busy as two of eight.  us, two rounds / one: LM heads of 16 rows (one
+// matrix, call after call), 51200 columns, 2048 / 4096 / 8192 inputs 41.7 / 37.6, 68.6 / 61.4, 122.5 / 111.7; two layers of the 70B shape (gate/up 14
 // tiles per CU) 636 / 621.  Fewer tiles run as 12 and gain nothing (40000 columns, 9.8 tiles: 16 rows 56.5 / 56.7, 5 rows 51.9 / 54.8), and so do
 // more rounds of wider workgroups (128256 columns: four rounds of eight 147 us, three of twelve 155).
 int fc_gemmco_grid(int NT, int most, bool wide) {

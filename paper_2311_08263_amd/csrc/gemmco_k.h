@@ -263,7 +263,7 @@ __global__ __launch_bounds__(512) void k_gemmco(GemmCoArgs a) {
         }
     } else walk(std::integral_constant<int, D>(), b, std::false_type());
 
-    // the eight K slices meet in LDS (each wave's partial tiles where its activations were): with up to eight output tiles every wave publishes its partial tiles and one
+    // the eight K slices meet in LDS: with up to eight output tiles every wave publishes its partial tiles and one
     // barrier later each tile's finisher adds the eight in wave order; with more tiles in two rounds, so that
     // four partial sets (4 x TW KB) are enough: waves 4..7 publish, waves 0..3 add those to their own and
     // publish the sums

@@ -10,7 +10,7 @@
 // comes out as it went in.  (Zeros have a code because they are not that rare: 3 in 10^8 of what torch.normal_ makes, 7 in 10^6
 // of sums of eight 16-bit numbers; outside the window, the few flagged pairs of a launch cost it about 2 us each at its end.)
 //
-// Kernels of up to 32 rows (gemmco.hip) read the copy.  Those of many rows, bound by the matrix cores, read the plain tiles: with
+// Kernels of up to 32 rows (gemmco_k.h) read the copy.  Those of many rows, bound by the matrix cores, read the plain tiles: with
 // 13 vector instructions a tile (without the code for zero) the many-row products were 8-10 % slower, and with the weights kept as two planes of bytes (4
 // instructions a tile, and 21 bits a weight in memory for 29) still 3-5 %.
 //
